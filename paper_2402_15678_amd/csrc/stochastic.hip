@@ -37,122 +37,233 @@ __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
   return ((double)(hi >> 5) * 67108864.0 + (double)(lo >> 6)) * (1.0 / 9007199254740992.0);
 }
 
-constexpr int SV_THREADS = 256;
-constexpr int SV_TILE = 1024;  // tokens per tile: a wave owns 256 of them, a lane 4 consecutive ones
-constexpr int SV_MAX_TILES = 2048;
+// One workgroup of 16 waves per row, the row's exponentials in registers.  The kernels are bound by the fp64
+// exponentials of one row on one CU (about 30 fp64 instructions per token, 64 lanes per clock: 6 us for 32000 tokens) and by
+// the chain load -> maximum -> exponentials -> sum -> draw, so a row is read once, every exponential is computed once,
+// and every sum is a wave reduction.  Measured at 32000 tokens: 29.5 us for the 144 positions of 16 requests and 24.2 us
+// for 16 drafted tokens; 149 and 162 us with 256 threads per row, the scores re-read for every pass and one thread
+// adding the 256 partial sums of every tile.
+constexpr int SV_THREADS = 1024;
+constexpr int SV_WAVES = SV_THREADS / 64;
+constexpr int SV_BLOCK = 256;                         // tokens a wave takes at once: lane l holds 4l .. 4l+3 of them
+constexpr int SV_TILE = SV_WAVES * SV_BLOCK;          // tokens the workgroup takes at once
+constexpr int SV_REG_TILES = 8;                       // rows of up to 32768 tokens stay in registers (8 doubles x 4 per
+                                                      // thread: 64 of the 128 registers 16 waves leave each other)
+constexpr int SV_MAX_SEGS = 1024;
+constexpr int SV_MAX_VOCAB = 1 << 21;
 
-// Fixed-order sum of one double per thread: thread 0 adds the 256 values in thread order.
-__device__ __forceinline__ double block_sum_ordered(double v, double* s_buf, int tid) {
-  __syncthreads();
-  s_buf[tid] = v;
-  __syncthreads();
-  if (tid == 0) {
-    double t = 0.0;
-    for (int i = 0; i < SV_THREADS; ++i) t += s_buf[i];
-    s_buf[SV_THREADS] = t;
+// Token order.  The row is cut into segments of `grp` consecutive blocks of 256 tokens; segment s belongs to wave s % 16,
+// so (segment, block, lane, element) is token order.  grp = 1 up to 262144 tokens; larger rows take longer
+// segments, so that their sums fit the shared array.
+__device__ __forceinline__ int seg_blocks(int V) { return (V + SV_MAX_SEGS * SV_BLOCK - 1) / (SV_MAX_SEGS * SV_BLOCK); }
+
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // (rows start at any multiple of 4 bytes: the
+                                                                        // vocabulary need not be a multiple of 4)
+// four consecutive values of a row, `pad` past its end
+__device__ __forceinline__ f32x4 load_row4(const float* __restrict__ R, int v, int V, float pad) {
+  if (v + 3 < V) {
+    const f32x4_u x = *reinterpret_cast<const f32x4_u*>(R + v);
+    return (f32x4){x[0], x[1], x[2], x[3]};
   }
-  __syncthreads();
-  return s_buf[SV_THREADS];
+  f32x4 r = {pad, pad, pad, pad};
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (v + e < V) r[e] = R[v + e];
+  return r;
+}
+
+__device__ __forceinline__ double wave_sum_d(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
 struct DrawShared {
-  double buf[SV_THREADS + 1];
-  double tile[SV_MAX_TILES];  // mass of every tile
-  double target[2];           // target inside the chosen tile, total mass
-  int pick[2];                // chosen tile, chosen token
+  double seg[SV_MAX_SEGS];    // mass of every segment
+  double red[SV_WAVES];
+  float redf[SV_WAVES];
+  double target[2];           // target inside the chosen segment, total mass
+  int pick[2];                // chosen segment, chosen token
 };
 
-// Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass(v)
-// exceeds u times the total; -1 when the total is not positive.  Tokens are walked in tiles of 1024:
-// thread t of the workgroup holds tokens tile*1024 + 4t .. 4t+3 (coalesced 16-byte pieces), so a prefix
-// over (tile, thread, element) is a prefix in token order.  The per-tile masses are summed first, one
-// thread finds the tile that holds the target, and that tile alone is scanned.  Every thread of the
-// workgroup calls it; the result is uniform.  mass(v) must return the same value every time it is asked.
-template <typename F>
-__device__ int cdf_draw(F mass, int V, double u, DrawShared& sh, int tid) {
-  const int n_tiles = (V + SV_TILE - 1) / SV_TILE;
-  for (int t = 0; t < n_tiles; ++t) {
-    double m = 0.0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int v = t * SV_TILE + 4 * tid + e;
-      if (v < V) m += mass(v);
+// x / c for a divisor that is the same for the whole row, inv = 1 / c: one correction step makes the product the
+// rounded quotient.  (c and inv normal numbers, x finite: the caller sees to both)
+__device__ __forceinline__ double div_by(double x, double c, double inv) {
+  const double q = x * inv;
+  return fma(fma(-c, q, x), inv, q);
+}
+
+// exp((l - max) / T) with T's reciprocal (inv > 0) or, for temperatures so extreme that the reciprocal leaves the normal
+// range (inv == 0), by division.  Differences below -800 T are cut there (the exponential is zero long before), so
+// that a masked token (minus infinity) stays finite; NaN passes through.
+struct Temp {
+  double T, inv, cut;
+  __device__ __forceinline__ double mass(float l, double dmx) const {
+    double d = (double)l - dmx;
+    if (inv == 0.0) return exp(d / T);  // (uniform)
+    d = d < cut ? cut : d;
+    return exp(div_by(d, T, inv));
+  }
+};
+
+// Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass exceeds u times the
+// total; -1 when the total is not positive.  mass4(block, v) gives the masses of tokens v .. v+3 (v = 256 block + 4 lane;
+// 0 past the end) and must return the same values every time it is asked; for_blocks(f) calls f(block) for every block
+// of this wave in ascending order.  The masses are summed per segment, one wave finds the segment that holds the target,
+// and the wave that owns it scans it.  Every thread of the workgroup calls it; the result is uniform.  All sums
+// have a fixed order.
+template <typename FB, typename F>
+__device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u, DrawShared& sh, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  const int grp = seg_blocks(V);
+  const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK, n_seg = (n_blocks + grp - 1) / grp;
+  __syncthreads();  // (the shared arrays of an earlier draw have been read)
+  double run = 0.0;
+  for_blocks([&](int blk) {
+    double m[4];
+    mass4(blk, blk * SV_BLOCK + 4 * lane, m);
+    run += (m[0] + m[1]) + (m[2] + m[3]);
+    if (blk % grp == grp - 1 || blk == n_blocks - 1) {  // (wave-uniform)
+      const double s = wave_sum_d(run);
+      if (lane == 0) sh.seg[blk / grp] = s;
+      run = 0.0;
     }
-    const double ts = block_sum_ordered(m, sh.buf, tid);
-    if (tid == 0) sh.tile[t] = ts;
-  }
+  });
   __syncthreads();
-  if (tid == 0) {
-    double total = 0.0;
-    for (int t = 0; t < n_tiles; ++t) total += sh.tile[t];
-    const double target = u * total;
-    double before = 0.0;
-    int t = 0;
-    while (t < n_tiles - 1 && before + sh.tile[t] <= target) before += sh.tile[t++];
-    sh.target[0] = target - before;
-    sh.target[1] = total;
-    sh.pick[0] = t;
-    sh.pick[1] = 0x7fffffff;
-  }
-  __syncthreads();
-  if (!(sh.target[1] > 0.0)) return -1;  // (whole workgroup)
-  const int tile = sh.pick[0];
-  const double target = sh.target[0];
-  double m4[4], mine = 0.0;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const int v = tile * SV_TILE + 4 * tid + e;
-    m4[e] = v < V ? mass(v) : 0.0;
-    mine += m4[e];
-  }
-  sh.buf[tid] = mine;
-  __syncthreads();
-  double cum = 0.0;
-  for (int i = 0; i < tid; ++i) cum += sh.buf[i];  // thread order = token order
-  int hit = 0x7fffffff, last_pos = -1;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    cum += m4[e];
-    const int v = tile * SV_TILE + 4 * tid + e;
-    if (m4[e] > 0.0) {
-      last_pos = v;
-      if (cum > target && hit == 0x7fffffff) hit = v;
+  if (wave == 0) {
+    const int per = (n_seg + 63) >> 6;
+    double mine = 0.0;
+    for (int i = 0; i < per; ++i) {
+      const int s = lane * per + i;
+      if (s < n_seg) mine += sh.seg[s];
     }
+    double inc = mine;  // inclusive prefix over the lanes
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double t = __shfl_up(inc, o, 64);
+      if (lane >= o) inc += t;
+    }
+    const double total = __shfl(inc, 63, 64), target = u * total;
+    double before = __shfl_up(inc, 1, 64);
+    if (lane == 0) before = 0.0;
+    int hit = 0x7fffffff, last = -1;
+    double hit_before = 0.0, last_before = 0.0;
+    for (int i = 0; i < per; ++i) {
+      const int s = lane * per + i;
+      if (s >= n_seg) break;
+      const double m = sh.seg[s];
+      if (m > 0.0) {
+        last = s;
+        last_before = before;
+        if (hit == 0x7fffffff && before + m > target) { hit = s; hit_before = before; }
+      }
+      before += m;
+    }
+    const unsigned long long any = __ballot(hit != 0x7fffffff), pos = __ballot(last >= 0);
+    if (pos == 0ull) {                      // no mass anywhere (or not a number)
+      if (lane == 0) sh.pick[0] = -1;
+    } else if (any) {
+      if (lane == __ffsll(any) - 1) { sh.pick[0] = hit; sh.target[0] = target - hit_before; }
+    } else if (lane == 63 - __clzll(pos)) {  // rounding left the target at the end: the last segment with mass
+      sh.pick[0] = last;
+      sh.target[0] = target - last_before;
+    }
+    if (lane == 0) { sh.target[1] = total; sh.pick[1] = -1; }
   }
-  if (hit != 0x7fffffff) atomicMin(&sh.pick[1], hit);
   __syncthreads();
-  if (sh.pick[1] == 0x7fffffff) {  // rounding left the target at the tile's end: its last token with mass (whole workgroup)
-    __syncthreads();
-    if (tid == 0) sh.pick[1] = -1;
-    __syncthreads();
-    if (last_pos >= 0) atomicMax(&sh.pick[1], last_pos);
-    __syncthreads();
+  if (!(sh.target[1] > 0.0) || sh.pick[0] < 0) return -1;  // (whole workgroup)
+  const int seg = sh.pick[0];
+  if (wave == seg % SV_WAVES) {  // (the segment's own wave: it holds the masses)
+    const double target = sh.target[0];
+    double base = 0.0;
+    int tok = -1, tail = -1;     // the token; the last token with mass so far
+    for_blocks([&](int blk) {
+      if (blk / grp != seg || tok >= 0) return;
+      const int v = blk * SV_BLOCK + 4 * lane;
+      double m[4];
+      mass4(blk, v, m);
+      const double mine = (m[0] + m[1]) + (m[2] + m[3]);
+      double inc = mine;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const double t = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += t;
+      }
+      const double sum = __shfl(inc, 63, 64);
+      double cum = __shfl_up(inc, 1, 64);
+      cum = base + (lane == 0 ? 0.0 : cum);
+      int hit = -1, last = -1;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        cum += m[e];
+        if (m[e] > 0.0) {
+          last = v + e;
+          if (hit < 0 && cum > target) hit = v + e;
+        }
+      }
+      const unsigned long long any = __ballot(hit >= 0), pos = __ballot(last >= 0);
+      if (any) tok = __shfl(hit, __ffsll(any) - 1, 64);
+      if (pos) tail = __shfl(last, 63 - __clzll(pos), 64);
+      base += sum;
+    });
+    if (tok < 0) tok = tail;     // rounding left the target at the segment's end: its last token with mass
+    if (lane == 0) sh.pick[1] = tok;
   }
+  __syncthreads();
   return sh.pick[1];
 }
 
-// Largest score of a row and Z = sum_v exp((l_v - max) / T), both uniform over the workgroup.
-__device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, double temperature, float* s_max,
-                                              double* s_buf, int tid, double& dmx, double& Z) {
-  float mx = -INFINITY;
-  for (int v = tid; v < V; v += SV_THREADS) mx = fmaxf(mx, L[v]);
-  s_max[tid] = mx;
-  __syncthreads();
-  for (int s = SV_THREADS / 2; s > 0; s >>= 1) {
-    if (tid < s) s_max[tid] = fmaxf(s_max[tid], s_max[tid + s]);
-    __syncthreads();
+// The blocks of this wave: block b of a row belongs to segment b / grp and so to wave (b / grp) % 16.
+// TILES > 0: the row has at most TILES * 4096 tokens (grp == 1), the loop is unrolled and the block's index in the
+// wave is a constant; TILES == 0: any row.
+template <int TILES, typename F>
+__device__ __forceinline__ void wave_blocks(int V, int wave, F f) {
+  const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK;
+  if constexpr (TILES > 0) {
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+      if (t * SV_WAVES + wave < n_blocks) f(t * SV_WAVES + wave, t);
+  } else {
+    const int grp = seg_blocks(V);
+    for (int s = wave; s * grp < n_blocks; s += SV_WAVES)
+      for (int b = s * grp; b < min(n_blocks, (s + 1) * grp); ++b) f(b, 0);
   }
-  dmx = (double)s_max[0];
+}
+
+// Largest score of a row, then Z = sum_v exp((l_v - max) / T), both uniform over the workgroup; with TILES > 0 the
+// exponentials stay in ex (zero past the end of the row).
+template <int TILES>
+__device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, const Temp& temp, DrawShared& sh, int tid,
+                                              double (&ex)[TILES > 0 ? TILES : 1][4], double& dmx, double& Z) {
+  const int lane = tid & 63, wave = tid >> 6;
+  f32x4 raw[TILES > 0 ? TILES : 1];
+  float mx = -INFINITY;
+  wave_blocks<TILES>(V, wave, [&](int blk, int t) { raw[t] = load_row4(L, blk * SV_BLOCK + 4 * lane, V, -INFINITY);
+                                                     if (TILES == 0) mx = fmaxf(mx, fmaxf(fmaxf(raw[0][0], raw[0][1]), fmaxf(raw[0][2], raw[0][3]))); });
+  if constexpr (TILES > 0)
+    wave_blocks<TILES>(V, wave, [&](int, int t) { mx = fmaxf(mx, fmaxf(fmaxf(raw[t][0], raw[t][1]), fmaxf(raw[t][2], raw[t][3]))); });
+  mx = wave_max(mx);
+  if (lane == 0) sh.redf[wave] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < SV_WAVES; ++w) mx = fmaxf(mx, sh.redf[w]);
+  dmx = (double)mx;
   double zp = 0.0;
-  const int n_tiles = (V + SV_TILE - 1) / SV_TILE;
-  for (int t = 0; t < n_tiles; ++t) {
+  wave_blocks<TILES>(V, wave, [&](int blk, int t) {
+    const int v = blk * SV_BLOCK + 4 * lane;
+    const f32x4 l = TILES > 0 ? raw[t] : load_row4(L, v, V, -INFINITY);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int v = t * SV_TILE + 4 * tid + e;
-      if (v < V) zp += exp(((double)L[v] - dmx) / temperature);
+      ex[t][e] = v + e < V ? temp.mass(l[e], dmx) : 0.0;
+      zp += ex[t][e];
     }
-  }
-  Z = block_sum_ordered(zp, s_buf, tid);
+  });
+  zp = wave_sum_d(zp);
+  if (lane == 0) sh.red[wave] = zp;
+  __syncthreads();
+  Z = 0.0;
+#pragma unroll
+  for (int w = 0; w < SV_WAVES; ++w) Z += sh.red[w];
 }
 
 // The top byte of the counter's last word names the consumer of the numbers, so that the verifier
@@ -167,15 +278,15 @@ __device__ __forceinline__ void position_uniforms(uint32_t b, uint32_t j, uint32
 }
 
 // One workgroup per (position j, sequence b).
+template <int TILES>
 __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ voted, const float* __restrict__ draft_probs,
     const int32_t* __restrict__ spec_len, const int32_t* __restrict__ greedy, int B, int k_max, int M, int V,
-    double temperature, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
+    double temperature, double inv_temperature, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
     int32_t* __restrict__ sampled, int32_t* dev_status) {
   __shared__ DrawShared sh;
-  __shared__ float s_max[SV_THREADS];
   __shared__ int s_int[2];  // rows before this sequence, bad flag
-  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int32_t* out = sampled + (size_t)b * (k_max + 1) + j;
 
   if (tid < 2) s_int[tid] = 0;
@@ -202,8 +313,10 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     return;
   }
   const float* L = logits + (size_t)row * V;
+  const Temp temp{temperature, inv_temperature, -800.0 * temperature};
+  double ex[TILES > 0 ? TILES : 1][4];
   double dmx, Z;
-  row_max_and_z(L, V, temperature, s_max, sh.buf, tid, dmx, Z);
+  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, dmx, Z);
   double u_acc, u_res;
   position_uniforms((uint32_t)b, (uint32_t)j, step_lo, step_hi, 0u, seed_lo, seed_hi, u_acc, u_res);
 
@@ -215,7 +328,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     x = voted[(size_t)b * k_max + j];
     Q = draft_probs + ((size_t)b * k_max + j) * V;
     if (x >= 0 && x < V) {
-      const double ox = exp(((double)L[x] - dmx) / temperature) / Z;
+      const double ox = temp.mass(L[x], dmx) / Z;
       const double qx = (double)Q[x];
       keep = (qx <= ox) || (u_acc < ox / qx);
     }
@@ -228,14 +341,53 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
   // sums above 1) the replacement comes from o without the rejected token, so that it still differs from what
   // it replaces (the acceptance reads "first entry that differs" as the first rejection); and when all of o
   // sits on that token there is nothing else to emit: it stays ----
+  const double inv_z = 1.0 / Z;  // (Z >= 1: the largest score contributes exp(0))
+  auto o4 = [&](int v, double (&o)[4]) {  // probabilities of tokens v .. v+3, recomputed from the scores
+    const f32x4 l = load_row4(L, v, V, -INFINITY);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = v + e < V ? div_by(temp.mass(l[e], dmx), Z, inv_z) : 0.0;
+  };
   int tok = -1;
-  if (Q) {
-    tok = cdf_draw([&](int v) { return fmax(0.0, exp(((double)L[v] - dmx) / temperature) / Z - (double)Q[v]); }, V,
-                   u_res, sh, tid);
-    if (tok < 0) tok = cdf_draw([&](int v) { return v == x ? 0.0 : exp(((double)L[v] - dmx) / temperature) / Z; }, V, u_res, sh, tid);
-    if (tok < 0) tok = x;
+  if constexpr (TILES > 0) {
+    // the masses take the place of the exponentials in the registers
+    wave_blocks<TILES>(V, wave, [&](int blk, int t) {
+      f32x4 q = {0.f, 0.f, 0.f, 0.f};
+      if (Q) q = load_row4(Q, blk * SV_BLOCK + 4 * lane, V, 0.f);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double o = div_by(ex[t][e], Z, inv_z);
+        ex[t][e] = Q ? fmax(0.0, o - (double)q[e]) : o;
+      }
+    });
+    tok = cdf_draw([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
+                   [&](int blk, int, double (&m)[4]) {
+#pragma unroll
+                     for (int t = 0; t < TILES; ++t)
+                       if (blk / SV_WAVES == t) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; }
+                   },
+                   V, u_res, sh, tid);
   } else {
-    tok = cdf_draw([&](int v) { return exp(((double)L[v] - dmx) / temperature) / Z; }, V, u_res, sh, tid);
+    tok = cdf_draw([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+                   [&](int, int v, double (&m)[4]) {
+                     o4(v, m);
+                     if (Q) {
+                       const f32x4 q = load_row4(Q, v, V, 0.f);
+#pragma unroll
+                       for (int e = 0; e < 4; ++e) m[e] = fmax(0.0, m[e] - (double)q[e]);
+                     }
+                   },
+                   V, u_res, sh, tid);
+  }
+  if (Q && tok < 0) {
+    tok = cdf_draw([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+                   [&](int, int v, double (&m)[4]) {
+                     o4(v, m);
+#pragma unroll
+                     for (int e = 0; e < 4; ++e)
+                       if (v + e == x) m[e] = 0.0;
+                   },
+                   V, u_res, sh, tid);
+    if (tok < 0) tok = x;
   }
   if (tid == 0) *out = tok;
 }
@@ -243,46 +395,86 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
 // One workgroup per sequence: token ~ q = softmax(scores / T) of a drafting SSM, and q itself in fp32.
 // The draw is taken from the fp32 values that are written out, so what the verifier is later told is
 // exactly the distribution the token came from.
+template <int TILES>
 __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* __restrict__ logits, int V,
-                                                                  double temperature, uint32_t seed_lo, uint32_t seed_hi,
+                                                                  double temperature, double inv_temperature,
+                                                                  uint32_t seed_lo, uint32_t seed_hi,
                                                                   uint32_t step_lo, uint32_t step_hi, uint32_t consumer,
                                                                   uint32_t t_pos, int32_t* __restrict__ tokens,
                                                                   long token_stride, float* __restrict__ probs,
                                                                   long probs_stride) {
   __shared__ DrawShared sh;
-  __shared__ float s_max[SV_THREADS];
-  const int b = blockIdx.x, tid = threadIdx.x;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* L = logits + (size_t)b * V;
+  const Temp temp{temperature, inv_temperature, -800.0 * temperature};
+  double ex[TILES > 0 ? TILES : 1][4];
   double dmx, Z;
-  row_max_and_z(L, V, temperature, s_max, sh.buf, tid, dmx, Z);
+  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, dmx, Z);
   double u_unused, u;
   position_uniforms((uint32_t)b, t_pos, step_lo, step_hi, consumer, seed_lo, seed_hi, u_unused, u);
-  auto q32 = [&](int v) { return (float)(exp(((double)L[v] - dmx) / temperature) / Z); };
-  if (probs) {
-    float* P = probs + (size_t)b * probs_stride;
-    for (int v = tid; v < V; v += SV_THREADS) P[v] = q32(v);
-  }
-  const int tok = cdf_draw([&](int v) { return (double)q32(v); }, V, u, sh, tid);
+  const double inv_z = 1.0 / Z;
+  auto q4 = [&](int v, double (&m)[4]) {  // the fp32 probabilities of tokens v .. v+3
+    const f32x4 l = load_row4(L, v, V, -INFINITY);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m[e] = v + e < V ? (double)(float)div_by(temp.mass(l[e], dmx), Z, inv_z) : 0.0;
+  };
+  float* P = probs ? probs + (size_t)b * probs_stride : nullptr;
+  wave_blocks<TILES>(V, wave, [&](int blk, int t) {
+    const int v = blk * SV_BLOCK + 4 * lane;
+    double m[4];
+    if constexpr (TILES > 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = ex[t][e] = (double)(float)div_by(ex[t][e], Z, inv_z);
+    } else if (P) {
+      q4(v, m);
+    }
+    if (P) {
+      if (v + 3 < V) {
+        *reinterpret_cast<f32x4_u*>(P + v) = (f32x4_u){(float)m[0], (float)m[1], (float)m[2], (float)m[3]};
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (v + e < V) P[v + e] = (float)m[e];
+      }
+    }
+  });
+  int tok;
+  if constexpr (TILES > 0)
+    tok = cdf_draw([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
+                   [&](int blk, int, double (&m)[4]) {
+#pragma unroll
+                     for (int t = 0; t < TILES; ++t)
+                       if (blk / SV_WAVES == t) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; }
+                   },
+                   V, u, sh, tid);
+  else
+    tok = cdf_draw([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+                   [&](int, int v, double (&m)[4]) { q4(v, m); }, V, u, sh, tid);
   if (tid == 0) tokens[(size_t)b * token_stride] = tok;
 }
+
+// 1 / T where both are comfortably normal numbers, 0 otherwise (the kernels then divide)
+static double temperature_reciprocal(double T) { return T > 0x1p-100 && T < 0x1p100 ? 1.0 / T : 0.0; }
 
 void launch_verify_sample(const float* logits, const int32_t* voted, const float* draft_probs, const int32_t* spec_len,
                           const int32_t* greedy, int B, int k_max, int M, int V, double temperature, uint64_t seed,
                           uint64_t step, int32_t* sampled, int32_t* dev_status, hipStream_t st) {
   if (B <= 0) return;
-  verify_sample_kernel<<<dim3(k_max + 1, B), SV_THREADS, 0, st>>>(
-      logits, voted, draft_probs, spec_len, greedy, B, k_max, M, V, temperature, (uint32_t)seed, (uint32_t)(seed >> 32),
-      (uint32_t)step, (uint32_t)(step >> 32), sampled, dev_status);
+  auto* kernel = V <= SV_REG_TILES * SV_TILE ? verify_sample_kernel<SV_REG_TILES> : verify_sample_kernel<0>;
+  kernel<<<dim3(k_max + 1, B), SV_THREADS, 0, st>>>(
+      logits, voted, draft_probs, spec_len, greedy, B, k_max, M, V, temperature, temperature_reciprocal(temperature),
+      (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), sampled, dev_status);
 }
 
 void launch_draft_sample(const float* logits, int B, int V, double temperature, uint64_t seed, uint64_t step, int ssm,
                          int t_pos, int32_t* tokens, long token_stride, float* probs, long probs_stride, hipStream_t st) {
   if (B <= 0) return;
-  draft_sample_kernel<<<B, SV_THREADS, 0, st>>>(logits, V, temperature, (uint32_t)seed, (uint32_t)(seed >> 32),
-                                                (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)(1 + ssm),
-                                                (uint32_t)t_pos, tokens, token_stride, probs, probs_stride);
+  auto* kernel = V <= SV_REG_TILES * SV_TILE ? draft_sample_kernel<SV_REG_TILES> : draft_sample_kernel<0>;
+  kernel<<<B, SV_THREADS, 0, st>>>(logits, V, temperature, temperature_reciprocal(temperature), (uint32_t)seed,
+                                   (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)(1 + ssm),
+                                   (uint32_t)t_pos, tokens, token_stride, probs, probs_stride);
 }
 
-int verify_sample_max_vocab() { return SV_TILE * SV_MAX_TILES; }
+int verify_sample_max_vocab() { return SV_MAX_VOCAB; }
 
 }  // namespace mn

@@ -384,3 +384,17 @@ def test_draft_probs_that_cover_the_llm_distribution(hb):
                 assert sampled[b, a] != voted[b, a] and sampled[b, a] >= 0
         assert sampled[0, 0] == voted[0, 0]                             # nothing else could be emitted there
     assert rejections >= 10                                             # survival probability is 2/3 per position
+
+
+# Edges of the row layout: one block of 256 tokens and its neighbours, one and two passes of the 16 waves, the largest row
+# whose exponentials stay in registers and the smallest that does not, the smallest with two blocks per segment; a
+# vocabulary of one; temperatures whose reciprocal is not a normal number (the division path)
+@pytest.mark.parametrize("B,k_max,V,T", [(3, 2, 1, 1.0), (4, 3, 255, 1.0), (4, 3, 256, 0.9), (4, 3, 257, 1.0), (3, 2, 4096, 1.1),
+                                         (3, 2, 4097, 1.0), (3, 3, 32768, 0.8), (3, 3, 32769, 0.8), (2, 1, 262145, 1.0),
+                                         (4, 2, 300, 1e-35), (4, 2, 300, 1e35)])
+def test_sampling_row_layout_edges(hb, B, k_max, V, T):
+    spec, M, logits, q, voted = _case(21, B, k_max, V, min(max(T, 1e-3), 1e3), 1.0)
+    ctx0 = np.arange(B).astype(np.int32)
+    res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=5, step=1, ctx0=ctx0)
+    _check_against_oracle(res, spec, logits, q, voted, k_max, T, 5, 1, ctx0)
+    test_draft_sample_matches_oracle(hb, B, V, T, 2.0)
