@@ -474,10 +474,6 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     // single-position passes multiply)
     r.M = M; r.H = d.n_heads; r.Hkv = d.n_kv_heads; r.hd = d.head_dim; r.dtype = d.dtype;
     r.dev_status = dev_status;
-    {
-      Tap t(&c->prof, MN_PROF_ROPE_APPEND, st);
-      launch_rope_append(r, st);
-    }
     AttnArgs at{};
     at.q = r.q; at.out = w.at<void>(w.L.attn); at.rows = rows; at.kv = r.kv;
     at.B = B; at.M = M; at.H = d.n_heads; at.Hkv = d.n_kv_heads; at.hd = d.head_dim; at.dtype = d.dtype;
@@ -485,6 +481,13 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     at.scratch = w.at<float>(w.L.attn_scratch); at.scratch_bytes = w.L.attn_scratch_bytes;
     at.items = w.at<int32_t>(w.L.attn_items); at.items_capacity = w.L.attn_items_capacity;
     at.row_splits = w.at<int32_t>(w.L.attn_row_splits);
+    if (attention_fuses_append(at)) {  // (the same for every layer)
+      at.qkv = r.qkv; at.n_partials = r.n_partials; at.bias = r.bias; at.rope_cos = r.rope_cos; at.rope_sin = r.rope_sin;
+      at.dev_status = dev_status;
+    } else {
+      Tap t(&c->prof, MN_PROF_ROPE_APPEND, st);
+      launch_rope_append(r, st);
+    }
     if (l == 0) {  // the list of attention workgroups is the same for every layer
       Tap t(&c->prof, MN_PROF_PREPARE, st);
       launch_attention_plan(at, st);

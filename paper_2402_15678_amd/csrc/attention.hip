@@ -13,8 +13,8 @@
 //    waves: the page layouts put 8 consecutive contraction elements in 16 bytes for both
 //    products (head-dim chunks for K, tokens for V).  The KV range of a sequence is split across
 //    workgroups; partial (max, sum, output) triples are merged by attn_merge_kernel.
-//  * attn_fewrow_kernel  fp16 pages / fp16 queries, head_dim 64, at most 4 stacked query rows per KV head
-//    (a small drafting model decoding token by token): wide loads, plain FMA.
+//  * attn_keys_kernel  fp16 pages / fp16 queries, head_dim 64 or 128, 16-token blocks, few stacked query rows per KV head
+//    (decoding token by token, models without head groups, drafting models): the waves split the keys.
 //  * attn_generic_kernel  any storage type / head_dim / block size; plain FMA, one (row, head)
 //    per workgroup.  Used by the fp32 model and as the fallback.
 #include "launch.h"
@@ -150,10 +150,11 @@ __device__ __forceinline__ float max3(float x, float y, float z) { return __buil
 
 // Online-softmax step of one column tile on one key tile.  S0/S1: scores of keys 8g+0..3 / 8g+4..7 of
 // this lane's query row, already minus the reference (negm4 = -reference in all four elements, 0 while
-// nothing was seen).  Returns the probabilities as the B operand of the second product.
-template <bool MASK>
+// nothing was seen).  Returns the probabilities as the B operand of the second product, and with SPLIT what their
+// rounding to fp16 left over as a second operand in `rest`.
+template <bool MASK, int NU, bool SPLIT = false>
 __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, float& run_m, f32x4& negm4, float& thr,
-                                              f32x4 (&O)[8], f32x4& L, int keyg, int lim) {
+                                              f32x4 (&O)[NU], f32x4& L, int keyg, int lim, f16x8* rest = nullptr) {
   float sc[8] = {S0[0], S0[1], S0[2], S0[3], S1[0], S1[1], S1[2], S1[3]};
   if (MASK) {
 #pragma unroll
@@ -177,12 +178,21 @@ __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, 
 #pragma unroll
     for (int e = 0; e < 8; ++e) sc[e] -= d;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < NU; ++u) {
       O[u][0] *= alpha; O[u][1] *= alpha; O[u][2] *= alpha; O[u][3] *= alpha;
     }
     L[0] *= alpha; L[1] *= alpha; L[2] *= alpha; L[3] *= alpha;
   }
   union { f16x8 v; uint32_t u[4]; } pf;
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float p = __builtin_amdgcn_exp2f(sc[e]);
+      pf.v[e] = (f16_t)p;
+      (*rest)[e] = (f16_t)(p - (float)pf.v[e]);
+    }
+    return pf.v;
+  }
 #pragma unroll
   for (int e = 0; e < 4; ++e)
     pf.u[e] = pack2h(__builtin_amdgcn_exp2f(sc[2 * e]), __builtin_amdgcn_exp2f(sc[2 * e + 1]));
@@ -366,7 +376,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
           S0[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[s], qf[ct][s], S0[ct], 0, 0, 0);
           S1[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[4 + s], qf[ct][s], S1[ct], 0, 0, 0);
         }
-        P[ct - 1] = softmax_tile<SLOW>(S0[ct - 1], S1[ct - 1], run_m[ct - 1], negm4[ct - 1], thr[ct - 1], O[ct - 1], L[ct - 1], keyg, lim[ct - 1]);
+        P[ct - 1] = softmax_tile<SLOW, 8>(S0[ct - 1], S1[ct - 1], run_m[ct - 1], negm4[ct - 1], thr[ct - 1], O[ct - 1], L[ct - 1], keyg, lim[ct - 1]);
         __builtin_amdgcn_sched_barrier(0);
       }
       // every LDS read of tile i has been issued; tile i+1 has landed once every loader's own wait is over
@@ -384,7 +394,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
           for (int u = 0; u < 8; ++u) O[ct][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[u], P[ct], O[ct][u], 0, 0, 0);
           L[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, P[ct], L[ct], 0, 0, 0);
         }
-        P[NCT - 1] = softmax_tile<SLOW>(S0[NCT - 1], S1[NCT - 1], run_m[NCT - 1], negm4[NCT - 1], thr[NCT - 1], O[NCT - 1], L[NCT - 1], keyg, lim[NCT - 1]);
+        P[NCT - 1] = softmax_tile<SLOW, 8>(S0[NCT - 1], S1[NCT - 1], run_m[NCT - 1], negm4[NCT - 1], thr[NCT - 1], O[NCT - 1], L[NCT - 1], keyg, lim[NCT - 1]);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < 8; ++u) O[NCT - 1][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[u], P[NCT - 1], O[NCT - 1][u], 0, 0, 0);
@@ -444,6 +454,316 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// MFMA kernel for few rows (fp16 pages, fp16 queries, head_dim 64 or 128, block 16)
+// ------------------------------------------------------------------------------------------
+// Up to 16 * CT query rows per KV head: one row per sequence of a decoding step, the few rows of a model without head
+// groups, a drafting model catching up.  There is nothing for the waves of a workgroup to share, so instead of staging
+// tiles in LDS behind a barrier every wave takes key tiles of its own (wave w of a workgroup the tiles w, w + NW, ... of
+// its range), loads their K and V pieces straight into the operand registers of its MFMAs, the next tile's loads in
+// flight while it works on this one, and keeps its own (max, sum, output).  The waves' results meet once, in LDS, at the end.
+// Measured per layer, rotary/append included: 95 rows of 16 requests x 12 heads of 64, contexts 200-1500: 139 -> 16.2 us;
+// 16 x 1024 keys of the same model 17.1 -> 15.7 us; 8 x 512 keys x 40 heads of 128 29.2 -> 25.0 us.
+// Bound by the KV stream and, at short contexts, by the chain record -> block table -> first tile -> merge (about 6 us).
+// FUSED: the workgroup also turns its rows' QKV partial sums into queries (kept in LDS) and K/V rows (written to the pages
+// before the tiles that hold them are read), which saves a launch of its own per layer; a sequence must then be in one KV
+// split, so that the rows have one writer.  When every workgroup is resident at once and nothing is split (no list:
+// a.items null) the workgroups take (sequence, KV head) from their index: one dependent load less before the first tile.
+// Products and operand order are those of the kernel above; record list and KV splits likewise.  With head_dim 64
+// (the shapes that used to run on plain fp32 FMA) nothing is rounded to 16 bits on the way: the queries go into the first
+// product as they are and the scale is applied to its fp32 result, and a probability goes into the second product as two
+// fp16 terms, which hold 22 bits of it (the extra products hide behind the stream).
+template <int HDIM, int CT, int NW, bool FUSED>
+__global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT == 1 ? 2 : 1))
+    attn_keys_kernel(AttnArgs a, float* __restrict__ o_part, float* __restrict__ ml_part) {
+  constexpr bool WIDE = HDIM == 64;                          // fp32 queries and probabilities
+  constexpr int HS = HDIM / 32, NU = HDIM / 16, OROW = HDIM + 4;  // (padded rows: the merge's 16-byte accesses spread over the banks)
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* s_o = reinterpret_cast<float*>(smem);               // [NW][16][OROW], one column tile at a time
+  __shared__ float s_m[CT][NW][16], s_l[CT][NW][16];
+  const int item = blockIdx.x / a.Hkv, kvh = blockIdx.x % a.Hkv;
+  int b, split = 0, my_splits = 1, row0, qb, ok, ctx;
+  if (a.items) {  // (uniform)
+    const int4 rec0 = reinterpret_cast<const int4*>(a.items)[2 * item];
+    const int4 rec1 = reinterpret_cast<const int4*>(a.items)[2 * item + 1];
+    b = rec0.x;
+    if (b < 0 || rec0.y != 0) return;                        // past the end of the list (whole workgroup)
+    split = rec0.z; my_splits = rec0.w;
+    row0 = rec1.x; qb = rec1.y; ok = rec1.z; ctx = rec1.w;
+  } else {
+    b = item;
+    row0 = a.rows.seq_row0[b]; qb = a.rows.seq_row0[b + 1] - row0; ok = a.rows.seq_ok[b]; ctx = a.rows.seq_ctx[b];
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int G = a.H / a.Hkv;
+  const int R = G * qb;                                      // query rows sharing this KV head; row r = j*G + gi
+  if (qb <= 0 || split >= my_splits) return;                 // (whole workgroup)
+  const int nkeys = ok ? ctx + qb : 0;
+  const int n_tiles = (nkeys + KT - 1) / KT;
+  const int t_begin = (int)(((long)n_tiles * split) / my_splits);
+  const int t_end = (int)(((long)n_tiles * (split + 1)) / my_splits);
+  const int t0 = t_begin + wave;                             // this wave's tiles: t0, t0 + NW, ...
+  const int n = t0 < t_end ? (t_end - t0 + NW - 1) / NW : 0;
+
+  const int32_t* bt = a.kv.block_tables + (size_t)b * a.kv.max_blocks_per_seq;
+  const int last_blk = ok ? (nkeys - 1) / BS : 0;
+  const uint32_t blk_bytes = (uint32_t)a.Hkv * (HDIM * BS) * (uint32_t)sizeof(f16_t);
+  const uint32_t blk_last = (uint32_t)max(a.kv.num_blocks - 1, 0);
+  const size_t head_bytes = (size_t)kvh * (HDIM * BS) * sizeof(f16_t);
+  // this lane's pieces (see the kernel above): K row l16 = 4g'+r of half t is key 8g' + 4t + r, head-dim chunk 4s + g;
+  // V head-dim row 16u + l16, keys 8g .. 8g+7
+  const char* kbase = reinterpret_cast<const char*>(a.kv.k) + head_bytes + (size_t)(g * BS + 8 * ((l16 >> 2) & 1) + (l16 & 3)) * 16;
+  const char* vbase = reinterpret_cast<const char*>(a.kv.v) + head_bytes + (size_t)l16 * (BS * sizeof(f16_t)) + 16 * (g & 1);
+  const bool ksel = (l16 >> 3) != 0, vsel = (g >> 1) != 0;   // which of the tile's two blocks the pieces live in
+  struct Tile {
+    u32x4 k[2 * HS], v[NU];
+  };
+  // (block ids are clamped: a damaged table never becomes a wild address)
+  auto load = [&](Tile& t, int i) {
+    const int tile = t0 + NW * i;
+    const uint32_t b0 = min((uint32_t)bt[min(2 * tile, last_blk)], blk_last);
+    const uint32_t b1 = min((uint32_t)bt[min(2 * tile + 1, last_blk)], blk_last);
+    const char* kp = kbase + (uint64_t)(ksel ? b1 : b0) * blk_bytes;
+    const char* vp = vbase + (uint64_t)(vsel ? b1 : b0) * blk_bytes;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int s = 0; s < HS; ++s) t.k[h * HS + s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + h * 64 + s * (4 * BS * 16)));
+#pragma unroll
+    for (int u = 0; u < NU; ++u) t.v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + u * (16 * BS * (int)sizeof(f16_t))));
+  };
+  Tile ta, tb;
+  // (FUSED: a first tile that holds rows of this step is asked for after they have been written)
+  const bool early = !FUSED || (t0 + 1) * KT <= ctx;         // (wave-uniform)
+  if (n > 0 && early) load(ta, 0);
+
+  constexpr int QROW = HDIM + 8;
+  f16_t* s_q = reinterpret_cast<f16_t*>(smem);               // [R][QROW] (the merge reuses the space behind a barrier)
+  if constexpr (FUSED) {
+    // thread item = four pairs (t .. t+3, and + hd/2) of one head of one row: the G query heads, the key head, the value head
+    constexpr int HALF = HDIM / 2, Q4 = HALF / 4;
+    const int ncols = (a.H + 2 * a.Hkv) * HDIM;
+    bool bad = false;
+    for (int idx = tid; idx < (G + 2) * qb * Q4; idx += NW * 64) {
+      const int t = (idx % Q4) * 4, rr = idx / Q4, j = rr % qb, hh = rr / qb;
+      const int m = row0 + j;
+      const int head = hh < G ? kvh * G + hh : (hh == G ? a.H + kvh : a.H + a.Hkv + kvh);
+      const int c0 = head * HDIM + t;
+      f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
+      f32x4 cs = {1.f, 1.f, 1.f, 1.f}, sn = v0;
+      if (a.rope_cos && hh <= G) {
+        cs = *reinterpret_cast<const f32x4*>(a.rope_cos + (size_t)m * HALF + t);
+        sn = *reinterpret_cast<const f32x4*>(a.rope_sin + (size_t)m * HALF + t);
+      }
+      // partials fetched four at a time before any is added; the order of the sum is that of rope_append_kernel
+      for (int s0 = 0; s0 < a.n_partials; s0 += 4) {
+        f32x4 p0[4], p1[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float* p = a.qkv + ((size_t)min(s0 + k, a.n_partials - 1) * a.M + m) * ncols + c0;
+          p0[k] = *reinterpret_cast<const f32x4*>(p);
+          p1[k] = *reinterpret_cast<const f32x4*>(p + HALF);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (s0 + k < a.n_partials) { v0 += p0[k]; v1 += p1[k]; }
+      }
+      if (a.bias) {
+        const f32x4_u b0 = *reinterpret_cast<const f32x4_u*>(a.bias + c0), b1 = *reinterpret_cast<const f32x4_u*>(a.bias + c0 + HALF);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { v0[e] += b0[e]; v1[e] += b1[e]; }
+      }
+      if (a.rope_cos && hh <= G) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float x = v0[e], y = v1[e];
+          v0[e] = x * cs[e] - y * sn[e];
+          v1[e] = y * cs[e] + x * sn[e];
+        }
+      }
+      if (hh > G - 1 && !ok) continue;                       // disabled sequence: nothing is written to the cache
+      const uint2 w0 = make_uint2(pack2h_sat(v0[0], v0[1], bad), pack2h_sat(v0[2], v0[3], bad));
+      const uint2 w1 = make_uint2(pack2h_sat(v1[0], v1[1], bad), pack2h_sat(v1[2], v1[3], bad));
+      if (hh < G) {
+        f16_t* q = s_q + (size_t)(j * G + hh) * QROW + t;
+        *reinterpret_cast<uint2*>(q) = w0;
+        *reinterpret_cast<uint2*>(q + HALF) = w1;
+      } else {
+        const int p = ctx + j;
+        const uint32_t blk = min((uint32_t)bt[min(p / BS, last_blk)], blk_last);
+        const int off = p % BS;
+        if (hh == G) {  // K: [hd/8][bs][8]
+          f16_t* base = reinterpret_cast<f16_t*>(a.kv.k) + ((size_t)blk * a.Hkv + kvh) * (HDIM * BS);
+          *reinterpret_cast<uint2*>(base + ((t >> 3) * BS + off) * 8 + (t & 7)) = w0;
+          *reinterpret_cast<uint2*>(base + (((t + HALF) >> 3) * BS + off) * 8 + (t & 7)) = w1;
+        } else {        // V: [hd][bs]
+          uint16_t* base = reinterpret_cast<uint16_t*>(a.kv.v) + ((size_t)blk * a.Hkv + kvh) * (HDIM * BS) + (size_t)t * BS + off;
+          base[0] = (uint16_t)w0.x; base[BS] = (uint16_t)(w0.x >> 16); base[2 * BS] = (uint16_t)w0.y; base[3 * BS] = (uint16_t)(w0.y >> 16);
+          base += (size_t)HALF * BS;
+          base[0] = (uint16_t)w1.x; base[BS] = (uint16_t)(w1.x >> 16); base[2 * BS] = (uint16_t)w1.y; base[3 * BS] = (uint16_t)(w1.y >> 16);
+        }
+      }
+    }
+    if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
+    __syncthreads();  // the queries are in LDS; the K/V rows are visible to the whole workgroup
+    if (n > 0 && !early) load(ta, 0);
+  }
+
+  const float sscale = rsqrtf((float)HDIM) * LOG2E;
+  const f16_t* Q = reinterpret_cast<const f16_t*>(a.q);
+  f16x8 qf[CT][HS];
+  f32x4 O[CT][NU], L[CT], negm4[CT];
+  float run_m[CT], thr[CT];
+  int lim[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    run_m[ct] = -INFINITY;
+    thr[ct] = -INFINITY;
+    negm4[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    L[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const int r = ct * 16 + l16;
+    lim[ct] = ctx + min(r / G, qb - 1);                      // last visible key of this lane's query row
+#pragma unroll
+    for (int u = 0; u < NU; ++u) O[ct][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < HS; ++s) {
+      f16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (r < R) {
+        if constexpr (FUSED) v = *reinterpret_cast<const f16x8*>(s_q + (size_t)r * QROW + 32 * s + 8 * g);
+        else v = *reinterpret_cast<const f16x8*>(Q + ((size_t)(row0 + r / G) * a.H + kvh * G + r % G) * HDIM + 32 * s + 8 * g);
+        if (!WIDE) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = (f16_t)((float)v[e] * sscale);
+        }
+      }
+      qf[ct][s] = v;
+    }
+  }
+
+  const f16x8 ones = {1, 1, 1, 1, 1, 1, 1, 1};
+  // SLOW: the tile may reach past ctx (masked scores, V slots past the end read as zeros: 0 * garbage must stay 0)
+  auto work = [&](auto slow_c, Tile& t, int i) {
+    constexpr bool SLOW = decltype(slow_c)::value != 0;
+    const int keyg = (t0 + NW * i) * KT + 8 * g;
+    f32x4 S0[CT], S1[CT];
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      S0[ct] = WIDE ? (f32x4){0.f, 0.f, 0.f, 0.f} : negm4[ct];
+      S1[ct] = S0[ct];
+#pragma unroll
+      for (int s = 0; s < HS; ++s) {
+        S0[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.k[s]), qf[ct][s], S0[ct], 0, 0, 0);
+        S1[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.k[HS + s]), qf[ct][s], S1[ct], 0, 0, 0);
+      }
+      if (WIDE) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          S0[ct][e] = fmaf(S0[ct][e], sscale, negm4[ct][e]);
+          S1[ct][e] = fmaf(S1[ct][e], sscale, negm4[ct][e]);
+        }
+      }
+    }
+    if (SLOW) {
+      const int past = keyg + 8 - nkeys;                     // how many of this lane's 8 keys lie past the end
+      if (past > 0) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const uint32_t keep = (2 * w < 8 - past ? 0x0000ffffu : 0u) | (2 * w + 1 < 8 - past ? 0xffff0000u : 0u);
+#pragma unroll
+          for (int u = 0; u < NU; ++u) t.v[u][w] &= keep;
+        }
+      }
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      f16x8 rest;
+      const f16x8 P = softmax_tile<SLOW, NU, WIDE>(S0[ct], S1[ct], run_m[ct], negm4[ct], thr[ct], O[ct], L[ct], keyg, lim[ct], &rest);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) O[ct][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.v[u]), P, O[ct][u], 0, 0, 0);
+      L[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, P, L[ct], 0, 0, 0);
+      if (WIDE) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) O[ct][u] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, t.v[u]), rest, O[ct][u], 0, 0, 0);
+        L[ct] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, rest, L[ct], 0, 0, 0);
+      }
+    }
+  };
+  // Two tiles per pass of the loop, every load in it unconditional (behind a branch the compiler's wait counts would drain
+  // the load queue).  Only a wave's last tile can reach past ctx: the rows of a sequence span at most CT <= NW - 1 tiles
+  // beyond the first, and tiles are dealt to the waves in turn.
+  if (n > 0) {
+    int i = 0;
+    for (; i + 2 < n; i += 2) {
+      load(tb, i + 1);
+      work(IntC<0>{}, ta, i);
+      load(ta, i + 2);
+      work(IntC<0>{}, tb, i + 1);
+    }
+    if (i + 1 < n) {
+      load(tb, i + 1);
+      work(IntC<0>{}, ta, i);
+      work(IntC<1>{}, tb, i + 1);
+    } else {
+      work(IntC<1>{}, ta, i);
+    }
+  }
+
+  // ---- merge over the waves, output ----
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+    if (g == 0) {
+      s_m[ct][wave][l16] = run_m[ct];
+      s_l[ct][wave][l16] = L[ct][0];
+    }
+  __syncthreads();
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    if (ct * 16 >= R) break;                                 // (whole workgroup)
+    float gm = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) gm = fmaxf(gm, s_m[ct][w][l16]);
+    const float f = run_m[ct] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(run_m[ct] - gm);
+    if (ct > 0) __syncthreads();                             // (the previous column tile has been read)
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const f32x4 v = O[ct][u];
+      *reinterpret_cast<float4*>(s_o + (size_t)(wave * 16 + l16) * OROW + 16 * u + 4 * g) = make_float4(v[0] * f, v[1] * f, v[2] * f, v[3] * f);
+    }
+    __syncthreads();
+    for (int c = tid; c < 16 * (HDIM / 4); c += NW * 64) {
+      const int row = c / (HDIM / 4), e = (c % (HDIM / 4)) * 4, r = ct * 16 + row;
+      if (r >= R) continue;
+      float rm = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) rm = fmaxf(rm, s_m[ct][w][row]);
+      float l = 0.f;
+      float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float mw = s_m[ct][w][row];
+        l += (mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - rm)) * s_l[ct][w][row];
+        const float4 x = *reinterpret_cast<const float4*>(s_o + (size_t)(w * 16 + row) * OROW + e);
+        o.x += x.x; o.y += x.y; o.z += x.z; o.w += x.w;
+      }
+      const int m = row0 + r / G, h = kvh * G + r % G;
+      if (my_splits == 1) {
+        const float inv = (ok && l > 0.f) ? 1.f / l : 0.f;
+        *reinterpret_cast<uint2*>(reinterpret_cast<f16_t*>(a.out) + ((size_t)m * a.H + h) * HDIM + e) =
+            make_uint2(pack2h(o.x * inv, o.y * inv), pack2h(o.z * inv, o.w * inv));
+      } else {
+        *reinterpret_cast<float4*>(o_part + (((size_t)split * a.M + m) * a.H + h) * HDIM + e) = o;
+        if (e == 0) {
+          float* ml = ml_part + (((size_t)split * a.M + m) * a.H + h) * 2;
+          ml[0] = rm;
+          ml[1] = l;
+        }
+      }
+    }
+  }
+}
+
 // One wave per (row, head): merge the split partials, normalise, store fp16.  Rows of sequences that ran as
 // one split were written in final form by the attention kernel and are left alone.
 __global__ void __launch_bounds__(256) attn_merge_kernel(const float* __restrict__ o_part, const float* __restrict__ ml_part,
@@ -469,192 +789,6 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const float* __restrict
   }
   const float inv = l > 0.f ? 1.f / l : 0.f;
   *reinterpret_cast<uint32_t*>(out + (size_t)wid * HD + lane * 2) = pack2h(o0 * inv, o1 * inv);
-}
-
-// ------------------------------------------------------------------------------------------
-// few-row kernel (fp16 pages, fp16 queries, head_dim 64, 16-token blocks, at most 4 stacked rows per KV head)
-// ------------------------------------------------------------------------------------------
-// The shape of a small model decoding one token per sequence (the SSMs that draft for the vote): one or
-// a few query rows against the whole context.  There is nothing for a matrix instruction to share, the
-// job is to keep the K/V pages streaming with wide loads.  Workgroup = one (KV head, sequence), 8 or 16 waves;
-// a wave takes the key range in steps of four blocks (64 keys):
-//  * K: lane (token t = lane % 16, group g = lane / 16) loads head-dim chunks g and g + 4 of token t of
-//    each of the four blocks (16 bytes each, a quarter wave reads 256 contiguous bytes), multiplies
-//    them with its part of q and adds up over the four groups with two cross-lane steps; group g then
-//    keeps the score of block g: one key per lane;
-//  * softmax: running maximum per wave (log2 units), per-lane partial sums of the probabilities;
-//  * V: lane = head dimension; the 64 probabilities go through LDS (read back as broadcasts) and meet
-//    the 16 tokens x 4 blocks of that dimension (32 contiguous bytes per block).
-// The waves' (max, sum, output) are merged through LDS.
-constexpr int FR_HD = 64;
-
-// the two fp16 values of a 32-bit word of a page
-__device__ __forceinline__ float h_lo(uint32_t w) { return (float)__builtin_bit_cast(f16x2, w)[0]; }
-__device__ __forceinline__ float h_hi(uint32_t w) { return (float)__builtin_bit_cast(f16x2, w)[1]; }
-
-template <int RR, int FR_NW>  // rows held, waves per workgroup
-__global__ void __launch_bounds__(FR_NW * 64) attn_fewrow_kernel(AttnArgs a) {
-  __shared__ __attribute__((aligned(16))) float s_p[FR_NW][RR][64];
-  __shared__ float s_o[FR_NW][RR][64];
-  __shared__ float s_m[FR_NW][RR], s_l[FR_NW][RR];
-  const int kvh = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int t = lane & 15, g = lane >> 4;
-  const int G = a.H / a.Hkv;
-  // (the sequence's scalars in one round trip, as in the MFMA kernel)
-  const int row0 = a.rows.seq_row0[b], row1 = a.rows.seq_row0[b + 1];
-  const int seq_ok = a.rows.seq_ok[b];
-  const int ctx = a.rows.seq_ctx[b];
-  asm volatile("" ::"r"(seq_ok), "r"(ctx));
-  const int qb = row1 - row0;
-  if (qb <= 0) return;                       // (whole workgroup)
-  const int R = min(G * qb, RR);             // stacked rows r = j*G + gi (the host launches RR >= G * max_q)
-  f16_t* out = reinterpret_cast<f16_t*>(a.out);
-  if (!seq_ok) {                             // disabled sequence: zeros (whole workgroup)
-    if (wave < R) out[((size_t)(row0 + wave / G) * a.H + kvh * G + wave % G) * FR_HD + lane] = (f16_t)0.f;
-    return;
-  }
-  const f16_t* Q = reinterpret_cast<const f16_t*>(a.q);
-  const int n_pk = ctx + qb;                 // the cached keys and this step's own
-  const float sscale = rsqrtf((float)FR_HD) * LOG2E;
-
-  float qf[RR][16];   // q of row r, head-dim chunks g and g + 4 (the lane's share of a dot product)
-  float m[RR], l[RR], acc[RR];
-  int lim[RR];        // keys [0, lim) of the pages are visible to row r
-#pragma unroll
-  for (int r = 0; r < RR; ++r) {
-    m[r] = -INFINITY;
-    l[r] = 0.f;
-    acc[r] = 0.f;
-    lim[r] = 0;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) qf[r][i] = 0.f;
-    if (r < R) {
-      const f16_t* qp = Q + ((size_t)(row0 + r / G) * a.H + kvh * G + r % G) * FR_HD;
-      const f16x8 p0 = *reinterpret_cast<const f16x8*>(qp + 8 * g);
-      const f16x8 p1 = *reinterpret_cast<const f16x8*>(qp + 8 * (g + 4));
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        qf[r][i] = (float)p0[i] * sscale;
-        qf[r][8 + i] = (float)p1[i] * sscale;
-      }
-      lim[r] = min(n_pk, ctx + r / G + 1);
-    }
-  }
-
-  const int32_t* bt = a.kv.block_tables + (size_t)b * a.kv.max_blocks_per_seq;
-  const int last_blk = max(0, (n_pk - 1) / BS);
-  const uint32_t blk_last = (uint32_t)max(a.kv.num_blocks - 1, 0);
-  const size_t head_stride = (size_t)FR_HD * BS * sizeof(f16_t);  // one (block, KV head) of K or of V
-  const char* Kb = reinterpret_cast<const char*>(a.kv.k) + (size_t)kvh * head_stride + (size_t)(g * BS + t) * 16;
-  const char* Vb = reinterpret_cast<const char*>(a.kv.v) + (size_t)kvh * head_stride + (size_t)lane * (BS * sizeof(f16_t));
-  const int n_steps = (n_pk + 63) >> 6;
-  for (int s = wave; s < n_steps; s += FR_NW) {
-    uint4 kp[4][2], vp[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t blk = min((uint32_t)bt[min(4 * s + i, last_blk)], blk_last);
-      const size_t off = (size_t)blk * a.Hkv * head_stride;
-      kp[i][0] = *reinterpret_cast<const uint4*>(Kb + off);
-      kp[i][1] = *reinterpret_cast<const uint4*>(Kb + off + 4 * BS * 16);
-      vp[i][0] = *reinterpret_cast<const uint4*>(Vb + off);
-      vp[i][1] = *reinterpret_cast<const uint4*>(Vb + off + 16);
-    }
-    if ((s + 1) * 64 > n_pk) {               // (wave-uniform) V slots past the sequence end may hold anything, and
-#pragma unroll                               // 0 * garbage must stay 0: read them as zeros
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          uint32_t w[4] = {vp[i][c].x, vp[i][c].y, vp[i][c].z, vp[i][c].w};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int tok = (4 * s + i) * BS + 8 * c + 2 * j;
-            w[j] &= (tok < n_pk ? 0x0000ffffu : 0u) | (tok + 1 < n_pk ? 0xffff0000u : 0u);
-          }
-          vp[i][c] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-    }
-    const int key = (4 * s + g) * BS + t;    // the key whose score this lane keeps
-#pragma unroll
-    for (int r = 0; r < RR; ++r) {
-      float sv = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        float d = 0.f;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const uint4 w = kp[i][c];
-          const float* qq = &qf[r][8 * c];
-          d = fmaf(qq[0], h_lo(w.x), d); d = fmaf(qq[1], h_hi(w.x), d);
-          d = fmaf(qq[2], h_lo(w.y), d); d = fmaf(qq[3], h_hi(w.y), d);
-          d = fmaf(qq[4], h_lo(w.z), d); d = fmaf(qq[5], h_hi(w.z), d);
-          d = fmaf(qq[6], h_lo(w.w), d); d = fmaf(qq[7], h_hi(w.w), d);
-        }
-        d += __shfl_xor(d, 16);
-        d += __shfl_xor(d, 32);
-        if (g == i) sv = d;
-      }
-      if (key >= lim[r]) sv = -INFINITY;
-      const float new_m = fmaxf(m[r], wave_max(sv));
-      const float alpha = (m[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m[r] - new_m);
-      const float p = (sv == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(sv - new_m);
-      m[r] = new_m;
-      l[r] = l[r] * alpha + p;
-      acc[r] *= alpha;
-      s_p[wave][r][lane] = p;
-    }
-    // (the wave reads back what it has just written: LDS operations of one wave stay in order)
-#pragma unroll
-    for (int r = 0; r < RR; ++r) {
-      float o = acc[r];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float4* pp = reinterpret_cast<const float4*>(&s_p[wave][r][16 * i]);
-        const float4 p0 = pp[0], p1 = pp[1], p2 = pp[2], p3 = pp[3];
-        const uint4 v0 = vp[i][0], v1 = vp[i][1];
-        o = fmaf(p0.x, h_lo(v0.x), o); o = fmaf(p0.y, h_hi(v0.x), o);
-        o = fmaf(p0.z, h_lo(v0.y), o); o = fmaf(p0.w, h_hi(v0.y), o);
-        o = fmaf(p1.x, h_lo(v0.z), o); o = fmaf(p1.y, h_hi(v0.z), o);
-        o = fmaf(p1.z, h_lo(v0.w), o); o = fmaf(p1.w, h_hi(v0.w), o);
-        o = fmaf(p2.x, h_lo(v1.x), o); o = fmaf(p2.y, h_hi(v1.x), o);
-        o = fmaf(p2.z, h_lo(v1.y), o); o = fmaf(p2.w, h_hi(v1.y), o);
-        o = fmaf(p3.x, h_lo(v1.z), o); o = fmaf(p3.y, h_hi(v1.z), o);
-        o = fmaf(p3.z, h_lo(v1.w), o); o = fmaf(p3.w, h_hi(v1.w), o);
-      }
-      acc[r] = o;
-    }
-  }
-
-#pragma unroll
-  for (int r = 0; r < RR; ++r) {
-    const float lt = wave_sum(l[r]);
-    s_o[wave][r][lane] = acc[r];
-    if (lane == 0) {
-      s_m[wave][r] = m[r];
-      s_l[wave][r] = lt;
-    }
-  }
-  __syncthreads();
-  {
-    const int r = wave;                      // wave r merges row r (R <= 4 <= FR_NW)
-    if (r < R) {
-      float gm = -INFINITY;
-#pragma unroll
-      for (int w = 0; w < FR_NW; ++w) gm = fmaxf(gm, s_m[w][r]);
-      float lt = 0.f, o = 0.f;
-#pragma unroll
-      for (int w = 0; w < FR_NW; ++w) {
-        const float f = (s_m[w][r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(s_m[w][r] - gm);
-        lt += f * s_l[w][r];
-        o += f * s_o[w][r][lane];
-      }
-      out[((size_t)(row0 + r / G) * a.H + kvh * G + r % G) * FR_HD + lane] = (f16_t)(lt > 0.f ? o / lt : 0.f);
-    }
-  }
-}
-
-static bool fewrow_supported(const AttnArgs& a, int G) {
-  return a.dtype == MN_DT_BF16 && a.hd == FR_HD && a.kv.block_size == BS && a.Hkv > 0 && a.H % a.Hkv == 0 &&
-         G * a.max_q <= 4;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -758,9 +892,22 @@ size_t attention_items_capacity(int B, int M, int H, int Hkv) {
   return 16 * (G * (size_t)(M > 0 ? M : 0) / 64 + (size_t)(B > 0 ? B : 0)) + 16;
 }
 
+constexpr int KEYS_MAX_CT = 2;       // most column tiles of the few-row kernel
+constexpr int KEYS_RESIDENT = 512;   // its 4-wave workgroups that are resident at once (two per CU): up to here the order of
+                                     // the work does not matter and no list is made
+static bool keys_path(const AttnArgs& a) {
+  if (MN_TUNE("MN_ATTN_GENERIC", 0) || a.dtype != MN_DT_BF16 || (a.hd != 64 && a.hd != HD) || a.kv.block_size != BS ||
+      a.Hkv <= 0 || a.H % a.Hkv != 0 || a.items == nullptr || a.row_splits == nullptr ||
+      a.items_capacity < attention_items_capacity(a.B, a.M, a.H, a.Hkv))
+    return false;
+  if (a.hd == HD && (a.scratch == nullptr || a.scratch_bytes < attention_scratch_bytes(a.M, a.H, a.hd, a.max_ctx, a.dtype))) return false;
+  return (a.H / a.Hkv * a.max_q + 15) / 16 <= MN_TUNE("MN_ATTN_KEYS_CT", KEYS_MAX_CT);
+}
 // Shape of the MFMA launch, from what the host knows (largest row count of a sequence, longest context).
 struct MfmaShape {
   int ctw, nw, n_rg, n_splits, grid_items;
+  bool keys;  // attn_keys_kernel
+  bool list;  // the kernel takes its work from the list
 };
 static MfmaShape mfma_shape(const AttnArgs& a) {
   const int G = a.Hkv > 0 ? a.H / a.Hkv : 1;
@@ -769,11 +916,17 @@ static MfmaShape mfma_shape(const AttnArgs& a) {
   // row groups
   const int nt16_max = (G * a.max_q + 15) / 16;
   MfmaShape s;
+  s.keys = keys_path(a);
   s.ctw = nt16_max <= 4 ? 1 : MAX_CT;
   s.nw = 4;
-  if ((nt16_max == 5 || nt16_max == 6) && MN_TUNE("MN_ATTN_NW", 0) != 4) { s.ctw = 1; s.nw = nt16_max; }
+  if (s.keys) {
+    s.ctw = nt16_max;
+    s.nw = 1;  // (waves share the column tiles: a workgroup covers ctw of them)
+    s.n_rg = 1;
+  } else if ((nt16_max == 5 || nt16_max == 6) && MN_TUNE("MN_ATTN_NW", 0) != 4) { s.ctw = 1; s.nw = nt16_max; }
   s.n_rg = (nt16_max + s.nw * s.ctw - 1) / (s.nw * s.ctw);
-  s.n_splits = pick_splits(a.max_ctx);
+  s.n_splits = a.hd == HD ? pick_splits(a.max_ctx) : 1;
+  s.list = !(s.keys && s.n_splits == 1 && (long)a.B * a.Hkv <= KEYS_RESIDENT);
   const size_t bound = (size_t)a.B * s.n_rg * s.n_splits;
   s.grid_items = (int)(bound < a.items_capacity ? bound : a.items_capacity);
   return s;
@@ -789,15 +942,60 @@ static bool mfma_path(const AttnArgs& a) {
 }
 
 void launch_attention_plan(const AttnArgs& a, hipStream_t st) {
-  if (a.M <= 0 || a.B <= 0 || !mfma_path(a)) return;
+  if (a.M <= 0 || a.B <= 0 || !(keys_path(a) || mfma_path(a))) return;
   const MfmaShape s = mfma_shape(a);
+  if (!s.list) return;
   attn_plan_kernel<<<1, 1024, 0, st>>>(a.rows, a.B, a.H / a.Hkv, s.nw * s.ctw, s.n_splits, s.grid_items, a.items, a.M,
                                        a.row_splits);
 }
 
+static void launch_merge(const AttnArgs& a, int n_splits, const float* o_part, const float* ml_part, hipStream_t st) {
+  if (n_splits <= 1) return;
+  const int waves = a.M * a.H;
+  attn_merge_kernel<<<(waves + 3) / 4, 256, 0, st>>>(o_part, ml_part, n_splits, a.M, a.H, a.row_splits, reinterpret_cast<f16_t*>(a.out));
+}
+
+// A workgroup's waves split its keys: 8 waves up to one workgroup per CU, 4 (two workgroups per CU) beyond.  Measured with
+// the append inside: 256 workgroups of 300-2000 keys 38.9 us with 8 waves, 42.0 with 4; 192 of 1024 keys 15.7 / 17.6; 320 of
+// 512 keys 28.3 / 25.0.
+template <int HDIM, int CT, int NW, bool FUSED>
+static hipError_t launch_keys_nw(const AttnArgs& a, const MfmaShape& sh, float* o_part, float* ml_part, hipStream_t st) {
+  constexpr size_t smem = (size_t)NW * 16 * (HDIM + 4) * sizeof(float);
+  static std::once_flag attr_once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(attr_once, [] {
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_keys_kernel<HDIM, CT, NW, FUSED>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  attn_keys_kernel<HDIM, CT, NW, FUSED><<<(unsigned)a.Hkv * (unsigned)sh.grid_items, NW * 64, smem, st>>>(a, o_part, ml_part);
+  return hipSuccess;
+}
+template <int HDIM, int CT>
+static hipError_t launch_keys(const AttnArgs& a, const MfmaShape& sh, float* o_part, float* ml_part, hipStream_t st) {
+  const int nw = MN_TUNE("MN_ATTN_KEYS_NW", 0);
+  if constexpr (!(HDIM == 128 && CT == 2)) {
+    if (nw ? nw == 8 : a.B * a.Hkv <= 256)
+      return a.qkv ? launch_keys_nw<HDIM, CT, 8, true>(a, sh, o_part, ml_part, st) : launch_keys_nw<HDIM, CT, 8, false>(a, sh, o_part, ml_part, st);
+  }
+  return a.qkv ? launch_keys_nw<HDIM, CT, 4, true>(a, sh, o_part, ml_part, st) : launch_keys_nw<HDIM, CT, 4, false>(a, sh, o_part, ml_part, st);
+}
+
+bool attention_fuses_append(const AttnArgs& a) { return a.M > 0 && a.B > 0 && keys_path(a) && mfma_shape(a).n_splits == 1 && !MN_TUNE("MN_ATTN_NOFUSE", 0); }
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.B <= 0) return hipSuccess;
-  const int G = a.Hkv > 0 ? a.H / a.Hkv : 1;
+  if (keys_path(a)) {
+    const MfmaShape sh = mfma_shape(a);
+    AttnArgs k = a;
+    if (!sh.list) k.items = nullptr;
+    float* o_part = a.scratch;
+    float* ml_part = a.scratch + (size_t)sh.n_splits * a.M * a.H * HD;
+    hipError_t e;
+    if (a.hd == 64) e = sh.ctw == 1 ? launch_keys<64, 1>(k, sh, o_part, ml_part, st) : launch_keys<64, 2>(k, sh, o_part, ml_part, st);
+    else e = sh.ctw == 1 ? launch_keys<128, 1>(k, sh, o_part, ml_part, st) : launch_keys<128, 2>(k, sh, o_part, ml_part, st);
+    if (e == hipSuccess) launch_merge(a, sh.n_splits, o_part, ml_part, st);
+    return e;
+  }
   if (mfma_path(a)) {
     const MfmaShape sh = mfma_shape(a);
     const int n_splits = sh.n_splits;
@@ -826,19 +1024,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     else if (sh.nw == 6) attn_mfma_kernel<1, 6><<<grid, 384, smem, st>>>(a, o_part, ml_part);
     else if (sh.ctw == 1) attn_mfma_kernel<1, 4><<<grid, 256, smem, st>>>(a, o_part, ml_part);
     else attn_mfma_kernel<2, 4><<<grid, 256, smem, st>>>(a, o_part, ml_part);
-    if (n_splits > 1) {
-      const int waves = a.M * a.H;
-      attn_merge_kernel<<<(waves + 3) / 4, 256, 0, st>>>(o_part, ml_part, n_splits, a.M, a.H, a.row_splits, reinterpret_cast<f16_t*>(a.out));
-    }
-    return hipSuccess;
-  }
-  if (!MN_TUNE("MN_ATTN_GENERIC", 0) && fewrow_supported(a, G)) {
-    const dim3 fg(a.Hkv, a.B);
-    const int rr = G * a.max_q;
-    // a single row leaves registers for 16 waves (one step of 64 keys each at 1024 keys of context)
-    if (rr <= 1) attn_fewrow_kernel<1, 16><<<fg, 1024, 0, st>>>(a);
-    else if (rr <= 2) attn_fewrow_kernel<2, 8><<<fg, 512, 0, st>>>(a);
-    else attn_fewrow_kernel<4, 8><<<fg, 512, 0, st>>>(a);
+    launch_merge(a, n_splits, o_part, ml_part, st);
     return hipSuccess;
   }
   dim3 grid(a.H, a.M);

@@ -12,6 +12,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // four consecutive floats at any float's address
 
 // Precision note.  In bf16 models the weights arrive as bf16.  Every bf16 value
 // in the normal fp16 range is exactly representable in fp16 (8 significant bits into 11), so the

@@ -117,12 +117,20 @@ struct AttnArgs {
   int32_t* items;        // work list of the MFMA kernel, 8 int32 per record (see launch_attention_plan), or null
   size_t items_capacity; // records the buffer holds
   int32_t* row_splits;   // [M] KV splits of the row's sequence (written by the plan, read by the merge), or null
+  // Rotary embedding and KV append inside the attention kernel (attention_fuses_append): the QKV projection's partial
+  // sums as in RopeAppendArgs; q is not read then.  qkv null: q holds the queries and the pages hold every row.
+  const float* qkv;      // [S][M][(H+2Hkv)*hd]
+  int n_partials;
+  const float* bias;
+  const float *rope_cos, *rope_sin;
+  int32_t* dev_status;
 };
 size_t attention_scratch_bytes(int M, int H, int hd, int max_ctx, int dtype);
 bool attention_mfma_supported(int H, int Hkv, int hd, int block_size, int dtype);
 int attention_min_tiles();  // fewest key tiles an attention workgroup should take (32)
 int attention_target_workgroups();  // attention workgroups with work the plan aims for (320)
 size_t attention_items_capacity(int B, int M, int H, int Hkv);
+bool attention_fuses_append(const AttnArgs& a);  // the kernel that will run can take qkv (needs everything else set)
 // once per step, after the row bookkeeping and before the first launch_attention: the list of workgroups
 void launch_attention_plan(const AttnArgs& a, hipStream_t st);
 // hipSuccess, or the error of a one-time kernel attribute setting that failed (nothing is launched then)

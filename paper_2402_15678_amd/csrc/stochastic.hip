@@ -57,8 +57,7 @@ constexpr int SV_MAX_VOCAB = 1 << 21;
 // segments, so that their sums fit the shared array.
 __device__ __forceinline__ int seg_blocks(int V) { return (V + SV_MAX_SEGS * SV_BLOCK - 1) / (SV_MAX_SEGS * SV_BLOCK); }
 
-typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // (rows start at any multiple of 4 bytes: the
-                                                                        // vocabulary need not be a multiple of 4)
+// (rows start at any multiple of 4 bytes: the vocabulary need not be a multiple of 4)
 // four consecutive values of a row, `pad` past its end
 __device__ __forceinline__ f32x4 load_row4(const float* __restrict__ R, int v, int V, float pad) {
   if (v + 3 < V) {

@@ -184,6 +184,24 @@ def test_attention_matches_oracle(hb, name, desc, ctx_lens, spec_lens):
     _check_attention(hb, desc, ctx_lens, spec_lens)
 
 
+# The few-row kernel (waves split the keys): 1 to 32 stacked rows per KV head on both head widths, with 4 and 8 waves per
+# workgroup (more and fewer workgroups than CUs), contexts around its tile of 32 keys and its waves' turns, KV splits with
+# a merge, rows whose causal limit lies in the last and the last but one tile
+@pytest.mark.parametrize("name,desc,ctx_lens,spec_lens", [
+    ("hd128-g1-edges", synth.OPT_13B.with_layers(1), [0, 1, 30, 31, 32, 33, 255, 256, 257], [0, 15, 1, 0, 3, 15, 2, 8, 15]),
+    ("hd128-g1-two-tiles", synth.OPT_13B.with_layers(1), [40, 0, 97, 1023], [31, 20, 16, 31]),
+    ("hd128-g8-decode", synth.LLAMA2_70B.with_layers(1), [1999, 300, 0, 5, 640], [0, 0, 1, 0, 1]),
+    ("hd128-g8-q4", synth.LLAMA2_70B.with_layers(1), [513, 60, 28], [3, 3, 2]),
+    ("hd128-g8-decode-many", synth.LLAMA2_70B.with_layers(1), [300 + 41 * i for i in range(36)], [0] * 36),
+    ("hd128-g8-splits", synth.LLAMA2_70B.with_layers(1), [5003, 4100, 17], [1, 0, 0]),
+    ("hd64-rows16", synth.LLAMA_160M.with_layers(1), [700, 31, 0, 256], [15, 8, 5, 0]),
+    ("hd64-rows32", synth.LLAMA_160M.with_layers(1), [700, 3, 97], [31, 16, 20]),
+    ("hd64-many", synth.LLAMA_160M.with_layers(1), [64 * i + 7 for i in range(24)], [i % 9 for i in range(24)]),
+])
+def test_attention_few_rows(hb, name, desc, ctx_lens, spec_lens):
+    _check_attention(hb, desc, ctx_lens, spec_lens)
+
+
 @pytest.mark.parametrize("seed", list(range(10)))
 def test_attention_drawn_batches(hb, seed):
     """Drawn batches for the MFMA kernel and its work list: 1-24 sequences, contexts 0-2500 (a few of them long, so

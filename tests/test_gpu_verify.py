@@ -236,6 +236,26 @@ def test_llama160m_width_few_rows(hb):
     print("llama160m-width few rows max |dlogit| = %.2e, decisive %d/10" % (err, dec))
 
 
+# Rotary embedding and KV append inside the few-row attention kernel: 1 and 2 column tiles, both head widths, with and without
+# rotation and biases, 4 and 8 waves (12 and 300 workgroups); contexts 0 (every key is this step's own) and around the
+# kernel's tiles of 32 keys and the pages of 16, so that the new rows start, end and cross them, and the first tile of
+# a wave holds new rows.  The last case has more workgroups than fit at once (its work list).
+@pytest.mark.parametrize("name,desc,ctx,ks", [
+    ("llama-hd128-g2", synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 512, 4, 2, 128, 512, 500, 1024),
+     [0, 1, 15, 16, 31, 32], [12, 3, 0, 1, 5, 15]),
+    ("opt-hd64", synth.ModelDesc(synth.ARCH_OPT, synth.DT_BF16, 2, 256, 4, 4, 64, 512, 500, 1024), [0, 28, 63, 250], [15, 8, 1, 0]),
+    ("llama-hd64-g2-two-tiles", synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 256, 4, 2, 64, 512, 500, 1024),
+     [17, 0, 95, 96], [15, 9, 12, 0]),
+    ("opt-hd128-many", synth.ModelDesc(synth.ARCH_OPT, synth.DT_BF16, 1, 768, 6, 6, 128, 512, 500, 1024),
+     [5 * i for i in range(50)], [i % 4 for i in range(50)]),
+    ("opt-hd64-list", synth.ModelDesc(synth.ARCH_OPT, synth.DT_BF16, 1, 512, 8, 8, 64, 512, 500, 1024),
+     [3 * i for i in range(70)], [i % 3 for i in range(70)]),
+])
+def test_append_inside_attention(hb, name, desc, ctx, ks):
+    wl = synth.Workload(name, desc, len(ctx), 0, 300, 0, 15, 2, 0.3, seed=9100)
+    _reduced_case(hb, wl, desc.n_layers, len(ctx), 1, ctx_override=ctx, k_override=ks, min_decisive=0)
+
+
 def test_one_pass_equals_sequential_decodes_two_layers(hb):
     """Scoring k + 1 positions in one pass against k + 1 single-position passes of the library itself (section 2.1:
     the speculated tokens are scored in parallel with the outcome of scoring them one by one), at the 70B width and
