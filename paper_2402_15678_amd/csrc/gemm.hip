@@ -731,6 +731,31 @@ static int big_min_m() { return MN_TUNE("MN_GEMM_BIG_MIN_M", 0); }
 struct GemmPlan {
   int nw, split;
 };
+
+// Four-wave workgroups in splits of at least 8 iterations would be fewer than 64: a projection of a drafting model.
+static bool small_matrix(int slices, int iters) {
+  const int gx = (slices + 3) / 4;
+  const int split = 256 / gx < iters / 8 ? 256 / gx : iters / 8;
+  return gx * (split > 1 ? split : 1) < 64;
+}
+
+// Waves per workgroup at 96 rows or fewer, for a matrix of so many 32-column slices cut into `split` k-splits.  Unsplit
+// matrices: a CU with w workgroups of NW waves takes about 0.15 + w (0.27 + 0.13 NW) us per iteration (the tile and the
+// barrier are paid per workgroup, the stream per wave), so the count that gives the busiest CU the least is taken.  Measured
+// at 40 rows, NW = 2 .. 8: 20480 x 5120 (640 slices) 48.9 38.5 42.2 48.5 53.7 58.6 63.5 us; 50272 x 5120 (1572 slices) 99.6 103.4
+// 92.6 104.3 117.7 81.5 82.3 us.  Small matrices: see gemm_plan (6144 x 768 at 16 rows, NW = 1 .. 4: 5.5 5.8 6.6 7.4 us).
+// Split matrices have their split picked for 4 waves.
+static int few_rows_nw(int M, int slices, int iters, int split) {
+  if (small_matrix(slices, iters)) return M <= 32 ? 1 : 2;
+  if (split > 1) return 4;
+  int best = 4, best_cost = 1 << 30;
+  for (int nw : {4, 3, 7, 8}) {
+    const int wgs = (slices + nw - 1) / nw, cost = 15 + (wgs + 255) / 256 * (27 + 13 * nw);
+    if (cost < best_cost) { best = nw; best_cost = cost; }
+  }
+  return best;
+}
+
 static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
   const int forced_nw = MN_TUNE("MN_GEMM_NW", 0);
   const int slices = ((N + NWG - 1) / NWG) * 4;  // 32-column wave slices of the padded matrix
@@ -761,15 +786,19 @@ static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
     return best;
   }
   if (M <= 96) {
-    // up to six row tiles: 4-wave workgroups.  Few rows make an iteration cheap, so a split may be as short
-    // as 8 iterations, and one workgroup per CU is enough (measured at 40 rows: the 5120 x 5120 matrix
+    // up to six row tiles: the k-split is picked for 4-wave workgroups.  Few rows make an iteration cheap, so a split may be
+    // as short as 8 iterations, and one workgroup per CU is enough (measured at 40 rows: the 5120 x 5120 matrix
     // gains 30 % from 5 splits over 2, the 20480-column one loses with any split)
     const int gx = (slices + 3) / 4;
     best.split = splits_for(gx, tune().target / 2, 8);
-    // small matrices (the drafting models: a few hundred KB per projection) would leave most of the chip
-    // idle at that rule, and their time is launch and memory latency rather than bandwidth: splits as short
-    // as one iteration, up to about a hundred workgroups
-    if (gx * best.split < 64) best.split = splits_for(gx, 96, 1);
+    // small matrices (the drafting models: a few hundred KB per projection) would leave most of the chip idle at that rule,
+    // and their time is launch and memory latency rather than bandwidth: workgroups of one wave (two above 32 rows, where the
+    // tile is worth sharing) and splits as short as one iteration, up to 192 (128) of them.  One pass of the 12-layer, 768-wide
+    // model at 16 rows, up to 64 / 96 / 128 / 192 / 256 workgroups: 600 571 574 552 557 us of kernels; at 95 rows, up to
+    // 72 / 96 / 128 / 192: 684 681 677 685 (four-wave workgroups, up to 96: 620 and 738)
+    if (small_matrix(slices, iters))
+      best.split = M <= 32 ? splits_for(slices, 192, 1) : splits_for((slices + 1) / 2, 128, 1);
+    best.nw = few_rows_nw(M, slices, iters, best.split);
     return best;
   }
   int best_cus = 0, best_waves = 0;
@@ -825,6 +854,18 @@ static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
     gemm_w16_kernel<MT, NTW, EPI_RELU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.relu_act, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
   else
     gemm_w16_kernel<MT, NTW, EPI_PARTIAL, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.out, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+}
+
+template <int MT>
+static void launch_few_rows(const GemmArgs& a, hipStream_t st) {
+  switch (few_rows_nw(a.M, ((a.N + NWG - 1) / NWG) * 4, a.K / KB, a.split_k)) {
+    case 1: launch_bf16_mt<MT, 1>(a, 1, st); break;
+    case 2: launch_bf16_mt<MT, 2>(a, 1, st); break;
+    case 3: launch_bf16_mt<MT, 3>(a, 1, st); break;
+    case 7: launch_bf16_mt<MT, 7>(a, 1, st); break;
+    case 8: launch_bf16_mt<MT, 8>(a, 1, st); break;
+    default: launch_bf16_mt<MT, 4>(a, 1, st); break;
+  }
 }
 
 // rows per workgroup of the big-tile kernel: the AT (row tiles per wave, two waves deep) that pads M least
@@ -887,11 +928,11 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
   }
   const int tiles = (a.M + 15) / 16;
   // row tiles per workgroup: everything in one chunk up to 9 tiles (144 rows), else chunks of 8
-  if (tiles <= 1) launch_bf16_mt<1, 4>(a, 1, st);
-  else if (tiles <= 2) launch_bf16_mt<2, 4>(a, 1, st);
-  else if (tiles <= 3) launch_bf16_mt<3, 4>(a, 1, st);
-  else if (tiles <= 4) launch_bf16_mt<4, 4>(a, 1, st);
-  else if (tiles <= 6) launch_bf16_mt<6, 4>(a, 1, st);
+  if (tiles <= 1) launch_few_rows<1>(a, st);
+  else if (tiles <= 2) launch_few_rows<2>(a, st);
+  else if (tiles <= 3) launch_few_rows<3>(a, st);
+  else if (tiles <= 4) launch_few_rows<4>(a, st);
+  else if (tiles <= 6) launch_few_rows<6>(a, st);
   else if (tiles <= 9 && !(big_min_m() > 0 && a.M >= big_min_m())) {
     switch (gemm_plan(a.M, a.N, a.K, a.split_k).nw) {
       case 8: launch_bf16_mt<9, 8>(a, 1, st); break;

@@ -133,7 +133,12 @@ def _check_accept(hb, g, B, k_max):
                                          # ragged row blocks, a column count short of a 256-column group, one k block,
                                          # forced splits, vocabulary-sized N
                                          (145, 384, 256, 0), (320, 10240, 512, 0), (321, 130, 128, 1), (700, 1000, 1024, 3),
-                                         (631, 32000, 512, 2), (1024, 512, 2048, 4)])
+                                         (631, 32000, 512, 2), (1024, 512, 2048, 4),
+                                         # waves per workgroup at few rows: one (small matrices up to 32 rows), two (above),
+                                         # three, seven and eight (the balance over the CUs), column counts short of a block
+                                         (16, 2304, 768, 0), (32, 700, 3072, 0), (33, 700, 3072, 0), (95, 2304, 768, 0),
+                                         (5, 20480, 256, 1), (48, 20400, 128, 1), (64, 50272, 128, 1), (1, 64000, 128, 1),
+                                         (96, 63990, 128, 1)])
 def test_proj_gemm_matches_fp64(hb, M, N, K, split):
     harness, binding = hb
     g = synth.stream(79, M, N, K)
