@@ -152,7 +152,7 @@ extern "C" void mn_destroy(mn_ctx* ctx) { delete ctx; }
 static size_t al(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct Layout {
-  size_t row_seq, row_j, row_pos, row_tok, row_slot, seq_row0, seq_ctx, seq_ok, attn_tps, rope_cos, rope_sin;
+  size_t row_seq, row_j, row_pos, row_tok, row_slot, seq_row0, seq_ctx, seq_ok, rope_cos, rope_sin;
   size_t x, h, q, attn, act, partials, logits, attn_scratch, attn_items, attn_row_splits, total;
   size_t partials_bytes, attn_scratch_bytes, attn_items_capacity;
 };
@@ -174,7 +174,6 @@ static Layout make_layout(const mn_model_desc& d, int B, int M, int max_ctx) {
   L.row_seq = take(Mr * 4); L.row_j = take(Mr * 4); L.row_pos = take(Mr * 4); L.row_tok = take(Mr * 4);
   L.row_slot = take(Mr * 4);
   L.seq_row0 = take(((size_t)B + 1) * 4); L.seq_ctx = take((size_t)B * 4 + 4); L.seq_ok = take((size_t)B * 4 + 4);
-  L.attn_tps = take(4);
   L.rope_cos = take(Mr * (d.head_dim / 2) * 4); L.rope_sin = take(Mr * (d.head_dim / 2) * 4);
   L.x = take(Mr * d.d_model * 4);
   L.h = take(Mr * d.d_model * es);
@@ -359,13 +358,26 @@ static RowInfo row_info(const Ws& w) {
   r.seq_row0 = w.at<int32_t>(w.L.seq_row0);
   r.seq_ctx = w.at<int32_t>(w.L.seq_ctx);
   r.seq_ok = w.at<int32_t>(w.L.seq_ok);
-  r.attn_tps = w.at<int32_t>(w.L.attn_tps);
   return r;
 }
 
-static void run_prepare(mn_ctx* c, const Ws& w, const int32_t* last_tok, const int32_t* voted, const int32_t* spec_len,
-                        int B, int k_max, int M, int max_ctx, const mn_kv* kv, bool tokens, int32_t* dev_status,
-                        hipStream_t st) {
+// The attention call of one layer, everything but its queries and pages.
+static AttnArgs attn_args(const mn_ctx* c, const Ws& w, int B, int M, int max_ctx, int max_q, const mn_kv* kv) {
+  const mn_model_desc& d = c->d;
+  AttnArgs at{};
+  at.rows = row_info(w);
+  at.kv = KvView{nullptr, nullptr, kv->block_tables, kv->block_size, kv->num_blocks, kv->max_blocks_per_seq};
+  at.B = B; at.M = M; at.H = d.n_heads; at.Hkv = d.n_kv_heads; at.hd = d.head_dim; at.dtype = d.dtype;
+  at.max_ctx = max_ctx; at.max_q = max_q;
+  at.scratch = w.at<float>(w.L.attn_scratch); at.scratch_bytes = w.L.attn_scratch_bytes;
+  at.items = w.at<int32_t>(w.L.attn_items); at.items_capacity = w.L.attn_items_capacity;
+  at.row_splits = w.at<int32_t>(w.L.attn_row_splits);
+  return at;
+}
+
+static hipError_t run_prepare(mn_ctx* c, const Ws& w, const int32_t* last_tok, const int32_t* voted, const int32_t* spec_len,
+                              int B, int k_max, int M, int max_ctx, const mn_kv* kv, bool tokens, const AttnPlan& plan,
+                              int32_t* dev_status, hipStream_t st) {
   PrepArgs p{};
   p.last_tok = tokens ? last_tok : nullptr;
   p.voted = voted;
@@ -383,15 +395,13 @@ static void run_prepare(mn_ctx* c, const Ws& w, const int32_t* last_tok, const i
   p.row_pos = w.at<int32_t>(w.L.row_pos); p.row_tok = w.at<int32_t>(w.L.row_tok);
   p.row_slot = w.at<int32_t>(w.L.row_slot);
   p.seq_row0 = w.at<int32_t>(w.L.seq_row0); p.seq_ctx = w.at<int32_t>(w.L.seq_ctx); p.seq_ok = w.at<int32_t>(w.L.seq_ok);
-  p.attn_tps = w.at<int32_t>(w.L.attn_tps);
   p.kv_heads = c->d.n_kv_heads;
   p.q_per_kv = c->d.n_heads / c->d.n_kv_heads;
-  p.attn_wgs = attention_target_workgroups();
-  p.attn_min_tiles = attention_min_tiles();
+  p.plan = plan;
   p.rope_cos = w.at<float>(w.L.rope_cos); p.rope_sin = w.at<float>(w.L.rope_sin);
   p.dev_status = dev_status;
   Tap t(&c->prof, MN_PROF_PREPARE, st);
-  launch_prepare(p, st);
+  return launch_prepare(p, st);
 }
 
 // ---- verify forward -------------------------------------------------------------------------------
@@ -421,8 +431,14 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     if (!kv->k_layers[l] || !kv->v_layers[l]) return fail(c, MN_ENULL, "%s: kv layer %d pointer is NULL", who, l);
 
   hipStream_t st = (hipStream_t)stream;
-  run_prepare(c, w, last_tok, voted, spec_len, B, k_max, M, max_ctx, kv, true, dev_status, st);
+  hipError_t lerr = hipSuccess;  // first refusal of a launcher (a kernel attribute the runtime would not set)
+  auto keep = [&](hipError_t e) { if (e != hipSuccess && lerr == hipSuccess) lerr = e; };
   const RowInfo rows = row_info(w);
+  const AttnArgs attn = attn_args(c, w, B, M, max_ctx, max_q, kv);
+  const AttnPlan no_layers{};
+  keep(run_prepare(c, w, last_tok, voted, spec_len, B, k_max, M, max_ctx, kv, true, d.n_layers > 0 ? attention_plan(attn) : no_layers,
+                   dev_status, st));
+  if (lerr != hipSuccess) return fail(c, MN_EHIP, "%s: kernel attribute: %s", who, hipGetErrorString(lerr));
   const bool llama = d.arch == MN_ARCH_LLAMA;
   const int nqkv = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int w1r = d.d_ffn * (llama ? 2 : 1);
@@ -436,8 +452,6 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   int pend_n = 0;
   const float* pend_bias = nullptr;
 
-  hipError_t lerr = hipSuccess;  // first refusal of a launcher (a kernel attribute the runtime would not set)
-  auto keep = [&](hipError_t e) { if (e != hipSuccess && lerr == hipSuccess) lerr = e; };
   auto norm = [&](const float* gain, const float* shift, bool embed) {
     NormArgs n{};
     n.x = x; n.partials = pend; n.n_partials = pend_n; n.bias = pend_bias;
@@ -474,23 +488,14 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     // single-position passes multiply)
     r.M = M; r.H = d.n_heads; r.Hkv = d.n_kv_heads; r.hd = d.head_dim; r.dtype = d.dtype;
     r.dev_status = dev_status;
-    AttnArgs at{};
-    at.q = r.q; at.out = w.at<void>(w.L.attn); at.rows = rows; at.kv = r.kv;
-    at.B = B; at.M = M; at.H = d.n_heads; at.Hkv = d.n_kv_heads; at.hd = d.head_dim; at.dtype = d.dtype;
-    at.max_ctx = max_ctx; at.max_q = max_q;
-    at.scratch = w.at<float>(w.L.attn_scratch); at.scratch_bytes = w.L.attn_scratch_bytes;
-    at.items = w.at<int32_t>(w.L.attn_items); at.items_capacity = w.L.attn_items_capacity;
-    at.row_splits = w.at<int32_t>(w.L.attn_row_splits);
+    AttnArgs at = attn;
+    at.q = r.q; at.out = w.at<void>(w.L.attn); at.kv = r.kv;
     if (attention_fuses_append(at)) {  // (the same for every layer)
       at.qkv = r.qkv; at.n_partials = r.n_partials; at.bias = r.bias; at.rope_cos = r.rope_cos; at.rope_sin = r.rope_sin;
       at.dev_status = dev_status;
     } else {
       Tap t(&c->prof, MN_PROF_ROPE_APPEND, st);
       launch_rope_append(r, st);
-    }
-    if (l == 0) {  // the list of attention workgroups is the same for every layer
-      Tap t(&c->prof, MN_PROF_PREPARE, st);
-      launch_attention_plan(at, st);
     }
     {
       Tap t(&c->prof, MN_PROF_ATTENTION, st);
@@ -530,19 +535,12 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   }
   norm((const float*)c->final_norm_g, (const float*)c->final_norm_b, d.n_layers == 0);
   float* lg = logits ? logits : w.at<float>(w.L.logits);
-  {
-    const int s = gemm_pick_split(M, d.vocab, d.d_model, d.dtype);
-    if (s == 1) {
-      gemm(h, c->lm_head, lg, d.vocab, d.d_model, 1);
-    } else {
-      gemm(h, c->lm_head, part, d.vocab, d.d_model, s);
-      Tap t(&c->prof, MN_PROF_ARGMAX, st);
-      launch_reduce_partials(part, s, (size_t)M * d.vocab, lg, (size_t)M * d.vocab, st);
-    }
-  }
+  // (a split head's partial sums are added, and the scores written, by the argmax)
+  const int hs = gemm_pick_split(M, d.vocab, d.d_model, d.dtype);
+  gemm(h, c->lm_head, hs == 1 ? lg : part, d.vocab, d.d_model, hs);
   {
     Tap t(&c->prof, MN_PROF_ARGMAX, st);
-    launch_argmax_rows(lg, M, d.vocab, rows, k_max, greedy, B, st);
+    launch_argmax_rows(lg, hs == 1 ? nullptr : part, hs, M, d.vocab, rows, k_max, greedy, B, st);
   }
   if (lerr != hipSuccess) return fail(c, MN_EHIP, "%s: kernel attribute: %s", who, hipGetErrorString(lerr));
   return hip_check(c, who);
@@ -684,18 +682,11 @@ extern "C" mn_status mn_attention(mn_ctx* c, const void* q, const int32_t* spec_
   if (workspace_bytes < w.L.total) return fail(c, MN_EWORKSPACE, "%s: workspace %zu bytes, need %zu", who, workspace_bytes, w.L.total);
   hipStream_t st = (hipStream_t)stream;
   // row bookkeeping only (no tokens): positions are ctx_b + j, the rows' K/V are already cached
-  run_prepare(c, w, nullptr, nullptr, spec_len, B, k_max, M, max_ctx, kv, false, dev_status, st);
-  AttnArgs at{};
-  at.q = q; at.out = out; at.rows = row_info(w);
-  at.kv = KvView{kv->k_layers[layer], kv->v_layers[layer], kv->block_tables, kv->block_size, kv->num_blocks, kv->max_blocks_per_seq};
-  at.B = B; at.M = M; at.H = d.n_heads; at.Hkv = d.n_kv_heads; at.hd = d.head_dim; at.dtype = d.dtype;
-  at.max_ctx = max_ctx; at.max_q = max_q;
-  at.scratch = w.at<float>(w.L.attn_scratch); at.scratch_bytes = w.L.attn_scratch_bytes;
-  at.items = w.at<int32_t>(w.L.attn_items); at.items_capacity = w.L.attn_items_capacity;
-  at.row_splits = w.at<int32_t>(w.L.attn_row_splits);
-  launch_attention_plan(at, st);
-  hipError_t lerr = hipSuccess;
-  {
+  AttnArgs at = attn_args(c, w, B, M, max_ctx, max_q, kv);
+  at.q = q; at.out = out;
+  at.kv.k = kv->k_layers[layer]; at.kv.v = kv->v_layers[layer];
+  hipError_t lerr = run_prepare(c, w, nullptr, nullptr, spec_len, B, k_max, M, max_ctx, kv, false, attention_plan(at), dev_status, st);
+  if (lerr == hipSuccess) {
     Tap t(&c->prof, MN_PROF_ATTENTION, st);
     lerr = launch_attention(at, st);
   }

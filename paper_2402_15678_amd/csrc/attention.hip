@@ -201,11 +201,6 @@ __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, 
 
 template <int N> struct IntC { static constexpr int value = N; };
 
-// KV splits of a sequence with n_tiles key tiles when a workgroup should take about tps of them
-__device__ __forceinline__ int seq_splits(int n_tiles, int tps, int n_splits_max) {
-  return max(1, min(n_splits_max, (n_tiles + tps - 1) / max(tps, 1)));
-}
-
 // Partials: o_part [split][M][H][HD] fp32 (unnormalised), ml_part [split][M][H][2] = (max in log2 units, sum)
 // NW waves per workgroup.  Waves 0-3 are the loaders (the tile's 16 fragments are dealt to four waves); with 5 or
 // 6 waves the others only multiply: a stack of 65-96 query rows (5 or 6 column tiles, e.g. 8 query heads per KV
@@ -217,7 +212,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   f16_t* s_kv = reinterpret_cast<f16_t*>(smem);                          // [NS][16 fragments][64 lanes][8]
   int32_t* s_bidx = reinterpret_cast<int32_t*>(smem + NS * TILE_BYTES);  // physical block of every block of the split
-  // Work list: workgroup (item, KV head) takes record `item` of the list attn_plan_kernel wrote for this step:
+  // Work list: workgroup (item, KV head) takes record `item` of the list prepare_kernel wrote for this step:
   // {sequence, row group, split, splits of the sequence, first row, rows, enabled, context}.  The list holds
   // only workgroups that have work, longest first, and the KV head is the fast index: workgroup ids are dealt
   // round-robin over the 8 XCDs and, inside an XCD, over its CUs, strictly in id order, so work has to be
@@ -794,59 +789,11 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const float* __restrict
 // ------------------------------------------------------------------------------------------
 // launch
 // ------------------------------------------------------------------------------------------
-// The list of workgroups of the MFMA kernel for this step (the same for every layer): one record of 8 int32 per
-// (sequence, row group, KV split) that has work: {sequence, row group, split, splits of the sequence, first
-// row, rows, enabled, context}.  Sequences are ordered by descending key tiles per workgroup (ties by index),
-// so the longest workgroups start first and the short ones fill the end of the launch; the records of the
-// grid past the last real one get sequence = -1.  One workgroup; ranking is a comparison of every pair of
-// sequences (B <= 4096, once per step).
-__global__ void __launch_bounds__(1024) attn_plan_kernel(RowInfo rows, int B, int G, int tiles16_per_wg, int n_splits_max,
-                                                         int grid_items, int32_t* __restrict__ items, int M,
-                                                         int32_t* __restrict__ row_splits) {
-  __shared__ int s_key[MN_MAX_BATCH], s_cnt[MN_MAX_BATCH], s_spl[MN_MAX_BATCH];
-  __shared__ int s_total;
-  const int tid = threadIdx.x;
-  const int tps = rows.attn_tps[0];
-  for (int m = tid; m < M; m += blockDim.x) row_splits[m] = 0;   // rows of no sequence (a disabled batch) merge nothing
-  for (int b = tid; b < B; b += blockDim.x) {
-    const int q = rows.seq_row0[b + 1] - rows.seq_row0[b];
-    const int n_tiles = rows.seq_ok[b] ? (rows.seq_ctx[b] + q + KT - 1) / KT : 0;
-    const int nt16 = (G * q + 15) >> 4;
-    const int n_rg = q > 0 ? (nt16 + tiles16_per_wg - 1) / tiles16_per_wg : 0;
-    const int spl = seq_splits(n_tiles, tps, n_splits_max);
-    s_spl[b] = spl;
-    s_cnt[b] = n_rg * spl;                       // a disabled sequence keeps one workgroup per row group: it writes zeros
-    s_key[b] = (n_tiles + spl - 1) / spl;
-  }
-  __syncthreads();
-  for (int b = tid; b < B; b += blockDim.x) {
-    const int key = s_key[b], cnt = s_cnt[b], spl = s_spl[b];
-    int off = 0, total = 0;
-    for (int b2 = 0; b2 < B; ++b2) {
-      const int c = s_cnt[b2], k2 = s_key[b2];
-      total += c;
-      if (k2 > key || (k2 == key && b2 < b)) off += c;
-    }
-    if (b == 0) s_total = total;
-    const int row0 = rows.seq_row0[b], q = rows.seq_row0[b + 1] - row0, ok = rows.seq_ok[b], ctx = rows.seq_ctx[b];
-    for (int j = 0; j < q; ++j) row_splits[row0 + j] = spl;   // for the merge: which rows have partials at all
-    for (int i = 0; i < cnt; ++i) {
-      if (off + i >= grid_items) break;        // (cannot happen: the grid holds every real record)
-      int4* rec = reinterpret_cast<int4*>(items) + 2 * (size_t)(off + i);
-      rec[0] = make_int4(b, i / spl, i % spl, spl);
-      rec[1] = make_int4(row0, q, ok, ctx);
-    }
-  }
-  __syncthreads();
-  for (int i = s_total + tid; i < grid_items; i += blockDim.x)
-    reinterpret_cast<int4*>(items)[2 * (size_t)i] = make_int4(-1, 0, 0, 1);
-}
-
 // Fewest key tiles a workgroup should take: below that the lead-in of a workgroup, the fp32 partial it writes and the
 // merge launch behind cost as much as the parallelism wins (measured at 33 tiles per sequence and 128 (sequence, KV
 // head) pairs: one split 2.10 ms of attention per step, two splits + merge 2.13-2.17, three or four 2.8-2.9; 16 and
 // 32 give the same times at the other benchmark shapes, where the batch size decides the splits).
-int attention_min_tiles() {
+static int attention_min_tiles() {
   const int x = MN_TUNE("MN_ATTN_MIN_TILES", 32);
   return x > 0 ? x : 32;
 }
@@ -854,13 +801,13 @@ int attention_min_tiles() {
 // 1.25 workgroups with work per CU: measured flat between 1 and 1.3 per CU, slower beyond (every further split of
 // a sequence writes and re-reads one more fp32 partial of its rows, and workgroups beyond the 512 that are
 // resident at once start when the first ones end)
-int attention_target_workgroups() {
+static int attention_target_workgroups() {
   const int x = MN_TUNE("MN_ATTN_WGS", 320);
   return x > 0 ? x : 320;
 }
 
 // Largest number of KV splits any sequence of the batch may get (it sizes the partials and bounds the work list;
-// every sequence then takes what its own length asks for, see seq_splits): one per attention_min_tiles() key
+// every sequence then takes what its own length asks for, see prepare_kernel): one per attention_min_tiles() key
 // tiles of the longest context, 16 at most.
 static int pick_splits(int max_ctx) {
   const int forced = MN_TUNE("MN_ATTN_SPLITS", 0);
@@ -941,12 +888,15 @@ static bool mfma_path(const AttnArgs& a) {
          a.items_capacity >= attention_items_capacity(a.B, a.M, a.H, a.Hkv);
 }
 
-void launch_attention_plan(const AttnArgs& a, hipStream_t st) {
-  if (a.M <= 0 || a.B <= 0 || !(keys_path(a) || mfma_path(a))) return;
+AttnPlan attention_plan(const AttnArgs& a) {
+  AttnPlan p{};
+  if (a.M <= 0 || a.B <= 0 || !(keys_path(a) || mfma_path(a))) return p;
   const MfmaShape s = mfma_shape(a);
-  if (!s.list) return;
-  attn_plan_kernel<<<1, 1024, 0, st>>>(a.rows, a.B, a.H / a.Hkv, s.nw * s.ctw, s.n_splits, s.grid_items, a.items, a.M,
-                                       a.row_splits);
+  if (!s.list) return p;
+  p.items = a.items; p.row_splits = a.row_splits; p.grid_items = s.grid_items;
+  p.tiles16_per_wg = s.nw * s.ctw; p.n_splits_max = s.n_splits;
+  p.target_wgs = attention_target_workgroups(); p.min_tiles = attention_min_tiles();
+  return p;
 }
 
 static void launch_merge(const AttnArgs& a, int n_splits, const float* o_part, const float* ml_part, hipStream_t st) {

@@ -25,6 +25,14 @@ void launch_draft_sample(const float* logits, int B, int V, double temperature, 
 int verify_sample_max_vocab();
 
 // ---- rows.hip ----
+// Work list of the attention kernels, written once per step with the row bookkeeping (attention_plan fills this in).
+struct AttnPlan {
+  int32_t* items;       // [grid_items] records of 8 int32, or null: the kernel that will run needs no list
+  int32_t* row_splits;  // [M]
+  int grid_items, tiles16_per_wg, n_splits_max;
+  int target_wgs;       // workgroups with work to aim for
+  int min_tiles;        // fewest key tiles a workgroup should take
+};
 struct PrepArgs {
   const int32_t *last_tok, *voted, *spec_len, *ctx_lens, *block_tables;
   int B, k_max, M, vocab, max_pos, block_size, num_blocks, max_blocks_per_seq;
@@ -32,15 +40,14 @@ struct PrepArgs {
   int rope_half;     // head_dim/2 for rotary models, 0 otherwise
   float rope_base;
   int32_t *row_seq, *row_j, *row_pos, *row_tok, *row_slot, *seq_row0, *seq_ctx, *seq_ok;
-  int32_t* attn_tps;           // [1] out: key tiles per attention workgroup (see RowInfo)
   int kv_heads;                // KV heads of the model (the attention grid has one workgroup row per KV head)
   int q_per_kv;                // query heads per KV head (a workgroup covers 128 rows of query position x head)
-  int attn_wgs;                // number of attention workgroups to aim for
-  int attn_min_tiles;          // fewest key tiles a workgroup should take
+  AttnPlan plan;               // the attention work list to write (items null: none)
   float *rope_cos, *rope_sin;  // [M][rope_half]
   int32_t* dev_status;
 };
-void launch_prepare(const PrepArgs& a, hipStream_t st);
+// hipSuccess, or the error of a one-time kernel attribute setting that failed (nothing is launched then)
+hipError_t launch_prepare(const PrepArgs& a, hipStream_t st);
 
 struct NormArgs {
   // source of the row: either the residual stream x (+ partial sums + bias), or the embeddings
@@ -83,7 +90,8 @@ struct ActArgs {
 };
 void launch_act(const ActArgs& a, hipStream_t st);
 
-void launch_argmax_rows(const float* logits, int M, int V, const RowInfo& rows, int k_max, int32_t* greedy, int B,
+// partials non-null: the scores are the sums of S partial sums [S][M][V] and are written to logits first
+void launch_argmax_rows(float* logits, const float* partials, int S, int M, int V, const RowInfo& rows, int k_max, int32_t* greedy, int B,
                         hipStream_t st);
 
 // ---- gemm.hip ----
@@ -114,7 +122,7 @@ struct AttnArgs {
   int max_q;       // largest number of rows of one sequence (host knowledge)
   float* scratch;  // split-KV partials
   size_t scratch_bytes;
-  int32_t* items;        // work list of the MFMA kernel, 8 int32 per record (see launch_attention_plan), or null
+  int32_t* items;        // work list of the MFMA kernel, 8 int32 per record (see prepare_kernel), or null
   size_t items_capacity; // records the buffer holds
   int32_t* row_splits;   // [M] KV splits of the row's sequence (written by the plan, read by the merge), or null
   // Rotary embedding and KV append inside the attention kernel (attention_fuses_append): the QKV projection's partial
@@ -127,12 +135,9 @@ struct AttnArgs {
 };
 size_t attention_scratch_bytes(int M, int H, int hd, int max_ctx, int dtype);
 bool attention_mfma_supported(int H, int Hkv, int hd, int block_size, int dtype);
-int attention_min_tiles();  // fewest key tiles an attention workgroup should take (32)
-int attention_target_workgroups();  // attention workgroups with work the plan aims for (320)
 size_t attention_items_capacity(int B, int M, int H, int Hkv);
 bool attention_fuses_append(const AttnArgs& a);  // the kernel that will run can take qkv (needs everything else set)
-// once per step, after the row bookkeeping and before the first launch_attention: the list of workgroups
-void launch_attention_plan(const AttnArgs& a, hipStream_t st);
+AttnPlan attention_plan(const AttnArgs& a);  // what the kernels that will run need from the row bookkeeping
 // hipSuccess, or the error of a one-time kernel attribute setting that failed (nothing is launched then)
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);
 

@@ -5,29 +5,94 @@
 #include "launch.h"
 #include "../../include/minions_verify.h"
 
+#include <mutex>
+
 namespace mn {
 
 // ------------------------------------------------------------------------------------------
-// prepare: validate the batch on the device and lay out the packed rows
+// prepare: validate the batch on the device, lay out the packed rows, list the attention workgroups, rotary table
 // ------------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(1024) prepare_kernel(PrepArgs a) {
-  __shared__ int32_t s_row0[MN_MAX_BATCH + 1];
-  __shared__ int32_t s_ok[MN_MAX_BATCH];
-  __shared__ int32_t s_nb[MN_MAX_BATCH];  // blocks each sequence needs mapped (0: nothing to check)
-  __shared__ int s_bad;
+// One launch per step.  Workgroup 0 does the bookkeeping and then, from the same LDS arrays, the attention work list (the
+// same for every layer); the other workgroups fill the rotary table beside it, from the inputs alone (a row's sequence
+// and position need only the speculation lengths and contexts).  Bound by dependent round trips, so every table is
+// walked by all threads side by side.  Three launches before; 845 prompt rows in 3 sequences took 100 us when a thread
+// laid out a whole sequence's rows (120 us with the other two launches, 9.9 now; 618 rows of 64 sequences 32 -> 15, 144 of 16
+// 17 -> 9).
+constexpr int PREP_THREADS = 1024;
+
+// s_row0[b] = first row of sequence b (b = 0 .. B), from s_row0[b + 1] = rows of sequence b.  Every thread of the workgroup.
+__device__ __forceinline__ void scan_rows(int32_t* s_row0, int B, int32_t* s_wave) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int per = (B + PREP_THREADS - 1) / PREP_THREADS, lo = min(tid * per, B), hi = min(lo + per, B);
+  int sum = 0;
+  for (int b = lo; b < hi; ++b) sum += s_row0[b + 1];
+  int inc = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int t = __shfl_up(inc, o, 64);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  int at = inc - sum;
+  for (int w = 0; w < wave; ++w) at += s_wave[w];
+  for (int b = lo; b < hi; ++b) {
+    at += s_row0[b + 1];
+    s_row0[b + 1] = at;
+  }
+  if (tid == 0) s_row0[0] = 0;
+  __syncthreads();
+}
+// the sequence of row m: largest b with s_row0[b] <= m (every sequence has at least one row)
+__device__ __forceinline__ int seq_of_row(const int32_t* s_row0, int B, int m) {
+  int lo = 0, hi = B - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (s_row0[mid] <= m) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+
+// cos/sin of the rotary angles, evaluated in double once per step and shared by all layers
+__device__ __forceinline__ void rope_rows(const PrepArgs& a, const int32_t* s_row0, const int32_t* s_ctx) {
+  const int half = a.rope_half, rows = PREP_THREADS / half;
+  const int m = ((int)blockIdx.x - 1) * rows + (int)threadIdx.x / half, i = (int)threadIdx.x % half;
+  if (m >= a.M || (int)threadIdx.x >= rows * half) return;
+  const int b = seq_of_row(s_row0, a.B, m);
+  const int p = s_ctx[b] + m - s_row0[b];  // (the rows of a disabled sequence are never used)
+  const double inv = pow((double)a.rope_base, -2.0 * (double)i / (double)(2 * half));
+  const double ang = (double)p * inv;
+  a.rope_cos[(size_t)m * half + i] = (float)cos(ang);
+  a.rope_sin[(size_t)m * half + i] = (float)sin(ang);
+}
+
+// LDS: six int32 arrays of B + 1 entries
+__global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
+  extern __shared__ __attribute__((aligned(16))) int32_t s_prep[];
+  __shared__ int32_t s_wave[PREP_THREADS / 64];
+  __shared__ int s_bad, s_tps;
   __shared__ unsigned long long s_tiles;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, B = a.B;
+  int32_t* s_row0 = s_prep;                 // [B + 1]
+  int32_t* s_ok = s_row0 + B + 1;           // [B]
+  int32_t* s_nb = s_ok + B + 1;             // [B] blocks a sequence needs mapped (0: nothing to check); later tiles per workgroup
+  int32_t* s_cnt = s_nb + B + 1;            // [B] attention workgroups of a sequence
+  int32_t* s_spl = s_cnt + B + 1;           // [B] its KV splits
+  int32_t* s_ctx = s_spl + B + 1;           // [B] context
   if (tid == 0) { s_bad = 0; s_tiles = 0ull; }
   __syncthreads();
   // pass 1: per-sequence validation
-  for (int b = tid; b < a.B; b += blockDim.x) {
+  for (int b = tid; b < B; b += PREP_THREADS) {
     const int k = a.spec_len[b];
     const int ctx = a.ctx_lens[b];
+    s_row0[b + 1] = (k < 0 || k > a.k_max) ? 1 : k + 1;
+    s_ctx[b] = ctx;
+    if (blockIdx.x > 0) continue;
     int ok = 1;
     int flags = 0;
     int nb = 0;
     if (k < 0 || k > a.k_max) { ok = 0; flags |= MN_DEV_SPEC_LEN; }
-    s_row0[b + 1] = (k < 0 || k > a.k_max) ? 1 : k + 1;
     if (ok) {
       const long need = (long)ctx + k + 1;
       if (ctx < 0 || need > (long)a.max_blocks_per_seq * a.block_size) { ok = 0; flags |= MN_DEV_BLOCK_TABLE; }
@@ -44,20 +109,37 @@ __global__ void __launch_bounds__(1024) prepare_kernel(PrepArgs a) {
     }
   }
   __syncthreads();
-  // pass 1b: every mapped block of every sequence, all threads side by side (a long context has
-  // hundreds of table entries; one thread walking them is a chain of dependent loads)
-  for (long idx = tid; idx < (long)a.B * a.max_blocks_per_seq; idx += blockDim.x) {
-    const int b = (int)(idx / a.max_blocks_per_seq), i = (int)(idx % a.max_blocks_per_seq);
-    if (i >= s_nb[b]) continue;
-    const int pb = a.block_tables[idx];
-    if (pb < 0 || pb >= a.num_blocks) {
-      atomicAnd(&s_ok[b], 0);
-      if (a.dev_status) atomicOr(a.dev_status, MN_DEV_BLOCK_TABLE);
+  if (blockIdx.x > 0) {                     // (whole workgroup)
+    scan_rows(s_row0, B, s_wave);
+    rope_rows(a, s_row0, s_ctx);
+    return;
+  }
+  // pass 1b: every mapped block of every sequence, all threads side by side (a long context has hundreds of table
+  // entries; one thread walking them is a chain of dependent loads), eight entries per thread in flight
+  {
+    const int mb = a.max_blocks_per_seq, step_b = PREP_THREADS / mb, step_i = PREP_THREADS % mb;
+    int b = tid / mb, i = tid % mb;
+    while (b < B) {
+      int pb[8], bb[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        bb[u] = b < B && i < s_nb[b] ? b : -1;
+        pb[u] = bb[u] >= 0 ? a.block_tables[(size_t)b * mb + i] : 0;
+        b += step_b;
+        i += step_i;
+        if (i >= mb) { i -= mb; ++b; }
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (bb[u] >= 0 && (pb[u] < 0 || pb[u] >= a.num_blocks)) {
+          atomicAnd(&s_ok[bb[u]], 0);
+          if (a.dev_status) atomicOr(a.dev_status, MN_DEV_BLOCK_TABLE);
+        }
     }
   }
   // pass 1c: every input token of every sequence that passed the shape checks, likewise
   if (a.last_tok) {
-    for (long idx = tid; idx < (long)a.B * (a.k_max + 1); idx += blockDim.x) {
+    for (long idx = tid; idx < (long)B * (a.k_max + 1); idx += PREP_THREADS) {
       const int b = (int)(idx / (a.k_max + 1)), j = (int)(idx % (a.k_max + 1));
       if (s_nb[b] == 0 || j >= s_row0[b + 1]) continue;  // (s_row0[b+1] still holds q_b = k_b + 1 here)
       const int tok = (j == 0) ? a.last_tok[b] : a.voted[(size_t)b * a.k_max + j - 1];
@@ -68,74 +150,114 @@ __global__ void __launch_bounds__(1024) prepare_kernel(PrepArgs a) {
     }
   }
   __syncthreads();
-  if (tid == 0) {
-    s_row0[0] = 0;
-    for (int b = 0; b < a.B; ++b) s_row0[b + 1] += s_row0[b];
-    if (s_row0[a.B] != a.M) {
-      s_bad = 1;
-      if (a.dev_status) atomicOr(a.dev_status, MN_DEV_SPEC_LEN);
-    }
+  scan_rows(s_row0, B, s_wave);
+  if (tid == 0 && s_row0[B] != a.M) {
+    s_bad = 1;
+    if (a.dev_status) atomicOr(a.dev_status, MN_DEV_SPEC_LEN);
   }
   __syncthreads();
-  const bool bad = s_bad != 0;
   // a device spec_len that disagrees with the launch geometry disables the whole batch
-  if (bad) {
-    if (tid == 0 && a.attn_tps) a.attn_tps[0] = 1 << 20;
-    for (int b = tid; b <= a.B; b += blockDim.x) a.seq_row0[b] = 0;
-    for (int b = tid; b < a.B; b += blockDim.x) { a.seq_ctx[b] = 0; a.seq_ok[b] = 0; }
-    for (int m = tid; m < a.M; m += blockDim.x) { a.row_seq[m] = 0; a.row_j[m] = 0; a.row_pos[m] = -1; a.row_tok[m] = 0; a.row_slot[m] = -1; }
+  if (s_bad != 0) {
+    for (int b = tid; b <= B; b += PREP_THREADS) a.seq_row0[b] = 0;
+    for (int b = tid; b < B; b += PREP_THREADS) { a.seq_ctx[b] = 0; a.seq_ok[b] = 0; }
+    for (int m = tid; m < a.M; m += PREP_THREADS) {
+      a.row_seq[m] = 0; a.row_j[m] = 0; a.row_pos[m] = -1; a.row_tok[m] = 0; a.row_slot[m] = -1;
+      if (a.plan.items) a.plan.row_splits[m] = 0;
+    }
+    if (a.plan.items)
+      for (int i = tid; i < a.plan.grid_items; i += PREP_THREADS) reinterpret_cast<int4*>(a.plan.items)[2 * (size_t)i] = make_int4(-1, 0, 0, 1);
     return;
   }
-  for (int b = tid; b <= a.B; b += blockDim.x) a.seq_row0[b] = s_row0[b];
-  for (int b = tid; b < a.B; b += blockDim.x) {
-    const int ok = s_ok[b];
-    const int ctx = ok ? a.ctx_lens[b] : 0;
+  for (int b = tid; b <= B; b += PREP_THREADS) a.seq_row0[b] = s_row0[b];
+  for (int b = tid; b < B; b += PREP_THREADS) {
+    const int ok = s_ok[b], ctx = ok ? s_ctx[b] : 0, q = s_row0[b + 1] - s_row0[b];
     a.seq_ctx[b] = ctx;
     a.seq_ok[b] = ok;
-    const int r0 = s_row0[b], q = s_row0[b + 1] - s_row0[b];
-    for (int j = 0; j < q; ++j) {
-      a.row_seq[r0 + j] = b;
-      a.row_j[r0 + j] = j;
-      a.row_pos[r0 + j] = ok ? ctx + j : -1;
-      // where the row's K/V are written, looked up once per step instead of once per layer and head
-      a.row_slot[r0 + j] = ok ? a.block_tables[(size_t)b * a.max_blocks_per_seq + (ctx + j) / a.block_size] * a.block_size +
-                                    (ctx + j) % a.block_size
-                              : -1;
-      a.row_tok[r0 + j] = (ok && a.last_tok) ? ((j == 0) ? a.last_tok[b] : a.voted[(size_t)b * a.k_max + j - 1]) : 0;
-    }
     // key tiles of 32, once per group of 128 (query position x head) rows: the work of the sequence in units of
     // one workgroup's tile (integer sum: order-free)
-    if (ok && q > 0)
-      atomicAdd(&s_tiles, (unsigned long long)((ctx + q + 31) >> 5) * (unsigned long long)((q * max(a.q_per_kv, 1) + 127) >> 7));
+    s_nb[b] = ok ? (ctx + q + 31) >> 5 : 0;
+    if (ok) atomicAdd(&s_tiles, (unsigned long long)s_nb[b] * (unsigned long long)((q * max(a.q_per_kv, 1) + 127) >> 7));
+  }
+  for (int m = tid; m < a.M; m += PREP_THREADS) {
+    const int b = seq_of_row(s_row0, B, m), j = m - s_row0[b], ok = s_ok[b];
+    const int p = ok ? s_ctx[b] + j : -1;
+    a.row_seq[m] = b;
+    a.row_j[m] = j;
+    a.row_pos[m] = p;
+    // where the row's K/V are written, looked up once per step instead of once per layer and head
+    a.row_slot[m] = ok ? a.block_tables[(size_t)b * a.max_blocks_per_seq + p / a.block_size] * a.block_size + p % a.block_size : -1;
+    a.row_tok[m] = (ok && a.last_tok) ? ((j == 0) ? a.last_tok[b] : a.voted[(size_t)b * a.k_max + j - 1]) : 0;
+  }
+  if (!a.plan.items) return;
+  __syncthreads();
+  // ---- the attention work list: one record of 8 int32 per (sequence, row group, KV split) that has work: {sequence, row
+  // group, split, splits of the sequence, first row, rows, enabled, context}.  Sequences are ordered by descending key
+  // tiles per workgroup (ties by index), so the longest workgroups start first and the short ones fill the end of
+  // the launch; the records of the grid past the last real one get sequence = -1.  Ranking is a comparison of every pair of
+  // sequences (B <= 4096, once per step).
+  // Balance: a workgroup should take about (all key tiles x KV heads) / (the number of workgroups aimed for) tiles, at
+  // least min_tiles (below that the lead-in of a workgroup and the partial sums cost more than the parallelism wins).
+  // Long sequences of a ragged batch are then cut into more splits than short ones.
+  if (tid == 0) {
+    const unsigned long long w = (unsigned long long)max(a.plan.target_wgs, 1);
+    const unsigned long long per = (s_tiles * (unsigned long long)max(a.kv_heads, 1) + w - 1) / w;
+    s_tps = (int)min(max(per, (unsigned long long)max(a.plan.min_tiles, 1)), (unsigned long long)(1 << 20));
   }
   __syncthreads();
-  // Balance of the attention grid: a workgroup should take about (all key tiles x KV heads) / (the number of
-  // workgroups aimed for) tiles, at least 32 (below that the lead-in of a workgroup and the partial sums cost more than
-  // the parallelism wins).  Long sequences of a ragged batch are then cut into more splits than short ones.
-  if (tid == 0 && a.attn_tps) {
-    const unsigned long long w = (unsigned long long)max(a.attn_wgs, 1);
-    const unsigned long long per = (s_tiles * (unsigned long long)max(a.kv_heads, 1) + w - 1) / w;
-    a.attn_tps[0] = (int)min(max(per, (unsigned long long)max(a.attn_min_tiles, 1)), (unsigned long long)(1 << 20));
+  const int tps = s_tps;
+  for (int b = tid; b < B; b += PREP_THREADS) {
+    const int q = s_row0[b + 1] - s_row0[b], n_tiles = s_nb[b];
+    const int n_rg = (((a.q_per_kv * q + 15) >> 4) + a.plan.tiles16_per_wg - 1) / a.plan.tiles16_per_wg;
+    const int spl = max(1, min(a.plan.n_splits_max, (n_tiles + tps - 1) / max(tps, 1)));
+    s_spl[b] = spl;
+    s_cnt[b] = n_rg * spl;                  // a disabled sequence keeps one workgroup per row group: it writes zeros
+    s_nb[b] = (n_tiles + spl - 1) / spl;
   }
+  __syncthreads();
+  for (int m = tid; m < a.M; m += PREP_THREADS) a.plan.row_splits[m] = s_spl[seq_of_row(s_row0, B, m)];  // for the merge
+  // a wave per sequence: its place among the others, then its records
+  int total = 0;
+  for (int b = tid >> 6; b < B; b += PREP_THREADS / 64) {
+    const int lane = tid & 63, key = s_nb[b], cnt = s_cnt[b], spl = s_spl[b];
+    int off = 0;
+    total = 0;
+    for (int b2 = lane; b2 < B; b2 += 64) {
+      const int c = s_cnt[b2], k2 = s_nb[b2];
+      total += c;
+      if (k2 > key || (k2 == key && b2 < b)) off += c;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      off += __shfl_xor(off, o, 64);
+      total += __shfl_xor(total, o, 64);
+    }
+    const int row0 = s_row0[b], q = s_row0[b + 1] - row0, ok = s_ok[b], ctx = ok ? s_ctx[b] : 0;
+    for (int i = lane; i < cnt; i += 64) {
+      if (off + i >= a.plan.grid_items) break;  // (cannot happen: the grid holds every real record)
+      int4* rec = reinterpret_cast<int4*>(a.plan.items) + 2 * (size_t)(off + i);
+      rec[0] = make_int4(b, i / spl, i % spl, spl);
+      rec[1] = make_int4(row0, q, ok, ctx);
+    }
+  }
+  if ((tid >> 6) < B)                       // (every wave that had a sequence knows the total)
+    for (int i = total + tid; i < a.plan.grid_items; i += min(B, PREP_THREADS / 64) * 64)
+      reinterpret_cast<int4*>(a.plan.items)[2 * (size_t)i] = make_int4(-1, 0, 0, 1);
 }
 
-// cos/sin of the rotary angles, evaluated in double once per step and shared by all layers.
-__global__ void rope_table_kernel(const int32_t* __restrict__ row_pos, int half, float base, float* __restrict__ c,
-                                  float* __restrict__ s) {
-  const int m = blockIdx.x;
-  const int p = row_pos[m] < 0 ? 0 : row_pos[m];
-  for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    const double inv = pow((double)base, -2.0 * (double)i / (double)(2 * half));
-    const double ang = (double)p * inv;
-    c[(size_t)m * half + i] = (float)cos(ang);
-    s[(size_t)m * half + i] = (float)sin(ang);
-  }
-}
-
-void launch_prepare(const PrepArgs& a, hipStream_t st) {
-  // one workgroup; 1024 threads walk the block tables side by side (32 sequences x 512 blocks took 45 us with 256)
-  prepare_kernel<<<1, 1024, 0, st>>>(a);
-  if (a.rope_half > 0 && a.M > 0) rope_table_kernel<<<a.M, 64, 0, st>>>(a.row_pos, a.rope_half, a.rope_base, a.rope_cos, a.rope_sin);
+hipError_t launch_prepare(const PrepArgs& a, hipStream_t st) {
+  const size_t smem = (size_t)6 * (a.B + 1) * sizeof(int32_t);
+  // once per process, whichever thread comes first; a refusal is returned by every call and nothing is launched
+  static std::once_flag attr_once;
+  static hipError_t attr_err = hipSuccess;
+  std::call_once(attr_once, [] {
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(prepare_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)(6 * (MN_MAX_BATCH + 1) * sizeof(int32_t)));
+  });
+  if (attr_err != hipSuccess) return attr_err;
+  const int rows = a.rope_half > 0 ? PREP_THREADS / a.rope_half : 1;
+  const int rope_wgs = a.rope_half > 0 && a.M > 0 ? (a.M + rows - 1) / rows : 0;
+  prepare_kernel<<<1 + rope_wgs, PREP_THREADS, smem, st>>>(a);
+  return hipSuccess;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -402,10 +524,18 @@ __device__ __forceinline__ void arg_better(float& bv, int& bi, float v, int i) {
   if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
 }
 
-__global__ void __launch_bounds__(256) argmax_rows_kernel(const float* __restrict__ logits, int M, int V, RowInfo rows,
-                                                          int k_max, int32_t* __restrict__ greedy, int B) {
-  __shared__ float sv[4];
-  __shared__ int si[4];
+// One workgroup per row with eight 16-byte pieces in flight per thread.  Up to ARGMAX_WIDE_ROWS rows (fewer than CUs) it has 16
+// waves: a row of 32000 scores is asked for at once (16 rows 9.6 -> 7.3 us); with more rows the chip is full either way and
+// 4 waves leave more workgroups per CU (618 rows 17.8 us, 25.0 with 16 waves).  It also adds up the partial sums of a
+// split vocabulary projection (144 rows, two splits: 22 us as a launch of its own and the argmax, 14 together).
+constexpr int ARGMAX_WIDE_ROWS = 256;
+template <int ARGMAX_THREADS>
+__global__ void __launch_bounds__(ARGMAX_THREADS) argmax_rows_kernel(float* __restrict__ logits, const float* __restrict__ partials,
+                                                                     int S, int M, int V, RowInfo rows, int k_max,
+                                                                     int32_t* __restrict__ greedy, int B) {
+  constexpr int NW = ARGMAX_THREADS / 64;
+  __shared__ float sv[NW];
+  __shared__ int si[NW];
   const int tid = threadIdx.x;
   if ((int)blockIdx.x >= M) {
     // padding blocks: one per sequence
@@ -415,21 +545,34 @@ __global__ void __launch_bounds__(256) argmax_rows_kernel(const float* __restric
     return;
   }
   const int m = blockIdx.x;
-  const float* r = logits + (size_t)m * V;
+  float* r = logits + (size_t)m * V;
+  const float* src = partials ? partials + (size_t)m * V : r;
+  const size_t stride = (size_t)M * V;
   float bv = -INFINITY;
   int bi = 0x7FFFFFFF;
-  if ((V & 3) == 0) {
+  if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(logits) & 15) == 0) {
     // 16-byte pieces, eight in flight per thread before any is looked at (one piece per round trip is bound
     // by memory latency); a thread's indices grow, and ties between threads are settled by arg_better
-    const float4* r4 = reinterpret_cast<const float4*>(r);
     const int n4 = V >> 2;
-    for (int i0 = tid; i0 < n4; i0 += 8 * 256) {
+    for (int i0 = tid; i0 < n4; i0 += 8 * ARGMAX_THREADS) {
       float4 p[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) p[u] = r4[min(i0 + u * 256, n4 - 1)];
+      for (int u = 0; u < 8; ++u) p[u] = reinterpret_cast<const float4*>(src)[min(i0 + u * ARGMAX_THREADS, n4 - 1)];
+      if (partials) {
+        for (int s = 1; s < S; ++s) {       // (fixed order)
+          float4 x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) x[u] = reinterpret_cast<const float4*>(src + s * stride)[min(i0 + u * ARGMAX_THREADS, n4 - 1)];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) { p[u].x += x[u].x; p[u].y += x[u].y; p[u].z += x[u].z; p[u].w += x[u].w; }
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (i0 + u * ARGMAX_THREADS < n4) reinterpret_cast<float4*>(r)[i0 + u * ARGMAX_THREADS] = p[u];
+      }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int i4 = i0 + u * 256;
+        const int i4 = i0 + u * ARGMAX_THREADS;
         if (i4 < n4) {
           arg_better(bv, bi, p[u].x, 4 * i4);
           arg_better(bv, bi, p[u].y, 4 * i4 + 1);
@@ -439,7 +582,14 @@ __global__ void __launch_bounds__(256) argmax_rows_kernel(const float* __restric
       }
     }
   } else {
-    for (int i = tid; i < V; i += blockDim.x) arg_better(bv, bi, r[i], i);
+    for (int i = tid; i < V; i += ARGMAX_THREADS) {
+      float v = src[i];
+      if (partials) {
+        for (int s = 1; s < S; ++s) v += src[s * stride + i];
+        r[i] = v;
+      }
+      arg_better(bv, bi, v, i);
+    }
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
@@ -450,17 +600,18 @@ __global__ void __launch_bounds__(256) argmax_rows_kernel(const float* __restric
   if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < 4; ++w) arg_better(bv, bi, sv[w], si[w]);
+    for (int w = 1; w < NW; ++w) arg_better(bv, bi, sv[w], si[w]);
     if (bi >= V) bi = 0;
     const int b = rows.row_seq[m];
     if (rows.seq_ok[b]) greedy[(size_t)b * (k_max + 1) + rows.row_j[m]] = bi;
   }
 }
 
-void launch_argmax_rows(const float* logits, int M, int V, const RowInfo& rows, int k_max, int32_t* greedy, int B,
-                        hipStream_t st) {
+void launch_argmax_rows(float* logits, const float* partials, int S, int M, int V, const RowInfo& rows, int k_max,
+                        int32_t* greedy, int B, hipStream_t st) {
   if (M + B <= 0) return;
-  argmax_rows_kernel<<<M + B, 256, 0, st>>>(logits, M, V, rows, k_max, greedy, B);
+  if (M <= ARGMAX_WIDE_ROWS) argmax_rows_kernel<1024><<<M + B, 1024, 0, st>>>(logits, partials, S, M, V, rows, k_max, greedy, B);
+  else argmax_rows_kernel<256><<<M + B, 256, 0, st>>>(logits, partials, S, M, V, rows, k_max, greedy, B);
 }
 
 }  // namespace mn

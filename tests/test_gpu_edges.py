@@ -378,3 +378,35 @@ def _subset_kv(kvh, seqs):
     """A PagedKV image restricted to some sequences (same pages, only their block-table rows)."""
     import dataclasses
     return dataclasses.replace(kvh, block_tables=kvh.block_tables[seqs], ctx_lens=np.asarray(kvh.ctx_lens)[seqs])
+
+
+@pytest.mark.parametrize("mb", [1, 1024, 1700])
+def test_table_check_reaches_every_entry(mb):
+    """The row bookkeeping walks the block tables with a fixed stride: a damaged entry in the last place of a table as long
+    as, shorter and longer than that stride disables its sequence only."""
+    from paper_2402_15678_amd import binding, harness
+    desc = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 1, 128, 2, 2, 64, 128, 8, 32768)
+    model = harness.DeviceModel.from_host(desc, synth.make_weights(desc, 1))
+    B, ctx = 3, mb * 16 - 1
+    kvd = harness.DeviceKV.random_on_device(desc, [ctx] * B, [0] * B, 5)
+    q = torch.randn((B, 2, 64), device="cuda:0").half()
+    spec = _i32(np.zeros(B))
+
+    def run():
+        out, st = torch.full((B, 128), 7.0, dtype=torch.float16, device="cuda:0"), _i32([0])
+        wsb = binding.mn_workspace_bytes(model.ctx, B, B, ctx + 1)
+        ws = torch.empty(wsb, dtype=torch.uint8, device="cuda:0")
+        binding.mn_attention(model.ctx, q.data_ptr(), spec.data_ptr(), binding.host_i32([0] * B), B, ctx + 1, kvd.c, 0,
+                             out.data_ptr(), ws.data_ptr(), wsb, st.data_ptr(), harness.stream_ptr())
+        torch.cuda.synchronize()
+        return out, st.item()
+
+    ref, st = run()
+    assert st == 0 and torch.isfinite(ref).all()
+    for b in range(B):
+        saved = kvd.block_tables.clone()
+        kvd.block_tables[b, mb - 1] = 10 ** 6
+        got, st = run()
+        kvd.block_tables.copy_(saved)
+        others = [i for i in range(B) if i != b]
+        assert st == binding.MN_DEV_BLOCK_TABLE and (got[b] == 0).all() and torch.equal(got[others], ref[others])
