@@ -85,12 +85,13 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// Sum over a block of NW waves; every thread gets the result.  `red` holds NW floats.
-template <int NW>
+// Sum over a block of NW waves; every thread gets the result.  `red` holds NW floats; FRESH: nothing of the block has read
+// or written it yet.
+template <int NW, bool FRESH = false>
 __device__ __forceinline__ float block_sum(float v, float* red) {
   v = wave_sum(v);
   const int w = threadIdx.x >> 6;
-  __syncthreads();
+  if (!FRESH) __syncthreads();
   if ((threadIdx.x & 63) == 0) red[w] = v;
   __syncthreads();
   float t = 0.f;
