@@ -68,10 +68,13 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
       const int off = key % bs;
       float d = 0.f;
       const T* kb = Kp + ((size_t)pb * a.Hkv + kh) * (size_t)hd * bs;
+      // (eight consecutive elements at once, four pieces in flight: one element per load was a chain of round trips)
+#pragma unroll 4
       for (int c = 0; c < hd / 8; ++c) {
-        const T* kk = kb + ((size_t)c * bs + off) * 8;
+        struct __attribute__((aligned(sizeof(T)))) Piece { T x[8]; };
+        const Piece kk = *reinterpret_cast<const Piece*>(kb + ((size_t)c * bs + off) * 8);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) d = fmaf(s_q[c * 8 + i], Store<T>::load(kk + i), d);
+        for (int i = 0; i < 8; ++i) d = fmaf(s_q[c * 8 + i], (float)kk.x[i], d);
       }
       s = d;
     }
@@ -92,6 +95,7 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
     acc *= alpha;
     const int cnt = min(GEN_THREADS, nkeys - k0);
     if (kg < ng) {
+#pragma unroll 8
       for (int i = kg; i < cnt; i += ng) {
         const int key2 = k0 + i;
         const T* vb = Vp + ((size_t)s_pb[i] * a.Hkv + kh) * (size_t)hd * bs;

@@ -670,8 +670,11 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int3
   pack_weight_kernel<<<(int)blocks, 256, 0, st>>>(reinterpret_cast<const bf16_t*>(src), reinterpret_cast<bf16_t*>(dst), N, K, half, status);
 }
 
-// fp32 model (the small configuration): one wave per output column, lanes split k, up to 8 rows
-// at a time.  Plain FMA; the summation order is fixed (per-lane partial sums, then a xor tree).
+// fp32 model (the small configuration): one wave per output column, lanes split k in pieces of four, up to 8 rows at a
+// time.  Plain FMA; bound by memory latency, so a trip's loads (F32_TRIP pieces of the column and of every row) all go
+// out before any is used, and the eight sums are reduced over the lanes together (10 exchanges instead of 48).  The
+// summation order is fixed.  5 rows: 256 columns x 1024 16.5 -> 3.5 us, 4096 x 256 10.0 -> 6.6 (one element per lane and trip before).
+constexpr int F32_TRIP = 4;
 __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        float* __restrict__ out, const float* __restrict__ bias, int M,
                                                        int N, int K) {
@@ -683,17 +686,40 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] = 0.f;
   const float* wr = W + (size_t)n * K;
-  for (int k = lane; k < K; k += 64) {
-    const float w = wr[k];
+  const int rows = min(8, M - m0);
+  for (int k0 = 4 * lane; k0 < K; k0 += F32_TRIP * 256) {
+    f32x4_u w[F32_TRIP], x[8][F32_TRIP];
+#pragma unroll
+    for (int t = 0; t < F32_TRIP; ++t) w[t] = *reinterpret_cast<const f32x4_u*>(wr + min(k0 + t * 256, K - 4));
 #pragma unroll
     for (int i = 0; i < 8; ++i)
-      if (m0 + i < M) acc[i] = fmaf(A[(size_t)(m0 + i) * K + k], w, acc[i]);
-  }
+      if (i < rows) {  // (uniform)
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const float s = wave_sum(acc[i]);
-    if (lane == 0 && m0 + i < M) out[(size_t)(m0 + i) * N + n] = s + (bias ? bias[n] : 0.f);
+        for (int t = 0; t < F32_TRIP; ++t) x[i][t] = *reinterpret_cast<const f32x4_u*>(A + (size_t)(m0 + i) * K + min(k0 + t * 256, K - 4));
+      }
+#pragma unroll
+    for (int t = 0; t < F32_TRIP; ++t) {
+      if (k0 + t * 256 >= K) break;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (i < rows) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[i] = fmaf(x[i][t][e], w[t][e], acc[i]);
+        }
+    }
   }
+  // sums over the lanes: every exchange with the lane 32, 16, 8 away halves the rows a lane still carries
+  float s4[4], s2[2], s;
+  const bool hi = lane & 32, mid = lane & 16, lo = lane & 8;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s4[i] = (hi ? acc[4 + i] : acc[i]) + __shfl_xor(hi ? acc[i] : acc[4 + i], 32, 64);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) s2[i] = (mid ? s4[2 + i] : s4[i]) + __shfl_xor(mid ? s4[i] : s4[2 + i], 16, 64);
+  s = (lo ? s2[1] : s2[0]) + __shfl_xor(lo ? s2[0] : s2[1], 8, 64);
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  const int row = lane >> 3;  // = 4 hi + 2 mid + lo
+  if ((lane & 7) == 0 && row < rows) out[(size_t)(m0 + row) * N + n] = s + (bias ? bias[n] : 0.f);
 }
 
 // out[i] = sum_s partials[s][i], ascending s

@@ -256,6 +256,27 @@ def test_append_inside_attention(hb, name, desc, ctx, ks):
     _reduced_case(hb, wl, desc.n_layers, len(ctx), 1, ctx_override=ctx, k_override=ks, min_decisive=0)
 
 
+@pytest.mark.parametrize("d,heads,ffn,vocab,ks", [(64, 2, 64, 1, [0]), (192, 3, 320, 37, [7, 0, 8]), (1088, 4, 1024, 130, [2, 3])])
+def test_fp32_projection_edges(hb, d, heads, ffn, vocab, ks):
+    """The fp32 projection's pieces: contractions shorter than a wave's 256 elements, between one and four pieces per lane and
+    just past them, column counts short of a workgroup, 1, 7, 8, 9 and 18 rows."""
+    desc = synth.ModelDesc(synth.ARCH_OPT, synth.DT_F32, 1, d, heads, heads, 64 if d != 1088 else 256, ffn, vocab, 512)
+    wl = synth.Workload("fp32-edges", desc, len(ks), 0, 40, 0, 8, 2, 0.3, seed=9200)
+    if vocab == 1:                                       # a vocabulary of one: nothing to corrupt a draft with
+        W = synth.make_weights(desc, 1)
+        harness, _ = hb
+        kvh = synth.make_paged_kv(desc, [5], [0], 1)
+        ses = harness.VerifySession(harness.DeviceModel.from_host(desc, W), harness.DeviceKV.from_host(desc, kvh), 1, 0, 1, 6,
+                                    want_logits=True)
+        t = _i32([0])
+        ses.forward(t, t, [0])
+        want = orc.decoder_step(desc, W, [[0]], util.oracle_caches(desc, kvh))[0]
+        torch.cuda.synchronize()
+        assert np.abs(ses.logits.cpu().numpy() - want).max() < 1e-4
+        return
+    _reduced_case(hb, wl, 1, len(ks), 1, ctx_override=[20 + i for i in range(len(ks))], k_override=ks, min_decisive=0)
+
+
 def test_one_pass_equals_sequential_decodes_two_layers(hb):
     """Scoring k + 1 positions in one pass against k + 1 single-position passes of the library itself (section 2.1:
     the speculated tokens are scored in parallel with the outcome of scoring them one by one), at the 70B width and
