@@ -183,15 +183,21 @@ static Layout make_layout(const mn_model_desc& d, int B, int M, int max_ctx) {
   // Partial sums of the widest projection at the largest split it can get with M rows OR FEWER: a workspace
   // sized for max_rows must serve every step with at most that many rows, and the k-split a projection gets is
   // not monotone in the row count (it drops where the kernel family changes and where a further row block
-  // starts).  The split is constant between those borders, all of which are multiples of 16, so the largest
-  // need is found at the right ends: M itself and every multiple of 16 below it.
+  // starts).  Up to 144 rows the split is constant between borders that are multiples of 16, so the largest
+  // need is found at the right ends: M itself and every multiple of 16 below it; beyond, the planner gives a bound.
   const int nqkv = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int w1r = d.d_ffn * (d.arch == MN_ARCH_LLAMA ? 2 : 1);
   size_t pmax = 0;
   const int Ns[5] = {nqkv, d.d_model, w1r, d.d_model, d.vocab};
   const int Ks[5] = {d.d_model, d.n_heads * d.head_dim, d.d_model, d.d_ffn, d.d_model};
   for (int i = 0; i < 5; ++i) {
-    for (int m2 = (int)Mr;; m2 = (m2 - 1) / 16 * 16) {
+    int m2 = (int)Mr;
+    if (m2 > 144) {
+      const size_t rows = d.dtype == MN_DT_BF16 ? gemm_big_partial_rows(m2, Ns[i]) : (size_t)m2;
+      if (rows * Ns[i] * 4 > pmax) pmax = rows * Ns[i] * 4;
+      m2 = 144;
+    }
+    for (;; m2 = (m2 - 1) / 16 * 16) {
       const size_t s = (size_t)gemm_pick_split(m2, Ns[i], Ks[i], d.dtype);
       const size_t b = s * (size_t)m2 * Ns[i] * 4;
       if (b > pmax) pmax = b;

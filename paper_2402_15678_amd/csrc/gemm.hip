@@ -782,6 +782,51 @@ static int few_rows_nw(int M, int slices, int iters, int split) {
   return best;
 }
 
+// Big-tile kernel: row tiles per wave (AT, a workgroup has 32 AT rows x 256 columns) and k-splits together.  One workgroup
+// per CU, so the launch is whole rounds of 256 workgroups; a k-step of 32 takes about 0.13 + 0.0875 AT us, a split's
+// partial sums are written and read once more at about 5 TB/s.  The split is the largest that stays within one round
+// (at least 16 blocks of 128 k each).  Measured at 845 rows, AT = 5 .. 10: 57344 x 8192 876 833 788 850 727 783 us, 32000 x 8192
+// 498 510 453 487 467 498; 8192 x 28672 in 2 splits, AT = 7, 9, 10: 358 376 401 (AT = 10 was taken for each before,
+// which pads 845 rows to 960 and leaves 64 CUs idle in the split matrices); at 618 rows AT = 10 is best everywhere.
+// The partial-sum term takes the rows in steps of 16: the split is constant between multiples of 16 (see make_layout).
+struct BigPlan {
+  int at, split;
+};
+constexpr int BIG_WGS = 256;
+static BigPlan big_plan(int M, int N, int K, int forced_split) {
+  const int gx = ((N + NWG - 1) / NWG + 1) / 2, iters = K / KB;
+  BigPlan best{10, 1};
+  long best_cost = -1;
+  for (int at = 10; at >= 5; --at) {
+    const int rb = (M + 32 * at - 1) / (32 * at);
+    int s = forced_split;
+    if (s < 1) {
+      s = BIG_WGS / ((long)gx * rb < BIG_WGS ? gx * rb : BIG_WGS);
+      if (s > iters / 16) s = iters / 16;
+      if (s > MN_MAX_SPLIT_K) s = MN_MAX_SPLIT_K;
+      if (s < 1) s = 1;
+    }
+    const int per = (iters + s - 1) / s;
+    s = (iters + per - 1) / per;  // drop splits that would get no iteration
+    const long rounds = ((long)gx * rb * s + BIG_WGS - 1) / BIG_WGS;
+    const long cost = rounds * per * KS * (1300 + 875 * at) / 10 + (long)s * ((M + 15) / 16 * 16) * N * 8 / 5000;  // ns
+    if (best_cost < 0 || cost < best_cost) {
+      best = BigPlan{at, s};
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+// Upper bound of split * rows over all row counts from 145 to M of the big-tile kernel's plans: a split launch is at most
+// BIG_WGS workgroups of at most 320 rows.
+size_t gemm_big_partial_rows(int M, int N) {
+  const size_t gx = ((N + NWG - 1) / NWG + 1) / 2, rows = M;
+  const size_t split_rows = BIG_WGS / (gx < BIG_WGS ? gx : BIG_WGS) * 320;
+  const size_t most = split_rows < (size_t)MN_MAX_SPLIT_K * rows ? split_rows : (size_t)MN_MAX_SPLIT_K * rows;
+  return most > rows ? most : rows;
+}
+
 static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
   const int forced_nw = MN_TUNE("MN_GEMM_NW", 0);
   const int slices = ((N + NWG - 1) / NWG) * 4;  // 32-column wave slices of the padded matrix
@@ -799,18 +844,7 @@ static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
   // (tuning builds: the plan of the projection with N output columns by hand)
   if (MN_TUNE("MN_GEMM_PLAN_N", 0) == N && MN_TUNE("MN_GEMM_PLAN_K", 0) == K && M > 96 && M <= 144)
     return GemmPlan{MN_TUNE("MN_GEMM_PLAN_NW", 4), MN_TUNE("MN_GEMM_PLAN_SPLIT", 1)};
-  if (M > 144 || (big_min_m() > 0 && M >= big_min_m())) {  // big-tile kernel: 256-column groups x row blocks, one workgroup per CU
-    const int gx = (slices / 4 + 1) / 2;
-    int rb = 1 << 30;
-    for (int at : {10, 8, 6}) rb = min(rb, (M + 32 * at - 1) / (32 * at) * at);  // (rows padded least; see big_at)
-    int blocks = 1;
-    for (int at : {10, 8, 6})
-      if ((M + 32 * at - 1) / (32 * at) * at == rb) { blocks = (M + 32 * at - 1) / (32 * at); break; }
-    if (M <= 160) blocks = 1;
-    best.nw = 8;
-    best.split = splits_for(gx * blocks, tune().target / 2);
-    return best;
-  }
+  if (M > 144 || (big_min_m() > 0 && M >= big_min_m())) return GemmPlan{8, big_plan(M, N, K, forced_split).split};
   if (M <= 96) {
     // up to six row tiles: the k-split is picked for 4-wave workgroups.  Few rows make an iteration cheap, so a split may be
     // as short as 8 iterations, and one workgroup per CU is enough (measured at 40 rows: the 5120 x 5120 matrix
@@ -894,20 +928,6 @@ static void launch_few_rows(const GemmArgs& a, hipStream_t st) {
   }
 }
 
-// rows per workgroup of the big-tile kernel: the AT (row tiles per wave, two waves deep) that pads M least
-static int big_at(int M) {
-  if (M <= 160) return 5;
-  int best = 10, best_rows = 1 << 30;
-  for (int at : {10, 8, 6}) {
-    const int rb = (M + 32 * at - 1) / (32 * at);
-    if (rb * 32 * at < best_rows) {
-      best_rows = rb * 32 * at;
-      best = at;
-    }
-  }
-  return best;
-}
-
 template <int AT>
 static hipError_t launch_big(const GemmArgs& a, hipStream_t st) {
   const int iters = a.K / KB;
@@ -972,11 +992,13 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
     if (!MN_TUNE("MN_GEMM_BIG", 1)) {  // 0 = chunks of the streaming kernel
       launch_bf16_mt<8, 4>(a, (tiles + 7) / 8, st);
     } else {
-      switch (big_at(a.M)) {
+      switch (big_plan(a.M, a.N, a.K, a.split_k).at) {
         case 5: return launch_big<5>(a, st);
-        case 10: return launch_big<10>(a, st);
+        case 6: return launch_big<6>(a, st);
+        case 7: return launch_big<7>(a, st);
         case 8: return launch_big<8>(a, st);
-        default: return launch_big<6>(a, st);
+        case 9: return launch_big<9>(a, st);
+        default: return launch_big<10>(a, st);
       }
     }
   }

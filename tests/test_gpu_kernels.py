@@ -138,7 +138,12 @@ def _check_accept(hb, g, B, k_max):
                                          # three, seven and eight (the balance over the CUs), column counts short of a block
                                          (16, 2304, 768, 0), (32, 700, 3072, 0), (33, 700, 3072, 0), (95, 2304, 768, 0),
                                          (5, 20480, 256, 1), (48, 20400, 128, 1), (64, 50272, 128, 1), (1, 64000, 128, 1),
-                                         (96, 63990, 128, 1)])
+                                         (96, 63990, 128, 1),
+                                         # the many-rows kernel at every tile height (160 to 320 rows), each one row over and
+                                         # under it, its splits chosen and forced
+                                         (146, 4096, 4096, 0), (160, 200, 256, 1), (161, 4096, 4096, 0), (193, 8192, 2048, 0),
+                                         (224, 300, 384, 3), (225, 8192, 2048, 0), (257, 8192, 2048, 0), (288, 520, 512, 2),
+                                         (289, 2000, 2048, 0), (845, 4096, 4096, 0), (449, 57344, 256, 1), (864, 57344, 128, 1)])
 def test_proj_gemm_matches_fp64(hb, M, N, K, split):
     harness, binding = hb
     g = synth.stream(79, M, N, K)
