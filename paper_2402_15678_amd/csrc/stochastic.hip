@@ -38,9 +38,9 @@ __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
 }
 
 // One workgroup of 16 waves per row, the row's exponentials in registers.  The kernels are bound by the fp64
-// exponentials of one row on one CU (about 30 fp64 instructions per token, 64 lanes per clock: 6 us for 32000 tokens) and by
+// exponentials of one row on one CU (about 25 fp64 instructions per token, 64 lanes per clock: 6 us for 32000 tokens) and by
 // the chain load -> maximum -> exponentials -> sum -> draw, so a row is read once, every exponential is computed once,
-// and every sum is a wave reduction.  Measured at 32000 tokens: 29.5 us for the 144 positions of 16 requests and 24.2 us
+// and every sum is a wave reduction.  Measured at 32000 tokens: 25.3 us for the 144 positions of 16 requests and 20.2 us
 // for 16 drafted tokens; 149 and 162 us with 256 threads per row, the scores re-read for every pass and one thread
 // adding the 256 partial sums of every tile.
 constexpr int SV_THREADS = 1024;
@@ -79,6 +79,7 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 
 struct DrawShared {
   double seg[SV_MAX_SEGS];    // mass of every segment
+  double2 pow2[64];           // 2^(j/64), rest
   double red[SV_WAVES];
   float redf[SV_WAVES];
   double target[2];           // target inside the chosen segment, total mass
@@ -92,16 +93,75 @@ __device__ __forceinline__ double div_by(double x, double c, double inv) {
   return fma(fma(-c, q, x), inv, q);
 }
 
-// exp((l - max) / T) with T's reciprocal (inv > 0) or, for temperatures so extreme that the reciprocal leaves the normal
-// range (inv == 0), by division.  Differences below -800 T are cut there (the exponential is zero long before), so
-// that a masked token (minus infinity) stays finite; NaN passes through.
+// 2^(j/64), j = 0 .. 63, each as its nearest double and what that leaves over
+__device__ const double kPow2[128] = {
+    0x1.0000000000000p+0, 0x0.0p+0, 0x1.02c9a3e778061p+0, -0x1.19083535b085dp-56,
+    0x1.059b0d3158574p+0, 0x1.d73e2a475b465p-55, 0x1.0874518759bc8p+0, 0x1.186be4bb284ffp-57,
+    0x1.0b5586cf9890fp+0, 0x1.8a62e4adc610bp-54, 0x1.0e3ec32d3d1a2p+0, 0x1.03a1727c57b53p-59,
+    0x1.11301d0125b51p+0, -0x1.6c51039449b3ap-54, 0x1.1429aaea92de0p+0, -0x1.32fbf9af1369ep-54,
+    0x1.172b83c7d517bp+0, -0x1.19041b9d78a76p-55, 0x1.1a35beb6fcb75p+0, 0x1.e5b4c7b4968e4p-55,
+    0x1.1d4873168b9aap+0, 0x1.e016e00a2643cp-54, 0x1.2063b88628cd6p+0, 0x1.dc775814a8495p-55,
+    0x1.2387a6e756238p+0, 0x1.9b07eb6c70573p-54, 0x1.26b4565e27cddp+0, 0x1.2bd339940e9d9p-55,
+    0x1.29e9df51fdee1p+0, 0x1.612e8afad1255p-55, 0x1.2d285a6e4030bp+0, 0x1.0024754db41d5p-54,
+    0x1.306fe0a31b715p+0, 0x1.6f46ad23182e4p-55, 0x1.33c08b26416ffp+0, 0x1.32721843659a6p-54,
+    0x1.371a7373aa9cbp+0, -0x1.63aeabf42eae2p-54, 0x1.3a7db34e59ff7p+0, -0x1.5e436d661f5e3p-56,
+    0x1.3dea64c123422p+0, 0x1.ada0911f09ebcp-55, 0x1.4160a21f72e2ap+0, -0x1.ef3691c309278p-58,
+    0x1.44e086061892dp+0, 0x1.89b7a04ef80d0p-59, 0x1.486a2b5c13cd0p+0, 0x1.3c1a3b69062f0p-56,
+    0x1.4bfdad5362a27p+0, 0x1.d4397afec42e2p-56, 0x1.4f9b2769d2ca7p+0, -0x1.4b309d25957e3p-54,
+    0x1.5342b569d4f82p+0, -0x1.07abe1db13cadp-55, 0x1.56f4736b527dap+0, 0x1.9bb2c011d93adp-54,
+    0x1.5ab07dd485429p+0, 0x1.6324c054647adp-54, 0x1.5e76f15ad2148p+0, 0x1.ba6f93080e65ep-54,
+    0x1.6247eb03a5585p+0, -0x1.383c17e40b497p-54, 0x1.6623882552225p+0, -0x1.bb60987591c34p-54,
+    0x1.6a09e667f3bcdp+0, -0x1.bdd3413b26456p-54, 0x1.6dfb23c651a2fp+0, -0x1.bbe3a683c88abp-57,
+    0x1.71f75e8ec5f74p+0, -0x1.16e4786887a99p-55, 0x1.75feb564267c9p+0, -0x1.0245957316dd3p-54,
+    0x1.7a11473eb0187p+0, -0x1.41577ee04992fp-55, 0x1.7e2f336cf4e62p+0, 0x1.05d02ba15797ep-56,
+    0x1.82589994cce13p+0, -0x1.d4c1dd41532d8p-54, 0x1.868d99b4492edp+0, -0x1.fc6f89bd4f6bap-54,
+    0x1.8ace5422aa0dbp+0, 0x1.6e9f156864b27p-54, 0x1.8f1ae99157736p+0, 0x1.5cc13a2e3976cp-55,
+    0x1.93737b0cdc5e5p+0, -0x1.75fc781b57ebcp-57, 0x1.97d829fde4e50p+0, -0x1.d185b7c1b85d1p-54,
+    0x1.9c49182a3f090p+0, 0x1.c7c46b071f2bep-56, 0x1.a0c667b5de565p+0, -0x1.359495d1cd533p-54,
+    0x1.a5503b23e255dp+0, -0x1.d2f6edb8d41e1p-54, 0x1.a9e6b5579fdbfp+0, 0x1.0fac90ef7fd31p-54,
+    0x1.ae89f995ad3adp+0, 0x1.7a1cd345dcc81p-54, 0x1.b33a2b84f15fbp+0, -0x1.2805e3084d708p-57,
+    0x1.b7f76f2fb5e47p+0, -0x1.5584f7e54ac3bp-56, 0x1.bcc1e904bc1d2p+0, 0x1.23dd07a2d9e84p-55,
+    0x1.c199bdd85529cp+0, 0x1.11065895048ddp-55, 0x1.c67f12e57d14bp+0, 0x1.2884dff483cadp-54,
+    0x1.cb720dcef9069p+0, 0x1.503cbd1e949dbp-56, 0x1.d072d4a07897cp+0, -0x1.cbc3743797a9cp-54,
+    0x1.d5818dcfba487p+0, 0x1.2ed02d75b3707p-55, 0x1.da9e603db3285p+0, 0x1.c2300696db532p-54,
+    0x1.dfc97337b9b5fp+0, -0x1.1a5cd4f184b5cp-54, 0x1.e502ee78b3ff6p+0, 0x1.39e8980a9cc8fp-55,
+    0x1.ea4afa2a490dap+0, -0x1.e9c23179c2893p-54, 0x1.efa1bee615a27p+0, 0x1.dc7f486a4b6b0p-54,
+    0x1.f50765b6e4540p+0, 0x1.9d3e12dd8a18bp-54, 0x1.fa7c1819e90d8p+0, 0x1.74853f3a5931ep-55,
+};
+
+// exp((l - max) / T), table-driven (P. T. P. Tang, ACM TOMS 15(2), 1989): (l - max) / T = n ln2/64 + r with |r| <= ln2/128, and
+// exp = 2^(n >> 6) * 2^((n & 63)/64) * (1 + r + .. + r^5/120), the sixth-order term below 2^-54.  The 64 powers lie in LDS, in
+// two pieces (their rounding would be the largest error).  Relative error against 64-bit mantissas, 400000 arguments
+// in [-20, 0]: rms 4.8e-17, largest 1.4e-16 (a correctly rounded exponential: 4.7e-17 and 1.1e-16).
+// About half the instructions of the general function (arguments are never positive), which is most of these kernels' time.
+// The quotient is not rounded on its own: r comes out of one fma with T's reciprocal, so its error is the reciprocal's
+// rounding, what a rounded quotient's would be.  For temperatures so extreme that the reciprocal leaves the normal
+// range (inv == 0) the general function and a division.  Scores more than 800 T below the maximum are cut there (the
+// exponential is zero long before), so that a masked token (minus infinity) stays finite; NaN passes through.
 struct Temp {
-  double T, inv, cut;
-  __device__ __forceinline__ double mass(float l, double dmx) const {
-    double d = (double)l - dmx;
-    if (inv == 0.0) return exp(d / T);  // (uniform)
-    d = d < cut ? cut : d;
-    return exp(div_by(d, T, inv));
+  double T, inv, per_step;   // 1 / T, 64 / (T ln2)
+  const double2* pow2;       // [64] 2^(j/64), rest
+  double dmx;                // largest score of the row
+  float cut;
+  __device__ __forceinline__ void set_max(float mx) {
+    dmx = (double)mx;
+    cut = fmaxf((float)(dmx - 800.0 * T), -3.0e38f);
+  }
+  __device__ __forceinline__ double mass(float l) const {
+    if (inv == 0.0) return exp(((double)l - dmx) / T);  // (uniform)
+    l = l < cut ? cut : l;
+    const double d = (double)l - dmx;
+    const double t = fma(d, per_step, 6755399441055744.0);  // 1.5 * 2^52: the nearest whole number sits in the low bits
+    const double nd = t - 6755399441055744.0;
+    const int n = (int)(uint32_t)__double_as_longlong(t);
+    double r = fma(d, inv, nd * -0x1.62e42fefap-7);   // ln2/64, its first 33 bits (the product with n is exact) ...
+    r = fma(nd, -0x1.cf79abc9e3b3ap-46, r);           // ... and the rest
+    double p = fma(r, 1.0 / 120.0, 1.0 / 24.0);
+    p = fma(r, p, 1.0 / 6.0);
+    p = fma(r, p, 0.5);
+    p = fma(r * r, p, r);
+    const double2 c = pow2[n & 63];
+    return ldexp(c.x + fma(c.x, p, c.y), n >> 6);
   }
 };
 
@@ -111,10 +171,10 @@ struct Temp {
 // of this wave in ascending order.  The masses are summed per segment, one wave finds the segment that holds the target,
 // and the wave that owns it scans it.  Every thread of the workgroup calls it; the result is uniform.  All sums
 // have a fixed order.
-template <typename FB, typename F>
+template <bool ONE, typename FB, typename F>  // ONE: a block per segment (rows of up to 262144 tokens)
 __device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u, DrawShared& sh, int tid) {
   const int lane = tid & 63, wave = tid >> 6;
-  const int grp = seg_blocks(V);
+  const int grp = ONE ? 1 : seg_blocks(V);
   const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK, n_seg = (n_blocks + grp - 1) / grp;
   __syncthreads();  // (the shared arrays of an earlier draw have been read)
   double run = 0.0;
@@ -232,8 +292,8 @@ __device__ __forceinline__ void wave_blocks(int V, int wave, F f) {
 // Largest score of a row, then Z = sum_v exp((l_v - max) / T), both uniform over the workgroup; with TILES > 0 the
 // exponentials stay in ex (zero past the end of the row).
 template <int TILES>
-__device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, const Temp& temp, DrawShared& sh, int tid,
-                                              double (&ex)[TILES > 0 ? TILES : 1][4], double& dmx, double& Z) {
+__device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, Temp& temp, DrawShared& sh, int tid,
+                                              double (&ex)[TILES > 0 ? TILES : 1][4], double& Z) {
   const int lane = tid & 63, wave = tid >> 6;
   f32x4 raw[TILES > 0 ? TILES : 1];
   float mx = -INFINITY;
@@ -243,17 +303,18 @@ __device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V
     wave_blocks<TILES>(V, wave, [&](int, int t) { mx = fmaxf(mx, fmaxf(fmaxf(raw[t][0], raw[t][1]), fmaxf(raw[t][2], raw[t][3]))); });
   mx = wave_max(mx);
   if (lane == 0) sh.redf[wave] = mx;
+  if (tid < 64) sh.pow2[tid] = make_double2(kPow2[2 * tid], kPow2[2 * tid + 1]);
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < SV_WAVES; ++w) mx = fmaxf(mx, sh.redf[w]);
-  dmx = (double)mx;
+  temp.set_max(mx);
   double zp = 0.0;
   wave_blocks<TILES>(V, wave, [&](int blk, int t) {
     const int v = blk * SV_BLOCK + 4 * lane;
     const f32x4 l = TILES > 0 ? raw[t] : load_row4(L, v, V, -INFINITY);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ex[t][e] = v + e < V ? temp.mass(l[e], dmx) : 0.0;
+      ex[t][e] = v + e < V ? temp.mass(l[e]) : 0.0;
       zp += ex[t][e];
     }
   });
@@ -312,10 +373,10 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     return;
   }
   const float* L = logits + (size_t)row * V;
-  const Temp temp{temperature, inv_temperature, -800.0 * temperature};
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, 0.f};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
-  double dmx, Z;
-  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, dmx, Z);
+  double Z;
+  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
   double u_acc, u_res;
   position_uniforms((uint32_t)b, (uint32_t)j, step_lo, step_hi, 0u, seed_lo, seed_hi, u_acc, u_res);
 
@@ -327,7 +388,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     x = voted[(size_t)b * k_max + j];
     Q = draft_probs + ((size_t)b * k_max + j) * V;
     if (x >= 0 && x < V) {
-      const double ox = temp.mass(L[x], dmx) / Z;
+      const double ox = temp.mass(L[x]) / Z;
       const double qx = (double)Q[x];
       keep = (qx <= ox) || (u_acc < ox / qx);
     }
@@ -344,7 +405,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
   auto o4 = [&](int v, double (&o)[4]) {  // probabilities of tokens v .. v+3, recomputed from the scores
     const f32x4 l = load_row4(L, v, V, -INFINITY);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = v + e < V ? div_by(temp.mass(l[e], dmx), Z, inv_z) : 0.0;
+    for (int e = 0; e < 4; ++e) o[e] = v + e < V ? div_by(temp.mass(l[e]), Z, inv_z) : 0.0;
   };
   int tok = -1;
   if constexpr (TILES > 0) {
@@ -358,7 +419,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
         ex[t][e] = Q ? fmax(0.0, o - (double)q[e]) : o;
       }
     });
-    tok = cdf_draw([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
                    [&](int blk, int, double (&m)[4]) {
 #pragma unroll
                      for (int t = 0; t < TILES; ++t)
@@ -366,7 +427,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
                    },
                    V, u_res, sh, tid);
   } else {
-    tok = cdf_draw([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
                    [&](int, int v, double (&m)[4]) {
                      o4(v, m);
                      if (Q) {
@@ -378,7 +439,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
                    V, u_res, sh, tid);
   }
   if (Q && tok < 0) {
-    tok = cdf_draw([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
                    [&](int, int v, double (&m)[4]) {
                      o4(v, m);
 #pragma unroll
@@ -405,17 +466,17 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   __shared__ DrawShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* L = logits + (size_t)b * V;
-  const Temp temp{temperature, inv_temperature, -800.0 * temperature};
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, 0.f};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
-  double dmx, Z;
-  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, dmx, Z);
+  double Z;
+  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
   double u_unused, u;
   position_uniforms((uint32_t)b, t_pos, step_lo, step_hi, consumer, seed_lo, seed_hi, u_unused, u);
   const double inv_z = 1.0 / Z;
   auto q4 = [&](int v, double (&m)[4]) {  // the fp32 probabilities of tokens v .. v+3
     const f32x4 l = load_row4(L, v, V, -INFINITY);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = v + e < V ? (double)(float)div_by(temp.mass(l[e], dmx), Z, inv_z) : 0.0;
+    for (int e = 0; e < 4; ++e) m[e] = v + e < V ? (double)(float)div_by(temp.mass(l[e]), Z, inv_z) : 0.0;
   };
   float* P = probs ? probs + (size_t)b * probs_stride : nullptr;
   wave_blocks<TILES>(V, wave, [&](int blk, int t) {
@@ -439,7 +500,7 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   });
   int tok;
   if constexpr (TILES > 0)
-    tok = cdf_draw([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
                    [&](int blk, int, double (&m)[4]) {
 #pragma unroll
                      for (int t = 0; t < TILES; ++t)
@@ -447,8 +508,16 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
                    },
                    V, u, sh, tid);
   else
-    tok = cdf_draw([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
-                   [&](int, int v, double (&m)[4]) { q4(v, m); }, V, u, sh, tid);
+    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+                   [&](int, int v, double (&m)[4]) {
+                     if (P && v + 3 < V) {  // (this thread wrote them itself: cheaper than the exponentials again)
+                       const f32x4_u q = *reinterpret_cast<const f32x4_u*>(P + v);
+                       m[0] = (double)q[0]; m[1] = (double)q[1]; m[2] = (double)q[2]; m[3] = (double)q[3];
+                     } else {
+                       q4(v, m);
+                     }
+                   },
+                   V, u, sh, tid);
   if (tid == 0) tokens[(size_t)b * token_stride] = tok;
 }
 
