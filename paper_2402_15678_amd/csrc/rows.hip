@@ -409,48 +409,59 @@ void launch_norm(const NormArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------------------
 // rotary embedding + tentative KV append
 // ------------------------------------------------------------------------------------------
-// grid (ceil((H + 2 Hkv) / heads per block), M), 256 threads: a block takes 512 / hd consecutive heads of one row
-// (one-wave blocks were bound by the rate at which workgroups can be dispatched: 11520 of them at the 70B shape);
-// thread (head, t) owns the pair (t, t + hd/2) of its head.
+// grid (ceil(heads / heads per block), M), 256 threads: a thread owns four pairs (t .. t+3, and + hd/2) of one head, so a
+// block takes 2048 / hd consecutive heads of one row and every load of the partial sums is 16 bytes (one pair per thread, 4-byte
+// loads: 845 rows of the 70B shape 28.4 -> 23.0 us, 618 rows 23.3 -> 19.9, 144 rows 8.0 and 8.3).
 // TA: activation type of the query buffer; T: storage type of the KV pages
 constexpr int ROPE_THREADS = 256;
 template <typename TA, typename T>
 __global__ void __launch_bounds__(ROPE_THREADS) rope_append_kernel(RopeAppendArgs a) {
   const int m = blockIdx.y;
-  const int hd = a.hd, half = hd >> 1;
-  const int head = blockIdx.x * (ROPE_THREADS / half) + (int)threadIdx.x / half;
-  const int t = (int)threadIdx.x % half;
+  const int hd = a.hd, half = hd >> 1, q4 = half >> 2;         // (head_dim is a multiple of 8)
+  const int head = blockIdx.x * (ROPE_THREADS / q4) + (int)threadIdx.x / q4;
+  const int t = ((int)threadIdx.x % q4) << 2;
   if (head >= a.H + 2 * a.Hkv) return;
   const int slot = a.rows.row_slot[m];  // (asked for first: the stores at the end wait for nothing else)
   const int ncols = (a.H + 2 * a.Hkv) * hd;
   const int c0 = head * hd + t, c1 = c0 + half;
-  float v0 = 0.f, v1 = 0.f;
-  // partials fetched eight at a time before any is added (see norm_kernel); the order of the sum is fixed
-  for (int s0 = 0; s0 < a.n_partials; s0 += 8) {
-    float p0[8], p1[8];
+  const bool is_v = head >= a.H + a.Hkv, turn = a.rope_cos && !is_v;
+  f32x4 cs = {1.f, 1.f, 1.f, 1.f}, sn = {0.f, 0.f, 0.f, 0.f};
+  if (turn) {
+    cs = *reinterpret_cast<const f32x4*>(a.rope_cos + (size_t)m * half + t);
+    sn = *reinterpret_cast<const f32x4*>(a.rope_sin + (size_t)m * half + t);
+  }
+  f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
+  // partials fetched four at a time before any is added (see norm_kernel); the order of the sum is fixed
+  for (int s0 = 0; s0 < a.n_partials; s0 += 4) {
+    f32x4 p0[4], p1[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
+    for (int j = 0; j < 4; ++j) {
       const float* p = a.qkv + ((size_t)min(s0 + j, a.n_partials - 1) * a.M + m) * ncols;
-      p0[j] = p[c0];
-      p1[j] = p[c1];
+      p0[j] = *reinterpret_cast<const f32x4*>(p + c0);
+      p1[j] = *reinterpret_cast<const f32x4*>(p + c1);
     }
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
+    for (int j = 0; j < 4; ++j)
       if (s0 + j < a.n_partials) { v0 += p0[j]; v1 += p1[j]; }
   }
-  if (a.bias) { v0 += a.bias[c0]; v1 += a.bias[c1]; }
-  const bool is_v = head >= a.H + a.Hkv;
-  if (a.rope_cos && !is_v) {
-    const float c = a.rope_cos[(size_t)m * half + t], s = a.rope_sin[(size_t)m * half + t];
-    const float r0 = v0 * c - v1 * s;
-    const float r1 = v1 * c + v0 * s;
-    v0 = r0; v1 = r1;
+  if (a.bias) {
+    const f32x4_u b0 = *reinterpret_cast<const f32x4_u*>(a.bias + c0), b1 = *reinterpret_cast<const f32x4_u*>(a.bias + c1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v0[e] += b0[e]; v1[e] += b1[e]; }
+  }
+  if (turn) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = v0[e], y = v1[e];
+      v0[e] = x * cs[e] - y * sn[e];
+      v1[e] = y * cs[e] + x * sn[e];
+    }
   }
   bool bad = false;
   if (head < a.H) {
     TA* q = reinterpret_cast<TA*>(a.q) + ((size_t)m * a.H + head) * hd;
-    store1<TA>(q + t, v0, bad);
-    store1<TA>(q + t + half, v1, bad);
+    store4<TA>(q + t, make_float4(v0[0], v0[1], v0[2], v0[3]), bad);
+    store4<TA>(q + t + half, make_float4(v1[0], v1[1], v1[2], v1[3]), bad);
     if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
     return;
   }
@@ -461,23 +472,30 @@ __global__ void __launch_bounds__(ROPE_THREADS) rope_append_kernel(RopeAppendArg
   if (!is_v) {
     const int kh = head - a.H;
     T* base = reinterpret_cast<T*>(a.kv.k) + ((size_t)pb * a.Hkv + kh) * (size_t)hd * bs;
-    // [hd/8][bs][8]
-    store1<T>(base + ((size_t)(t >> 3) * bs + off) * 8 + (t & 7), v0, bad);
-    const int t1 = t + half;
-    store1<T>(base + ((size_t)(t1 >> 3) * bs + off) * 8 + (t1 & 7), v1, bad);
+    // [hd/8][bs][8]: the four elements are neighbours inside their piece of eight
+    T* k0 = base + ((size_t)(t >> 3) * bs + off) * 8 + (t & 7);
+    T* k1 = base + ((size_t)((t + half) >> 3) * bs + off) * 8 + ((t + half) & 7);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      store1<T>(k0 + e, v0[e], bad);
+      store1<T>(k1 + e, v1[e], bad);
+    }
   } else {
     const int vh = head - a.H - a.Hkv;
     T* base = reinterpret_cast<T*>(a.kv.v) + ((size_t)pb * a.Hkv + vh) * (size_t)hd * bs;
     // [hd][bs]
-    store1<T>(base + (size_t)t * bs + off, v0, bad);
-    store1<T>(base + (size_t)(t + half) * bs + off, v1, bad);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      store1<T>(base + (size_t)(t + e) * bs + off, v0[e], bad);
+      store1<T>(base + (size_t)(t + half + e) * bs + off, v1[e], bad);
+    }
   }
   if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
 }
 
 void launch_rope_append(const RopeAppendArgs& a, hipStream_t st) {
   if (a.M <= 0) return;
-  const int per_block = ROPE_THREADS / (a.hd / 2);  // head_dim is one of 8 ... 256: hd/2 divides 256
+  const int per_block = ROPE_THREADS / (a.hd / 8);  // head_dim is one of 8 ... 256: hd/8 divides 256
   dim3 grid((a.H + 2 * a.Hkv + per_block - 1) / per_block, a.M);
   if (a.dtype == MN_DT_BF16) rope_append_kernel<f16_t, f16_t><<<grid, ROPE_THREADS, 0, st>>>(a);
   else rope_append_kernel<float, float><<<grid, ROPE_THREADS, 0, st>>>(a);
