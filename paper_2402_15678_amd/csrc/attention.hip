@@ -243,7 +243,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
   const bool loader = wave < 4;           // (wave-uniform)
   if (qb <= 0 || tile0 >= NT16 || split >= my_splits) return;  // (whole workgroup; the list holds no such record)
   const int nkeys = ok ? ctx + qb : 0;
-  const int n_tiles = (nkeys + KT - 1) / KT;
+  // keys this row group sees: a prompt's later keys are behind the causal limit of its earlier rows (845 prompt rows in three
+  // sequences: 26.7 -> 23.0 us)
+  const int seen = ok ? ctx + (min(R, (tile0 + NW * CTW) * 16) - 1) / G + 1 : 0;
+  const int n_tiles = (seen + KT - 1) / KT;
   const int t_begin = (int)(((long)n_tiles * split) / my_splits);
   const int t_end = (int)(((long)n_tiles * (split + 1)) / my_splits);
   const int n_my = max(0, t_end - t_begin);
@@ -766,31 +769,46 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
   }
 }
 
-// One wave per (row, head): merge the split partials, normalise, store fp16.  Rows of sequences that ran as
-// one split were written in final form by the attention kernel and are left alone.
+// Half a wave per (row, head): merge the split partials, normalise, store fp16.  Rows of sequences that ran as one split were
+// written in final form by the attention kernel and are left alone.  Bound by the partials' bytes and one round trip: four
+// splits' statistics and outputs are asked for at once, before any is looked at (512 rows x 64 heads in two splits: 14.5 -> 10.6 us).
 __global__ void __launch_bounds__(256) attn_merge_kernel(const float* __restrict__ o_part, const float* __restrict__ ml_part,
                                                          int n_splits_max, int M, int H,
                                                          const int32_t* __restrict__ row_splits, f16_t* __restrict__ out) {
-  const int wid = (blockIdx.x * 256 + threadIdx.x) >> 6, lane = threadIdx.x & 63;
+  const int wid = (blockIdx.x * 256 + threadIdx.x) >> 5, lane = threadIdx.x & 31;
   if (wid >= M * H) return;
   // (one read decides: most rows of a ragged batch have nothing to merge; the bound keeps a damaged entry from
   // reaching past the partials)
   const int n_splits = min(row_splits[wid / H], n_splits_max);
   if (n_splits <= 1) return;
-  float gm = -INFINITY;
-  for (int s = 0; s < n_splits; ++s) gm = fmaxf(gm, ml_part[((size_t)s * M * H + wid) * 2]);
-  const float ms = (gm == -INFINITY) ? 0.f : gm;
-  float l = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int s = 0; s < n_splits; ++s) {
-    const float* ml = ml_part + ((size_t)s * M * H + wid) * 2;
-    const float f = __builtin_amdgcn_exp2f(ml[0] - ms);
-    l += ml[1] * f;
-    const float2 v = *reinterpret_cast<const float2*>(o_part + ((size_t)s * M * H + wid) * HD + lane * 2);
-    o0 += v.x * f;
-    o1 += v.y * f;
+  float gm = -INFINITY, l = 0.f;
+  f32x4 o = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < n_splits; s0 += 4) {
+    float2 ml[4];
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const size_t at = (size_t)min(s0 + u, n_splits - 1) * M * H + wid;
+      ml[u] = *reinterpret_cast<const float2*>(ml_part + at * 2);
+      v[u] = *reinterpret_cast<const f32x4*>(o_part + at * HD + lane * 4);
+    }
+    float nm = gm;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) nm = fmaxf(nm, ml[u].x);
+    const float ms = (nm == -INFINITY) ? 0.f : nm, keep = __builtin_amdgcn_exp2f(gm - ms);
+    l *= keep;
+    o *= keep;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (s0 + u < n_splits) {
+        const float f = __builtin_amdgcn_exp2f(ml[u].x - ms);
+        l += ml[u].y * f;
+        o += v[u] * f;
+      }
+    gm = nm;
   }
   const float inv = l > 0.f ? 1.f / l : 0.f;
-  *reinterpret_cast<uint32_t*>(out + (size_t)wid * HD + lane * 2) = pack2h(o0 * inv, o1 * inv);
+  *reinterpret_cast<uint2*>(out + (size_t)wid * HD + lane * 4) = make_uint2(pack2h(o[0] * inv, o[1] * inv), pack2h(o[2] * inv, o[3] * inv));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -908,8 +926,7 @@ AttnPlan attention_plan(const AttnArgs& a) {
 
 static void launch_merge(const AttnArgs& a, int n_splits, const float* o_part, const float* ml_part, hipStream_t st) {
   if (n_splits <= 1) return;
-  const int waves = a.M * a.H;
-  attn_merge_kernel<<<(waves + 3) / 4, 256, 0, st>>>(o_part, ml_part, n_splits, a.M, a.H, a.row_splits, reinterpret_cast<f16_t*>(a.out));
+  attn_merge_kernel<<<(a.M * a.H + 7) / 8, 256, 0, st>>>(o_part, ml_part, n_splits, a.M, a.H, a.row_splits, reinterpret_cast<f16_t*>(a.out));
 }
 
 // A workgroup's waves split its keys: 8 waves up to one workgroup per CU, 4 (two workgroups per CU) beyond.  Measured with

@@ -204,6 +204,10 @@ def test_attention_matches_oracle(hb, name, desc, ctx_lens, spec_lens):
     ("hd128-g8-q4", synth.LLAMA2_70B.with_layers(1), [513, 60, 28], [3, 3, 2]),
     ("hd128-g8-decode-many", synth.LLAMA2_70B.with_layers(1), [300 + 41 * i for i in range(36)], [0] * 36),
     ("hd128-g8-splits", synth.LLAMA2_70B.with_layers(1), [5003, 4100, 17], [1, 0, 0]),
+    # several row groups of one sequence, each up to its own causal limit; more splits than the merge takes at once
+    ("hd128-g8-prompt", synth.LLAMA2_70B.with_layers(1), [0, 100, 0], [150, 47, 15]),
+    ("hd128-g1-prompt", synth.OPT_13B.with_layers(1), [0, 33], [300, 130]),
+    ("hd128-g8-many-splits", synth.LLAMA2_70B.with_layers(1), [8000, 6200], [1, 12]),
     ("hd64-rows16", synth.LLAMA_160M.with_layers(1), [700, 31, 0, 256], [15, 8, 5, 0]),
     ("hd64-rows32", synth.LLAMA_160M.with_layers(1), [700, 3, 97], [31, 16, 20]),
     ("hd64-many", synth.LLAMA_160M.with_layers(1), [64 * i + 7 for i in range(24)], [i % 9 for i in range(24)]),
