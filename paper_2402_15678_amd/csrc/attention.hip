@@ -532,10 +532,16 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
     const uint32_t b1 = min((uint32_t)bt[min(2 * tile + 1, last_blk)], blk_last);
     const char* kp = kbase + (uint64_t)(ksel ? b1 : b0) * blk_bytes;
     const char* vp = vbase + (uint64_t)(vsel ? b1 : b0) * blk_bytes;
+    // (the two halves of a K line are asked for by different instructions: with 8 waves, where the workgroup has its CU to
+    // itself, the lines stay without the non-temporal hint until both have been served: 256 workgroups of 300-2000 keys 38.8 ->
+    // 32.2 us; with 4 waves and two workgroups per CU the hint is as good or better: 960 workgroups 80.7 us, 82.0 without)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int s = 0; s < HS; ++s) t.k[h * HS + s] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(kp + h * 64 + s * (4 * BS * 16)));
+      for (int s = 0; s < HS; ++s) {
+        const u32x4* p = reinterpret_cast<const u32x4*>(kp + h * 64 + s * (4 * BS * 16));
+        t.k[h * HS + s] = NW == 8 ? *p : __builtin_nontemporal_load(p);
+      }
 #pragma unroll
     for (int u = 0; u < NU; ++u) t.v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + u * (16 * BS * (int)sizeof(f16_t))));
   };
@@ -930,8 +936,8 @@ static void launch_merge(const AttnArgs& a, int n_splits, const float* o_part, c
 }
 
 // A workgroup's waves split its keys: 8 waves up to one workgroup per CU, 4 (two workgroups per CU) beyond.  Measured with
-// the append inside: 256 workgroups of 300-2000 keys 38.9 us with 8 waves, 42.0 with 4; 192 of 1024 keys 15.7 / 17.6; 320 of
-// 512 keys 28.3 / 25.0.
+// the append inside: 256 workgroups of 300-2000 keys 38.9 us with 8 waves (32.2 with its key loads as they are now), 42.0 with
+// 4; 192 of 1024 keys 15.7 / 17.6; 320 of 512 keys 28.3 / 25.0.
 template <int HDIM, int CT, int NW, bool FUSED>
 static hipError_t launch_keys_nw(const AttnArgs& a, const MfmaShape& sh, float* o_part, float* ml_part, hipStream_t st) {
   constexpr size_t smem = (size_t)NW * 16 * (HDIM + 4) * sizeof(float);
