@@ -519,7 +519,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
       g.dev_status = dev_status;
       Tap t(&c->prof, MN_PROF_GEMM, st);
       keep(launch_gemm(g, st));
-    } else if (!llama && d.dtype == MN_DT_BF16 && gemm_pick_split(M, w1r, d.d_model, d.dtype) == 1) {
+    } else if (!llama && gemm_pick_split(M, w1r, d.d_model, d.dtype) == 1) {
       // one split: bias + ReLU applied in the kernel's epilogue, no partial sums and no activation kernel
       GemmArgs g{};
       g.a = h; g.w = c->w1[l]; g.relu_act = act; g.bias = (const float*)c->b1[l]; g.M = M; g.N = w1r; g.K = d.d_model;

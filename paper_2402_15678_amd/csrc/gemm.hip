@@ -677,7 +677,7 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int3
 constexpr int F32_TRIP = 4;
 __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        float* __restrict__ out, const float* __restrict__ bias, int M,
-                                                       int N, int K) {
+                                                       int N, int K, int relu) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blockIdx.x * 4 + wave;
   const int m0 = blockIdx.y * 8;
@@ -719,7 +719,10 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
 #pragma unroll
   for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
   const int row = lane >> 3;  // = 4 hi + 2 mid + lo
-  if ((lane & 7) == 0 && row < rows) out[(size_t)(m0 + row) * N + n] = s + (bias ? bias[n] : 0.f);
+  if ((lane & 7) == 0 && row < rows) {
+    s += bias ? bias[n] : 0.f;
+    out[(size_t)(m0 + row) * N + n] = relu ? fmaxf(s, 0.f) : s;
+  }
 }
 
 // out[i] = sum_s partials[s][i], ascending s
@@ -969,7 +972,8 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
   if (a.dtype != MN_DT_BF16) {
     dim3 grid((a.N + 3) / 4, (a.M + 7) / 8);
     gemm_f32_kernel<<<grid, 256, 0, st>>>(reinterpret_cast<const float*>(a.a), reinterpret_cast<const float*>(a.w),
-                                          a.out, a.bias, a.M, a.N, a.K);
+                                          a.relu_act ? reinterpret_cast<float*>(a.relu_act) : a.out, a.bias, a.M, a.N, a.K,
+                                          a.relu_act != nullptr);
     return hipSuccess;
   }
   const int tiles = (a.M + 15) / 16;
