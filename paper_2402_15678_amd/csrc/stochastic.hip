@@ -40,7 +40,7 @@ __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
 // One workgroup of 16 waves per row, the row's exponentials in registers.  The kernels are bound by the fp64
 // exponentials of one row on one CU (about 25 fp64 instructions per token, 64 lanes per clock: 6 us for 32000 tokens) and by
 // the chain load -> maximum -> exponentials -> sum -> draw, so a row is read once, every exponential is computed once,
-// and every sum is a wave reduction.  Measured at 32000 tokens: 25.3 us for the 144 positions of 16 requests and 20.2 us
+// and every sum is a wave reduction.  Measured at 32000 tokens: 21.8 us for the 144 positions of 16 requests and 16.6 us
 // for 16 drafted tokens; 149 and 162 us with 256 threads per row, the scores re-read for every pass and one thread
 // adding the 256 partial sums of every tile.
 constexpr int SV_THREADS = 1024;
@@ -166,9 +166,9 @@ struct Temp {
 };
 
 // Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass exceeds u times the
-// total; -1 when the total is not positive.  mass4(block, v) gives the masses of tokens v .. v+3 (v = 256 block + 4 lane;
-// 0 past the end) and must return the same values every time it is asked; for_blocks(f) calls f(block) for every block
-// of this wave in ascending order.  The masses are summed per segment, one wave finds the segment that holds the target,
+// total; -1 when the total is not positive.  for_blocks(f) calls f(block, t) for every block of this wave in ascending order
+// (see wave_blocks); mass4(t, v) gives the masses of tokens v .. v+3 of that block (v = 256 block + 4 lane; 0 past the end)
+// and must return the same values every time it is asked.  The masses are summed per segment, one wave finds the segment that holds the target,
 // and the wave that owns it scans it.  Every thread of the workgroup calls it; the result is uniform.  All sums
 // have a fixed order.
 template <bool ONE, typename FB, typename F>  // ONE: a block per segment (rows of up to 262144 tokens)
@@ -177,17 +177,39 @@ __device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u,
   const int grp = ONE ? 1 : seg_blocks(V);
   const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK, n_seg = (n_blocks + grp - 1) / grp;
   __syncthreads();  // (the shared arrays of an earlier draw have been read)
-  double run = 0.0;
-  for_blocks([&](int blk) {
-    double m[4];
-    mass4(blk, blk * SV_BLOCK + 4 * lane, m);
-    run += (m[0] + m[1]) + (m[2] + m[3]);
-    if (blk % grp == grp - 1 || blk == n_blocks - 1) {  // (wave-uniform)
-      const double s = wave_sum_d(run);
-      if (lane == 0) sh.seg[blk / grp] = s;
-      run = 0.0;
-    }
-  });
+  if constexpr (ONE) {
+    // the wave's eight segments are summed over the lanes together: every exchange with the lane 32, 16, 8 away halves the
+    // segments a lane still carries (10 exchanges instead of 48)
+    static_assert(SV_REG_TILES == 8, "three halvings");
+    double s8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for_blocks([&](int blk, int t) {
+      double m[4];
+      mass4(t, blk * SV_BLOCK + 4 * lane, m);
+      s8[t] = (m[0] + m[1]) + (m[2] + m[3]);
+    });
+    double s4[4], s2[2];
+    const bool hi = lane & 32, mid = lane & 16, lo = lane & 8;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s4[i] = (hi ? s8[4 + i] : s8[i]) + __shfl_xor(hi ? s8[i] : s8[4 + i], 32, 64);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s2[i] = (mid ? s4[2 + i] : s4[i]) + __shfl_xor(mid ? s4[i] : s4[2 + i], 16, 64);
+    double s = (lo ? s2[1] : s2[0]) + __shfl_xor(lo ? s2[0] : s2[1], 8, 64);
+#pragma unroll
+    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((lane & 7) == 0) sh.seg[(lane >> 3) * SV_WAVES + wave] = s;  // (segments past the row's end: zero)
+  } else {
+    double run = 0.0;
+    for_blocks([&](int blk, int t) {
+      double m[4];
+      mass4(t, blk * SV_BLOCK + 4 * lane, m);
+      run += (m[0] + m[1]) + (m[2] + m[3]);
+      if (blk % grp == grp - 1 || blk == n_blocks - 1) {  // (wave-uniform)
+        const double s = wave_sum_d(run);
+        if (lane == 0) sh.seg[blk / grp] = s;
+        run = 0.0;
+      }
+    });
+  }
   __syncthreads();
   if (wave == 0) {
     const int per = (n_seg + 63) >> 6;
@@ -236,11 +258,11 @@ __device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u,
     const double target = sh.target[0];
     double base = 0.0;
     int tok = -1, tail = -1;     // the token; the last token with mass so far
-    for_blocks([&](int blk) {
+    for_blocks([&](int blk, int t) {
       if (blk / grp != seg || tok >= 0) return;
       const int v = blk * SV_BLOCK + 4 * lane;
       double m[4];
-      mass4(blk, v, m);
+      mass4(t, v, m);
       const double mine = (m[0] + m[1]) + (m[2] + m[3]);
       double inc = mine;
 #pragma unroll
@@ -419,15 +441,11 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
         ex[t][e] = Q ? fmax(0.0, o - (double)q[e]) : o;
       }
     });
-    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
-                   [&](int blk, int, double (&m)[4]) {
-#pragma unroll
-                     for (int t = 0; t < TILES; ++t)
-                       if (blk / SV_WAVES == t) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; }
-                   },
+    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, f); },
+                   [&](int t, int, double (&m)[4]) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; },
                    V, u_res, sh, tid);
   } else {
-    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, f); },
                    [&](int, int v, double (&m)[4]) {
                      o4(v, m);
                      if (Q) {
@@ -439,7 +457,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
                    V, u_res, sh, tid);
   }
   if (Q && tok < 0) {
-    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, f); },
                    [&](int, int v, double (&m)[4]) {
                      o4(v, m);
 #pragma unroll
@@ -500,15 +518,11 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   });
   int tok;
   if constexpr (TILES > 0)
-    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, [&](int blk, int) { f(blk); }); },
-                   [&](int blk, int, double (&m)[4]) {
-#pragma unroll
-                     for (int t = 0; t < TILES; ++t)
-                       if (blk / SV_WAVES == t) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; }
-                   },
+    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, f); },
+                   [&](int t, int, double (&m)[4]) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; },
                    V, u, sh, tid);
   else
-    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, [&](int blk, int) { f(blk); }); },
+    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, f); },
                    [&](int, int v, double (&m)[4]) {
                      if (P && v + 3 < V) {  // (this thread wrote them itself: cheaper than the exponentials again)
                        const f32x4_u q = *reinterpret_cast<const f32x4_u*>(P + v);
