@@ -577,7 +577,7 @@ extern "C" mn_status mn_proj_gemm(mn_ctx* c, const void* a, const void* w, const
   if (split_k < 0 || split_k > MN_MAX_SPLIT_K) return fail(c, MN_EINVAL, "%s: split_k = %d", who, split_k);
   if (M == 0) return MN_OK;
   if (!a || !w || !out) return fail(c, MN_ENULL, "%s: a/w/out is NULL", who);
-  int s = split_k ? split_k : gemm_pick_split(M, N, K, MN_DT_BF16);
+  int s = split_k ? split_k : gemm_caller_split(M, N, K);
   if (s > K / 128) s = K / 128;
   hipStream_t st = (hipStream_t)stream;
   GemmArgs g{};
@@ -635,7 +635,7 @@ extern "C" mn_status mn_proj_gemm_noalloc(mn_ctx* c, const void* a, const void* 
   if (split_k < 0 || split_k > MN_MAX_SPLIT_K) return fail(c, MN_EINVAL, "%s: split_k = %d", who, split_k);
   if (M == 0) return MN_OK;
   if (!a || !w || !out) return fail(c, MN_ENULL, "%s: a/w/out is NULL", who);
-  int s = split_k ? split_k : gemm_pick_split(M, N, K, MN_DT_BF16);
+  int s = split_k ? split_k : gemm_caller_split(M, N, K);
   if (s > K / 128) s = K / 128;
   hipStream_t st = (hipStream_t)stream;
   GemmArgs g{};

@@ -899,6 +899,28 @@ int gemm_pick_split(int M, int N, int K, int dtype) {
   return gemm_plan(M, N, K, 0).split;
 }
 
+// The library's choice where the caller brings the room for the partial sums (or the built-in buffer is it): the plan's
+// split, above 144 rows at most the one that fills 256 workgroups with the tiles of 320, 256 or 192 rows that pad the rows
+// least.  Lower tiles can ask for more splits (513 rows on 15360 x 4096: 2 instead of 1), and a call that needed no room
+// would be refused without it.
+int gemm_caller_split(int M, int N, int K) {
+  const int s = gemm_pick_split(M, N, K, MN_DT_BF16);
+  if (M <= 144 || s <= 1) return s;
+  const int gx = ((N + NWG - 1) / NWG + 1) / 2, iters = K / KB;
+  int padded = 1 << 30, blocks = 1;
+  for (int at : {10, 8, 6}) {
+    const int b = (M + 32 * at - 1) / (32 * at);
+    if (b * at < padded) { padded = b * at; blocks = b; }
+  }
+  if (M <= 160) blocks = 1;
+  int most = BIG_WGS / (gx * blocks);
+  if (most > iters / 16) most = iters / 16;
+  if (most < 1) return 1;
+  const int per = (iters + most - 1) / most;
+  most = (iters + per - 1) / per;
+  return s < most ? s : most;
+}
+
 template <int MT, int NW, int NTW = 2, int RD = 2>
 static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
   const int iters = a.K / KB;

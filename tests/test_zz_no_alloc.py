@@ -80,3 +80,20 @@ def test_noalloc_projection_rejects_what_the_buffer_cannot_hold():
                                      harness.stream_ptr())
     assert e.value.status == binding.MN_ESHAPE
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("M,N,K", [(513, 15360, 4096), (1500, 6144, 8192)])
+def test_library_split_needs_no_room_where_one_split_fills_the_device(M, N, K):
+    """More than 144 rows, split left to the library: row blocks of fewer rows would fit two splits, whose partial sums
+    exceed the built-in buffer and need a workspace from the caller; one split fills the device and needs neither."""
+    from paper_2402_15678_amd import binding, harness
+    st = harness.stream_ptr()
+    assert 2 * M * N * 4 > binding.MN_NOALLOC_SCRATCH_BYTES
+    a_d, w_d, b_d, a, w, bias = _case(harness, binding, M, N, K, 0, M)
+    ref = a.astype(np.float64) @ w.astype(np.float64).T + bias
+    for call in (lambda o: binding.mn_proj_gemm(None, a_d.data_ptr(), w_d.data_ptr(), b_d.data_ptr(), o, M, N, K, 0, None, 0, st),
+                 lambda o: binding.mn_proj_gemm_noalloc(None, a_d.data_ptr(), w_d.data_ptr(), b_d.data_ptr(), o, M, N, K, 0, st)):
+        out = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda:0")
+        call(out.data_ptr())
+        torch.cuda.synchronize()
+        assert np.abs(out.cpu().numpy() - ref).max() < 2e-3 * max(1.0, np.sqrt(K / 1024.0))
