@@ -40,7 +40,7 @@ __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
 // One workgroup of 16 waves per row, the row's exponentials in registers.  The kernels are bound by the fp64
 // exponentials of one row on one CU (about 25 fp64 instructions per token, 64 lanes per clock: 6 us for 32000 tokens) and by
 // the chain load -> maximum -> exponentials -> sum -> draw, so a row is read once, every exponential is computed once,
-// and every sum is a wave reduction.  Measured at 32000 tokens: 21.8 us for the 144 positions of 16 requests and 16.6 us
+// and every sum is a wave reduction.  Measured at 32000 tokens: 21.9 us for the 144 positions of 16 requests and 16.8 us
 // for 16 drafted tokens; 149 and 162 us with 256 threads per row, the scores re-read for every pass and one thread
 // adding the 256 partial sums of every tile.
 constexpr int SV_THREADS = 1024;
@@ -136,21 +136,18 @@ __device__ const double kPow2[128] = {
 // About half the instructions of the general function (arguments are never positive), which is most of these kernels' time.
 // The quotient is not rounded on its own: r comes out of one fma with T's reciprocal, so its error is the reciprocal's
 // rounding, what a rounded quotient's would be.  For temperatures so extreme that the reciprocal leaves the normal
-// range (inv == 0) the general function and a division.  Scores more than 800 T below the maximum are cut there (the
-// exponential is zero long before), so that a masked token (minus infinity) stays finite; NaN passes through.
+// range (inv == 0) the general function and a division.  Differences below -800 T are cut there (the exponential is zero long
+// before), so that a masked token (minus infinity) stays finite; NaN passes through.  The cut is on the fp64 difference: 800 T
+// may be far below the spacing of the scores in fp32, and the largest score may be the type's lowest value.
 struct Temp {
   double T, inv, per_step;   // 1 / T, 64 / (T ln2)
   const double2* pow2;       // [64] 2^(j/64), rest
   double dmx;                // largest score of the row
-  float cut;
-  __device__ __forceinline__ void set_max(float mx) {
-    dmx = (double)mx;
-    cut = fmaxf((float)(dmx - 800.0 * T), -3.0e38f);
-  }
+  double lowest;             // -800 T
   __device__ __forceinline__ double mass(float l) const {
     if (inv == 0.0) return exp(((double)l - dmx) / T);  // (uniform)
-    l = l < cut ? cut : l;
-    const double d = (double)l - dmx;
+    double d = (double)l - dmx;
+    d = d < lowest ? lowest : d;
     const double t = fma(d, per_step, 6755399441055744.0);  // 1.5 * 2^52: the nearest whole number sits in the low bits
     const double nd = t - 6755399441055744.0;
     const int n = (int)(uint32_t)__double_as_longlong(t);
@@ -329,7 +326,7 @@ __device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < SV_WAVES; ++w) mx = fmaxf(mx, sh.redf[w]);
-  temp.set_max(mx);
+  temp.dmx = (double)mx;
   double zp = 0.0;
   wave_blocks<TILES>(V, wave, [&](int blk, int t) {
     const int v = blk * SV_BLOCK + 4 * lane;
@@ -395,7 +392,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     return;
   }
   const float* L = logits + (size_t)row * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, 0.f};  // 64 / ln2
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
   double Z;
   row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
@@ -484,7 +481,7 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   __shared__ DrawShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* L = logits + (size_t)b * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, 0.f};  // 64 / ln2
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
   double Z;
   row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);

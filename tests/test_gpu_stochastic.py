@@ -398,3 +398,75 @@ def test_sampling_row_layout_edges(hb, B, k_max, V, T):
     res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=5, step=1, ctx0=ctx0)
     _check_against_oracle(res, spec, logits, q, voted, k_max, T, 5, 1, ctx0)
     test_draft_sample_matches_oracle(hb, B, V, T, 2.0)
+
+
+# Low temperatures: the scores' differences divided by T lie far outside the exponential's range, at maxima whose spacing in
+# fp32 is far below (0.5), near (30) and far above (1000) the temperature; rows held in registers and rows that are not.
+# A runner-up one fp32 step below the maximum and one at the maximum itself keep some rows from being plainly greedy.
+@pytest.mark.parametrize("V", [700, 40001])
+@pytest.mark.parametrize("top", [0.5, 30.0, 1000.0])
+@pytest.mark.parametrize("T", [1e-6, 1e-9, 1e-12, 1e-25])
+def test_low_temperatures_against_oracle(hb, T, top, V):
+    harness, binding = hb
+    B, k_max = 6, 3
+    spec, M, logits, q, voted = _case(31, B, k_max, V, 1.0, 1.0)
+    logits += (np.float32(top) - logits.max(axis=1, keepdims=True)).astype(np.float32)
+    g = synth.stream(4106, V)
+    first = np.argmax(logits, axis=1)
+    logits[np.arange(M), first] = top
+    other = (first + 1 + g.integers(0, V - 1, size=M)) % V
+    kind = g.integers(0, 3, size=M)
+    logits[np.arange(M), other] = np.where(kind == 0, np.float32(top), np.where(
+        kind == 1, np.nextafter(np.float32(top), np.float32(0)), np.float32(top - 1.0)))
+    masked = g.random((M, V)) < 0.3
+    masked[np.arange(M), first] = masked[np.arange(M), other] = False
+    logits[masked] = -np.inf
+    row = 0
+    for b in range(B):                                    # half of the speculated tokens are the LLM's best one
+        for j in range(int(spec[b])):
+            if (b + j) % 2 == 0:
+                voted[b, j] = first[row + j]
+        row += int(spec[b]) + 1
+    ctx0 = np.arange(B).astype(np.int32)
+    for step in (0, 1):
+        res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=6, step=step, ctx0=ctx0)
+        _check_against_oracle(res, spec, logits, q, voted, k_max, T, 6, step, ctx0)
+    _check_draft_rows(hb, logits, T)
+
+
+# The largest score of a row may be any finite fp32 value: rows masked with the type's lowest value throughout, with minus
+# infinity beside it, and rows near the type's largest
+@pytest.mark.parametrize("T", [1e-9, 1.0, 1e28])
+@pytest.mark.parametrize("V", [300, 33000])
+def test_rows_at_the_ends_of_the_range_against_oracle(hb, V, T):
+    low, high = np.finfo(np.float32).min, np.finfo(np.float32).max
+    logits = np.full((6, V), low, np.float32)
+    logits[1, ::2] = -np.inf
+    logits[2, 5] = np.float32(-3.2e38)
+    logits[3] = -np.inf
+    logits[3, V - 1] = low
+    logits[4, :] = high
+    logits[4, 1::3] = low
+    logits[5, 7] = high
+    _check_draft_rows(hb, logits, T)
+    B, k_max = 6, 0                                       # no speculation: one token from every row
+    res = _run_gpu(hb, np.zeros(B, np.int32), B, logits, np.zeros((B, 1, V), np.float32), np.full((B, 1), -1, np.int32), k_max,
+                   V, T, seed=8, step=0, ctx0=np.zeros(B, np.int32))
+    _check_against_oracle(res, np.zeros(B, np.int32), logits, np.zeros((B, 1, V), np.float32), np.full((B, 1), -1, np.int32),
+                          k_max, T, 8, 0, np.zeros(B, np.int32))
+
+
+def _check_draft_rows(hb, logits, T):
+    harness, binding = hb
+    B, V = logits.shape
+    log_d = _dev(logits, torch.float32)
+    tok_d = torch.full((B,), -5, dtype=torch.int32, device="cuda:0")
+    q_d = torch.full((B, V), -1.0, dtype=torch.float32, device="cuda:0")
+    binding.mn_draft_sample(None, log_d.data_ptr(), B, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
+    torch.cuda.synchronize()
+    tok, q = tok_d.cpu().numpy(), q_d.cpu().numpy()
+    for b in range(B):
+        want, q32, gap = orc.draft_sample(logits[b], T, 9, 2, 1, b, 3)
+        assert np.allclose(q[b], q32, rtol=3e-7, atol=1e-45), b
+        if gap > 1e-6:
+            assert tok[b] == want, (b, tok[b], want)
