@@ -156,17 +156,12 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
     if (a.dev_status) atomicOr(a.dev_status, MN_DEV_SPEC_LEN);
   }
   __syncthreads();
-  // a device spec_len that disagrees with the launch geometry disables the whole batch
+  // a device spec_len that disagrees with the launch geometry disables the whole batch: every sequence, each with an even share
+  // of the rows (at least one, at most the host's longest run), so that the attention kernels write zeros to all of them
   if (s_bad != 0) {
-    for (int b = tid; b <= B; b += PREP_THREADS) a.seq_row0[b] = 0;
-    for (int b = tid; b < B; b += PREP_THREADS) { a.seq_ctx[b] = 0; a.seq_ok[b] = 0; }
-    for (int m = tid; m < a.M; m += PREP_THREADS) {
-      a.row_seq[m] = 0; a.row_j[m] = 0; a.row_pos[m] = -1; a.row_tok[m] = 0; a.row_slot[m] = -1;
-      if (a.plan.items) a.plan.row_splits[m] = 0;
-    }
-    if (a.plan.items)
-      for (int i = tid; i < a.plan.grid_items; i += PREP_THREADS) reinterpret_cast<int4*>(a.plan.items)[2 * (size_t)i] = make_int4(-1, 0, 0, 1);
-    return;
+    for (int b = tid; b <= B; b += PREP_THREADS) s_row0[b] = (int)((long)a.M * b / B);
+    for (int b = tid; b < B; b += PREP_THREADS) s_ok[b] = 0;
+    __syncthreads();
   }
   for (int b = tid; b <= B; b += PREP_THREADS) a.seq_row0[b] = s_row0[b];
   for (int b = tid; b < B; b += PREP_THREADS) {

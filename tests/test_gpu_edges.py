@@ -410,3 +410,25 @@ def test_table_check_reaches_every_entry(mb):
         kvd.block_tables.copy_(saved)
         others = [i for i in range(B) if i != b]
         assert st == binding.MN_DEV_BLOCK_TABLE and (got[b] == 0).all() and torch.equal(got[others], ref[others])
+
+
+# Both ways the few-row attention kernel takes its work: from the workgroup index, and (more than 512 workgroups) from a list
+@pytest.mark.parametrize("B", [2, 130])
+def test_attention_of_a_disabled_batch_is_zero(B):
+    """Device speculation lengths that do not add up to the host's rows disable the whole batch; with head_dim 64 and a few
+    stacked rows every output row is then zero, as a single disabled sequence's rows are."""
+    from paper_2402_15678_amd import binding, harness
+    desc = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 1, 256, 4, 4, 64, 256, 8, 512)
+    model = harness.DeviceModel.from_host(desc, synth.make_weights(desc, 1))
+    ctx, ks = [40] * B, [7] * B
+    kvd = harness.DeviceKV.random_on_device(desc, ctx, ks, 5)
+    M = 8 * B
+    q = torch.randn((M, 4, 64), device="cuda:0").half()
+    wrong = _i32(ks[:-1] + [3])
+    out, st = torch.full((M, 256), 7.0, dtype=torch.float16, device="cuda:0"), _i32([0])
+    wsb = binding.mn_workspace_bytes(model.ctx, B, M, 48)
+    ws = torch.empty(wsb, dtype=torch.uint8, device="cuda:0")
+    binding.mn_attention(model.ctx, q.data_ptr(), wrong.data_ptr(), binding.host_i32(ks), B, 48, kvd.c, 0, out.data_ptr(),
+                         ws.data_ptr(), wsb, st.data_ptr(), harness.stream_ptr())
+    torch.cuda.synchronize()
+    assert st.item() == binding.MN_DEV_SPEC_LEN and (out == 0).all()
