@@ -382,7 +382,7 @@ static AttnArgs attn_args(const mn_ctx* c, const Ws& w, int B, int M, int max_ct
 }
 
 static hipError_t run_prepare(mn_ctx* c, const Ws& w, const int32_t* last_tok, const int32_t* voted, const int32_t* spec_len,
-                              int B, int k_max, int M, int max_ctx, const mn_kv* kv, bool tokens, const AttnPlan& plan,
+                              int B, int k_max, int M, int max_ctx, int max_q, const mn_kv* kv, bool tokens, const AttnPlan& plan,
                               int32_t* dev_status, hipStream_t st) {
   PrepArgs p{};
   p.last_tok = tokens ? last_tok : nullptr;
@@ -394,6 +394,7 @@ static hipError_t run_prepare(mn_ctx* c, const Ws& w, const int32_t* last_tok, c
   p.vocab = tokens ? c->d.vocab : 0;
   p.max_pos = c->d.max_pos;
   p.max_ctx = max_ctx;
+  p.max_q = max_q;
   p.block_size = kv->block_size; p.num_blocks = kv->num_blocks; p.max_blocks_per_seq = kv->max_blocks_per_seq;
   p.rope_half = (tokens && c->d.arch == MN_ARCH_LLAMA) ? c->d.head_dim / 2 : 0;
   p.rope_base = c->d.rope_base;
@@ -442,7 +443,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   const RowInfo rows = row_info(w);
   const AttnArgs attn = attn_args(c, w, B, M, max_ctx, max_q, kv);
   const AttnPlan no_layers{};
-  keep(run_prepare(c, w, last_tok, voted, spec_len, B, k_max, M, max_ctx, kv, true, d.n_layers > 0 ? attention_plan(attn) : no_layers,
+  keep(run_prepare(c, w, last_tok, voted, spec_len, B, k_max, M, max_ctx, max_q, kv, true, d.n_layers > 0 ? attention_plan(attn) : no_layers,
                    dev_status, st));
   if (lerr != hipSuccess) return fail(c, MN_EHIP, "%s: kernel attribute: %s", who, hipGetErrorString(lerr));
   const bool llama = d.arch == MN_ARCH_LLAMA;
@@ -691,7 +692,7 @@ extern "C" mn_status mn_attention(mn_ctx* c, const void* q, const int32_t* spec_
   AttnArgs at = attn_args(c, w, B, M, max_ctx, max_q, kv);
   at.q = q; at.out = out;
   at.kv.k = kv->k_layers[layer]; at.kv.v = kv->v_layers[layer];
-  hipError_t lerr = run_prepare(c, w, nullptr, nullptr, spec_len, B, k_max, M, max_ctx, kv, false, attention_plan(at), dev_status, st);
+  hipError_t lerr = run_prepare(c, w, nullptr, nullptr, spec_len, B, k_max, M, max_ctx, max_q, kv, false, attention_plan(at), dev_status, st);
   if (lerr == hipSuccess) {
     Tap t(&c->prof, MN_PROF_ATTENTION, st);
     lerr = launch_attention(at, st);

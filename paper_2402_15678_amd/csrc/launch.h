@@ -37,6 +37,7 @@ struct PrepArgs {
   const int32_t *last_tok, *voted, *spec_len, *ctx_lens, *block_tables;
   int B, k_max, M, vocab, max_pos, block_size, num_blocks, max_blocks_per_seq;
   int max_ctx;       // the host's bound on ctx_b + k_b + 1 (it sized the attention launch)
+  int max_q;         // the host's largest number of rows of a sequence (likewise)
   int rope_half;     // head_dim/2 for rotary models, 0 otherwise
   float rope_base;
   int32_t *row_seq, *row_j, *row_pos, *row_tok, *row_slot, *seq_row0, *seq_ctx, *seq_ok;

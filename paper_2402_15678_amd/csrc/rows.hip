@@ -86,13 +86,14 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   for (int b = tid; b < B; b += PREP_THREADS) {
     const int k = a.spec_len[b];
     const int ctx = a.ctx_lens[b];
-    s_row0[b + 1] = (k < 0 || k > a.k_max) ? 1 : k + 1;
+    const bool fits = k >= 0 && k <= a.k_max && k < a.max_q;  // (the attention launches were sized for max_q rows)
+    s_row0[b + 1] = fits ? k + 1 : 1;
     s_ctx[b] = ctx;
     if (blockIdx.x > 0) continue;
     int ok = 1;
     int flags = 0;
     int nb = 0;
-    if (k < 0 || k > a.k_max) { ok = 0; flags |= MN_DEV_SPEC_LEN; }
+    if (!fits) { ok = 0; flags |= MN_DEV_SPEC_LEN; }
     if (ok) {
       const long need = (long)ctx + k + 1;
       if (ctx < 0 || need > (long)a.max_blocks_per_seq * a.block_size) { ok = 0; flags |= MN_DEV_BLOCK_TABLE; }

@@ -432,3 +432,39 @@ def test_attention_of_a_disabled_batch_is_zero(B):
                          ws.data_ptr(), wsb, st.data_ptr(), harness.stream_ptr())
     torch.cuda.synchronize()
     assert st.item() == binding.MN_DEV_SPEC_LEN and (out == 0).all()
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_device_spec_len_beyond_the_hosts_longest_run(hd):
+    """The attention launch is sized for the host's longest run of scored positions.  Device speculation lengths with a longer
+    run set MN_DEV_SPEC_LEN and disable the batch, also where their rows add up to the host's."""
+    from paper_2402_15678_amd import binding, harness
+    desc = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 1, 256, 256 // hd, 256 // hd, hd, 256, 500, 512)
+    model = harness.DeviceModel.from_host(desc, synth.make_weights(desc, 79))
+    k_max = 60
+    g = synth.stream(8, 5)
+
+    def run(ctx, host, device):
+        B = len(ctx)
+        kvh = synth.make_paged_kv(desc, np.array(ctx), np.full(B, k_max), 3)
+        kvd = harness.DeviceKV.from_host(desc, kvh)
+        before = kvd.k_pages[0].clone()
+        ses = harness.VerifySession(model, kvd, B, k_max, 1, max(ctx) + k_max + 1, max_rows=sum(host) + B, want_logits=True)
+        last, voted = _i32(np.arange(B) + 7), _i32(np.arange(B * k_max).reshape(B, k_max) % desc.vocab)
+        spec = _i32(device)
+        ses.forward(last, spec, list(host), voted=voted)
+        ses.accept(spec, voted=voted)
+        torch.cuda.synchronize()
+        changed = (kvd.k_pages[0] != before).flatten(1).any(dim=1).nonzero().flatten().cpu().tolist()
+        own = [set(r[r >= 0].tolist()) for r in kvh.block_tables]
+        return ses, ses.greedy.cpu().numpy(), [bool(set(changed) & o) for o in own], kvd.ctx_lens.cpu().tolist()
+
+    ctx = [30, 45, 61]
+    ref, _, wrote, _ = run(ctx, [1, 1, 1], [1, 1, 1])
+    assert ref.dev_status.item() == 0 and wrote == [True] * 3
+    # the same number of rows, distributed otherwise (48 stacked rows is more than the few-row attention kernel takes); rows
+    # that would add up if the long run counted as one
+    for device, host in [([0, 2, 1], [1, 1, 1]), ([0, 47, 0], [16, 16, 15]), ([57, 1, 1], [0, 1, 1])]:
+        ses, greedy, wrote, ctx1 = run(ctx, host, device)
+        assert ses.dev_status.item() == binding.MN_DEV_SPEC_LEN
+        assert (greedy == -1).all() and wrote == [False] * 3 and ctx1 == ctx
