@@ -152,13 +152,14 @@ constexpr int NS = 4;                          // tile slots in LDS (a ring of 8
 constexpr int MAX_CT = 2;                      // column tiles per wave; a workgroup covers 64 * MAX_CT stacked rows
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LAZY_MAX = 6.f;                // the reference moves when a score exceeds it by 2^6
+constexpr float SPLIT_SCALE = 512.f;           // probabilities in two fp16 terms: 2^9 times a probability of up to 2^6 stays in range
 
 __device__ __forceinline__ float max3(float x, float y, float z) { return __builtin_fmaxf(__builtin_fmaxf(x, y), z); }
 
 // Online-softmax step of one column tile on one key tile.  S0/S1: scores of keys 8g+0..3 / 8g+4..7 of
 // this lane's query row, already minus the reference (negm4 = -reference in all four elements, 0 while
-// nothing was seen).  Returns the probabilities as the B operand of the second product, and with SPLIT what their
-// rounding to fp16 left over as a second operand in `rest`.
+// nothing was seen).  Returns the probabilities as the B operand of the second product, and with SPLIT 2^9 times the
+// probabilities, what their rounding to fp16 left over as a second operand in `rest`.
 template <bool MASK, int NU, bool SPLIT = false>
 __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, float& run_m, f32x4& negm4, float& thr,
                                               f32x4 (&O)[NU], f32x4& L, int keyg, int lim, f16x8* rest = nullptr) {
@@ -194,7 +195,7 @@ __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, 
   if constexpr (SPLIT) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float p = __builtin_amdgcn_exp2f(sc[e]);
+      const float p = __builtin_amdgcn_exp2f(sc[e]) * SPLIT_SCALE;
       pf.v[e] = (f16_t)p;
       (*rest)[e] = (f16_t)(p - (float)pf.v[e]);
     }
@@ -475,13 +476,16 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
 // split, so that the rows have one writer.  When every workgroup is resident at once and nothing is split (no list:
 // a.items null) the workgroups take (sequence, KV head) from their index: one dependent load less before the first tile.
 // Products and operand order are those of the kernel above; record list and KV splits likewise.  With head_dim 64
-// (the shapes that used to run on plain fp32 FMA) nothing is rounded to 16 bits on the way: the queries go into the first
-// product as they are and the scale is applied to its fp32 result, and a probability goes into the second product as two
-// fp16 terms, which hold 22 bits of it (the extra products hide behind the stream).
+// (the shapes that used to run on plain fp32 FMA) the fp16 queries go into the first product as they are and the scale is
+// applied to its fp32 result, and a probability p goes into the second product as two fp16 terms of 2^9 p, in the sums of the
+// outputs and of the probabilities alike: off by at most 2^-23 p or 2^-34, whichever is larger, where the row's sum is at
+// least 1 and the fp32 sums round at 2^-24 of it (the extra products hide behind the stream).  Without the factor the fixed
+// step was 2^-25: with one key at probability 1 in every wave's share and the rest of a 2000-key row at 2^-19 (2^-23) each,
+// 1.1 % (17 %) of that rest was lost.
 template <int HDIM, int CT, int NW, bool FUSED>
 __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT == 1 ? 2 : 1))
     attn_keys_kernel(AttnArgs a, float* __restrict__ o_part, float* __restrict__ ml_part) {
-  constexpr bool WIDE = HDIM == 64;                          // fp32 queries and probabilities
+  constexpr bool WIDE = HDIM == 64;                          // queries unscaled, probabilities in two terms
   constexpr int HS = HDIM / 32, NU = HDIM / 16, OROW = HDIM + 4;  // (padded rows: the merge's 16-byte accesses spread over the banks)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float* s_o = reinterpret_cast<float*>(smem);               // [NW][16][OROW], one column tile at a time

@@ -216,6 +216,45 @@ def test_attention_few_rows(hb, name, desc, ctx_lens, spec_lens):
     _check_attention(hb, desc, ctx_lens, spec_lens)
 
 
+# head_dim 64 keeps the probabilities' fp32 worth through the second product, the small ones too: in every wave's share of the
+# keys one key carries probability 1 (and value 0), all the others probability p (and value 64), so the output is
+# 64 m p / (8 + m p) for m of them, as accurate as p.  A probability enters as two fp16 terms of 2^9 p, off by at most 2^-34
+# together; the output's own rounding is 2^-11, the exponential and the fp32 sums stay below 2^-16.
+@pytest.mark.parametrize("x", [8.25, 11.28125, 13.0625, 15.75])
+@pytest.mark.parametrize("ks", [(0, 0), (15, 3), (31, 20)])
+def test_attention_small_probabilities_hd64(hb, x, ks):
+    harness, binding = hb
+    desc = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 1, 256, 4, 4, 64, 256, 8, 8192)
+    ctx = np.array([2000, 715], np.int32)
+    model = harness.DeviceModel.from_host(desc, synth.make_weights(desc, 1))
+    kvd = harness.DeviceKV.random_on_device(desc, ctx.tolist(), list(ks), 3)
+    k, v, bt = kvd.k_pages[0], kvd.v_pages[0], kvd.block_tables.cpu().numpy()
+    k.zero_()
+    k[:, :, 0, :, 0] = -x                                  # (scores are q . k / 8 with q = 8 in dimension 0)
+    v.fill_(64.0)
+    for b in range(2):
+        for w in range(8):
+            blk, off = int(bt[b, 2 * w]), w                # one key of tile w
+            k[blk, :, 0, off, 0] = 0.0
+            v[blk, :, :, off] = 0.0
+    M = sum(ks) + 2
+    q = torch.zeros((M, 4, 64), dtype=torch.float16, device="cuda:0")
+    q[:, :, 0] = 8.0
+    out = torch.full((M, 4, 64), float("nan"), dtype=torch.float16, device="cuda:0")
+    max_ctx = int((ctx + np.array(ks) + 1).max())
+    wsb = binding.mn_workspace_bytes(model.ctx, 2, M, max_ctx)
+    ws, st, spec_d = torch.empty(wsb, dtype=torch.uint8, device="cuda:0"), _dev([0]), _dev(ks)
+    binding.mn_attention(model.ctx, q.data_ptr(), spec_d.data_ptr(), binding.host_i32(ks), 2, max_ctx, kvd.c, 0,
+                         out.data_ptr(), ws.data_ptr(), wsb, st.data_ptr(), harness.stream_ptr())
+    torch.cuda.synchronize()
+    assert st.item() == 0
+    p = np.exp(-np.float64(x))
+    m = np.concatenate([ctx[b] + np.arange(ks[b] + 1) + 1 - 8 for b in range(2)]).astype(np.float64)
+    want = (64.0 * m * p / (8.0 + m * p))[:, None, None]
+    err = np.abs(out.double().cpu().numpy() - want) / want
+    assert err.max() < 2.0 ** -11 + 2.0 ** -34 / p + 2.0 ** -16, err.max()
+
+
 @pytest.mark.parametrize("seed", list(range(10)))
 def test_attention_drawn_batches(hb, seed):
     """Drawn batches for the MFMA kernel and its work list: 1-24 sequences, contexts 0-2500 (a few of them long, so
