@@ -368,13 +368,13 @@ static RowInfo row_info(const Ws& w) {
 }
 
 // The attention call of one layer, everything but its queries and pages.
-static AttnArgs attn_args(const mn_ctx* c, const Ws& w, int B, int M, int max_ctx, int max_q, const mn_kv* kv) {
+static AttnArgs attn_args(const mn_ctx* c, const Ws& w, int B, int M, int max_ctx, int max_q, const mn_kv* kv, bool append) {
   const mn_model_desc& d = c->d;
   AttnArgs at{};
   at.rows = row_info(w);
   at.kv = KvView{nullptr, nullptr, kv->block_tables, kv->block_size, kv->num_blocks, kv->max_blocks_per_seq};
   at.B = B; at.M = M; at.H = d.n_heads; at.Hkv = d.n_kv_heads; at.hd = d.head_dim; at.dtype = d.dtype;
-  at.max_ctx = max_ctx; at.max_q = max_q;
+  at.max_ctx = max_ctx; at.max_q = max_q; at.append = append;
   at.scratch = w.at<float>(w.L.attn_scratch); at.scratch_bytes = w.L.attn_scratch_bytes;
   at.items = w.at<int32_t>(w.L.attn_items); at.items_capacity = w.L.attn_items_capacity;
   at.row_splits = w.at<int32_t>(w.L.attn_row_splits);
@@ -441,7 +441,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   hipError_t lerr = hipSuccess;  // first refusal of a launcher (a kernel attribute the runtime would not set)
   auto keep = [&](hipError_t e) { if (e != hipSuccess && lerr == hipSuccess) lerr = e; };
   const RowInfo rows = row_info(w);
-  const AttnArgs attn = attn_args(c, w, B, M, max_ctx, max_q, kv);
+  const AttnArgs attn = attn_args(c, w, B, M, max_ctx, max_q, kv, true);
   const AttnPlan no_layers{};
   keep(run_prepare(c, w, last_tok, voted, spec_len, B, k_max, M, max_ctx, max_q, kv, true, d.n_layers > 0 ? attention_plan(attn) : no_layers,
                    dev_status, st));
@@ -689,7 +689,7 @@ extern "C" mn_status mn_attention(mn_ctx* c, const void* q, const int32_t* spec_
   if (workspace_bytes < w.L.total) return fail(c, MN_EWORKSPACE, "%s: workspace %zu bytes, need %zu", who, workspace_bytes, w.L.total);
   hipStream_t st = (hipStream_t)stream;
   // row bookkeeping only (no tokens): positions are ctx_b + j, the rows' K/V are already cached
-  AttnArgs at = attn_args(c, w, B, M, max_ctx, max_q, kv);
+  AttnArgs at = attn_args(c, w, B, M, max_ctx, max_q, kv, false);
   at.q = q; at.out = out;
   at.kv.k = kv->k_layers[layer]; at.kv.v = kv->v_layers[layer];
   hipError_t lerr = run_prepare(c, w, nullptr, nullptr, spec_len, B, k_max, M, max_ctx, max_q, kv, false, attention_plan(at), dev_status, st);

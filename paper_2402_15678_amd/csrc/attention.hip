@@ -879,7 +879,12 @@ size_t attention_items_capacity(int B, int M, int H, int Hkv) {
   return 16 * (G * (size_t)(M > 0 ? M : 0) / 64 + (size_t)(B > 0 ? B : 0)) + 16;
 }
 
-constexpr int KEYS_MAX_CT = 2;       // most column tiles of the few-row kernel
+// 17 to 32 rows at head_dim 128: the second column tile takes the registers of a second workgroup per CU, and alone the kernel
+// is slower than the LDS-staged one (cold pages, 423 shapes of 1 to 64 sequences x 0 to 2000 keys: 1.13 times its time on
+// average).  What it can win is the rotary launch, where the workgroups just about fill the CUs and the contexts are short:
+// steps of four layers, 129 to 256 workgroups, at most 500 keys 0.89 to 0.99, 1000 keys 0.95 to 1.03; 8 to 128 workgroups 0.95
+// to 1.17, 257 to 640 workgroups 0.91 to 1.08.
+constexpr int KEYS_CT2_MIN_WGS = 129, KEYS_CT2_MAX_WGS = 256, KEYS_CT2_MAX_CTX = 768;
 constexpr int KEYS_RESIDENT = 512;   // its 4-wave workgroups that are resident at once (two per CU): up to here the order of
                                      // the work does not matter and no list is made
 static bool keys_path(const AttnArgs& a) {
@@ -888,7 +893,11 @@ static bool keys_path(const AttnArgs& a) {
       a.items_capacity < attention_items_capacity(a.B, a.M, a.H, a.Hkv))
     return false;
   if (a.hd == HD && (a.scratch == nullptr || a.scratch_bytes < attention_scratch_bytes(a.M, a.H, a.hd, a.max_ctx, a.dtype))) return false;
-  return (a.H / a.Hkv * a.max_q + 15) / 16 <= MN_TUNE("MN_ATTN_KEYS_CT", KEYS_MAX_CT);
+  const int ct = (a.H / a.Hkv * a.max_q + 15) / 16;
+  if (a.hd == 64 || ct == 1) return ct <= 2;
+  const int wgs = a.B * a.Hkv;
+  return ct == 2 && a.append && pick_splits(a.max_ctx) == 1 && !MN_TUNE("MN_ATTN_NOFUSE", 0) && a.max_ctx <= KEYS_CT2_MAX_CTX &&
+         wgs >= KEYS_CT2_MIN_WGS && wgs <= KEYS_CT2_MAX_WGS;
 }
 // Shape of the MFMA launch, from what the host knows (largest row count of a sequence, longest context).
 struct MfmaShape {
@@ -962,10 +971,8 @@ static hipError_t launch_keys_nw(const AttnArgs& a, const MfmaShape& sh, float* 
 template <int HDIM, int CT>
 static hipError_t launch_keys(const AttnArgs& a, const MfmaShape& sh, float* o_part, float* ml_part, hipStream_t st) {
   const int nw = MN_TUNE("MN_ATTN_KEYS_NW", 0);
-  if constexpr (!(HDIM == 128 && CT == 2)) {
-    if (nw ? nw == 8 : a.B * a.Hkv <= 256)
-      return a.qkv ? launch_keys_nw<HDIM, CT, 8, true>(a, sh, o_part, ml_part, st) : launch_keys_nw<HDIM, CT, 8, false>(a, sh, o_part, ml_part, st);
-  }
+  if (nw ? nw == 8 : a.B * a.Hkv <= 256)
+    return a.qkv ? launch_keys_nw<HDIM, CT, 8, true>(a, sh, o_part, ml_part, st) : launch_keys_nw<HDIM, CT, 8, false>(a, sh, o_part, ml_part, st);
   return a.qkv ? launch_keys_nw<HDIM, CT, 4, true>(a, sh, o_part, ml_part, st) : launch_keys_nw<HDIM, CT, 4, false>(a, sh, o_part, ml_part, st);
 }
 
@@ -981,7 +988,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     float* ml_part = a.scratch + (size_t)sh.n_splits * a.M * a.H * HD;
     hipError_t e;
     if (a.hd == 64) e = sh.ctw == 1 ? launch_keys<64, 1>(k, sh, o_part, ml_part, st) : launch_keys<64, 2>(k, sh, o_part, ml_part, st);
-    else e = sh.ctw == 1 ? launch_keys<128, 1>(k, sh, o_part, ml_part, st) : launch_keys<128, 2>(k, sh, o_part, ml_part, st);
+    else e = sh.ctw == 1 ? launch_keys<128, 1>(k, sh, o_part, ml_part, st) : launch_keys_nw<128, 2, 4, true>(k, sh, o_part, ml_part, st);
     if (e == hipSuccess) launch_merge(a, sh.n_splits, o_part, ml_part, st);
     return e;
   }

@@ -128,6 +128,7 @@ struct AttnArgs {
   int32_t* items;        // work list of the MFMA kernel, 8 int32 per record (see prepare_kernel), or null
   size_t items_capacity; // records the buffer holds
   int32_t* row_splits;   // [M] KV splits of the row's sequence (written by the plan, read by the merge), or null
+  bool append;           // this step's rows are still to be turned and appended, in the kernel or by a launch before it
   // Rotary embedding and KV append inside the attention kernel (attention_fuses_append): the QKV projection's partial
   // sums as in RopeAppendArgs; q is not read then.  qkv null: q holds the queries and the pages hold every row.
   const float* qkv;      // [S][M][(H+2Hkv)*hd]

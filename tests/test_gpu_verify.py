@@ -250,6 +250,11 @@ def test_llama160m_width_few_rows(hb):
      [5 * i for i in range(50)], [i % 4 for i in range(50)]),
     ("opt-hd64-list", synth.ModelDesc(synth.ARCH_OPT, synth.DT_BF16, 1, 512, 8, 8, 64, 512, 500, 1024),
      [3 * i for i in range(70)], [i % 3 for i in range(70)]),
+    # two column tiles at head_dim 128: 128 workgroups (not taken), 136 and 256 (taken), 264 (not taken), contexts up to the
+    # last one taken and one beyond
+    *[("opt-hd128-two-tiles-%d-%d" % (n, top), synth.ModelDesc(synth.ARCH_OPT, synth.DT_BF16, 1, 512, 8, 8, 128, 512, 500, 1024),
+       [7 * i for i in range(n - 1)] + [top], [16 + i % 16 for i in range(n - 1)] + [0])
+      for n, top in ((16, 300), (17, 767), (17, 768), (32, 300), (33, 300))],
 ])
 def test_append_inside_attention(hb, name, desc, ctx, ks):
     wl = synth.Workload(name, desc, len(ctx), 0, 300, 0, 15, 2, 0.3, seed=9100)
