@@ -19,6 +19,8 @@ namespace mn {
 // laid out a whole sequence's rows (120 us with the other two launches, 9.9 now; 618 rows of 64 sequences 32 -> 15, 144 of 16
 // 17 -> 9).
 constexpr int PREP_THREADS = 1024;
+constexpr int RANK_WAVES = 64;   // most sequences whose place in the attention work list is found by a wave each
+template <int N> struct IntC { static constexpr int value = N; };
 
 // s_row0[b] = first row of sequence b (b = 0 .. B), from s_row0[b + 1] = rows of sequence b.  Every thread of the workgroup.
 __device__ __forceinline__ void scan_rows(int32_t* s_row0, int B, int32_t* s_wave) {
@@ -190,7 +192,11 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   // group, split, splits of the sequence, first row, rows, enabled, context}.  Sequences are ordered by descending key
   // tiles per workgroup (ties by index), so the longest workgroups start first and the short ones fill the end of
   // the launch; the records of the grid past the last real one get sequence = -1.  Ranking is a comparison of every pair of
-  // sequences (B <= 4096, once per step).
+  // sequences (B <= 4096, once per step): by a wave per sequence while there are few (its lanes also share the records: three
+  // prompts of 250 to 700 tokens 47.4 us for the whole call, 52.5 with a thread each), beyond RANK_WAVES of them by a thread for
+  // each, or for each four, which reads every entry once.  The whole of mn_attention, 8 heads of 128, 30 to 80 keys, wave and
+  // thread: 128 sequences 28.2 and 26.0 us, 256 47.3 and 41.1, 384 68.2 and 55.9, 512 103 and 70, 1024 255 and 130, 4096 2456
+  // and 669; 64 ragged sequences of 256 to 2000 keys 78.2 and 77.5.
   // Balance: a workgroup should take about (all key tiles x KV heads) / (the number of workgroups aimed for) tiles, at
   // least min_tiles (below that the lead-in of a workgroup and the partial sums cost more than the parallelism wins).
   // Long sequences of a ragged batch are then cut into more splits than short ones.
@@ -207,32 +213,64 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
     const int spl = max(1, min(a.plan.n_splits_max, (n_tiles + tps - 1) / max(tps, 1)));
     s_spl[b] = spl;
     s_cnt[b] = n_rg * spl;                  // a disabled sequence keeps one workgroup per row group: it writes zeros
-    s_nb[b] = (n_tiles + spl - 1) / spl;
+    // order of the list in one number: longest workgroups first, then by index
+    s_nb[b] = (min((n_tiles + spl - 1) / spl, (1 << 19) - 1) << 12) | (MN_MAX_BATCH - 1 - b);
   }
   __syncthreads();
   for (int m = tid; m < a.M; m += PREP_THREADS) a.plan.row_splits[m] = s_spl[seq_of_row(s_row0, B, m)];  // for the merge
-  // a wave per sequence: its place among the others, then its records
-  int total = 0;
-  for (int b = tid >> 6; b < B; b += PREP_THREADS / 64) {
-    const int lane = tid & 63, key = s_nb[b], cnt = s_cnt[b], spl = s_spl[b];
-    int off = 0;
-    total = 0;
-    for (int b2 = lane; b2 < B; b2 += 64) {
-      const int c = s_cnt[b2], k2 = s_nb[b2];
-      total += c;
-      if (k2 > key || (k2 == key && b2 < b)) off += c;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      off += __shfl_xor(off, o, 64);
-      total += __shfl_xor(total, o, 64);
-    }
+  // records of sequence b, at place `off` of the list
+  auto write_records = [&](int b, int off, int first, int step) {
+    const int cnt = s_cnt[b], spl = s_spl[b];
     const int row0 = s_row0[b], q = s_row0[b + 1] - row0, ok = s_ok[b], ctx = ok ? s_ctx[b] : 0;
-    for (int i = lane; i < cnt; i += 64) {
+    for (int i = first; i < cnt; i += step) {
       if (off + i >= a.plan.grid_items) break;  // (cannot happen: the grid holds every real record)
       int4* rec = reinterpret_cast<int4*>(a.plan.items) + 2 * (size_t)(off + i);
       rec[0] = make_int4(b, i / spl, i % spl, spl);
       rec[1] = make_int4(row0, q, ok, ctx);
+    }
+  };
+  int total = 0;
+  auto rank_by_thread = [&](auto n_c) {
+    constexpr int N = decltype(n_c)::value;
+    int key[N], off[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+      const int b = tid + u * PREP_THREADS;
+      key[u] = b < B ? s_nb[b] : 0x7fffffff;
+      off[u] = 0;
+    }
+#pragma unroll 8
+    for (int b2 = 0; b2 < B; ++b2) {
+      const int c = s_cnt[b2], k2 = s_nb[b2];
+      total += c;
+#pragma unroll
+      for (int u = 0; u < N; ++u) off[u] += k2 > key[u] ? c : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+      if (tid + u * PREP_THREADS < B) write_records(tid + u * PREP_THREADS, off[u], 0, 1);
+  };
+  static_assert(MN_MAX_BATCH == 4096 && MN_MAX_BATCH <= 4 * PREP_THREADS, "order and ranking by thread");
+  if (B > PREP_THREADS) {
+    rank_by_thread(IntC<4>{});
+  } else if (B > RANK_WAVES) {
+    rank_by_thread(IntC<1>{});
+  } else {
+    for (int b = tid >> 6; b < B; b += PREP_THREADS / 64) {
+      const int lane = tid & 63, key = s_nb[b];
+      int off = 0;
+      total = 0;
+      for (int b2 = lane; b2 < B; b2 += 64) {
+        const int c = s_cnt[b2];
+        total += c;
+        off += s_nb[b2] > key ? c : 0;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        off += __shfl_xor(off, o, 64);
+        total += __shfl_xor(total, o, 64);
+      }
+      write_records(b, off, lane, 64);
     }
   }
   if ((tid >> 6) < B)                       // (every wave that had a sequence knows the total)

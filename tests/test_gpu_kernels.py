@@ -259,6 +259,13 @@ def test_attention_small_probabilities_hd64(hb, x, ks):
     assert err.max() < 2.0 ** -11 + 2.0 ** -34 / p + 2.0 ** -16, err.max()
 
 
+# The work list of many sequences: ranked by a wave each (64), by a thread each (65, 1024), by a thread for four (1025)
+@pytest.mark.parametrize("B", [64, 65, 1024, 1025])
+def test_attention_list_of_many_sequences(hb, B):
+    desc = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 1, 1280, 10, 10, 128, 1024, 64, 8192)
+    _check_attention(hb, desc, [(37 * i) % 90 for i in range(B - 1)] + [2300], [i % 3 for i in range(B)])
+
+
 @pytest.mark.parametrize("seed", list(range(10)))
 def test_attention_drawn_batches(hb, seed):
     """Drawn batches for the MFMA kernel and its work list: 1-24 sequences, contexts 0-2500 (a few of them long, so
