@@ -183,21 +183,15 @@ static Layout make_layout(const mn_model_desc& d, int B, int M, int max_ctx) {
   // Partial sums of the widest projection at the largest split it can get with M rows OR FEWER: a workspace
   // sized for max_rows must serve every step with at most that many rows, and the k-split a projection gets is
   // not monotone in the row count (it drops where the kernel family changes and where a further row block
-  // starts).  Up to 144 rows the split is constant between borders that are multiples of 16, so the largest
-  // need is found at the right ends: M itself and every multiple of 16 below it; beyond, the planner gives a bound.
+  // starts).  The split is constant between those borders, all of which are multiples of 16, so the largest
+  // need is found at the right ends: M itself and every multiple of 16 below it.
   const int nqkv = (d.n_heads + 2 * d.n_kv_heads) * d.head_dim;
   const int w1r = d.d_ffn * (d.arch == MN_ARCH_LLAMA ? 2 : 1);
   size_t pmax = 0;
   const int Ns[5] = {nqkv, d.d_model, w1r, d.d_model, d.vocab};
   const int Ks[5] = {d.d_model, d.n_heads * d.head_dim, d.d_model, d.d_ffn, d.d_model};
   for (int i = 0; i < 5; ++i) {
-    int m2 = (int)Mr;
-    if (m2 > 144) {
-      const size_t rows = d.dtype == MN_DT_BF16 ? gemm_big_partial_rows(m2, Ns[i]) : (size_t)m2;
-      if (rows * Ns[i] * 4 > pmax) pmax = rows * Ns[i] * 4;
-      m2 = 144;
-    }
-    for (;; m2 = (m2 - 1) / 16 * 16) {
+    for (int m2 = (int)Mr;; m2 = (m2 - 1) / 16 * 16) {
       const size_t s = (size_t)gemm_pick_split(m2, Ns[i], Ks[i], d.dtype);
       const size_t b = s * (size_t)m2 * Ns[i] * 4;
       if (b > pmax) pmax = b;
@@ -471,6 +465,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     launch_norm(n, st);
     pend = nullptr; pend_n = 0; pend_bias = nullptr;
   };
+  auto splits = [&](int N, int K) { return gemm_step_split(M, N, K, d.dtype, w.L.partials_bytes); };
   auto gemm = [&](const void* a, const void* wt, float* out, int N, int K, int split) {
     GemmArgs g{};
     g.a = a; g.w = wt; g.out = out; g.bias = nullptr; g.M = M; g.N = N; g.K = K; g.split_k = split; g.dtype = d.dtype;
@@ -481,7 +476,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
 
   for (int l = 0; l < d.n_layers; ++l) {
     norm((const float*)c->ln1_g[l], (const float*)c->ln1_b[l], l == 0);
-    int s = gemm_pick_split(M, nqkv, d.d_model, d.dtype);
+    int s = splits(nqkv, d.d_model);
     gemm(h, c->wqkv[l], part, nqkv, d.d_model, s);
     RopeAppendArgs r{};
     r.qkv = part; r.n_partials = s; r.bias = (const float*)c->bqkv[l];
@@ -508,7 +503,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
       Tap t(&c->prof, MN_PROF_ATTENTION, st);
       keep(launch_attention(at, st));
     }
-    s = gemm_pick_split(M, d.d_model, hdim, d.dtype);
+    s = splits(d.d_model, hdim);
     gemm(at.out, c->wo[l], part, d.d_model, hdim, s);
     pend = part; pend_n = s; pend_bias = (const float*)c->bo[l];
     norm((const float*)c->ln2_g[l], (const float*)c->ln2_b[l], false);
@@ -520,7 +515,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
       g.dev_status = dev_status;
       Tap t(&c->prof, MN_PROF_GEMM, st);
       keep(launch_gemm(g, st));
-    } else if (!llama && gemm_pick_split(M, w1r, d.d_model, d.dtype) == 1) {
+    } else if (!llama && splits(w1r, d.d_model) == 1) {
       // one split: bias + ReLU applied in the kernel's epilogue, no partial sums and no activation kernel
       GemmArgs g{};
       g.a = h; g.w = c->w1[l]; g.relu_act = act; g.bias = (const float*)c->b1[l]; g.M = M; g.N = w1r; g.K = d.d_model;
@@ -528,7 +523,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
       Tap t(&c->prof, MN_PROF_GEMM, st);
       keep(launch_gemm(g, st));
     } else {
-      s = gemm_pick_split(M, w1r, d.d_model, d.dtype);
+      s = splits(w1r, d.d_model);
       gemm(h, c->w1[l], part, w1r, d.d_model, s);
       ActArgs ac{};
       ac.partials = part; ac.n_partials = s; ac.bias = (const float*)c->b1[l]; ac.act = act;
@@ -536,14 +531,14 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
       Tap t(&c->prof, MN_PROF_ACT, st);
       launch_act(ac, st);
     }
-    s = gemm_pick_split(M, d.d_model, d.d_ffn, d.dtype);
+    s = splits(d.d_model, d.d_ffn);
     gemm(act, c->w2[l], part, d.d_model, d.d_ffn, s);
     pend = part; pend_n = s; pend_bias = (const float*)c->b2[l];
   }
   norm((const float*)c->final_norm_g, (const float*)c->final_norm_b, d.n_layers == 0);
   float* lg = logits ? logits : w.at<float>(w.L.logits);
   // (a split head's partial sums are added, and the scores written, by the argmax)
-  const int hs = gemm_pick_split(M, d.vocab, d.d_model, d.dtype);
+  const int hs = splits(d.vocab, d.d_model);
   gemm(h, c->lm_head, hs == 1 ? lg : part, d.vocab, d.d_model, hs);
   {
     Tap t(&c->prof, MN_PROF_ARGMAX, st);
@@ -578,7 +573,7 @@ extern "C" mn_status mn_proj_gemm(mn_ctx* c, const void* a, const void* w, const
   if (split_k < 0 || split_k > MN_MAX_SPLIT_K) return fail(c, MN_EINVAL, "%s: split_k = %d", who, split_k);
   if (M == 0) return MN_OK;
   if (!a || !w || !out) return fail(c, MN_ENULL, "%s: a/w/out is NULL", who);
-  int s = split_k ? split_k : gemm_caller_split(M, N, K);
+  int s = split_k ? split_k : gemm_pick_split(M, N, K, MN_DT_BF16);
   if (s > K / 128) s = K / 128;
   hipStream_t st = (hipStream_t)stream;
   GemmArgs g{};
@@ -636,7 +631,7 @@ extern "C" mn_status mn_proj_gemm_noalloc(mn_ctx* c, const void* a, const void* 
   if (split_k < 0 || split_k > MN_MAX_SPLIT_K) return fail(c, MN_EINVAL, "%s: split_k = %d", who, split_k);
   if (M == 0) return MN_OK;
   if (!a || !w || !out) return fail(c, MN_ENULL, "%s: a/w/out is NULL", who);
-  int s = split_k ? split_k : gemm_caller_split(M, N, K);
+  int s = split_k ? split_k : gemm_pick_split(M, N, K, MN_DT_BF16);
   if (s > K / 128) s = K / 128;
   hipStream_t st = (hipStream_t)stream;
   GemmArgs g{};

@@ -791,12 +791,12 @@ static int few_rows_nw(int M, int slices, int iters, int split) {
 // (at least 16 blocks of 128 k each).  Measured at 845 rows, AT = 5 .. 10: 57344 x 8192 876 833 788 850 727 783 us, 32000 x 8192
 // 498 510 453 487 467 498; 8192 x 28672 in 2 splits, AT = 7, 9, 10: 358 376 401 (AT = 10 was taken for each before,
 // which pads 845 rows to 960 and leaves 64 CUs idle in the split matrices); at 618 rows AT = 10 is best everywhere.
-// The partial-sum term takes the rows in steps of 16: the split is constant between multiples of 16 (see make_layout).
+// The partial-sum term takes the rows in steps of 16: the split is constant between multiples of 16, which make_layout relies on.
 struct BigPlan {
   int at, split;
 };
 constexpr int BIG_WGS = 256;
-static BigPlan big_plan(int M, int N, int K, int forced_split) {
+static BigPlan big_plan(int M, int N, int K, int forced_split, int most) {
   const int gx = ((N + NWG - 1) / NWG + 1) / 2, iters = K / KB;
   BigPlan best{10, 1};
   long best_cost = -1;
@@ -806,7 +806,7 @@ static BigPlan big_plan(int M, int N, int K, int forced_split) {
     if (s < 1) {
       s = BIG_WGS / ((long)gx * rb < BIG_WGS ? gx * rb : BIG_WGS);
       if (s > iters / 16) s = iters / 16;
-      if (s > MN_MAX_SPLIT_K) s = MN_MAX_SPLIT_K;
+      if (s > most) s = most;
       if (s < 1) s = 1;
     }
     const int per = (iters + s - 1) / s;
@@ -821,13 +821,23 @@ static BigPlan big_plan(int M, int N, int K, int forced_split) {
   return best;
 }
 
-// Upper bound of split * rows over all row counts from 145 to M of the big-tile kernel's plans: a split launch is at most
-// BIG_WGS workgroups of at most 320 rows.
-size_t gemm_big_partial_rows(int M, int N) {
-  const size_t gx = ((N + NWG - 1) / NWG + 1) / 2, rows = M;
-  const size_t split_rows = BIG_WGS / (gx < BIG_WGS ? gx : BIG_WGS) * 320;
-  const size_t most = split_rows < (size_t)MN_MAX_SPLIT_K * rows ? split_rows : (size_t)MN_MAX_SPLIT_K * rows;
-  return most > rows ? most : rows;
+// Most splits whose partial sums callers of the big-tile kernel are asked to bring room for: those that fill 256 workgroups with
+// the tiles of 320, 256 or 192 rows that pad the rows least.  Lower tiles can use more (513 rows on 15360 x 4096: 2 instead
+// of 1), and a buffer that was large enough, or a call that needed none, would be refused with them.
+static int big_room_split(int M, int N, int K) {
+  const int gx = ((N + NWG - 1) / NWG + 1) / 2, iters = K / KB;
+  int padded = 1 << 30, blocks = 1;
+  for (int at : {10, 8, 6}) {
+    const int b = (M + 32 * at - 1) / (32 * at);
+    if (b * at < padded) { padded = b * at; blocks = b; }
+  }
+  if (M <= 160) blocks = 1;
+  int s = BIG_WGS / (gx * blocks);
+  if (s > iters / 16) s = iters / 16;
+  if (s > MN_MAX_SPLIT_K) s = MN_MAX_SPLIT_K;
+  if (s < 1) return 1;
+  const int per = (iters + s - 1) / s;
+  return (iters + per - 1) / per;
 }
 
 static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
@@ -847,7 +857,7 @@ static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
   // (tuning builds: the plan of the projection with N output columns by hand)
   if (MN_TUNE("MN_GEMM_PLAN_N", 0) == N && MN_TUNE("MN_GEMM_PLAN_K", 0) == K && M > 96 && M <= 144)
     return GemmPlan{MN_TUNE("MN_GEMM_PLAN_NW", 4), MN_TUNE("MN_GEMM_PLAN_SPLIT", 1)};
-  if (M > 144 || (big_min_m() > 0 && M >= big_min_m())) return GemmPlan{8, big_plan(M, N, K, forced_split).split};
+  if (M > 144 || (big_min_m() > 0 && M >= big_min_m())) return GemmPlan{8, big_plan(M, N, K, forced_split, big_room_split(M, N, K)).split};
   if (M <= 96) {
     // up to six row tiles: the k-split is picked for 4-wave workgroups.  Few rows make an iteration cheap, so a split may be
     // as short as 8 iterations, and one workgroup per CU is enough (measured at 40 rows: the 5120 x 5120 matrix
@@ -899,26 +909,13 @@ int gemm_pick_split(int M, int N, int K, int dtype) {
   return gemm_plan(M, N, K, 0).split;
 }
 
-// The library's choice where the caller brings the room for the partial sums (or the built-in buffer is it): the plan's
-// split, above 144 rows at most the one that fills 256 workgroups with the tiles of 320, 256 or 192 rows that pad the rows
-// least.  Lower tiles can ask for more splits (513 rows on 15360 x 4096: 2 instead of 1), and a call that needed no room
-// would be refused without it.
-int gemm_caller_split(int M, int N, int K) {
-  const int s = gemm_pick_split(M, N, K, MN_DT_BF16);
-  if (M <= 144 || s <= 1) return s;
-  const int gx = ((N + NWG - 1) / NWG + 1) / 2, iters = K / KB;
-  int padded = 1 << 30, blocks = 1;
-  for (int at : {10, 8, 6}) {
-    const int b = (M + 32 * at - 1) / (32 * at);
-    if (b * at < padded) { padded = b * at; blocks = b; }
-  }
-  if (M <= 160) blocks = 1;
-  int most = BIG_WGS / (gx * blocks);
-  if (most > iters / 16) most = iters / 16;
-  if (most < 1) return 1;
-  const int per = (iters + most - 1) / most;
-  most = (iters + per - 1) / per;
-  return s < most ? s : most;
+// Split of a projection inside a step whose partial sums have `room` bytes (sized by gemm_pick_split, as the largest need of all
+// its projections): above 144 rows the plan may have more splits than the entry points' where they fit.
+int gemm_step_split(int M, int N, int K, int dtype, size_t room) {
+  const int s = gemm_pick_split(M, N, K, dtype);
+  if (dtype != MN_DT_BF16 || M <= 144) return s;
+  const int more = big_plan(M, N, K, 0, MN_MAX_SPLIT_K).split;
+  return (size_t)more * M * N * 4 <= room ? more : s;
 }
 
 template <int MT, int NW, int NTW = 2, int RD = 2>
@@ -1018,7 +1015,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
     if (!MN_TUNE("MN_GEMM_BIG", 1)) {  // 0 = chunks of the streaming kernel
       launch_bf16_mt<8, 4>(a, (tiles + 7) / 8, st);
     } else {
-      switch (big_plan(a.M, a.N, a.K, a.split_k).at) {
+      switch (big_plan(a.M, a.N, a.K, a.split_k, MN_MAX_SPLIT_K).at) {
         case 5: return launch_big<5>(a, st);
         case 6: return launch_big<6>(a, st);
         case 7: return launch_big<7>(a, st);

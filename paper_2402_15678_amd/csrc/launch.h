@@ -106,9 +106,8 @@ struct GemmArgs {
   int M, N, K, split_k, dtype;
   int32_t* dev_status;  // MN_DEV_RANGE is OR-ed in when a fused fp16 epilogue saturates a value, or null
 };
-int gemm_pick_split(int M, int N, int K, int dtype);
-int gemm_caller_split(int M, int N, int K);  // of the component entry points (16-bit models)
-size_t gemm_big_partial_rows(int M, int N);  // bound of split * rows over the row counts 145 .. M
+int gemm_pick_split(int M, int N, int K, int dtype);  // the library's choice; sizes the workspace
+int gemm_step_split(int M, int N, int K, int dtype, size_t room);
 size_t packed_weight_elems(int N, int K);
 void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int32_t* status, hipStream_t st);
 // hipSuccess, or the error of a one-time kernel attribute setting that failed (nothing is launched then)

@@ -154,6 +154,25 @@ def test_workspace_for_max_rows_serves_every_smaller_step(binding):
         binding.mn_destroy(ctx)
 
 
+def test_workspace_of_many_rows_asks_for_no_more_than_before(binding):
+    """A buffer sized by an earlier build stays large enough: (batch, rows, longest context) -> bytes as they were when the
+    many-rows kernel had the tile heights 160, 192, 256 and 320 only (lower tiles can use more splits; they do where they fit)."""
+    from paper_2402_15678_amd import synth
+    for d, known in [
+        (synth.OPT_13B, {(16, 145, 2048): 120573440, (16, 321, 2048): 266704640, (16, 845, 2048): 699416320}),
+        (synth.LLAMA2_70B, {(16, 145, 2048): 154077696, (64, 225, 2048): 239099648, (16, 513, 2048): 528272384}),
+        (synth.LLAMA_160M, {(16, 145, 2048): 39194112, (16, 321, 2048): 86734592, (1, 576, 300): 155590656}),
+        (synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 512, 8, 2, 64, 2048, 4096, 4096), {(16, 145, 2048): 6928384, (1, 320, 300): 13537792, (64, 2000, 2048): 84638720}),
+    ]:
+        w, keep = _weights(binding, 2)
+        kw = dict(arch=d.arch, dtype=d.dtype, n_layers=2, d_model=d.d_model, n_heads=d.n_heads, n_kv_heads=d.n_kv_heads,
+                  head_dim=d.head_dim, d_ffn=d.d_ffn, vocab=d.vocab, max_pos=d.max_pos)
+        ctx = binding.mn_create(_desc(binding, **kw), w)
+        for (B, rows, max_ctx), most in known.items():
+            assert 0 < binding.mn_workspace_bytes(ctx, B, rows, max_ctx) <= most, (d.d_model, B, rows)
+        binding.mn_destroy(ctx)
+
+
 def test_stochastic_entries_reject_bad_arguments_before_launch(binding):
     p = 0x1000
     vs = lambda **kw: binding.mn_verify_sample(None, kw.get("logits", p), p, p, p, p, kw.get("B", 2), kw.get("k_max", 3),
