@@ -785,12 +785,23 @@ static int few_rows_nw(int M, int slices, int iters, int split) {
   return best;
 }
 
-// Big-tile kernel: row tiles per wave (AT, a workgroup has 32 AT rows x 256 columns) and k-splits together.  One workgroup
-// per CU, so the launch is whole rounds of 256 workgroups; a k-step of 32 takes about 0.13 + 0.0875 AT us, a split's
-// partial sums are written and read once more at about 5 TB/s.  The split is the largest that stays within one round
-// (at least 16 blocks of 128 k each).  Measured at 845 rows, AT = 5 .. 10: 57344 x 8192 876 833 788 850 727 783 us, 32000 x 8192
-// 498 510 453 487 467 498; 8192 x 28672 in 2 splits, AT = 7, 9, 10: 358 376 401 (AT = 10 was taken for each before,
-// which pads 845 rows to 960 and leaves 64 CUs idle in the split matrices); at 618 rows AT = 10 is best everywhere.
+// (column group, split) pairs a launch of the big-tile kernel deals to one XCD
+static int big_per_xcd(int gx, int split) {
+  if (split <= 8 && 8 % split == 0) return (gx + 8 / split - 1) / (8 / split);
+  if (split % 8 == 0) return split / 8 * gx;
+  return (gx * split + 7) / 8;
+}
+
+// Big-tile kernel: row tiles per wave (AT, a workgroup has 32 AT rows x 256 columns) and k-splits together, by the least of
+//  * rounds x k-steps of 32 x (0.2 + 0.0875 AT us).  One workgroup per CU, dealt to 8 XCDs of 32 CUs: whole rounds are what the
+//    fullest XCD needs (11 column groups of 20 on it are 33 workgroups, two rounds, where 256 CUs would hold all 220), but a
+//    round that is not full also runs faster, so rounds and work (at least 20 of 32 CUs' worth) count half each;
+//  * the partial sums, written and read once more at about 5 TB/s;
+//  * the weights once more for the second and later row blocks, 90 ns a MB: their loads share the L2 only in part.
+// The split is the largest that stays within one round (at least 16 blocks of 128 k each).  Measured with cold weights on 509
+// shapes (145 to 3000 rows, 34 matrices of 512 to 57344 columns), every height and split: the plan is at 0.912 of the time that
+// heights of 320, 256 and 192 rows by least padding take (the best choice for each shape: 0.908), slower by more than 3 % on two
+// of them (3.4 %).  845 rows, AT = 5 .. 10: 57344 x 8192 876 833 788 850 727 783 us; 2000 rows on 5120 x 5120, AT = 6, 7: 180, 116.
 // The partial-sum term takes the rows in steps of 16: the split is constant between multiples of 16, which make_layout relies on.
 struct BigPlan {
   int at, split;
@@ -799,7 +810,7 @@ constexpr int BIG_WGS = 256;
 static BigPlan big_plan(int M, int N, int K, int forced_split, int most) {
   const int gx = ((N + NWG - 1) / NWG + 1) / 2, iters = K / KB;
   BigPlan best{10, 1};
-  long best_cost = -1;
+  double best_ns = -1.0;
   for (int at = 10; at >= 5; --at) {
     const int rb = (M + 32 * at - 1) / (32 * at);
     int s = forced_split;
@@ -811,11 +822,13 @@ static BigPlan big_plan(int M, int N, int K, int forced_split, int most) {
     }
     const int per = (iters + s - 1) / s;
     s = (iters + per - 1) / per;  // drop splits that would get no iteration
-    const long rounds = ((long)gx * rb * s + BIG_WGS - 1) / BIG_WGS;
-    const long cost = rounds * per * KS * (1300 + 875 * at) / 10 + (long)s * ((M + 15) / 16 * 16) * N * 8 / 5000;  // ns
-    if (best_cost < 0 || cost < best_cost) {
+    const long on_xcd = (long)big_per_xcd(gx, s) * rb;
+    const double rounds = 0.5 * (double)((on_xcd + 31) / 32) + 0.5 * (double)(on_xcd > 20 ? on_xcd : 20) / 32.0;
+    const double ns = rounds * per * KS * (200.0 + 87.5 * at) + (double)s * ((M + 15) / 16 * 16) * N * 8.0 / 5000.0 +
+                      (rb - 1.0) / rb * (double)N * K * 2.0 * 90e-6;
+    if (best_ns < 0.0 || ns < best_ns) {
       best = BigPlan{at, s};
-      best_cost = cost;
+      best_ns = ns;
     }
   }
   return best;
@@ -950,16 +963,16 @@ static void launch_few_rows(const GemmArgs& a, hipStream_t st) {
   }
 }
 
+// rows of a workgroup's tile in the big-tile kernel (more than 144 rows)
+int gemm_tile_rows(int M, int N, int K, int split) { return 32 * big_plan(M, N, K, split, MN_MAX_SPLIT_K).at; }
+
 template <int AT>
 static hipError_t launch_big(const GemmArgs& a, hipStream_t st) {
   const int iters = a.K / KB;
   const int per = (iters + a.split_k - 1) / a.split_k;  // 128-k blocks per split
   const int gx = ((a.N + NWG - 1) / NWG + 1) / 2;       // 256-column groups
   const int rb = (a.M + 32 * AT - 1) / (32 * AT);
-  int per_xcd = (gx * a.split_k + 7) / 8;               // (column group, split) pairs per XCD
-  if (a.split_k <= 8 && 8 % a.split_k == 0) per_xcd = (gx + 8 / a.split_k - 1) / (8 / a.split_k);
-  else if (a.split_k % 8 == 0) per_xcd = (a.split_k / 8) * gx;
-  const dim3 grid(8 * per_xcd * rb, 1, 1);
+  const dim3 grid(8 * big_per_xcd(gx, a.split_k) * rb, 1, 1);
   const size_t smem = (size_t)2 * 32 * AT * 128 + (size_t)BIG_NST * BIG_W_BYTES;
   const f16_t* A = reinterpret_cast<const f16_t*>(a.a);
   const bf16_t* W = reinterpret_cast<const bf16_t*>(a.w);
@@ -1015,7 +1028,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
     if (!MN_TUNE("MN_GEMM_BIG", 1)) {  // 0 = chunks of the streaming kernel
       launch_bf16_mt<8, 4>(a, (tiles + 7) / 8, st);
     } else {
-      switch (big_plan(a.M, a.N, a.K, a.split_k, MN_MAX_SPLIT_K).at) {
+      switch (gemm_tile_rows(a.M, a.N, a.K, a.split_k) / 32) {
         case 5: return launch_big<5>(a, st);
         case 6: return launch_big<6>(a, st);
         case 7: return launch_big<7>(a, st);

@@ -108,6 +108,7 @@ struct GemmArgs {
 };
 int gemm_pick_split(int M, int N, int K, int dtype);  // the library's choice; sizes the workspace
 int gemm_step_split(int M, int N, int K, int dtype, size_t room);
+int gemm_tile_rows(int M, int N, int K, int split);
 size_t packed_weight_elems(int N, int K);
 void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int32_t* status, hipStream_t st);
 // hipSuccess, or the error of a one-time kernel attribute setting that failed (nothing is launched then)

@@ -173,6 +173,18 @@ def test_workspace_of_many_rows_asks_for_no_more_than_before(binding):
         binding.mn_destroy(ctx)
 
 
+def test_many_rows_plan_counts_rounds_per_xcd(binding):
+    """The many-rows kernel's workgroups are dealt to 8 XCDs of 32 CUs: a tile height whose fullest XCD gets a 33rd workgroup
+    runs two rounds although the chip has 256 CUs (2000 rows on 5120 x 5120 in tiles of 192: 180 us, of 224: 116)."""
+    rows_of_tile = binding.lib._ZN2mn14gemm_tile_rowsEiiii          # mn::gemm_tile_rows(M, N, K, split)
+    for M, N, K in [(2000, 5120, 5120), (2000, 5120, 20480), (2000, 11008, 4096), (3000, 2304, 768)]:
+        h = rows_of_tile(M, N, K, 1)
+        groups = -(-(-(-N // 128)) // 2)
+        on_xcd = -(-groups // 8) * -(-M // h)
+        fewest = min(-(-(-(-groups // 8) * -(-M // x)) // 32) for x in (160, 192, 224, 256, 288, 320))
+        assert -(-on_xcd // 32) == fewest, (M, N, K, h)
+
+
 def test_stochastic_entries_reject_bad_arguments_before_launch(binding):
     p = 0x1000
     vs = lambda **kw: binding.mn_verify_sample(None, kw.get("logits", p), p, p, p, p, kw.get("B", 2), kw.get("k_max", 3),
