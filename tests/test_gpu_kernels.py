@@ -139,8 +139,8 @@ def _check_accept(hb, g, B, k_max):
                                          (16, 2304, 768, 0), (32, 700, 3072, 0), (33, 700, 3072, 0), (95, 2304, 768, 0),
                                          (5, 20480, 256, 1), (48, 20400, 128, 1), (64, 50272, 128, 1), (1, 64000, 128, 1),
                                          (96, 63990, 128, 1),
-                                         # the many-rows kernel at every tile height (160 to 320 rows), each one row over and
-                                         # under it, its splits chosen and forced
+                                         # the many-rows kernel at row counts beside multiples of 32, its splits chosen and
+                                         # forced (its tile heights: test_many_rows_tile_heights)
                                          (146, 4096, 4096, 0), (160, 200, 256, 1), (161, 4096, 4096, 0), (193, 8192, 2048, 0),
                                          (224, 300, 384, 3), (225, 8192, 2048, 0), (257, 8192, 2048, 0), (288, 520, 512, 2),
                                          (289, 2000, 2048, 0), (845, 4096, 4096, 0), (449, 57344, 256, 1), (864, 57344, 128, 1)])
@@ -168,6 +168,16 @@ def test_proj_gemm_matches_fp64(hb, M, N, K, split):
     # exact products, fp32 accumulation over K terms of magnitude ~0.05: far below 1e-3
     assert err < 2e-3 * max(1.0, np.sqrt(K / 1024.0)), err
     assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("height", [160, 192, 224, 256, 288, 320])
+def test_many_rows_tile_heights(hb, height):
+    """Every tile height of the many-rows kernel: a full tile in three splits, a ragged one, two of which one is ragged.  The
+    height is the launch's own choice, so the shapes are checked to be ones it takes that height for."""
+    rows_of_tile = hb[1].lib._ZN2mn14gemm_tile_rowsEiiii          # mn::gemm_tile_rows(M, N, K, split)
+    for M, N, K, split in [(height, 20400, 384, 3), (height - 13, 57340, 128, 1), (2 * height - 29, 31990, 384, 1)]:
+        assert rows_of_tile(M, N, K, split) == height, (M, N, K, split)
+        test_proj_gemm_matches_fp64(hb, M, N, K, split)
 
 
 # ---------------------------------------------------------------------------- attention
