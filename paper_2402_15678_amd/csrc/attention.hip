@@ -28,13 +28,14 @@ namespace mn {
 // ------------------------------------------------------------------------------------------
 // generic kernel
 // ------------------------------------------------------------------------------------------
-// 256 threads; 1024 beyond 256 keys of context where every workgroup has a CU to itself (GEN_ALONE): a chunk of keys is one
-// round trip to the pages and back, whatever its size.  With more workgroups the round trips of one hide behind another's, and
-// 1024 threads only leave fewer of them on a CU, most of their threads idle on a prompt's early rows.  Measured with cold
-// pages over 219 shapes (head_dim 32 to 256, fp32 and fp16 pages, 1 to 1000 rows), 1024 against 256 threads: up to 256
-// workgroups 0.70 to 1.00 of the time, 257 to 320 1.00 to 1.16, 513 to 1024 1.03 to 1.33, beyond 4096 1.05 to 2.30 (a drafting
-// model's 16 prompts of 300 tokens 1073 us with 256, 1740 with 1024).
-constexpr int GEN_ALONE = 256;
+// 256 threads; 1024 beyond 256 keys of context where every workgroup has a CU to itself, and up to two per CU at contexts beyond
+// 1024 keys: a chunk of keys is one round trip to the pages and back, whatever its size.  With more workgroups the round trips
+// of one hide behind another's, and 1024 threads only leave fewer of them on a CU, most of their threads idle on a prompt's early
+// rows.  Measured with cold pages (head_dim 32 to 256, fp32 and fp16 pages, 1 to 1000 rows, even and ragged contexts), 1024
+// against 256 threads: up to 256 workgroups 0.67 to 1.01 of the time; 257 to 512 workgroups 0.88 to 1.16 at 300 and 700 keys, 0.80
+// to 1.12 (0.97 on average) at 1500, 0.60 to 1.05 (0.91) at 3000 and 6000; 513 to 1024 workgroups 0.81 to 1.37 (1.12); beyond 4096
+// 1.05 to 2.30 (a drafting model's 16 prompts of 300 tokens 1073 us with 256, 1740 with 1024).
+constexpr int GEN_ALONE = 256, GEN_PAIRS = 512, GEN_LONG = 1024;
 
 // TA: activation type of q and out; T: storage type of the KV pages
 template <typename TA, typename T, int GEN_THREADS>
@@ -1024,7 +1025,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     return hipSuccess;
   }
   dim3 grid(a.H, a.M);
-  const bool wide = a.max_ctx > 256 && (long)a.M * a.H <= GEN_ALONE;
+  const bool wide = a.max_ctx > 256 && (long)a.M * a.H <= (a.max_ctx > GEN_LONG ? GEN_PAIRS : GEN_ALONE);
   if (a.dtype == MN_DT_BF16) {
     if (wide) attn_generic_kernel<f16_t, f16_t, 1024><<<grid, 1024, 0, st>>>(a);
     else attn_generic_kernel<f16_t, f16_t, 256><<<grid, 256, 0, st>>>(a);

@@ -188,9 +188,12 @@ def test_many_rows_tile_heights(hb, height):
     ("gqa-ragged", synth.LLAMA2_70B.with_layers(1), [256, 2047, 513, 15, 16, 1, 300], [1, 16, 7, 0, 3, 16, 12]),
     ("mha-opt13b", synth.OPT_13B.with_layers(1), [512, 100, 31], [4, 4, 0]),
     ("fp32-generic", synth.OPT_TINY.with_layers(1), [64, 0, 300], [4, 63, 2]),
-    # the fallback kernel's two sizes: as many workgroups as CUs at contexts beyond 256 keys, and one row more; a drafting prompt
-    ("fp32-wide", synth.OPT_TINY.with_layers(1), [1100, 0], [60, 2]),
-    ("fp32-wide-one-more", synth.OPT_TINY.with_layers(1), [1100, 0], [60, 3]),
+    # the fallback kernel's two sizes: as many workgroups as CUs at contexts beyond 256 keys and one row more, twice as many beyond
+    # 1024 keys and one row more; a drafting prompt
+    ("fp32-wide", synth.OPT_TINY.with_layers(1), [700, 0], [60, 2]),
+    ("fp32-wide-one-more", synth.OPT_TINY.with_layers(1), [700, 0], [60, 3]),
+    ("fp32-wide-long", synth.OPT_TINY.with_layers(1), [1100, 0], [60, 66]),
+    ("fp32-wide-long-one-more", synth.OPT_TINY.with_layers(1), [1100, 0], [60, 67]),
     ("hd64-prompt-generic", synth.LLAMA_160M.with_layers(1), [0, 10], [299, 40]),
     # head_dim 64, few rows per KV head: the drafting models' decode shape and its neighbours
     ("fewrow-mha-decode", synth.LLAMA_160M.with_layers(1), [1024, 1000, 37, 0, 63, 64, 65, 2047], [0] * 8),
