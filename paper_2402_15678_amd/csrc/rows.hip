@@ -443,59 +443,76 @@ void launch_norm(const NormArgs& a, hipStream_t st) {
 // ------------------------------------------------------------------------------------------
 // rotary embedding + tentative KV append
 // ------------------------------------------------------------------------------------------
-// grid (ceil(heads / heads per block), M), 256 threads: a thread owns four pairs (t .. t+3, and + hd/2) of one head, so a
-// block takes 2048 / hd consecutive heads of one row and every load of the partial sums is 16 bytes (one pair per thread, 4-byte
-// loads: 845 rows of the 70B shape 28.4 -> 23.0 us, 618 rows 23.3 -> 19.9, 144 rows 8.0 and 8.3).
+// grid (ceil(heads / heads per block), M), 256 threads: a thread owns W pairs (t .. t+W-1, and + hd/2) of one head, so a
+// block takes 512 W / hd consecutive heads of one row.  Four (16-byte loads of the partial sums) where most heads are query heads,
+// whose four elements are stored at once, and there are many rows: the elements of a K/V row go to the pages one by one, and
+// those stores are slower the fewer threads share them.  Four and one pair: 64 query heads of 128 over 8 KV heads 22.6 and 28.3 us
+// at 844 rows, 14.5 and 16.2 at 400, 11.4 both at 256, 7.9 both at 144 (a four-layer step 1590 and 1596), 6.5 and 6.0 at 96 (1452
+// and 1451); 32 over 8 22.7 and 29.4 at 1500 rows; 32 over 16 24.1 and 16.0 at 520; 40 over 40 67.3 and 42.0 at 844, 16.4 and 11.0
+// at 144.
 // TA: activation type of the query buffer; T: storage type of the KV pages
 constexpr int ROPE_THREADS = 256;
-template <typename TA, typename T>
+constexpr int ROPE_WIDE_ROWS = 97, ROPE_WIDE_GROUP = 4;  // fewest rows and query heads per KV head for four pairs
+template <typename TA, typename T, int W>
 __global__ void __launch_bounds__(ROPE_THREADS) rope_append_kernel(RopeAppendArgs a) {
+  struct alignas(4 * W) Piece { float x[W]; };
+  struct alignas(4) PieceU { float x[W]; };                    // (biases start at any float's address)
+  constexpr int PB = W == 1 ? 8 : 4;                           // partial sums in flight
   const int m = blockIdx.y;
-  const int hd = a.hd, half = hd >> 1, q4 = half >> 2;         // (head_dim is a multiple of 8)
-  const int head = blockIdx.x * (ROPE_THREADS / q4) + (int)threadIdx.x / q4;
-  const int t = ((int)threadIdx.x % q4) << 2;
+  const int hd = a.hd, half = hd >> 1, qw = half / W;          // (head_dim is a multiple of 8)
+  const int head = blockIdx.x * (ROPE_THREADS / qw) + (int)threadIdx.x / qw;
+  const int t = ((int)threadIdx.x % qw) * W;
   if (head >= a.H + 2 * a.Hkv) return;
   const int slot = a.rows.row_slot[m];  // (asked for first: the stores at the end wait for nothing else)
   const int ncols = (a.H + 2 * a.Hkv) * hd;
   const int c0 = head * hd + t, c1 = c0 + half;
   const bool is_v = head >= a.H + a.Hkv, turn = a.rope_cos && !is_v;
-  f32x4 cs = {1.f, 1.f, 1.f, 1.f}, sn = {0.f, 0.f, 0.f, 0.f};
-  if (turn) {
-    cs = *reinterpret_cast<const f32x4*>(a.rope_cos + (size_t)m * half + t);
-    sn = *reinterpret_cast<const f32x4*>(a.rope_sin + (size_t)m * half + t);
-  }
-  f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
-  // partials fetched four at a time before any is added (see norm_kernel); the order of the sum is fixed
-  for (int s0 = 0; s0 < a.n_partials; s0 += 4) {
-    f32x4 p0[4], p1[4];
+  Piece cs, sn, v0, v1;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+  for (int e = 0; e < W; ++e) { cs.x[e] = 1.f; sn.x[e] = v0.x[e] = v1.x[e] = 0.f; }
+  if (turn) {
+    cs = *reinterpret_cast<const Piece*>(a.rope_cos + (size_t)m * half + t);
+    sn = *reinterpret_cast<const Piece*>(a.rope_sin + (size_t)m * half + t);
+  }
+  // partials fetched PB at a time before any is added (see norm_kernel); the order of the sum is fixed
+  for (int s0 = 0; s0 < a.n_partials; s0 += PB) {
+    Piece p0[PB], p1[PB];
+#pragma unroll
+    for (int j = 0; j < PB; ++j) {
       const float* p = a.qkv + ((size_t)min(s0 + j, a.n_partials - 1) * a.M + m) * ncols;
-      p0[j] = *reinterpret_cast<const f32x4*>(p + c0);
-      p1[j] = *reinterpret_cast<const f32x4*>(p + c1);
+      p0[j] = *reinterpret_cast<const Piece*>(p + c0);
+      p1[j] = *reinterpret_cast<const Piece*>(p + c1);
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if (s0 + j < a.n_partials) { v0 += p0[j]; v1 += p1[j]; }
+    for (int j = 0; j < PB; ++j)
+      if (s0 + j < a.n_partials) {
+#pragma unroll
+        for (int e = 0; e < W; ++e) { v0.x[e] += p0[j].x[e]; v1.x[e] += p1[j].x[e]; }
+      }
   }
   if (a.bias) {
-    const f32x4_u b0 = *reinterpret_cast<const f32x4_u*>(a.bias + c0), b1 = *reinterpret_cast<const f32x4_u*>(a.bias + c1);
+    const PieceU b0 = *reinterpret_cast<const PieceU*>(a.bias + c0), b1 = *reinterpret_cast<const PieceU*>(a.bias + c1);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { v0[e] += b0[e]; v1[e] += b1[e]; }
+    for (int e = 0; e < W; ++e) { v0.x[e] += b0.x[e]; v1.x[e] += b1.x[e]; }
   }
   if (turn) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float x = v0[e], y = v1[e];
-      v0[e] = x * cs[e] - y * sn[e];
-      v1[e] = y * cs[e] + x * sn[e];
+    for (int e = 0; e < W; ++e) {
+      const float x = v0.x[e], y = v1.x[e];
+      v0.x[e] = x * cs.x[e] - y * sn.x[e];
+      v1.x[e] = y * cs.x[e] + x * sn.x[e];
     }
   }
   bool bad = false;
   if (head < a.H) {
     TA* q = reinterpret_cast<TA*>(a.q) + ((size_t)m * a.H + head) * hd;
-    store4<TA>(q + t, make_float4(v0[0], v0[1], v0[2], v0[3]), bad);
-    store4<TA>(q + t + half, make_float4(v1[0], v1[1], v1[2], v1[3]), bad);
+    if constexpr (W == 4) {
+      store4<TA>(q + t, make_float4(v0.x[0], v0.x[1], v0.x[2], v0.x[3]), bad);
+      store4<TA>(q + t + half, make_float4(v1.x[0], v1.x[1], v1.x[2], v1.x[3]), bad);
+    } else {
+      store1<TA>(q + t, v0.x[0], bad);
+      store1<TA>(q + t + half, v1.x[0], bad);
+    }
     if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
     return;
   }
@@ -506,33 +523,38 @@ __global__ void __launch_bounds__(ROPE_THREADS) rope_append_kernel(RopeAppendArg
   if (!is_v) {
     const int kh = head - a.H;
     T* base = reinterpret_cast<T*>(a.kv.k) + ((size_t)pb * a.Hkv + kh) * (size_t)hd * bs;
-    // [hd/8][bs][8]: the four elements are neighbours inside their piece of eight
+    // [hd/8][bs][8]: the W elements are neighbours inside their piece of eight
     T* k0 = base + ((size_t)(t >> 3) * bs + off) * 8 + (t & 7);
     T* k1 = base + ((size_t)((t + half) >> 3) * bs + off) * 8 + ((t + half) & 7);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      store1<T>(k0 + e, v0[e], bad);
-      store1<T>(k1 + e, v1[e], bad);
+    for (int e = 0; e < W; ++e) {
+      store1<T>(k0 + e, v0.x[e], bad);
+      store1<T>(k1 + e, v1.x[e], bad);
     }
   } else {
     const int vh = head - a.H - a.Hkv;
     T* base = reinterpret_cast<T*>(a.kv.v) + ((size_t)pb * a.Hkv + vh) * (size_t)hd * bs;
     // [hd][bs]
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      store1<T>(base + (size_t)(t + e) * bs + off, v0[e], bad);
-      store1<T>(base + (size_t)(t + half + e) * bs + off, v1[e], bad);
+    for (int e = 0; e < W; ++e) {
+      store1<T>(base + (size_t)(t + e) * bs + off, v0.x[e], bad);
+      store1<T>(base + (size_t)(t + half + e) * bs + off, v1.x[e], bad);
     }
   }
   if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
 }
 
+template <int W>
+static void launch_rope_w(const RopeAppendArgs& a, hipStream_t st) {
+  const int per_block = ROPE_THREADS / (a.hd / (2 * W));  // head_dim is one of 8 ... 256: hd/8 divides 256
+  dim3 grid((a.H + 2 * a.Hkv + per_block - 1) / per_block, a.M);
+  if (a.dtype == MN_DT_BF16) rope_append_kernel<f16_t, f16_t, W><<<grid, ROPE_THREADS, 0, st>>>(a);
+  else rope_append_kernel<float, float, W><<<grid, ROPE_THREADS, 0, st>>>(a);
+}
 void launch_rope_append(const RopeAppendArgs& a, hipStream_t st) {
   if (a.M <= 0) return;
-  const int per_block = ROPE_THREADS / (a.hd / 8);  // head_dim is one of 8 ... 256: hd/8 divides 256
-  dim3 grid((a.H + 2 * a.Hkv + per_block - 1) / per_block, a.M);
-  if (a.dtype == MN_DT_BF16) rope_append_kernel<f16_t, f16_t><<<grid, ROPE_THREADS, 0, st>>>(a);
-  else rope_append_kernel<float, float><<<grid, ROPE_THREADS, 0, st>>>(a);
+  if (a.M >= ROPE_WIDE_ROWS && a.H >= ROPE_WIDE_GROUP * a.Hkv) launch_rope_w<4>(a, st);
+  else launch_rope_w<1>(a, st);
 }
 
 // ------------------------------------------------------------------------------------------

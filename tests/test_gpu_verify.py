@@ -261,6 +261,19 @@ def test_append_inside_attention(hb, name, desc, ctx, ks):
     _reduced_case(hb, wl, desc.n_layers, len(ctx), 1, ctx_override=ctx, k_override=ks, min_decisive=0)
 
 
+# Rotary embedding and append as a launch of their own: four pairs per thread (97 rows and more, at least four query heads per
+# KV head) on every head width and both types, and one pair beside it (96 rows; three query heads per KV head)
+@pytest.mark.parametrize("dtype,H,Hkv,hd,rows", [(synth.DT_F32, 8, 1, 8, 97), (synth.DT_F32, 8, 2, 32, 145), (synth.DT_F32, 8, 2, 32, 96),
+                                                 (synth.DT_BF16, 12, 3, 32, 97), (synth.DT_BF16, 8, 2, 64, 150), (synth.DT_BF16, 16, 4, 64, 96),
+                                                 (synth.DT_BF16, 5, 1, 128, 99), (synth.DT_BF16, 6, 2, 128, 147), (synth.DT_BF16, 4, 1, 256, 97)])
+def test_rotary_append_widths(hb, dtype, H, Hkv, hd, rows):
+    d_model = 128 * -(-H * hd // 128)
+    desc = synth.ModelDesc(synth.ARCH_LLAMA, dtype, 1, d_model, H, Hkv, hd, 256, 300, 512)
+    ctx, ks = [0, 17, 33], [rows // 3 - 1, rows // 3 - 1, rows - 2 * (rows // 3) - 1]
+    wl = synth.Workload("rotary-widths", desc, 3, 0, 300, 0, 60, 2, 0.3, seed=9200)
+    _reduced_case(hb, wl, 1, 3, 1, ctx_override=ctx, k_override=ks, min_decisive=0)
+
+
 @pytest.mark.parametrize("d,heads,ffn,vocab,ks", [(64, 2, 64, 1, [0]), (192, 3, 320, 37, [7, 0, 8]), (1088, 4, 1024, 130, [2, 3])])
 def test_fp32_projection_edges(hb, d, heads, ffn, vocab, ks):
     """The fp32 projection's pieces: contractions shorter than a wave's 256 elements, between one and four pieces per lane and
