@@ -155,7 +155,7 @@ def test_workspace_for_max_rows_serves_every_smaller_step(binding):
 
 
 def test_workspace_of_many_rows_asks_for_no_more_than_before(binding):
-    """A buffer sized by an earlier build stays large enough: (batch, rows, longest context) -> bytes as they were when the
+    """A buffer sized by an earlier version stays large enough: (batch, rows, longest context) -> bytes as they were when the
     many-rows kernel had the tile heights 160, 192, 256 and 320 only (lower tiles can use more splits; they do where they fit)."""
     from paper_2402_15678_amd import synth
     for d, known in [
