@@ -448,6 +448,23 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   void* h = w.at<void>(w.L.h);
   float* part = w.at<float>(w.L.partials);
 
+  // Small RMSNorm models: the norms between the projections and the residual stream are folded into the projections
+  // (gemm_small.hip).  The rows' statistics lie behind the QKV sums, where the partial sums have room left.
+  const size_t row_stats = (size_t)(d.d_model / 16 + 2) * M;
+  const bool small = llama && d.dtype == MN_DT_BF16 && d.n_layers > 0 && attention_fuses_append(attn) && gemm_small_model(M, nqkv, d.d_model, hdim, w1r, d.d_ffn) &&
+                     ((size_t)M * nqkv + row_stats) * 4 <= w.L.partials_bytes;
+  float* row_ss = part + (size_t)M * nqkv;
+  float* row_sc = row_ss + (size_t)(d.d_model / 16) * M;
+  float* row_rstd = row_sc + M;
+  auto small_gemm = [&](int mode, const void* a, const void* wt, void* out, int N, int K, const float* gain, bool scaled) {
+    SmallGemmArgs g{};
+    g.a = a; g.w = wt; g.out = out; g.M = M; g.N = N; g.K = K;
+    g.ss = scaled ? row_ss : nullptr; g.inv_sc = row_sc; g.rstd = row_rstd; g.ss_tiles = d.d_model / 16;
+    g.inv_d = 1.f / (float)d.d_model; g.eps = d.norm_eps; g.x = x; g.gain = gain; g.dev_status = dev_status;
+    Tap t(&c->prof, MN_PROF_GEMM, st);
+    launch_gemm_small(g, mode, st);
+  };
+
   // partial sums of the previous projection, folded into the next norm
   const float* pend = nullptr;
   int pend_n = 0;
@@ -461,6 +478,8 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     n.row_tok = rows.row_tok; n.row_pos = rows.row_pos;
     n.gain = gain; n.shift = shift; n.eps = d.norm_eps; n.h = h; n.M = M; n.d = d.d_model; n.dtype = d.dtype;
     n.dev_status = dev_status;
+    n.rstd = embed && small ? row_rstd : nullptr;
+    n.operand = embed && small;
     Tap t(&c->prof, MN_PROF_NORM, st);
     launch_norm(n, st);
     pend = nullptr; pend_n = 0; pend_bias = nullptr;
@@ -475,9 +494,14 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   };
 
   for (int l = 0; l < d.n_layers; ++l) {
-    norm((const float*)c->ln1_g[l], (const float*)c->ln1_b[l], l == 0);
-    int s = splits(nqkv, d.d_model);
-    gemm(h, c->wqkv[l], part, nqkv, d.d_model, s);
+    int s = 1;
+    if (!small || l == 0) norm((const float*)c->ln1_g[l], (const float*)c->ln1_b[l], l == 0);
+    if (small) {
+      small_gemm(SMALL_OUT, h, c->wqkv[l], part, nqkv, d.d_model, (const float*)c->ln1_g[l], l > 0);
+    } else {
+      s = splits(nqkv, d.d_model);
+      gemm(h, c->wqkv[l], part, nqkv, d.d_model, s);
+    }
     RopeAppendArgs r{};
     r.qkv = part; r.n_partials = s; r.bias = (const float*)c->bqkv[l];
     r.rope_cos = llama ? w.at<float>(w.L.rope_cos) : nullptr;
@@ -491,7 +515,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     r.M = M; r.H = d.n_heads; r.Hkv = d.n_kv_heads; r.hd = d.head_dim; r.dtype = d.dtype;
     r.dev_status = dev_status;
     AttnArgs at = attn;
-    at.q = r.q; at.out = w.at<void>(w.L.attn); at.kv = r.kv;
+    at.q = r.q; at.out = w.at<void>(w.L.attn); at.kv = r.kv; at.operand = small;
     if (attention_fuses_append(at)) {  // (the same for every layer)
       at.qkv = r.qkv; at.n_partials = r.n_partials; at.bias = r.bias; at.rope_cos = r.rope_cos; at.rope_sin = r.rope_sin;
       at.dev_status = dev_status;
@@ -502,6 +526,14 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     {
       Tap t(&c->prof, MN_PROF_ATTENTION, st);
       keep(launch_attention(at, st));
+    }
+    if (small) {
+      void* act = w.at<void>(w.L.act);
+      small_gemm(SMALL_RESIDUAL, at.out, c->wo[l], h, d.d_model, hdim, (const float*)c->ln2_g[l], true);
+      small_gemm(SMALL_SWIGLU, h, c->w1[l], act, w1r, d.d_model, (const float*)c->ln2_g[l], true);
+      // (behind the last layer x is all that is read)
+      small_gemm(SMALL_RESIDUAL, act, c->w2[l], h, d.d_model, d.d_ffn, (const float*)(l + 1 < d.n_layers ? c->ln1_g[l + 1] : c->final_norm_g), true);
+      continue;
     }
     s = splits(d.d_model, hdim);
     gemm(at.out, c->wo[l], part, d.d_model, hdim, s);

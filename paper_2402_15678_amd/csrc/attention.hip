@@ -771,7 +771,8 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
       const int m = row0 + r / G, h = kvh * G + r % G;
       if (my_splits == 1) {
         const float inv = (ok && l > 0.f) ? 1.f / l : 0.f;
-        *reinterpret_cast<uint2*>(reinterpret_cast<f16_t*>(a.out) + ((size_t)m * a.H + h) * HDIM + e) =
+        const size_t at = FUSED && a.operand ? operand_at(m, h * HDIM + e, a.M, a.H * HDIM) : ((size_t)m * a.H + h) * HDIM + e;
+        *reinterpret_cast<uint2*>(reinterpret_cast<f16_t*>(a.out) + at) =
             make_uint2(pack2h(o.x * inv, o.y * inv), pack2h(o.z * inv, o.w * inv));
       } else {
         *reinterpret_cast<float4*>(o_part + (((size_t)split * a.M + m) * a.H + h) * HDIM + e) = o;

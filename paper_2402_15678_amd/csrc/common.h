@@ -24,6 +24,21 @@ typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));  // four 
 // (absolute error below 2^-24), which is far below every tolerance.
 
 constexpr int WAVE = 64;
+template <bool B> struct BoolC { static constexpr bool value = B; };
+
+// Packed weights (layout at the top of gemm.hip)
+constexpr int KSTEP = 32;         // k elements per MFMA
+constexpr int KS = 4;             // MFMA k-steps per packed block
+constexpr int KB = KS * KSTEP;    // k elements per packed block (128)
+constexpr int NWG = 128;          // output columns per packed block
+constexpr int WBLOCK = NWG * KB;  // elements of one packed 128 x 128 weight block (32 KB)
+
+// Activations in operand order (gemm_small.hip): [row tile of 16][k-step of 32][8 k's][row of the tile][k], a tile's rows being
+// those that exist, so an [M][K] matrix takes M * K elements as ever and a wave's fragment is one contiguous piece.
+__device__ __forceinline__ size_t operand_at(int m, int k, int M, int K) {
+  const int t = m >> 4, rows = min(16, M - 16 * t);
+  return (size_t)t * 16 * K + (size_t)(k >> 5) * (32 * rows) + (((k >> 3) & 3) * rows + (m & 15)) * 8 + (k & 7);
+}
 
 // fp32 -> bf16, round to nearest even (inputs are finite).
 __device__ __forceinline__ bf16_t f2bf(float f) {

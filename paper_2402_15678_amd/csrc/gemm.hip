@@ -28,12 +28,7 @@
 
 namespace mn {
 
-constexpr int KSTEP = 32;         // k elements per MFMA
-constexpr int KS = 4;             // MFMA k-steps per main-loop iteration
-constexpr int KB = KS * KSTEP;    // k elements per main-loop iteration (128)
 constexpr int LDS_ROW = KB;       // row of the activation tile in fp16 elements: 256 bytes, unpadded (see lds_slot)
-constexpr int NWG = 128;          // output columns per workgroup
-constexpr int WBLOCK = NWG * KB;  // elements of one packed 128 x 128 weight block (32 KB)
 
 // The activation tile keeps 256-byte rows (two buffers of a 144-row tile for two workgroups per CU
 // must fit the 160 KB of LDS, so there is no room for padding) and rotates the sixteen 16-byte
@@ -767,6 +762,8 @@ static bool small_matrix(int slices, int iters) {
   const int split = 256 / gx < iters / 8 ? 256 / gx : iters / 8;
   return gx * (split > 1 ? split : 1) < 64;
 }
+
+bool gemm_small_matrix(int N, int K) { return small_matrix((N + NWG - 1) / NWG * 4, K / KB); }
 
 // Waves per workgroup at 96 rows or fewer, for a matrix of so many 32-column slices cut into `split` k-splits.  Unsplit
 // matrices: a CU with w workgroups of NW waves takes about 0.15 + w (0.27 + 0.13 NW) us per iteration (the tile and the

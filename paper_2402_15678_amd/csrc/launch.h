@@ -64,6 +64,8 @@ struct NormArgs {
   void* h;                // [M][d] normalised output in the activation type
   int M, d, dtype;
   int32_t* dev_status;    // MN_DEV_RANGE is OR-ed in when an fp16 output saturates, or null
+  float* rstd;            // [M] 1 / rms of the rows, or null
+  bool operand;           // h in operand order (common.h)
 };
 void launch_norm(const NormArgs& a, hipStream_t st);
 
@@ -106,6 +108,7 @@ struct GemmArgs {
   int M, N, K, split_k, dtype;
   int32_t* dev_status;  // MN_DEV_RANGE is OR-ed in when a fused fp16 epilogue saturates a value, or null
 };
+bool gemm_small_matrix(int N, int K);  // so few weights that a projection is launch and memory latency
 int gemm_pick_split(int M, int N, int K, int dtype);  // the library's choice; sizes the workspace
 int gemm_step_split(int M, int N, int K, int dtype, size_t room);
 int gemm_tile_rows(int M, int N, int K, int split);
@@ -115,10 +118,32 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int3
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st);
 void launch_reduce_partials(const float* partials, int S, size_t stride, float* out, size_t n, hipStream_t st);
 
+// ---- gemm_small.hip ----
+enum { SMALL_OUT = 0, SMALL_SWIGLU = 1, SMALL_RESIDUAL = 2 };
+struct SmallGemmArgs {
+  const void* a;  // fp16 [M][K] in operand order (common.h)
+  const void* w;  // packed
+  int M, N, K;
+  // SMALL_OUT, SMALL_SWIGLU: with ss, row m of a is x * gain / inv_sc[m] and its norm is applied here; ss null: rows are used as they are.
+  // SMALL_RESIDUAL writes them for the projection behind it, from the 1 / rms that the one before it left in rstd.
+  float* ss;      // [K / 16] (SMALL_RESIDUAL: [N / 16]) [M] sums of squares of 16 columns of x; sign bit: see gemm_small.hip
+  float* inv_sc;  // [M]
+  float* rstd;    // [M] 1 / rms of the rows
+  int ss_tiles;
+  float inv_d, eps;
+  float* x;           // residual stream, K (SMALL_RESIDUAL: N, updated in place) columns
+  const float* gain;  // of the norm
+  void* out;          // SMALL_OUT: fp32 [M][N]; SMALL_SWIGLU: fp16 [M][N / 2], SMALL_RESIDUAL: fp16 x * gain / inv_sc, both in operand order
+  int32_t* dev_status;
+};
+bool gemm_small_model(int M, int n_qkv, int d_model, int hdim, int w1_rows, int d_ffn);
+void launch_gemm_small(const SmallGemmArgs& a, int mode, hipStream_t st);
+
 // ---- attention.hip ----
 struct AttnArgs {
   const void* q;  // [M][H][hd] activation type
   void* out;      // [M][H*hd] activation type
+  bool operand;   // out in operand order (common.h): only where attention_fuses_append
   RowInfo rows;
   KvView kv;      // every key is read from the pages, this step's own (appended before the call) included
   int B, M, H, Hkv, hd, dtype, max_ctx;

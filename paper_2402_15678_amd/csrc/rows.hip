@@ -408,6 +408,7 @@ __global__ void __launch_bounds__(NORM_THREADS) norm_kernel(NormArgs a) {
   }
   const float var = block_sum<NORM_THREADS / 64, true>(sq, red[1]) * inv_d;
   const float rstd = 1.f / sqrtf(var + a.eps);
+  if (a.rstd && tid == 0) a.rstd[m] = rstd;
   TA* hr = reinterpret_cast<TA*>(a.h) + (size_t)m * d;
   bool bad = false;
 #pragma unroll
@@ -422,7 +423,7 @@ __global__ void __launch_bounds__(NORM_THREADS) norm_kernel(NormArgs a) {
       if (a.shift) {
         o.x += sh[it].x; o.y += sh[it].y; o.z += sh[it].z; o.w += sh[it].w;
       }
-      store4<TA>(hr + e, o, bad);
+      store4<TA>(a.operand ? reinterpret_cast<TA*>(a.h) + operand_at(m, e, a.M, d) : hr + e, o, bad);
     }
   }
   if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);

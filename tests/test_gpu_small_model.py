@@ -1,0 +1,95 @@
+"""Small RMSNorm models, whose norms and residual stream are folded into the projections: logits and cache rows against the
+CPU oracle where the tiling changes, and where the rows leave the range in which a folded norm is exact."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import minions_oracle as orc
+from paper_2402_15678_amd import synth
+from tests import util
+
+pytestmark = pytest.mark.gpu
+
+NARROW = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 256, 4, 4, 64, 512, 500, 512)
+WIDE = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 1024, 16, 8, 64, 3584, 500, 512)     # longest K and most norm columns
+GROUPED = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 768, 6, 2, 128, 896, 500, 512)
+
+
+def _folded(desc, rows):
+    from paper_2402_15678_amd import binding
+    return bool(binding.lib._ZN2mn16gemm_small_modelEiiiiii(rows, desc.n_qkv, desc.d_model, desc.n_heads * desc.head_dim, desc.w1_rows, desc.d_ffn) & 1)
+
+
+def _check(desc, W, ctx, ks, seed, tol):
+    from paper_2402_15678_amd import harness
+    ctx, ks = np.asarray(ctx, np.int32), np.asarray(ks, np.int32)
+    B, k_max = len(ctx), max(1, int(ks.max()))
+    model = harness.DeviceModel.from_host(desc, W)
+    kvh = synth.make_paged_kv(desc, ctx, ks, seed)
+    kvd = harness.DeviceKV.from_host(desc, kvh)
+    g = synth.stream(seed, 1)
+    last = g.integers(0, desc.vocab, size=B).astype(np.int32)
+    voted = g.integers(0, desc.vocab, size=(B, k_max)).astype(np.int32)
+    dev = lambda a: torch.tensor(np.asarray(a, np.int32), device="cuda:0")
+    ses = harness.VerifySession(model, kvd, B, k_max, 1, int((ctx + ks + 1).max()), max_rows=int((ks + 1).sum()), want_logits=True)
+    t_last, t_k, t_voted = dev(last), dev(ks), dev(voted)
+    caches = util.oracle_caches(desc, kvh)
+    toks = [[int(last[b])] + voted[b, :ks[b]].tolist() for b in range(B)]
+    want = np.concatenate(orc.decoder_step(desc, util.weights_f64(W), toks, caches))
+    got = []
+    for _ in range(2):                       # (the second pass finds the first one's statistics in the workspace)
+        ses.forward(t_last, t_k, ks.tolist(), voted=t_voted)
+        torch.cuda.synchronize()
+        assert ses.dev_status.item() == 0
+        got.append(ses.logits.cpu().numpy().copy())
+    assert np.array_equal(got[0], got[1])
+    assert np.abs(got[0] - want).max() < tol, np.abs(got[0] - want).max()
+    for l in range(desc.n_layers):
+        kp, vp = kvd.download(l)
+        img = synth.PagedKV(16, kp.shape[0], kvh.block_tables.shape[1], kvh.block_tables, None, {l: kp}, {l: vp})
+        for b in range(B):
+            K, V = synth.gather_sequence_kv(img, l, b, int(ctx[b] + ks[b] + 1))
+            assert max(np.abs(K - caches[b].K[l]).max(), np.abs(V - caches[b].V[l]).max()) < tol
+    return got[0]
+
+
+@pytest.mark.parametrize("desc", [NARROW, WIDE, GROUPED], ids=["d256", "d1024", "d768-gqa"])
+@pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 95, 113])
+def test_folded_norms_match_oracle(desc, rows):
+    """One tile of rows, its edges, two, three and more, with a last tile that is not full."""
+    assert _folded(desc, rows)
+    B = -(-rows // 4)
+    ks = [3] * (B - 1) + [rows - 4 * (B - 1) - 1]
+    ctx = [(37 * b + 5) % 90 for b in range(B)]
+    _check(desc, synth.make_weights(desc, 91), ctx, ks, 92, util.TOL[desc.dtype])
+
+
+@pytest.mark.parametrize("rows,folded", [(640, True), (641, False)])
+def test_most_rows_of_folded_norms(rows, folded):
+    assert _folded(NARROW, rows) == folded
+    ks = [15] * 40 + [0] * (rows - 640)
+    _check(NARROW, synth.make_weights(NARROW, 91), [b % 50 for b in range(len(ks))], ks, 93, util.TOL[synth.DT_BF16])
+
+
+def test_rows_that_grow_or_shrink_between_two_norms():
+    """The scale that a row is stored with comes from its norm before: rows that outgrow it (projections 2^12 and 2^13
+    times their size on embeddings 2^-10 of theirs) or all but vanish (an output projection that takes the row back to 2^-7 of itself) are
+    normalised from the fp32 rows instead, to the same tolerance."""
+    W = synth.make_weights(NARROW, 91)
+    W["tok_emb"] = W["tok_emb"] * 2.0 ** -10
+    for L in W["layers"]:
+        L["wo"] = L["wo"] * 2.0 ** 12
+        L["w2"] = L["w2"] * 2.0 ** 13        # (as much from the FFN, which reads the folded norm)
+    _check(NARROW, W, [20, 0, 33, 7], [3, 2, 0, 3], 94, util.TOL[synth.DT_BF16])
+
+    desc = dataclasses.replace(NARROW, n_layers=1, d_model=128, n_heads=2, n_kv_heads=2, norm_eps=1e-9)
+    W = synth.make_weights(desc, 95)
+    W["tok_emb"] = (np.sign(W["tok_emb"]) + (W["tok_emb"] == 0)).astype(np.float32) * 2.0 ** -6
+    L = W["layers"][0]
+    L["ln1_g"] = np.ones_like(L["ln1_g"])
+    L["wqkv"] = L["wqkv"].copy()
+    L["wqkv"][256:384] = np.eye(128, dtype=np.float32)             # values = the normalised row, and no other key to see
+    L["wo"] = -np.eye(128, dtype=np.float32) * np.float32(2.0 ** -6 * (1 - 2.0 ** -7))
+    _check(desc, W, [0] * 5, [0] * 5, 96, util.TOL[synth.DT_BF16])
