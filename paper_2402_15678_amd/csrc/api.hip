@@ -9,6 +9,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace mn;
@@ -470,9 +471,16 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
   int pend_n = 0;
   const float* pend_bias = nullptr;
 
+  // fp32 models of narrow rows: the norm is done by the projection behind it (`folded` describes it); the residual stream then
+  // changes between its own buffer and the unused one of the norm's output, since every workgroup reads the old values, and
+  // the QKV sums go where the scores will be, since the partial sums are still being read (w1 and lm_head write elsewhere anyway)
+  const bool fold_f32 = !llama && d.dtype != MN_DT_BF16 && nqkv <= d.vocab && gemm_f32_folds_norm(M, d.d_model);
+  float* qkv = fold_f32 ? w.at<float>(w.L.logits) : part;
+  float *x_cur = x, *x_next = reinterpret_cast<float*>(h);
+  NormArgs folded{};
   auto norm = [&](const float* gain, const float* shift, bool embed) {
     NormArgs n{};
-    n.x = x; n.partials = pend; n.n_partials = pend_n; n.bias = pend_bias;
+    n.x = x_cur; n.partials = pend; n.n_partials = pend_n; n.bias = pend_bias;
     n.tok_emb = embed ? c->tok_emb : nullptr;
     n.pos_emb = embed ? c->pos_emb : nullptr;
     n.row_tok = rows.row_tok; n.row_pos = rows.row_pos;
@@ -480,13 +488,23 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     n.dev_status = dev_status;
     n.rstd = embed && small ? row_rstd : nullptr;
     n.operand = embed && small;
+    pend = nullptr; pend_n = 0; pend_bias = nullptr;
+    if (fold_f32) {
+      folded = n;
+      return;
+    }
     Tap t(&c->prof, MN_PROF_NORM, st);
     launch_norm(n, st);
-    pend = nullptr; pend_n = 0; pend_bias = nullptr;
+  };
+  auto fold = [&](GemmArgs& g) {  // the projection behind the last norm()
+    if (!fold_f32) return;
+    g.norm = &folded; g.x_new = x_next;
+    std::swap(x_cur, x_next);
   };
   auto splits = [&](int N, int K) { return gemm_step_split(M, N, K, d.dtype, w.L.partials_bytes); };
   auto gemm = [&](const void* a, const void* wt, float* out, int N, int K, int split) {
     GemmArgs g{};
+    if (a == h) fold(g);
     g.a = a; g.w = wt; g.out = out; g.bias = nullptr; g.M = M; g.N = N; g.K = K; g.split_k = split; g.dtype = d.dtype;
     g.dev_status = dev_status;
     Tap t(&c->prof, MN_PROF_GEMM, st);
@@ -500,10 +518,10 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
       small_gemm(SMALL_OUT, h, c->wqkv[l], part, nqkv, d.d_model, (const float*)c->ln1_g[l], l > 0);
     } else {
       s = splits(nqkv, d.d_model);
-      gemm(h, c->wqkv[l], part, nqkv, d.d_model, s);
+      gemm(h, c->wqkv[l], qkv, nqkv, d.d_model, s);
     }
     RopeAppendArgs r{};
-    r.qkv = part; r.n_partials = s; r.bias = (const float*)c->bqkv[l];
+    r.qkv = qkv; r.n_partials = s; r.bias = (const float*)c->bqkv[l];
     r.rope_cos = llama ? w.at<float>(w.L.rope_cos) : nullptr;
     r.rope_sin = llama ? w.at<float>(w.L.rope_sin) : nullptr;
     r.rows = rows;
@@ -550,6 +568,7 @@ extern "C" mn_status mn_verify_forward(mn_ctx* c, const int32_t* last_tok, const
     } else if (!llama && splits(w1r, d.d_model) == 1) {
       // one split: bias + ReLU applied in the kernel's epilogue, no partial sums and no activation kernel
       GemmArgs g{};
+      fold(g);
       g.a = h; g.w = c->w1[l]; g.relu_act = act; g.bias = (const float*)c->b1[l]; g.M = M; g.N = w1r; g.K = d.d_model;
       g.split_k = 1; g.dtype = d.dtype; g.dev_status = dev_status;
       Tap t(&c->prof, MN_PROF_GEMM, st);

@@ -665,11 +665,29 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int3
   pack_weight_kernel<<<(int)blocks, 256, 0, st>>>(reinterpret_cast<const bf16_t*>(src), reinterpret_cast<bf16_t*>(dst), N, K, half, status);
 }
 
+// Sums of eight values over the lanes, value i ending up in lanes 8i .. 8i + 7: every exchange with the lane 32, 16, 8 away halves
+// the values that a lane still carries
+__device__ __forceinline__ float f32_row_sum(const float (&acc)[8], int lane) {
+  float s4[4], s2[2], s;
+  const bool hi = lane & 32, mid = lane & 16, lo = lane & 8;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s4[i] = (hi ? acc[4 + i] : acc[i]) + __shfl_xor(hi ? acc[i] : acc[4 + i], 32, 64);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) s2[i] = (mid ? s4[2 + i] : s4[i]) + __shfl_xor(mid ? s4[i] : s4[2 + i], 16, 64);
+  s = (lo ? s2[1] : s2[0]) + __shfl_xor(lo ? s2[0] : s2[1], 8, 64);
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  return s;
+}
+
 // fp32 model (the small configuration): one wave per output column, lanes split k in pieces of four, up to 8 rows at a
 // time.  Plain FMA; bound by memory latency, so a trip's loads (F32_TRIP pieces of the column and of every row) all go
 // out before any is used, and the eight sums are reduced over the lanes together (10 exchanges instead of 48).  The
-// summation order is fixed.  5 rows: 256 columns x 1024 16.5 -> 3.5 us, 4096 x 256 10.0 -> 6.6 (one element per lane and trip before).
-constexpr int F32_TRIP = 4;
+// summation order is fixed.  5 rows: 256 columns x 1024 16.5 -> 3.8 us (one element per lane and trip before), 4096 x 256 10.0 -> 3.9
+// (6.5 when a row of 256 elements still took four pieces, three of them repeats, and the registers that go with them: two prompts of
+// 128 tokens on the 256-wide model 404 -> 188 us).
+constexpr int F32_TRIP = 4;                  // most pieces per trip; a row of 256 or 512 elements has one or two
+template <int F32_TRIP>
 __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
                                                        float* __restrict__ out, const float* __restrict__ bias, int M,
                                                        int N, int K, int relu) {
@@ -703,20 +721,88 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
         }
     }
   }
-  // sums over the lanes: every exchange with the lane 32, 16, 8 away halves the rows a lane still carries
-  float s4[4], s2[2], s;
-  const bool hi = lane & 32, mid = lane & 16, lo = lane & 8;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) s4[i] = (hi ? acc[4 + i] : acc[i]) + __shfl_xor(hi ? acc[i] : acc[4 + i], 32, 64);
-#pragma unroll
-  for (int i = 0; i < 2; ++i) s2[i] = (mid ? s4[2 + i] : s4[i]) + __shfl_xor(mid ? s4[i] : s4[2 + i], 16, 64);
-  s = (lo ? s2[1] : s2[0]) + __shfl_xor(lo ? s2[0] : s2[1], 8, 64);
-#pragma unroll
-  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  float s = f32_row_sum(acc, lane);
   const int row = lane >> 3;  // = 4 hi + 2 mid + lo
   if ((lane & 7) == 0 && row < rows) {
     s += bias ? bias[n] : 0.f;
     out[(size_t)(m0 + row) * N + n] = relu ? fmaxf(s, 0.f) : s;
+  }
+}
+
+// The same with the norm in front of the projection: a workgroup has 8 columns, a wave each, and wave w first adds up and
+// normalises row w of the 8 (norm_kernel's arithmetic), while its column's weights are on their way.  Every workgroup of a row group
+// does so, which costs less than the launch it saves while there are few rows: the 256-wide model's step, norms as launches and
+// folded, 5 rows 93 and 80 us, 32 rows 98 and 86, 64 rows 109 and 100, prompts of 128 tokens 129 and 128, of 256 188 and 195.
+constexpr int F32_NORM_K = F32_TRIP * 256;   // widest row: one trip of a wave
+template <int F32_TRIP>
+__global__ void __launch_bounds__(512) gemm_f32_norm_kernel(NormArgs r, float* __restrict__ x_new, const float* __restrict__ W, float* __restrict__ out,
+                                                            const float* __restrict__ bias, int M, int N, int relu) {
+  __shared__ f32x4 s_h[8][F32_TRIP * 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, K = r.d;
+  const int n = blockIdx.x * 8 + wave, m0 = blockIdx.y * 8, rows = min(8, M - m0);
+  f32x4 w[F32_TRIP], v[F32_TRIP], p[F32_TRIP], gn[F32_TRIP], sh[F32_TRIP];
+  const int m = m0 + min(wave, rows - 1);    // (spare waves repeat the last row and store nothing)
+  const bool embed = r.tok_emb != nullptr;
+  const float* src = embed ? reinterpret_cast<const float*>(r.tok_emb) + (size_t)r.row_tok[m] * K : r.x + (size_t)m * K;
+  const float* add = embed ? (r.pos_emb ? reinterpret_cast<const float*>(r.pos_emb) + (size_t)max(r.row_pos[m], 0) * K : nullptr)
+                           : (r.partials ? r.partials + (size_t)m * K : nullptr);
+#pragma unroll
+  for (int t = 0; t < F32_TRIP; ++t) {
+    const int k = min(4 * lane + t * 256, K - 4);
+    v[t] = *reinterpret_cast<const f32x4*>(src + k);
+    if (add) p[t] = *reinterpret_cast<const f32x4*>(add + k);
+    gn[t] = *reinterpret_cast<const f32x4*>(r.gain + k);
+    if (r.shift) sh[t] = *reinterpret_cast<const f32x4*>(r.shift + k);
+    w[t] = *reinterpret_cast<const f32x4_u*>(W + (size_t)min(n, N - 1) * K + k);
+  }
+  float sum = 0.f;
+#pragma unroll
+  for (int t = 0; t < F32_TRIP; ++t) {
+    if (add) v[t] += p[t];
+    if (!embed) {
+      for (int s = 1; s < r.n_partials; ++s) v[t] += *reinterpret_cast<const f32x4*>(add + (size_t)s * M * K + min(4 * lane + t * 256, K - 4));
+      if (r.bias) v[t] += *reinterpret_cast<const f32x4_u*>(r.bias + min(4 * lane + t * 256, K - 4));
+    }
+    if (4 * lane + t * 256 < K) sum += (v[t][0] + v[t][1]) + (v[t][2] + v[t][3]);
+  }
+  const float inv_d = 1.f / (float)K;
+  const float mean = r.shift ? wave_sum(sum) * inv_d : 0.f;
+  float sq = 0.f;
+#pragma unroll
+  for (int t = 0; t < F32_TRIP; ++t)
+    if (4 * lane + t * 256 < K) {
+      const f32x4 c = v[t] - mean;
+      sq += (c[0] * c[0] + c[1] * c[1]) + (c[2] * c[2] + c[3] * c[3]);
+    }
+  const float rstd = 1.f / sqrtf(wave_sum(sq) * inv_d + r.eps);
+#pragma unroll
+  for (int t = 0; t < F32_TRIP; ++t) {
+    const int k = 4 * lane + t * 256;
+    if (k >= K) break;
+    if (wave < rows && blockIdx.x == 0) *reinterpret_cast<f32x4*>(x_new + (size_t)m * K + k) = v[t];
+    f32x4 h = (v[t] - mean) * rstd * gn[t];
+    if (r.shift) h += sh[t];
+    s_h[wave][k >> 2] = h;
+  }
+  __syncthreads();
+  float acc[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+#pragma unroll
+  for (int t = 0; t < F32_TRIP; ++t) {
+    if (4 * lane + t * 256 >= K) break;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {            // (rows past the last one: copies of it)
+      const f32x4 h = s_h[i][lane + t * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i] = fmaf(h[e], w[t][e], acc[i]);
+    }
+  }
+  const float s = f32_row_sum(acc, lane);
+  const int row = lane >> 3;
+  if ((lane & 7) == 0 && row < rows && n < N) {
+    const float y = s + (bias ? bias[n] : 0.f);
+    out[(size_t)(m0 + row) * N + n] = relu ? fmaxf(y, 0.f) : y;
   }
 }
 
@@ -996,13 +1082,24 @@ static hipError_t launch_big(const GemmArgs& a, hipStream_t st) {
   return hipSuccess;
 }
 
+template <int TRIP>
+static void launch_f32(const GemmArgs& a, hipStream_t st) {
+  const float* W = reinterpret_cast<const float*>(a.w);
+  float* out = a.relu_act ? reinterpret_cast<float*>(a.relu_act) : a.out;
+  const int relu = a.relu_act != nullptr;
+  if (a.norm) gemm_f32_norm_kernel<TRIP><<<dim3((a.N + 7) / 8, (a.M + 7) / 8), 512, 0, st>>>(*a.norm, a.x_new, W, out, a.bias, a.M, a.N, relu);
+  else gemm_f32_kernel<TRIP><<<dim3((a.N + 3) / 4, (a.M + 7) / 8), 256, 0, st>>>(reinterpret_cast<const float*>(a.a), W, out, a.bias, a.M, a.N, a.K, relu);
+}
+
+constexpr int F32_NORM_ROWS = 64;
+bool gemm_f32_folds_norm(int M, int d_model) { return d_model <= F32_NORM_K && M <= MN_TUNE("MN_F32_NORM_ROWS", F32_NORM_ROWS); }
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.dtype != MN_DT_BF16) {
-    dim3 grid((a.N + 3) / 4, (a.M + 7) / 8);
-    gemm_f32_kernel<<<grid, 256, 0, st>>>(reinterpret_cast<const float*>(a.a), reinterpret_cast<const float*>(a.w),
-                                          a.relu_act ? reinterpret_cast<float*>(a.relu_act) : a.out, a.bias, a.M, a.N, a.K,
-                                          a.relu_act != nullptr);
+    if (a.K <= 256) launch_f32<1>(a, st);
+    else if (a.K <= 512) launch_f32<2>(a, st);
+    else launch_f32<F32_TRIP>(a, st);
     return hipSuccess;
   }
   const int tiles = (a.M + 15) / 16;

@@ -107,7 +107,10 @@ struct GemmArgs {
   const float* bias;
   int M, N, K, split_k, dtype;
   int32_t* dev_status;  // MN_DEV_RANGE is OR-ed in when a fused fp16 epilogue saturates a value, or null
+  const NormArgs* norm;  // non-null (fp32 models, gemm_f32_folds_norm): a is this norm's output, computed on the way; the residual
+  float* x_new;          // stream norm->x is left as it is and its new values go to x_new
 };
+bool gemm_f32_folds_norm(int M, int d_model);
 bool gemm_small_matrix(int N, int K);  // so few weights that a projection is launch and memory latency
 int gemm_pick_split(int M, int N, int K, int dtype);  // the library's choice; sizes the workspace
 int gemm_step_split(int M, int N, int K, int dtype, size_t room);
