@@ -38,11 +38,21 @@ namespace mn {
 constexpr int GEN_ALONE = 256, GEN_PAIRS = 512, GEN_LONG = 1024;
 
 // TA: activation type of q and out; T: storage type of the KV pages
-template <typename TA, typename T, int GEN_THREADS>
+// FUSED (fp32 models, few rows per sequence): the workgroup adds up its query and the K and V rows of this step that the query
+// sees from the QKV sums itself (in dynamic LDS, GEN_NEW_ROWS at most) and reads only older keys from the pages, to which the first
+// head of a KV head's group writes the row's own: no rotary/append launch.  Bound by its chain (row, block ids, keys, softmax,
+// values, and before them the QKV sums): 5 rows x 4 heads of 64 over 69 keys 7.5 us and 3.1 for the append before, 5.3 with the keys'
+// pieces and the first values asked for at once, 6.7 with the append inside.
+constexpr int GEN_NEW_ROWS = 17;
+constexpr int GEN_KPIECES = 8;
+constexpr int GEN_VPRE = 4;   // groups of four values of a chunk asked for before its softmax
+template <typename TA, typename T, int GEN_THREADS, bool FUSED>
 __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  float* s_new = reinterpret_cast<float*>(smem);  // [2][rows of the sequence up to m][hd]: K, V
   __shared__ float s_q[256];
-  __shared__ float s_p[GEN_THREADS];
-  __shared__ int s_pb[GEN_THREADS];
+  __shared__ __attribute__((aligned(16))) float s_p[GEN_THREADS];
+  __shared__ uint64_t s_at[GEN_THREADS];  // element 0 of a key's V column in the pages (element i: + i * bs), found once per chunk
   __shared__ float s_red[GEN_THREADS / 64];
   __shared__ float s_acc[GEN_THREADS];
   const int h = blockIdx.x, m = blockIdx.y, tid = threadIdx.x;
@@ -57,37 +67,101 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
   const int nkeys = pos + 1;
   const int kh = h / (a.H / a.Hkv);
   const float scale = rsqrtf((float)hd);
-  const TA* q = reinterpret_cast<const TA*>(a.q) + ((size_t)m * a.H + h) * hd;
-  for (int e = tid; e < hd; e += GEN_THREADS) s_q[e] = Store<TA>::load(q + e) * scale;
-  __syncthreads();
   const T* Kp = reinterpret_cast<const T*>(a.kv.k);
   const T* Vp = reinterpret_cast<const T*>(a.kv.v);
   const int32_t* bt = a.kv.block_tables + (size_t)b * a.kv.max_blocks_per_seq;
+  int old = nkeys;                  // keys read from the pages
+  if constexpr (FUSED) {
+    const int j = a.rows.row_j[m], slot = a.rows.row_slot[m], half = hd >> 1, ncols = (a.H + 2 * a.Hkv) * hd;
+    old = pos - j;
+    // item = one pair (t, t + hd/2): of the query, then of the K rows, then of the V rows
+    for (int idx = tid; idx < (2 * j + 3) * half; idx += GEN_THREADS) {
+      const int t = idx & (half - 1), which = idx >> (31 - __clz(half));          // 0: query; 1 .. j + 1: K of row which - 1; then V
+      const bool is_q = which == 0, is_v = which > j + 1;
+      const int jj = is_q ? j : (is_v ? which - j - 2 : which - 1), mm = m - j + jj;
+      const int c = (is_q ? h : (is_v ? a.H + a.Hkv : a.H) + kh) * hd + t;
+      const float* p = a.qkv + (size_t)mm * ncols + c;
+      float x = p[0], y = p[half], bx = 0.f, by = 0.f;
+      if (a.bias) { bx = a.bias[c]; by = a.bias[c + half]; }
+      for (int s = 1; s < a.n_partials; ++s) {
+        x += p[(size_t)s * a.M * ncols];
+        y += p[(size_t)s * a.M * ncols + half];
+      }
+      if (a.bias) { x += bx; y += by; }
+      if (a.rope_cos && !is_v) {
+        const float cs = a.rope_cos[(size_t)mm * half + t], sn = a.rope_sin[(size_t)mm * half + t], x0 = x;
+        x = x0 * cs - y * sn;
+        y = y * cs + x0 * sn;
+      }
+      if (is_q) {
+        s_q[t] = x * scale;
+        s_q[t + half] = y * scale;
+        continue;
+      }
+      float* r = s_new + ((is_v ? j + 1 : 0) + jj) * hd + t;
+      r[0] = x;
+      r[half] = y;
+      if (jj == j && h % (a.H / a.Hkv) == 0 && slot >= 0) {  // this row's own, to the pages
+        T* base = reinterpret_cast<T*>(is_v ? a.kv.v : a.kv.k) + ((size_t)(slot / bs) * a.Hkv + kh) * (size_t)hd * bs;
+        const int off = slot % bs, t1 = t + half;
+        Store<T>::store(base + (is_v ? (size_t)t * bs + off : ((size_t)(t >> 3) * bs + off) * 8 + (t & 7)), x);
+        Store<T>::store(base + (is_v ? (size_t)t1 * bs + off : ((size_t)(t1 >> 3) * bs + off) * 8 + (t1 & 7)), y);
+      }
+    }
+  } else {
+    const TA* q = reinterpret_cast<const TA*>(a.q) + ((size_t)m * a.H + h) * hd;
+    for (int e = tid; e < hd; e += GEN_THREADS) s_q[e] = Store<TA>::load(q + e) * scale;
+  }
+  __syncthreads();
   const int ng = GEN_THREADS / hd;  // key groups in the PV phase
-  const int e_own = tid % hd, kg = tid / hd;
+  const int e_own = tid & (hd - 1), kg = tid >> (31 - __clz(hd));  // (head_dim is a power of two)
   float run_m = -INFINITY, run_l = 0.f, acc = 0.f;
   for (int k0 = 0; k0 < nkeys; k0 += GEN_THREADS) {
     const int key = k0 + tid;
     float s = -INFINITY;
-    int pb = 0;
-    if (key < nkeys) {
-      pb = bt[key / bs];
-      const int off = key % bs;
+    const int blk = key / bs, off = key - blk * bs;
+    uint64_t page = 0;
+    if (key < old) {
+      page = ((uint64_t)(uint32_t)bt[blk] * a.Hkv + kh) * (uint64_t)(hd * bs);
+      s_at[tid] = page + off;
+    }
+    if (FUSED && key >= old && key < nkeys) {
+      const float* kr = s_new + (key - old) * hd;
       float d = 0.f;
-      const T* kb = Kp + ((size_t)pb * a.Hkv + kh) * (size_t)hd * bs;
-      // (eight consecutive elements at once, four pieces in flight: one element per load was a chain of round trips)
-#pragma unroll 4
-      for (int c = 0; c < hd / 8; ++c) {
-        struct __attribute__((aligned(sizeof(T)))) Piece { T x[8]; };
-        const Piece kk = *reinterpret_cast<const Piece*>(kb + ((size_t)c * bs + off) * 8);
+      for (int e = 0; e < hd; ++e) d = fmaf(s_q[e], kr[e], d);
+      s = d;
+    } else if (key < nkeys) {
+      float d = 0.f;
+      const T* kb = Kp + page;
+      // (eight consecutive elements at once, GEN_KPIECES pieces asked for before any is used: left to itself the compiler makes
+      // a round trip of every piece)
+      struct __attribute__((aligned(sizeof(T)))) Piece { T x[8]; };
+      for (int c0 = 0; c0 < hd / 8; c0 += GEN_KPIECES) {
+        Piece kk[GEN_KPIECES];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) d = fmaf(s_q[c * 8 + i], (float)kk.x[i], d);
+        for (int c = 0; c < GEN_KPIECES; ++c) kk[c] = *reinterpret_cast<const Piece*>(kb + ((size_t)min(c0 + c, hd / 8 - 1) * bs + off) * 8);
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int c = 0; c < GEN_KPIECES; ++c) {
+          if (c0 + c >= hd / 8) break;       // (uniform)
+#pragma unroll
+          for (int i = 0; i < 8; ++i) d = fmaf(s_q[(c0 + c) * 8 + i], (float)kk[c].x[i], d);
+        }
       }
       s = d;
     }
     // chunk maximum
     float cm = wave_max(s);
     __syncthreads();
+    const int cnt = min(GEN_THREADS, nkeys - k0), cnt_old = min(cnt, old - k0);
+    // the first values, on their way while the probabilities are worked out: four keys of a block at once (uniform)
+    struct __attribute__((aligned(sizeof(T)))) Quad { T x[4]; };
+    const int quads = (bs & 3) == 0 ? (cnt_old + 3) >> 2 : 0;
+    Quad vpre[GEN_VPRE];
+    if (quads > 0) {                  // (repeats past the end are not used)
+#pragma unroll
+      for (int u = 0; u < GEN_VPRE; ++u) vpre[u] = *reinterpret_cast<const Quad*>(Vp + (s_at[4 * min(kg + u * ng, quads - 1)] + (uint32_t)(e_own * bs)));
+    }
     if ((tid & 63) == 0) s_red[tid >> 6] = cm;
     __syncthreads();
     cm = s_red[0];
@@ -97,19 +171,38 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
     const float alpha = __expf(run_m - new_m);
     const float p = (key < nkeys) ? __expf(s - new_m) : 0.f;
     s_p[tid] = p;
-    s_pb[tid] = pb;
-    const float ps = block_sum<GEN_THREADS / 64>(p, s_red);  // also orders the s_p / s_pb writes
+    const float ps = block_sum<GEN_THREADS / 64>(p, s_red);  // also orders the s_p writes
     run_l = run_l * alpha + ps;
     run_m = new_m;
     acc *= alpha;
-    const int cnt = min(GEN_THREADS, nkeys - k0);
-    if (kg < ng) {
-#pragma unroll 8
-      for (int i = kg; i < cnt; i += ng) {
-        const int key2 = k0 + i;
-        const T* vb = Vp + ((size_t)s_pb[i] * a.Hkv + kh) * (size_t)hd * bs;
-        acc = fmaf(s_p[i], Store<T>::load(vb + (size_t)e_own * bs + key2 % bs), acc);
+    {
+      auto add = [&](const Quad& v, int q) {                 // (slots past the last key may hold anything)
+        const f32x4 p4 = *reinterpret_cast<const f32x4*>(s_p + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool in = 4 * q + e < cnt_old;
+          acc = fmaf(in ? p4[e] : 0.f, in ? (float)v.x[e] : 0.f, acc);
+        }
+      };
+      if (quads > 0) {
+#pragma unroll
+        for (int u = 0; u < GEN_VPRE; ++u) add(vpre[u], min(kg + u * ng, GEN_THREADS / 4 - 1));
       }
+#pragma unroll 1
+      for (int q0 = kg + GEN_VPRE * ng; q0 < quads; q0 += 4 * ng) {
+        Quad v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const Quad*>(Vp + (s_at[4 * min(q0 + u * ng, quads - 1)] + (uint32_t)(e_own * bs)));
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int u = 0; u < 4; ++u) add(v[u], min(q0 + u * ng, GEN_THREADS / 4 - 1));
+      }
+      if ((bs & 3) != 0) {
+#pragma unroll 8
+        for (int i = kg; i < cnt_old; i += ng) acc = fmaf(s_p[i], Store<T>::load(Vp + (s_at[i] + (uint32_t)(e_own * bs))), acc);
+      }
+      if (FUSED)
+        for (int i = max(cnt_old, 0) + kg; i < cnt; i += ng) acc = fmaf(s_p[i], s_new[(pos - old + 1 + k0 + i - old) * hd + e_own], acc);
     }
     __syncthreads();
   }
@@ -978,7 +1071,20 @@ static hipError_t launch_keys(const AttnArgs& a, const MfmaShape& sh, float* o_p
   return a.qkv ? launch_keys_nw<HDIM, CT, 4, true>(a, sh, o_part, ml_part, st) : launch_keys_nw<HDIM, CT, 4, false>(a, sh, o_part, ml_part, st);
 }
 
-bool attention_fuses_append(const AttnArgs& a) { return a.M > 0 && a.B > 0 && keys_path(a) && mfma_shape(a).n_splits == 1 && !MN_TUNE("MN_ATTN_NOFUSE", 0); }
+bool attention_fuses_append(const AttnArgs& a) {
+  if (a.M <= 0 || a.B <= 0 || MN_TUNE("MN_ATTN_NOFUSE", 0)) return false;
+  if (a.dtype != MN_DT_BF16) return a.max_q <= GEN_NEW_ROWS;  // (attn_generic_kernel)
+  return keys_path(a) && mfma_shape(a).n_splits == 1;
+}
+
+template <typename TA, typename T, bool FUSED>
+static void launch_generic(const AttnArgs& a, hipStream_t st) {
+  const dim3 grid(a.H, a.M);
+  const bool wide = a.max_ctx > 256 && (long)a.M * a.H <= (a.max_ctx > GEN_LONG ? GEN_PAIRS : GEN_ALONE);
+  const size_t smem = FUSED ? (size_t)2 * a.max_q * a.hd * sizeof(float) : 0;
+  if (wide) attn_generic_kernel<TA, T, 1024, FUSED><<<grid, 1024, smem, st>>>(a);
+  else attn_generic_kernel<TA, T, 256, FUSED><<<grid, 256, smem, st>>>(a);
+}
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.B <= 0) return hipSuccess;
@@ -1025,15 +1131,9 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     launch_merge(a, n_splits, o_part, ml_part, st);
     return hipSuccess;
   }
-  dim3 grid(a.H, a.M);
-  const bool wide = a.max_ctx > 256 && (long)a.M * a.H <= (a.max_ctx > GEN_LONG ? GEN_PAIRS : GEN_ALONE);
-  if (a.dtype == MN_DT_BF16) {
-    if (wide) attn_generic_kernel<f16_t, f16_t, 1024><<<grid, 1024, 0, st>>>(a);
-    else attn_generic_kernel<f16_t, f16_t, 256><<<grid, 256, 0, st>>>(a);
-  } else {
-    if (wide) attn_generic_kernel<float, float, 1024><<<grid, 1024, 0, st>>>(a);
-    else attn_generic_kernel<float, float, 256><<<grid, 256, 0, st>>>(a);
-  }
+  if (a.dtype == MN_DT_BF16) launch_generic<f16_t, f16_t, false>(a, st);
+  else if (a.qkv) launch_generic<float, float, true>(a, st);
+  else launch_generic<float, float, false>(a, st);
   return hipSuccess;
 }
 
