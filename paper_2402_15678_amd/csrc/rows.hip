@@ -614,7 +614,8 @@ __device__ __forceinline__ void arg_better(float& bv, int& bi, float v, int i) {
 }
 
 // One workgroup per row with eight 16-byte pieces in flight per thread.  Up to ARGMAX_WIDE_ROWS rows (fewer than CUs) it has 16
-// waves: a row of 32000 scores is asked for at once (16 rows 9.6 -> 7.3 us); with more rows the chip is full either way and
+// waves: a row of 32000 scores is asked for at once (16 rows 9.6 -> 7.3 us, 6.5 since the row's place is asked for with the scores and
+// one wave compares the waves' results); with more rows the chip is full either way and
 // 4 waves leave more workgroups per CU (618 rows 17.8 us, 25.0 with 16 waves).  It also adds up the partial sums of a
 // split vocabulary projection (144 rows, two splits: 22 us as a launch of its own and the argmax, 14 together).
 constexpr int ARGMAX_WIDE_ROWS = 256;
@@ -634,6 +635,7 @@ __global__ void __launch_bounds__(ARGMAX_THREADS) argmax_rows_kernel(float* __re
     return;
   }
   const int m = blockIdx.x;
+  const int b = rows.row_seq[m], row_j = rows.row_j[m], ok = rows.seq_ok[b];  // (asked for first: the answer waits for nothing else)
   float* r = logits + (size_t)m * V;
   const float* src = partials ? partials + (size_t)m * V : r;
   const size_t stride = (size_t)M * V;
@@ -645,8 +647,14 @@ __global__ void __launch_bounds__(ARGMAX_THREADS) argmax_rows_kernel(float* __re
     const int n4 = V >> 2;
     for (int i0 = tid; i0 < n4; i0 += 8 * ARGMAX_THREADS) {
       float4 p[8];
+      if (i0 - tid + ARGMAX_THREADS >= n4) {  // (uniform: short rows have one piece per thread)
+        p[0] = reinterpret_cast<const float4*>(src)[min(i0, n4 - 1)];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) p[u] = reinterpret_cast<const float4*>(src)[min(i0 + u * ARGMAX_THREADS, n4 - 1)];
+        for (int u = 1; u < 8; ++u) p[u] = p[0];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) p[u] = reinterpret_cast<const float4*>(src)[min(i0 + u * ARGMAX_THREADS, n4 - 1)];
+      }
       if (partials) {
         for (int s = 1; s < S; ++s) {       // (fixed order)
           float4 x[8];
@@ -688,11 +696,17 @@ __global__ void __launch_bounds__(ARGMAX_THREADS) argmax_rows_kernel(float* __re
   }
   if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
   __syncthreads();
-  if (tid == 0) {
-    for (int w = 1; w < NW; ++w) arg_better(bv, bi, sv[w], si[w]);
+  if (tid < 64) {
+    bv = sv[min(tid, NW - 1)];
+    bi = si[min(tid, NW - 1)];
+#pragma unroll
+    for (int o = NW / 2; o > 0; o >>= 1) {
+      const float ov = __shfl_xor(bv, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      arg_better(bv, bi, ov, oi);
+    }
     if (bi >= V) bi = 0;
-    const int b = rows.row_seq[m];
-    if (rows.seq_ok[b]) greedy[(size_t)b * (k_max + 1) + rows.row_j[m]] = bi;
+    if (tid == 0 && ok) greedy[(size_t)b * (k_max + 1) + row_j] = bi;
   }
 }
 
