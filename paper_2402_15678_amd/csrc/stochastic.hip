@@ -144,10 +144,16 @@ struct Temp {
   const double2* pow2;       // [64] 2^(j/64), rest
   double dmx;                // largest score of the row
   double lowest;             // -800 T
-  __device__ __forceinline__ double mass(float l) const {
-    if (inv == 0.0) return exp(((double)l - dmx) / T);  // (uniform)
+  float near;                // scores from here on are within 690 T of the largest (see mass4); NaN or more than any score: none are
+  __device__ __forceinline__ void largest(float mx) {
+    dmx = (double)mx;
+    near = inv == 0.0 ? INFINITY : __double2float_ru(dmx - 690.0 * T);
+  }
+  // SMALL: the result may be below the normal range, the argument below the cut or not a number
+  template <bool SMALL>
+  __device__ __forceinline__ double table_exp(float l) const {
     double d = (double)l - dmx;
-    d = d < lowest ? lowest : d;
+    if (SMALL) d = d < lowest ? lowest : d;
     const double t = fma(d, per_step, 6755399441055744.0);  // 1.5 * 2^52: the nearest whole number sits in the low bits
     const double nd = t - 6755399441055744.0;
     const int n = (int)(uint32_t)__double_as_longlong(t);
@@ -158,7 +164,25 @@ struct Temp {
     p = fma(r, p, 0.5);
     p = fma(r * r, p, r);
     const double2 c = pow2[n & 63];
-    return ldexp(c.x + fma(c.x, p, c.y), n >> 6);
+    const double y = c.x + fma(c.x, p, c.y);
+    if (SMALL) return ldexp(y, n >> 6);
+    return __hiloint2double(__double2hiint(y) + ((n & ~63) << 14), __double2loint(y));
+  }
+  __device__ __forceinline__ double mass(float l) const {
+    if (inv == 0.0) return exp(((double)l - dmx) / T);  // (uniform)
+    return table_exp<true>(l);
+  }
+  // The masses of four scores, bit for bit those of mass().  Where every score of the wave is within 690 T of the largest the
+  // powers of two are added to the exponent field and nothing is cut: the comparison, the selections and the ldexp were a quarter
+  // of these kernels' arithmetic.
+  __device__ __forceinline__ void mass4(const f32x4& l, double (&m)[4]) const {
+    if (__all(l[0] >= near && l[1] >= near && l[2] >= near && l[3] >= near)) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = table_exp<false>(l[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = mass(l[e]);
+    }
   }
 };
 
@@ -326,14 +350,15 @@ __device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < SV_WAVES; ++w) mx = fmaxf(mx, sh.redf[w]);
-  temp.dmx = (double)mx;
+  temp.largest(mx);
   double zp = 0.0;
   wave_blocks<TILES>(V, wave, [&](int blk, int t) {
     const int v = blk * SV_BLOCK + 4 * lane;
     const f32x4 l = TILES > 0 ? raw[t] : load_row4(L, v, V, -INFINITY);
+    temp.mass4(l, ex[t]);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      ex[t][e] = v + e < V ? temp.mass(l[e]) : 0.0;
+      if (v + e >= V) ex[t][e] = 0.0;
       zp += ex[t][e];
     }
   });
@@ -392,7 +417,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     return;
   }
   const float* L = logits + (size_t)row * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature};  // 64 / ln2
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 0.f};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
   double Z;
   row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
@@ -423,8 +448,9 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
   const double inv_z = 1.0 / Z;  // (Z >= 1: the largest score contributes exp(0))
   auto o4 = [&](int v, double (&o)[4]) {  // probabilities of tokens v .. v+3, recomputed from the scores
     const f32x4 l = load_row4(L, v, V, -INFINITY);
+    temp.mass4(l, o);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = v + e < V ? div_by(temp.mass(l[e]), Z, inv_z) : 0.0;
+    for (int e = 0; e < 4; ++e) o[e] = v + e < V ? div_by(o[e], Z, inv_z) : 0.0;
   };
   int tok = -1;
   if constexpr (TILES > 0) {
@@ -481,7 +507,7 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   __shared__ DrawShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* L = logits + (size_t)b * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature};  // 64 / ln2
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 0.f};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
   double Z;
   row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
@@ -490,8 +516,9 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   const double inv_z = 1.0 / Z;
   auto q4 = [&](int v, double (&m)[4]) {  // the fp32 probabilities of tokens v .. v+3
     const f32x4 l = load_row4(L, v, V, -INFINITY);
+    temp.mass4(l, m);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) m[e] = v + e < V ? (double)(float)div_by(temp.mass(l[e]), Z, inv_z) : 0.0;
+    for (int e = 0; e < 4; ++e) m[e] = v + e < V ? (double)(float)div_by(m[e], Z, inv_z) : 0.0;
   };
   float* P = probs ? probs + (size_t)b * probs_stride : nullptr;
   wave_blocks<TILES>(V, wave, [&](int blk, int t) {
