@@ -272,8 +272,11 @@ __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, 
   // thr is -inf until the row has seen a key, LAZY_MAX afterwards: probabilities up to 2^6 are fine
   // in fp16 and in the fp32 accumulators, so the common tile needs no exchange and no rescale
   if (__any(tm > thr)) {
-    tm = __builtin_fmaxf(tm, __shfl_xor(tm, 16, 64));
-    tm = __builtin_fmaxf(tm, __shfl_xor(tm, 32, 64));
+    uint32_t x, y;
+    lane_pair<16>(__float_as_uint(tm), x, y);
+    tm = __builtin_fmaxf(__uint_as_float(x), __uint_as_float(y));
+    lane_pair<32>(__float_as_uint(tm), x, y);
+    tm = __builtin_fmaxf(__uint_as_float(x), __uint_as_float(y));
     const bool fresh = run_m == -INFINITY;
     float d = fresh ? tm : __builtin_fmaxf(tm, 0.f);  // how far the reference moves (shifted units)
     if (d == -INFINITY) d = 0.f;                      // still nothing visible

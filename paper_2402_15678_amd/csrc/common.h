@@ -89,15 +89,40 @@ template <> struct Store<bf16_t> {
   static __device__ __forceinline__ void store(bf16_t* p, float v) { *p = f2bf(v); }
 };
 
+// Reductions over the lanes on the vector unit: exchanges inside a row of 16 lanes by DPP, between the rows by the permlane swaps.
+// Through the LDS unit (__shfl_xor) each of the six steps is a round trip of about 100 cycles.  The steps pair lanes whose groups
+// already agree, so the mirrors stand for the exchanges 4 and 8 lanes away; every lane gets the result.
+enum LaneStep { LANE_1 = 0xB1, LANE_2 = 0x4E, LANE_4 = 0x141, LANE_8 = 0x140 };  // quad_perm [1,0,3,2], [2,3,0,1], half mirror, mirror
+template <int STEP>
+__device__ __forceinline__ uint32_t lane_swap(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, STEP, 0xf, 0xf, true);
+}
+// (x of this lane's half, x of the other half) for lanes 16 and 32 away, in an order that depends on the half
+template <int DIST>
+__device__ __forceinline__ void lane_pair(uint32_t v, uint32_t& a, uint32_t& b) {
+  static_assert(DIST == 16 || DIST == 32, "rows of 16 lanes");
+  const auto r = DIST == 16 ? __builtin_amdgcn_permlane16_swap(v, v, false, false) : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  a = r[0];
+  b = r[1];
+}
+template <typename F>
+__device__ __forceinline__ float wave_reduce(float v, F f) {
+  auto step = [&](uint32_t o) { v = f(v, __uint_as_float(o)); };
+  step(lane_swap<LANE_1>(__float_as_uint(v)));
+  step(lane_swap<LANE_2>(__float_as_uint(v)));
+  step(lane_swap<LANE_4>(__float_as_uint(v)));
+  step(lane_swap<LANE_8>(__float_as_uint(v)));
+  uint32_t a, b;
+  lane_pair<16>(__float_as_uint(v), a, b);
+  v = f(__uint_as_float(a), __uint_as_float(b));
+  lane_pair<32>(__float_as_uint(v), a, b);
+  return f(__uint_as_float(a), __uint_as_float(b));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // Sum over a block of NW waves; every thread gets the result.  `red` holds NW floats; FRESH: nothing of the block has read

@@ -666,18 +666,24 @@ void launch_pack_weight(const void* src, void* dst, int N, int K, int half, int3
 }
 
 // Sums of eight values over the lanes, value i ending up in lanes 8i .. 8i + 7: every exchange with the lane 32, 16, 8 away halves
-// the values that a lane still carries
+// the values that a lane still carries (a swap of two registers' halves does what two selections and an exchange would)
 __device__ __forceinline__ float f32_row_sum(const float (&acc)[8], int lane) {
-  float s4[4], s2[2], s;
-  const bool hi = lane & 32, mid = lane & 16, lo = lane & 8;
+  float s4[4], s2[2];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) s4[i] = (hi ? acc[4 + i] : acc[i]) + __shfl_xor(hi ? acc[i] : acc[4 + i], 32, 64);
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[i]), __float_as_uint(acc[4 + i]), false, false);
+    s4[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
 #pragma unroll
-  for (int i = 0; i < 2; ++i) s2[i] = (mid ? s4[2 + i] : s4[i]) + __shfl_xor(mid ? s4[i] : s4[2 + i], 16, 64);
-  s = (lo ? s2[1] : s2[0]) + __shfl_xor(lo ? s2[0] : s2[1], 8, 64);
-#pragma unroll
-  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  return s;
+  for (int i = 0; i < 2; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(s4[i]), __float_as_uint(s4[2 + i]), false, false);
+    s2[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  }
+  const bool lo = lane & 8;
+  float s = (lo ? s2[1] : s2[0]) + __uint_as_float(lane_swap<0x128>(__float_as_uint(lo ? s2[0] : s2[1])));  // row_ror:8
+  s += __uint_as_float(lane_swap<LANE_1>(__float_as_uint(s)));
+  s += __uint_as_float(lane_swap<LANE_2>(__float_as_uint(s)));
+  return s + __uint_as_float(lane_swap<LANE_4>(__float_as_uint(s)));
 }
 
 // fp32 model (the small configuration): one wave per output column, lanes split k in pieces of four, up to 8 rows at a

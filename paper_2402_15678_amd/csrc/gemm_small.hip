@@ -157,10 +157,18 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
         sq += __builtin_fabsf(ss_v[u]);
         mark |= __float_as_uint(ss_v[u]);
       }
-#pragma unroll
-    for (int o = ROWS; o < 64 && LP > 1; o <<= 1) {
-      sq += __shfl_xor(sq, o, 64);
-      mark |= __shfl_xor(mark, o, 64);
+    uint32_t x, y;
+    if (LP == 4) {
+      lane_pair<16>(__float_as_uint(sq), x, y);
+      sq = __uint_as_float(x) + __uint_as_float(y);
+      lane_pair<16>(mark, x, y);
+      mark = x | y;
+    }
+    if (LP >= 2) {
+      lane_pair<32>(__float_as_uint(sq), x, y);
+      sq = __uint_as_float(x) + __uint_as_float(y);
+      lane_pair<32>(mark, x, y);
+      mark = x | y;
     }
     // (the mark travels in the sign)
     if (lane < ROWS) s_part[wave][lane] = __uint_as_float((__float_as_uint(sq) & 0x7fffffffu) | (mark & 0x80000000u));
@@ -227,11 +235,15 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
         h[e] = __builtin_fminf(__builtin_fmaxf(h[e], -ROW_MARK), ROW_MARK);
         q += v[e] * v[e];
       }
-      int o = over;
-      q += __shfl_xor(q, 16, 64);
-      o |= __shfl_xor(o, 16, 64);
-      q += __shfl_xor(q, 32, 64);
-      o |= __shfl_xor(o, 32, 64);
+      uint32_t o = over, y0, y1;
+      lane_pair<16>(__float_as_uint(q), y0, y1);
+      q = __uint_as_float(y0) + __uint_as_float(y1);
+      lane_pair<32>(__float_as_uint(q), y0, y1);
+      q = __uint_as_float(y0) + __uint_as_float(y1);
+      lane_pair<16>(o, y0, y1);
+      o = y0 | y1;
+      lane_pair<32>(o, y0, y1);
+      o = y0 | y1;
       if (piece) {
         *reinterpret_cast<f32x4*>(a.x + (size_t)pm * a.N + pn) = v;
         *reinterpret_cast<uint2*>(reinterpret_cast<f16_t*>(a.out) + operand_at(pm, pn, a.M, a.N)) = make_uint2(pack2h(h[0], h[1]), pack2h(h[2], h[3]));

@@ -688,23 +688,32 @@ __global__ void __launch_bounds__(ARGMAX_THREADS) argmax_rows_kernel(float* __re
       arg_better(bv, bi, v, i);
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ov = __shfl_xor(bv, o, 64);
-    const int oi = __shfl_xor(bi, o, 64);
-    arg_better(bv, bi, ov, oi);
-  }
+  auto meet = [&](uint32_t v, uint32_t i) { arg_better(bv, bi, __uint_as_float(v), (int)i); };
+  auto row_of_16 = [&](bool all) {                           // (all: 16 lanes, else 4)
+    meet(lane_swap<LANE_1>(__float_as_uint(bv)), lane_swap<LANE_1>((uint32_t)bi));
+    meet(lane_swap<LANE_2>(__float_as_uint(bv)), lane_swap<LANE_2>((uint32_t)bi));
+    if (!all) return;
+    meet(lane_swap<LANE_4>(__float_as_uint(bv)), lane_swap<LANE_4>((uint32_t)bi));
+    meet(lane_swap<LANE_8>(__float_as_uint(bv)), lane_swap<LANE_8>((uint32_t)bi));
+  };
+  auto across = [&](auto dist) {
+    uint32_t va, vb, ia, ib;
+    lane_pair<decltype(dist)::value>(__float_as_uint(bv), va, vb);
+    lane_pair<decltype(dist)::value>((uint32_t)bi, ia, ib);
+    bv = __uint_as_float(va);
+    bi = (int)ia;
+    meet(vb, ib);
+  };
+  row_of_16(true);
+  across(IntC<16>{});
+  across(IntC<32>{});
   if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
   __syncthreads();
   if (tid < 64) {
     bv = sv[min(tid, NW - 1)];
     bi = si[min(tid, NW - 1)];
-#pragma unroll
-    for (int o = NW / 2; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(bv, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      arg_better(bv, bi, ov, oi);
-    }
+    static_assert(NW == 16 || NW == 4, "the waves' results in one row of lanes");
+    row_of_16(NW == 16);
     if (bi >= V) bi = 0;
     if (tid == 0 && ok) greedy[(size_t)b * (k_max + 1) + row_j] = bi;
   }

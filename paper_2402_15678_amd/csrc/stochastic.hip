@@ -71,10 +71,51 @@ __device__ __forceinline__ f32x4 load_row4(const float* __restrict__ R, int v, i
   return r;
 }
 
+// (see wave_reduce)
+template <typename F>
+__device__ __forceinline__ double both_halves(double v, F f) {
+  return __hiloint2double((int)f((uint32_t)__double2hiint(v)), (int)f((uint32_t)__double2loint(v)));
+}
+template <int STEP>
+__device__ __forceinline__ double lane_swap_d(double v) {
+  return both_halves(v, [](uint32_t x) { return lane_swap<STEP>(x); });
+}
+// x and y hold values of lanes; afterwards a lane's sum is that of its x (lower half of the pair) or y (upper half) and the same
+// of the lane DIST away
+template <int DIST>
+__device__ __forceinline__ double lane_halve_d(double x, double y) {
+  const uint32_t xl = (uint32_t)__double2loint(x), yl = (uint32_t)__double2loint(y), xh = (uint32_t)__double2hiint(x), yh = (uint32_t)__double2hiint(y);
+  const auto l = DIST == 16 ? __builtin_amdgcn_permlane16_swap(xl, yl, false, false) : __builtin_amdgcn_permlane32_swap(xl, yl, false, false);
+  const auto h = DIST == 16 ? __builtin_amdgcn_permlane16_swap(xh, yh, false, false) : __builtin_amdgcn_permlane32_swap(xh, yh, false, false);
+  return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+}
 __device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  v += lane_swap_d<LANE_1>(v);
+  v += lane_swap_d<LANE_2>(v);
+  v += lane_swap_d<LANE_4>(v);
+  v += lane_swap_d<LANE_8>(v);
+  v = lane_halve_d<16>(v, v);
+  return lane_halve_d<32>(v, v);
+}
+
+// one double from another lane by DPP, 0 where there is none or the row (of 16 lanes) is not in ROWS
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double lane_get_d(double v) {
+  return both_halves(v, [](uint32_t x) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xf, false); });
+}
+// inclusive prefix sums over the lanes (row_shr 1, 2, 4, 8, then the last lane of row 0 and 2 to the next row, of row 1 to 2 and 3)
+__device__ __forceinline__ double wave_scan_d(double v) {
+  v += lane_get_d<0x111, 0xf>(v);
+  v += lane_get_d<0x112, 0xf>(v);
+  v += lane_get_d<0x114, 0xf>(v);
+  v += lane_get_d<0x118, 0xf>(v);
+  v += lane_get_d<0x142, 0xa>(v);
+  v += lane_get_d<0x143, 0xc>(v);
   return v;
+}
+__device__ __forceinline__ double lane_before_d(double v) { return lane_get_d<0x138, 0xf>(v); }  // wave_shr:1; 0 in lane 0
+__device__ __forceinline__ double lane_63_d(double v) {
+  return both_halves(v, [](uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); });
 }
 
 struct DrawShared {
@@ -209,14 +250,15 @@ __device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u,
       s8[t] = (m[0] + m[1]) + (m[2] + m[3]);
     });
     double s4[4], s2[2];
-    const bool hi = lane & 32, mid = lane & 16, lo = lane & 8;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) s4[i] = (hi ? s8[4 + i] : s8[i]) + __shfl_xor(hi ? s8[i] : s8[4 + i], 32, 64);
+    for (int i = 0; i < 4; ++i) s4[i] = lane_halve_d<32>(s8[i], s8[4 + i]);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) s2[i] = (mid ? s4[2 + i] : s4[i]) + __shfl_xor(mid ? s4[i] : s4[2 + i], 16, 64);
-    double s = (lo ? s2[1] : s2[0]) + __shfl_xor(lo ? s2[0] : s2[1], 8, 64);
-#pragma unroll
-    for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    for (int i = 0; i < 2; ++i) s2[i] = lane_halve_d<16>(s4[i], s4[2 + i]);
+    const bool lo = lane & 8;
+    double s = (lo ? s2[1] : s2[0]) + lane_swap_d<0x128>(lo ? s2[0] : s2[1]);  // row_ror:8
+    s += lane_swap_d<LANE_1>(s);
+    s += lane_swap_d<LANE_2>(s);
+    s += lane_swap_d<LANE_4>(s);
     if ((lane & 7) == 0) sh.seg[(lane >> 3) * SV_WAVES + wave] = s;  // (segments past the row's end: zero)
   } else {
     double run = 0.0;
@@ -239,15 +281,9 @@ __device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u,
       const int s = lane * per + i;
       if (s < n_seg) mine += sh.seg[s];
     }
-    double inc = mine;  // inclusive prefix over the lanes
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const double t = __shfl_up(inc, o, 64);
-      if (lane >= o) inc += t;
-    }
-    const double total = __shfl(inc, 63, 64), target = u * total;
-    double before = __shfl_up(inc, 1, 64);
-    if (lane == 0) before = 0.0;
+    const double inc = wave_scan_d(mine);
+    const double total = lane_63_d(inc), target = u * total;
+    double before = lane_before_d(inc);
     int hit = 0x7fffffff, last = -1;
     double hit_before = 0.0, last_before = 0.0;
     for (int i = 0; i < per; ++i) {
@@ -285,15 +321,9 @@ __device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u,
       double m[4];
       mass4(t, v, m);
       const double mine = (m[0] + m[1]) + (m[2] + m[3]);
-      double inc = mine;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const double t = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += t;
-      }
-      const double sum = __shfl(inc, 63, 64);
-      double cum = __shfl_up(inc, 1, 64);
-      cum = base + (lane == 0 ? 0.0 : cum);
+      const double inc = wave_scan_d(mine);
+      const double sum = lane_63_d(inc);
+      double cum = base + lane_before_d(inc);
       int hit = -1, last = -1;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
