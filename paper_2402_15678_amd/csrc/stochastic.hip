@@ -127,6 +127,14 @@ struct DrawShared {
   int pick[2];                // chosen segment, chosen token
 };
 
+// a * b + c with c in scalar registers.  (The compiler's choice is the two-address form with the constant copied to vector
+// registers first, three instructions for one.)
+__device__ __forceinline__ double fma_vvs(double a, double b, double c) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+  return r;
+}
+
 // x / c for a divisor that is the same for the whole row, inv = 1 / c: one correction step makes the product the
 // rounded quotient.  (c and inv normal numbers, x finite: the caller sees to both)
 __device__ __forceinline__ double div_by(double x, double c, double inv) {
@@ -185,41 +193,66 @@ struct Temp {
   const double2* pow2;       // [64] 2^(j/64), rest
   double dmx;                // largest score of the row
   double lowest;             // -800 T
+  double sixth_order;        // 1 / 120 (in vector registers: an instruction reads one scalar constant)
   float near;                // scores from here on are within 690 T of the largest (see mass4); NaN or more than any score: none are
   __device__ __forceinline__ void largest(float mx) {
     dmx = (double)mx;
     near = inv == 0.0 ? INFINITY : __double2float_ru(dmx - 690.0 * T);
   }
-  // SMALL: the result may be below the normal range, the argument below the cut or not a number
-  template <bool SMALL>
-  __device__ __forceinline__ double table_exp(float l) const {
-    double d = (double)l - dmx;
-    if (SMALL) d = d < lowest ? lowest : d;
-    const double t = fma(d, per_step, 6755399441055744.0);  // 1.5 * 2^52: the nearest whole number sits in the low bits
-    const double nd = t - 6755399441055744.0;
-    const int n = (int)(uint32_t)__double_as_longlong(t);
-    double r = fma(d, inv, nd * -0x1.62e42fefap-7);   // ln2/64, its first 33 bits (the product with n is exact) ...
-    r = fma(nd, -0x1.cf79abc9e3b3ap-46, r);           // ... and the rest
-    double p = fma(r, 1.0 / 120.0, 1.0 / 24.0);
-    p = fma(r, p, 1.0 / 6.0);
-    p = fma(r, p, 0.5);
-    p = fma(r * r, p, r);
-    const double2 c = pow2[n & 63];
-    const double y = c.x + fma(c.x, p, c.y);
-    if (SMALL) return ldexp(y, n >> 6);
-    return __hiloint2double(__double2hiint(y) + ((n & ~63) << 14), __double2loint(y));
+  // N exponentials side by side (one is a chain of fifteen dependent operations and an LDS read).  SMALL: a result may be below the
+  // normal range, an argument below the cut or not a number.
+  template <bool SMALL, int N>
+  __device__ __forceinline__ void table_exp(const float (&l)[N], double (&m)[N]) const {
+    double d[N], t[N], nd[N], r[N], p[N], sq[N];
+    double2 c[N];
+    int n[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      d[e] = (double)l[e] - dmx;
+      if (SMALL) d[e] = d[e] < lowest ? lowest : d[e];
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) t[e] = fma_vvs(d[e], per_step, 6755399441055744.0);  // 1.5 * 2^52: the nearest whole number sits in the low bits
+#pragma unroll
+    for (int e = 0; e < N; ++e) n[e] = (int)(uint32_t)__double_as_longlong(t[e]);
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = pow2[n[e] & 63];
+#pragma unroll
+    for (int e = 0; e < N; ++e) nd[e] = t[e] - 6755399441055744.0;
+#pragma unroll
+    for (int e = 0; e < N; ++e) r[e] = fma(d[e], inv, nd[e] * -0x1.62e42fefap-7);  // ln2/64, its first 33 bits (the product with n is exact) ...
+#pragma unroll
+    for (int e = 0; e < N; ++e) r[e] = fma(nd[e], -0x1.cf79abc9e3b3ap-46, r[e]);   // ... and the rest
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma_vvs(r[e], sixth_order, 1.0 / 24.0);
+#pragma unroll
+    for (int e = 0; e < N; ++e) sq[e] = r[e] * r[e];
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma_vvs(r[e], p[e], 1.0 / 6.0);
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma(r[e], p[e], 0.5);
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma(sq[e], p[e], r[e]);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const double y = c[e].x + fma(c[e].x, p[e], c[e].y);
+      m[e] = SMALL ? ldexp(y, n[e] >> 6) : __hiloint2double(__double2hiint(y) + ((n[e] & ~63) << 14), __double2loint(y));
+    }
   }
   __device__ __forceinline__ double mass(float l) const {
     if (inv == 0.0) return exp(((double)l - dmx) / T);  // (uniform)
-    return table_exp<true>(l);
+    const float one[1] = {l};
+    double m[1];
+    table_exp<true, 1>(one, m);
+    return m[0];
   }
   // The masses of four scores, bit for bit those of mass().  Where every score of the wave is within 690 T of the largest the
   // powers of two are added to the exponent field and nothing is cut: the comparison, the selections and the ldexp were a quarter
   // of these kernels' arithmetic.
   __device__ __forceinline__ void mass4(const f32x4& l, double (&m)[4]) const {
+    const float x[4] = {l[0], l[1], l[2], l[3]};
     if (__all(l[0] >= near && l[1] >= near && l[2] >= near && l[3] >= near)) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m[e] = table_exp<false>(l[e]);
+      table_exp<false, 4>(x, m);
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) m[e] = mass(l[e]);
@@ -368,6 +401,8 @@ template <int TILES>
 __device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, Temp& temp, DrawShared& sh, int tid,
                                               double (&ex)[TILES > 0 ? TILES : 1][4], double& Z) {
   const int lane = tid & 63, wave = tid >> 6;
+  double2 power = make_double2(0.0, 0.0);    // (asked for ahead of the row)
+  if (tid < 64) power = make_double2(kPow2[2 * tid], kPow2[2 * tid + 1]);
   f32x4 raw[TILES > 0 ? TILES : 1];
   float mx = -INFINITY;
   wave_blocks<TILES>(V, wave, [&](int blk, int t) { raw[t] = load_row4(L, blk * SV_BLOCK + 4 * lane, V, -INFINITY);
@@ -376,7 +411,7 @@ __device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V
     wave_blocks<TILES>(V, wave, [&](int, int t) { mx = fmaxf(mx, fmaxf(fmaxf(raw[t][0], raw[t][1]), fmaxf(raw[t][2], raw[t][3]))); });
   mx = wave_max(mx);
   if (lane == 0) sh.redf[wave] = mx;
-  if (tid < 64) sh.pow2[tid] = make_double2(kPow2[2 * tid], kPow2[2 * tid + 1]);
+  if (tid < 64) sh.pow2[tid] = power;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < SV_WAVES; ++w) mx = fmaxf(mx, sh.redf[w]);
@@ -386,11 +421,13 @@ __device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V
     const int v = blk * SV_BLOCK + 4 * lane;
     const f32x4 l = TILES > 0 ? raw[t] : load_row4(L, v, V, -INFINITY);
     temp.mass4(l, ex[t]);
+    if ((blk + 1) * SV_BLOCK > V) {          // (wave-uniform)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      if (v + e >= V) ex[t][e] = 0.0;
-      zp += ex[t][e];
+      for (int e = 0; e < 4; ++e)
+        if (v + e >= V) ex[t][e] = 0.0;
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) zp += ex[t][e];
   });
   zp = wave_sum_d(zp);
   if (lane == 0) sh.red[wave] = zp;
@@ -447,7 +484,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     return;
   }
   const float* L = logits + (size_t)row * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 0.f};  // 64 / ln2
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 1.0 / 120.0, 0.f};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
   double Z;
   row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
@@ -537,7 +574,7 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   __shared__ DrawShared sh;
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float* L = logits + (size_t)b * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 0.f};  // 64 / ln2
+  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 1.0 / 120.0, 0.f};  // 64 / ln2
   double ex[TILES > 0 ? TILES : 1][4];
   double Z;
   row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
