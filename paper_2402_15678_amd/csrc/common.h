@@ -125,6 +125,27 @@ __device__ __forceinline__ float wave_max(float v) {
   return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
+__device__ __forceinline__ int wave_sum_i(int v) {
+  v += (int)lane_swap<LANE_1>((uint32_t)v);
+  v += (int)lane_swap<LANE_2>((uint32_t)v);
+  v += (int)lane_swap<LANE_4>((uint32_t)v);
+  v += (int)lane_swap<LANE_8>((uint32_t)v);
+  uint32_t a, b;
+  lane_pair<16>((uint32_t)v, a, b);
+  lane_pair<32>(a + b, a, b);
+  return (int)(a + b);
+}
+// inclusive prefix sums over the lanes (row_shr 1, 2, 4, 8, then a row's last lane to the rows behind it)
+__device__ __forceinline__ int wave_scan_i(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
 // Sum over a block of NW waves; every thread gets the result.  `red` holds NW floats; FRESH: nothing of the block has read
 // or written it yet.
 template <int NW, bool FRESH = false>

@@ -25,15 +25,19 @@ template <int N> struct IntC { static constexpr int value = N; };
 // s_row0[b] = first row of sequence b (b = 0 .. B), from s_row0[b + 1] = rows of sequence b.  Every thread of the workgroup.
 __device__ __forceinline__ void scan_rows(int32_t* s_row0, int B, int32_t* s_wave) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (B <= 64) {                            // one wave holds them all
+    if (tid < 64) {
+      const int inc = wave_scan_i(tid < B ? s_row0[tid + 1] : 0);
+      if (tid < B) s_row0[tid + 1] = inc;
+      if (tid == 0) s_row0[0] = 0;
+    }
+    __syncthreads();
+    return;
+  }
   const int per = (B + PREP_THREADS - 1) / PREP_THREADS, lo = min(tid * per, B), hi = min(lo + per, B);
   int sum = 0;
   for (int b = lo; b < hi; ++b) sum += s_row0[b + 1];
-  int inc = sum;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int t = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += t;
-  }
+  const int inc = wave_scan_i(sum);
   if (lane == 63) s_wave[wave] = inc;
   __syncthreads();
   int at = inc - sum;
@@ -73,7 +77,7 @@ __device__ __forceinline__ void rope_rows(const PrepArgs& a, const int32_t* s_ro
 __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   extern __shared__ __attribute__((aligned(16))) int32_t s_prep[];
   __shared__ int32_t s_wave[PREP_THREADS / 64];
-  __shared__ int s_bad, s_tps;
+  __shared__ int s_bad;
   __shared__ unsigned long long s_tiles;
   const int tid = threadIdx.x, B = a.B;
   int32_t* s_row0 = s_prep;                 // [B + 1]
@@ -82,12 +86,28 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   int32_t* s_cnt = s_nb + B + 1;            // [B] attention workgroups of a sequence
   int32_t* s_spl = s_cnt + B + 1;           // [B] its KV splits
   int32_t* s_ctx = s_spl + B + 1;           // [B] context
+  // The first loads of every table go out at once, the numbers that the others wait for first: none of them needs another's answer
+  // to know its place.  Block table: entry tid + 1024 u of it; token: input idx = tid of (sequence, input) pairs, max_q per sequence.
+  const int mb = a.max_blocks_per_seq, nq = a.max_q;
+  const int b_q = tid / nq, j_q = tid - b_q * nq;
+  int k_first = 0, ctx_first = 0, pb_first[8], tok_first = 0;
+  if (tid < B) {
+    k_first = a.spec_len[tid];
+    ctx_first = a.ctx_lens[tid];
+  }
+  auto token = [&](int b, int j) { return j == 0 ? a.last_tok[b] : a.voted[(size_t)b * a.k_max + j - 1]; };  // (j < max_q <= k_max + 1)
+  if (blockIdx.x == 0) {
+    const long last = (long)B * mb - 1;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) pb_first[u] = a.block_tables[min((long)(tid + u * PREP_THREADS), last)];
+    if (a.last_tok) tok_first = token(min(b_q, B - 1), j_q);
+  }
   if (tid == 0) { s_bad = 0; s_tiles = 0ull; }
   __syncthreads();
   // pass 1: per-sequence validation
   for (int b = tid; b < B; b += PREP_THREADS) {
-    const int k = a.spec_len[b];
-    const int ctx = a.ctx_lens[b];
+    const int k = b == tid ? k_first : a.spec_len[b];
+    const int ctx = b == tid ? ctx_first : a.ctx_lens[b];
     const bool fits = k >= 0 && k <= a.k_max && k < a.max_q;  // (the attention launches were sized for max_q rows)
     s_row0[b + 1] = fits ? k + 1 : 1;
     s_ctx[b] = ctx;
@@ -120,14 +140,15 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   // pass 1b: every mapped block of every sequence, all threads side by side (a long context has hundreds of table
   // entries; one thread walking them is a chain of dependent loads), eight entries per thread in flight
   {
-    const int mb = a.max_blocks_per_seq, step_b = PREP_THREADS / mb, step_i = PREP_THREADS % mb;
+    const int step_b = PREP_THREADS / mb, step_i = PREP_THREADS % mb;
     int b = tid / mb, i = tid % mb;
-    while (b < B) {
+    for (bool first = true; b < B; first = false) {
       int pb[8], bb[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         bb[u] = b < B && i < s_nb[b] ? b : -1;
-        pb[u] = bb[u] >= 0 ? a.block_tables[(size_t)b * mb + i] : 0;
+        if (first) pb[u] = pb_first[u];
+        else pb[u] = bb[u] >= 0 ? a.block_tables[(size_t)b * mb + i] : 0;
         b += step_b;
         i += step_i;
         if (i >= mb) { i -= mb; ++b; }
@@ -142,14 +163,18 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   }
   // pass 1c: every input token of every sequence that passed the shape checks, likewise
   if (a.last_tok) {
-    for (long idx = tid; idx < (long)B * (a.k_max + 1); idx += PREP_THREADS) {
-      const int b = (int)(idx / (a.k_max + 1)), j = (int)(idx % (a.k_max + 1));
-      if (s_nb[b] == 0 || j >= s_row0[b + 1]) continue;  // (s_row0[b+1] still holds q_b = k_b + 1 here)
-      const int tok = (j == 0) ? a.last_tok[b] : a.voted[(size_t)b * a.k_max + j - 1];
-      if (tok < 0 || tok >= a.vocab) {
-        atomicAnd(&s_ok[b], 0);
-        if (a.dev_status) atomicOr(a.dev_status, MN_DEV_TOKEN);
+    int b = b_q, j = j_q;
+    for (bool first = true; b < B; first = false) {
+      if (s_nb[b] != 0 && j < s_row0[b + 1]) {  // (s_row0[b+1] still holds q_b = k_b + 1 here)
+        const int tok = first ? tok_first : token(b, j);
+        if (tok < 0 || tok >= a.vocab) {
+          atomicAnd(&s_ok[b], 0);
+          if (a.dev_status) atomicOr(a.dev_status, MN_DEV_TOKEN);
+        }
       }
+      b += PREP_THREADS / nq;
+      j += PREP_THREADS % nq;
+      if (j >= nq) { j -= nq; ++b; }
     }
   }
   __syncthreads();
@@ -176,16 +201,35 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
     s_nb[b] = ok ? (ctx + q + 31) >> 5 : 0;
     if (ok) atomicAdd(&s_tiles, (unsigned long long)s_nb[b] * (unsigned long long)((q * max(a.q_per_kv, 1) + 127) >> 7));
   }
-  for (int m = tid; m < a.M; m += PREP_THREADS) {
-    const int b = seq_of_row(s_row0, B, m), j = m - s_row0[b], ok = s_ok[b];
-    const int p = ok ? s_ctx[b] + j : -1;
+  // rows: by (sequence, input) pair where that is not many more than the rows, the first of which have their token already; a search
+  // for the row's sequence otherwise (thousands of sequences, one of them long)
+  const bool pairs = (long)B * nq <= 2l * a.M + PREP_THREADS;
+  auto for_rows = [&](auto f) {             // f(row, sequence, input, first)
+    if (pairs) {
+      int b = b_q, j = j_q;
+      for (bool first = true; b < B; first = false) {
+        const int row0 = s_row0[b];
+        if (j < s_row0[b + 1] - row0) f(row0 + j, b, j, first);
+        b += PREP_THREADS / nq;
+        j += PREP_THREADS % nq;
+        if (j >= nq) { j -= nq; ++b; }
+      }
+    } else {
+      for (int m = tid; m < a.M; m += PREP_THREADS) {
+        const int b = seq_of_row(s_row0, B, m);
+        f(m, b, m - s_row0[b], false);
+      }
+    }
+  };
+  for_rows([&](int m, int b, int j, bool first) {
+    const int ok = s_ok[b], p = ok ? s_ctx[b] + j : -1, blk = p / a.block_size;
     a.row_seq[m] = b;
     a.row_j[m] = j;
     a.row_pos[m] = p;
     // where the row's K/V are written, looked up once per step instead of once per layer and head
-    a.row_slot[m] = ok ? a.block_tables[(size_t)b * a.max_blocks_per_seq + p / a.block_size] * a.block_size + p % a.block_size : -1;
-    a.row_tok[m] = (ok && a.last_tok) ? ((j == 0) ? a.last_tok[b] : a.voted[(size_t)b * a.k_max + j - 1]) : 0;
-  }
+    a.row_slot[m] = ok ? a.block_tables[(size_t)b * mb + blk] * a.block_size + p - blk * a.block_size : -1;
+    a.row_tok[m] = (ok && a.last_tok) ? (first ? tok_first : token(b, j)) : 0;
+  });
   if (!a.plan.items) return;
   __syncthreads();
   // ---- the attention work list: one record of 8 int32 per (sequence, row group, KV split) that has work: {sequence, row
@@ -200,13 +244,12 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
   // Balance: a workgroup should take about (all key tiles x KV heads) / (the number of workgroups aimed for) tiles, at
   // least min_tiles (below that the lead-in of a workgroup and the partial sums cost more than the parallelism wins).
   // Long sequences of a ragged batch are then cut into more splits than short ones.
-  if (tid == 0) {
-    const unsigned long long w = (unsigned long long)max(a.plan.target_wgs, 1);
-    const unsigned long long per = (s_tiles * (unsigned long long)max(a.kv_heads, 1) + w - 1) / w;
-    s_tps = (int)min(max(per, (unsigned long long)max(a.plan.min_tiles, 1)), (unsigned long long)(1 << 20));
+  int tps;
+  {  // (every thread for itself)
+    const unsigned long long w = (unsigned long long)max(a.plan.target_wgs, 1), all = s_tiles * (unsigned long long)max(a.kv_heads, 1) + w - 1;
+    const unsigned long long per = all >> 32 ? all / w : (unsigned long long)((uint32_t)all / (uint32_t)w);
+    tps = (int)min(max(per, (unsigned long long)max(a.plan.min_tiles, 1)), (unsigned long long)(1 << 20));
   }
-  __syncthreads();
-  const int tps = s_tps;
   for (int b = tid; b < B; b += PREP_THREADS) {
     const int q = s_row0[b + 1] - s_row0[b], n_tiles = s_nb[b];
     const int n_rg = (((a.q_per_kv * q + 15) >> 4) + a.plan.tiles16_per_wg - 1) / a.plan.tiles16_per_wg;
@@ -217,7 +260,7 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
     s_nb[b] = (min((n_tiles + spl - 1) / spl, (1 << 19) - 1) << 12) | (MN_MAX_BATCH - 1 - b);
   }
   __syncthreads();
-  for (int m = tid; m < a.M; m += PREP_THREADS) a.plan.row_splits[m] = s_spl[seq_of_row(s_row0, B, m)];  // for the merge
+  for_rows([&](int m, int b, int, bool) { a.plan.row_splits[m] = s_spl[b]; });  // for the merge
   // records of sequence b, at place `off` of the list
   auto write_records = [&](int b, int off, int first, int step) {
     const int cnt = s_cnt[b], spl = s_spl[b];
@@ -257,19 +300,9 @@ __global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
     rank_by_thread(IntC<1>{});
   } else {
     for (int b = tid >> 6; b < B; b += PREP_THREADS / 64) {
-      const int lane = tid & 63, key = s_nb[b];
-      int off = 0;
-      total = 0;
-      for (int b2 = lane; b2 < B; b2 += 64) {
-        const int c = s_cnt[b2];
-        total += c;
-        off += s_nb[b2] > key ? c : 0;
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        off += __shfl_xor(off, o, 64);
-        total += __shfl_xor(total, o, 64);
-      }
+      const int lane = tid & 63, key = s_nb[b], c = lane < B ? s_cnt[lane] : 0;  // (at most 64 sequences)
+      total = wave_sum_i(c);
+      const int off = wave_sum_i(lane < B && s_nb[lane] > key ? c : 0);
       write_records(b, off, lane, 64);
     }
   }
