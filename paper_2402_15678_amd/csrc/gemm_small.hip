@@ -40,10 +40,11 @@ __device__ __forceinline__ f16x8 norm8(const float* x, const float* gain, float 
   return r.v;
 }
 
-// CT x RT tiles of 16 columns x 16 rows per workgroup, NW waves along k, UF k-steps of 32 in flight per wave.
-template <int CT, int RT, int NW, int UF, int MODE>
+// CT x RT tiles of 16 columns x 16 rows per workgroup (HALF: 8 rows, each twice in the MFMA, whose other half is thrown away), NW waves
+// along k, UF k-steps of 32 in flight per wave.
+template <int CT, int RT, int NW, int UF, int MODE, bool HALF = false>
 __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(SmallGemmArgs a) {
-  constexpr int NT = NW * 64, ROWS = 16 * RT, TILES = CT * RT;
+  constexpr int NT = NW * 64, ROWS = HALF ? 8 : 16 * RT, TILES = CT * RT;
   constexpr bool TWO = NW * TILES > 48;      // the upper half of the waves hands its sums to the lower half first
   constexpr int NA = TWO ? NW / 2 : NW;
   constexpr int LP = 64 / ROWS;              // lanes of a wave that share a row's sums of squares
@@ -69,10 +70,10 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
     for (int u = 0; u < SS; ++u) ss_v[u] = a.ss[(size_t)min(share + u * SHARES, a.ss_tiles - 1) * a.M + m];
   }
   // the residual stream's old values and the next norm's gains (each thread owns one piece of four columns of a row)
-  const int pm = m0 + (tid >> 6) % RT * 16 + l16, pn = (t0 + (tid >> 6) / RT) * 16 + 4 * g;  // tile = ct * RT + rt
+  const int pm = m0 + (tid >> 6) % RT * 16 + (HALF ? l16 & 7 : l16), pn = (t0 + (tid >> 6) / RT) * 16 + 4 * g;  // tile = ct * RT + rt
   f32x4 x_old = {0.f, 0.f, 0.f, 0.f}, gain = x_old;
   float rs_old = 1.f;
-  const bool piece = MODE == SMALL_RESIDUAL && tid < TILES * 64 && pm < a.M && pn < a.N;
+  const bool piece = MODE == SMALL_RESIDUAL && tid < TILES * 64 && pm < a.M && pn < a.N && !(HALF && l16 >= 8);
   if (piece) {
     x_old = *reinterpret_cast<const f32x4*>(a.x + (size_t)pm * a.N + pn);
     gain = *reinterpret_cast<const f32x4*>(a.gain + pn);
@@ -90,7 +91,7 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
   for (int r = 0; r < RT; ++r) {
     const int t = min(m0 / 16 + r, (a.M - 1) / 16), rows = min(16, a.M - 16 * t);
     a_step[r] = 32 * rows;
-    a_tile[r] = A + (size_t)t * 16 * a.K + (g * rows + min(l16, rows - 1)) * 8;
+    a_tile[r] = A + (size_t)t * 16 * a.K + (g * rows + min(HALF ? (m0 & 8) + (l16 & 7) : l16, rows - 1)) * 8;
   }
   bool bad = false;
   float rstd = 0.f, f = 1.f;                 // of row m0 + lane (lanes below ROWS)
@@ -257,16 +258,17 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
   if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
 }
 
-template <int CT, int RT, int NW, int UF, int MODE>
+template <int CT, int RT, int NW, int UF, int MODE, bool HALF = false>
 static void launch_small_u(const SmallGemmArgs& a, hipStream_t st) {
-  const int groups = ((a.N + 15) / 16 + CT - 1) / CT, rgs = (a.M + 16 * RT - 1) / (16 * RT);
-  gemm_small_kernel<CT, RT, NW, UF, MODE><<<(groups + 7) / 8 * 8 * rgs, NW * 64, 0, st>>>(a);
+  constexpr int ROWS = HALF ? 8 : 16 * RT;
+  const int groups = ((a.N + 15) / 16 + CT - 1) / CT, rgs = (a.M + ROWS - 1) / ROWS;
+  gemm_small_kernel<CT, RT, NW, UF, MODE, HALF><<<(groups + 7) / 8 * 8 * rgs, NW * 64, 0, st>>>(a);
 }
 // waves: three k-steps each for K up to 768, six in 16 waves where the residual stream wants whole sums of a long K
-template <int CT, int RT, int MODE>
+template <int CT, int RT, int MODE, bool HALF = false>
 static void launch_small(const SmallGemmArgs& a, hipStream_t st) {
-  if (MODE == SMALL_RESIDUAL && a.K > 8 * 3 * KSTEP) launch_small_u<CT, RT, 16, 6, MODE>(a, st);
-  else launch_small_u<CT, RT, 8, 3, MODE>(a, st);
+  if (MODE == SMALL_RESIDUAL && a.K > 8 * 3 * KSTEP) launch_small_u<CT, RT, 16, 6, MODE, HALF>(a, st);
+  else launch_small_u<CT, RT, 8, 3, MODE, HALF>(a, st);
 }
 
 // Rows up to which a model whose matrices are all small (gemm.hip) takes these kernels.  Every row group reads the weights again
@@ -282,11 +284,13 @@ bool gemm_small_model(int M, int n_qkv, int d_model, int hdim, int w1_rows, int 
 
 // Tiles per workgroup.  95 rows, microseconds: QKV 1 x 3 tiles (columns x rows) 7.0, 1 x 2 6.0, 2 x 3 6.5, 2 x 2 5.7, 2 x 1 6.2;
 // gate||up 2 x 3 9.2, 2 x 2 9.8, 2 x 1 11.6, 4 x 3 9.1 (48 to 80 rows 1 to 5 % of the pass slower); residual 1 x 1 and 1 x 2 alike,
-// 1 x 3 10.8 (spills).  4 waves with six k-steps each are no faster than 8 with three.
+// 1 x 3 10.8 (spills).  From 9 to 32 rows the residual kernels take 8 rows per workgroup: as many weights, half the activations for
+// each of twice the CUs (16 rows, K = 3072: 6.6 -> 6.0 us; whole passes at 16, 24 and 32 rows 465 -> 455, 512 -> 486, 544 -> 512; at 48 no
+// change, at 96 490 -> 523).  QKV at 17 to 32 rows 2 x 2 tiles -> 1 x 1: 1 % of the pass; gate||up 2 x 2 -> 2 x 1 2 % slower.  4 waves with six k-steps each are no faster than 8 with three.
 void launch_gemm_small(const SmallGemmArgs& a, int mode, hipStream_t st) {
   const int tiles = (a.M + 15) / 16;
   if (mode == SMALL_OUT) {
-    if (tiles == 1) launch_small<1, 1, SMALL_OUT>(a, st);
+    if (tiles <= 2) launch_small<1, 1, SMALL_OUT>(a, st);
     else launch_small<2, 2, SMALL_OUT>(a, st);
   } else if (mode == SMALL_SWIGLU) {
     if (tiles == 1) launch_small<2, 1, SMALL_SWIGLU>(a, st);
@@ -294,7 +298,8 @@ void launch_gemm_small(const SmallGemmArgs& a, int mode, hipStream_t st) {
     else if (MN_TUNE("MN_SMALL_RT1", 4) == 4) launch_small<4, 3, SMALL_SWIGLU>(a, st);
     else launch_small<2, 3, SMALL_SWIGLU>(a, st);
   } else {
-    if (tiles == 1) launch_small<1, 1, SMALL_RESIDUAL>(a, st);
+    if (a.M > 8 && tiles <= 2) launch_small<1, 1, SMALL_RESIDUAL, true>(a, st);
+    else if (tiles == 1) launch_small<1, 1, SMALL_RESIDUAL>(a, st);
     else launch_small<1, 2, SMALL_RESIDUAL>(a, st);
   }
 }

@@ -56,9 +56,9 @@ def _check(desc, W, ctx, ks, seed, tol):
 
 
 @pytest.mark.parametrize("desc", [NARROW, WIDE, GROUPED], ids=["d256", "d1024", "d768-gqa"])
-@pytest.mark.parametrize("rows", [1, 15, 16, 17, 33, 48, 95, 113])
+@pytest.mark.parametrize("rows", [1, 8, 9, 15, 16, 17, 25, 32, 33, 48, 95, 113])
 def test_folded_norms_match_oracle(desc, rows):
-    """One tile of rows, its edges, two, three and more, with a last tile that is not full."""
+    """Up to half a tile of rows, a whole one (in halves), its edges, two, three and more, with a last tile that is not full."""
     assert _folded(desc, rows)
     B = -(-rows // 4)
     ks = [3] * (B - 1) + [rows - 4 * (B - 1) - 1]
