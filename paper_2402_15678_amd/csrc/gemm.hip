@@ -839,14 +839,11 @@ static GemmTune tune() { return GemmTune{MN_TUNE("MN_GEMM_SPLIT", 0), MN_TUNE("M
 // rows from which the big-tile kernel takes over (0: above 144)
 static int big_min_m() { return MN_TUNE("MN_GEMM_BIG_MIN_M", 0); }
 
-// Shape of the grid for one projection: waves per workgroup (each wave owns 32 columns; all waves of a
-// workgroup share the activation tile, so more waves mean less L2 -> LDS traffic per weight byte) and
-// k-splits.  Goal: every CU streams (a CU's share of the HBM rate is bounded by what its waves keep in
-// flight), the whole grid is resident at once, and every split runs at least 16 iterations (measured:
-// shorter splits lose more to ramp-up and partial sums than the extra workgroups win).
-struct GemmPlan {
-  int nw, split;
-};
+static bool many_rows(int M) { return M > 144 || (big_min_m() > 0 && M >= big_min_m()); }
+
+// Shape of the grid for one projection of the streaming kernel: waves per workgroup (each wave owns 32 columns; all waves of a
+// workgroup share the activation tile, so more waves mean less L2 -> LDS traffic per weight byte) and k-splits.  Goal: every CU
+// streams (a CU's share of the HBM rate is bounded by what its waves keep in flight) and the whole grid is resident at once.
 
 // Four-wave workgroups in splits of at least 8 iterations would be fewer than 64: a projection of a drafting model.
 static bool small_matrix(int slices, int iters) {
@@ -857,11 +854,11 @@ static bool small_matrix(int slices, int iters) {
 
 bool gemm_small_matrix(int N, int K) { return small_matrix((N + NWG - 1) / NWG * 4, K / KB); }
 
-// Waves per workgroup at 96 rows or fewer, for a matrix of so many 32-column slices cut into `split` k-splits.  Unsplit
+// Waves per workgroup at 144 rows or fewer, for a matrix of so many 32-column slices cut into `split` k-splits.  Unsplit
 // matrices: a CU with w workgroups of NW waves takes about 0.15 + w (0.27 + 0.13 NW) us per iteration (the tile and the
 // barrier are paid per workgroup, the stream per wave), so the count that gives the busiest CU the least is taken.  Measured
 // at 40 rows, NW = 2 .. 8: 20480 x 5120 (640 slices) 48.9 38.5 42.2 48.5 53.7 58.6 63.5 us; 50272 x 5120 (1572 slices) 99.6 103.4
-// 92.6 104.3 117.7 81.5 82.3 us.  Small matrices: see gemm_plan (6144 x 768 at 16 rows, NW = 1 .. 4: 5.5 5.8 6.6 7.4 us).
+// 92.6 104.3 117.7 81.5 82.3 us.  Small matrices: see stream_split (6144 x 768 at 16 rows, NW = 1 .. 4: 5.5 5.8 6.6 7.4 us).
 // Split matrices have their split picked for 4 waves.
 static int few_rows_nw(int M, int slices, int iters, int split) {
   if (small_matrix(slices, iters)) return M <= 32 ? 1 : 2;
@@ -942,12 +939,24 @@ static int big_room_split(int M, int N, int K) {
   return (iters + per - 1) / per;
 }
 
-static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
-  const int forced_nw = MN_TUNE("MN_GEMM_NW", 0);
+// k-splits of the streaming kernel (144 rows or fewer).  The split is picked for 4-wave workgroups, one per CU.  Few rows make an
+// iteration cheap, so a split may be as short as 8 iterations (measured at 40 rows: the 5120 x 5120 matrix gains 30 % from 5 splits
+// over 2, the 20480-column one loses with any split).  Above 96 rows callers of the component entry points are not asked to bring room
+// for more than splits of 16 iterations (`most` false), which is what they were asked for when those rows had a plan of their own.
+// Small matrices (the drafting models: a few hundred KB per projection) would leave most of the chip idle at that rule, and their
+// time is launch and memory latency rather than bandwidth: workgroups of one wave (two above 32 rows, where the tile is worth
+// sharing) and splits as short as one iteration, up to 192 (128) of them.  One pass of a 12-layer, 768-wide model at 16 rows, up to
+// 64 / 96 / 128 / 192 / 256 workgroups: 600 571 574 552 557 us of kernels; at 95 rows, up to 72 / 96 / 128 / 192: 684 681 677 685
+// (four-wave workgroups, up to 96: 620 and 738).
+// The same waves and splits serve 97 to 144 rows, where the plan once filled the CUs with workgroups of 8 waves and splits of at least
+// 16 iterations: steps of the 5120-wide model at 104 rows 622 -> 542 us, at 144 671 -> 604 (two layers; its matrices got 40 to 80
+// workgroups), of the 70B one at 104 479 -> 457, at 144 1594 -> 1583 (four layers; the projections take the same time, but the down
+// projection has half the partial sums and the vocabulary projection none).
+static int stream_split(int M, int N, int K, int forced_split, bool most) {
   const int slices = ((N + NWG - 1) / NWG) * 4;  // 32-column wave slices of the padded matrix
   const int iters = K / KB;
   if (forced_split < 1 && tune().split >= 1) forced_split = tune().split;
-  auto splits_for = [&](int gx, int slots, int min_iters = 16) {
+  auto splits_for = [&](int gx, int slots, int min_iters) {
     int s = forced_split >= 1 ? forced_split : slots / gx;
     if (forced_split < 1 && s > iters / min_iters) s = iters / min_iters;
     if (s > MN_MAX_SPLIT_K) s = MN_MAX_SPLIT_K;
@@ -955,68 +964,22 @@ static GemmPlan gemm_plan(int M, int N, int K, int forced_split) {
     const int per = (iters + s - 1) / s;  // drop splits that would get no iteration
     return (iters + per - 1) / per;
   };
-  GemmPlan best{4, 1};
-  // (tuning builds: the plan of the projection with N output columns by hand)
-  if (MN_TUNE("MN_GEMM_PLAN_N", 0) == N && MN_TUNE("MN_GEMM_PLAN_K", 0) == K && M > 96 && M <= 144)
-    return GemmPlan{MN_TUNE("MN_GEMM_PLAN_NW", 4), MN_TUNE("MN_GEMM_PLAN_SPLIT", 1)};
-  if (M > 144 || (big_min_m() > 0 && M >= big_min_m())) return GemmPlan{8, big_plan(M, N, K, forced_split, big_room_split(M, N, K)).split};
-  if (M <= 96) {
-    // up to six row tiles: the k-split is picked for 4-wave workgroups.  Few rows make an iteration cheap, so a split may be
-    // as short as 8 iterations, and one workgroup per CU is enough (measured at 40 rows: the 5120 x 5120 matrix
-    // gains 30 % from 5 splits over 2, the 20480-column one loses with any split)
-    const int gx = (slices + 3) / 4;
-    best.split = splits_for(gx, tune().target / 2, 8);
-    // small matrices (the drafting models: a few hundred KB per projection) would leave most of the chip idle at that rule,
-    // and their time is launch and memory latency rather than bandwidth: workgroups of one wave (two above 32 rows, where the
-    // tile is worth sharing) and splits as short as one iteration, up to 192 (128) of them.  One pass of the 12-layer, 768-wide
-    // model at 16 rows, up to 64 / 96 / 128 / 192 / 256 workgroups: 600 571 574 552 557 us of kernels; at 95 rows, up to
-    // 72 / 96 / 128 / 192: 684 681 677 685 (four-wave workgroups, up to 96: 620 and 738)
-    if (small_matrix(slices, iters))
-      best.split = M <= 32 ? splits_for(slices, 192, 1) : splits_for((slices + 1) / 2, 128, 1);
-    best.nw = few_rows_nw(M, slices, iters, best.split);
-    return best;
-  }
-  int best_cus = 0, best_waves = 0;
-  for (int nw = 8; nw >= 4; --nw) {
-    if (forced_nw && nw != forced_nw) continue;
-    const int gx = (slices + nw - 1) / nw;
-    const int slots = nw == 4 ? tune().target : tune().target / 2;  // 4 waves: two workgroups per CU
-    const int sp = splits_for(gx, slots);
-    const int wgs = gx * sp;
-    const int cus = wgs < 256 ? wgs : 256;
-    const int waves = (wgs < slots ? wgs : slots) * nw;
-    // fewer waves per workgroup only when that puts clearly more CUs (or waves) to work (measured at 144
-    // rows: 224 -> 256 CUs, 8 -> 7 waves, gains 2 % on the 57344-column matrix since the ring keeps its
-    // registers (nothing before); 160 -> 256 gains 6 % on the 10240-column one)
-    if (best_cus == 0 || cus * 100 >= best_cus * 112 || (cus >= best_cus && waves * 100 >= best_waves * 115)) {
-      best = GemmPlan{nw, sp};
-      best_cus = cus;
-      best_waves = waves;
-    }
-  }
-  // Short splits pay more for ramp-up, tail and partial sums than they win: where the plan above cuts k into
-  // pieces of fewer than 24 iterations, one 4-wave workgroup per CU with fewer, longer splits is faster if it
-  // still covers nine CUs in ten (measured at 144 rows on the 10240 x 8192 matrix: 4 waves x 80 column groups
-  // x 3 splits = 240 workgroups take 49.8 us against 52.5 for 5 x 64 x 4, and write a quarter less partial sums)
-  if (!forced_nw && forced_split < 1 && best.split > 1 && (iters + best.split - 1) / best.split < 24) {
-    const int gx4 = (slices + 3) / 4;
-    const int sp4 = 256 / gx4;
-    if (sp4 >= 1 && sp4 < best.split && gx4 * sp4 * 10 >= 256 * 9) best = GemmPlan{4, sp4};
-  }
-  return best;
+  if (small_matrix(slices, iters) && M <= 96) return M <= 32 ? splits_for(slices, 192, 1) : splits_for((slices + 1) / 2, 128, 1);
+  return splits_for((slices + 3) / 4, tune().target / 2, M <= 96 || most ? 8 : 16);
 }
 
 int gemm_pick_split(int M, int N, int K, int dtype) {
   if (dtype != MN_DT_BF16) return 1;
-  return gemm_plan(M, N, K, 0).split;
+  if (many_rows(M)) return big_plan(M, N, K, 0, big_room_split(M, N, K)).split;
+  return stream_split(M, N, K, 0, false);
 }
 
 // Split of a projection inside a step whose partial sums have `room` bytes (sized by gemm_pick_split, as the largest need of all
-// its projections): above 144 rows the plan may have more splits than the entry points' where they fit.
+// its projections): above 96 rows the plan may have more splits than the entry points' where they fit.
 int gemm_step_split(int M, int N, int K, int dtype, size_t room) {
   const int s = gemm_pick_split(M, N, K, dtype);
-  if (dtype != MN_DT_BF16 || M <= 144) return s;
-  const int more = big_plan(M, N, K, 0, MN_MAX_SPLIT_K).split;
+  if (dtype != MN_DT_BF16) return s;
+  const int more = many_rows(M) ? big_plan(M, N, K, 0, MN_MAX_SPLIT_K).split : stream_split(M, N, K, 0, true);
   return (size_t)more * M * N * 4 <= room ? more : s;
 }
 
@@ -1100,6 +1063,21 @@ static void launch_f32(const GemmArgs& a, hipStream_t st) {
 constexpr int F32_NORM_ROWS = 64;
 bool gemm_f32_folds_norm(int M, int d_model) { return d_model <= F32_NORM_K && M <= MN_TUNE("MN_F32_NORM_ROWS", F32_NORM_ROWS); }
 
+static hipError_t launch_many_rows(const GemmArgs& a, hipStream_t st) {
+  if (!MN_TUNE("MN_GEMM_BIG", 1)) {  // 0 = chunks of the streaming kernel
+    launch_bf16_mt<8, 4>(a, (a.M + 127) / 128, st);
+    return hipSuccess;
+  }
+  switch (gemm_tile_rows(a.M, a.N, a.K, a.split_k) / 32) {
+    case 5: return launch_big<5>(a, st);
+    case 6: return launch_big<6>(a, st);
+    case 7: return launch_big<7>(a, st);
+    case 8: return launch_big<8>(a, st);
+    case 9: return launch_big<9>(a, st);
+    default: return launch_big<10>(a, st);
+  }
+}
+
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.dtype != MN_DT_BF16) {
@@ -1109,35 +1087,16 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t st) {
     return hipSuccess;
   }
   const int tiles = (a.M + 15) / 16;
-  // row tiles per workgroup: everything in one chunk up to 9 tiles (144 rows), else chunks of 8
+  // row tiles per workgroup: all of them up to 9 (144 rows)
   if (tiles <= 1) launch_few_rows<1>(a, st);
   else if (tiles <= 2) launch_few_rows<2>(a, st);
   else if (tiles <= 3) launch_few_rows<3>(a, st);
   else if (tiles <= 4) launch_few_rows<4>(a, st);
   else if (tiles <= 6) launch_few_rows<6>(a, st);
-  else if (tiles <= 9 && !(big_min_m() > 0 && a.M >= big_min_m())) {
-    switch (gemm_plan(a.M, a.N, a.K, a.split_k).nw) {
-      case 8: launch_bf16_mt<9, 8>(a, 1, st); break;
-      case 7: launch_bf16_mt<9, 7>(a, 1, st); break;
-      case 6: launch_bf16_mt<9, 6>(a, 1, st); break;
-      case 5: launch_bf16_mt<9, 5>(a, 1, st); break;
-      default: launch_bf16_mt<9, 4>(a, 1, st); break;
-    }
-  }
-  else {
-    if (!MN_TUNE("MN_GEMM_BIG", 1)) {  // 0 = chunks of the streaming kernel
-      launch_bf16_mt<8, 4>(a, (tiles + 7) / 8, st);
-    } else {
-      switch (gemm_tile_rows(a.M, a.N, a.K, a.split_k) / 32) {
-        case 5: return launch_big<5>(a, st);
-        case 6: return launch_big<6>(a, st);
-        case 7: return launch_big<7>(a, st);
-        case 8: return launch_big<8>(a, st);
-        case 9: return launch_big<9>(a, st);
-        default: return launch_big<10>(a, st);
-      }
-    }
-  }
+  else if (many_rows(a.M)) return launch_many_rows(a, st);
+  else if (tiles <= 7) launch_few_rows<7>(a, st);
+  else if (tiles <= 8) launch_few_rows<8>(a, st);
+  else launch_few_rows<9>(a, st);
   return hipSuccess;
 }
 
