@@ -176,8 +176,8 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
     run_m = new_m;
     acc *= alpha;
     {
-      auto add = [&](const Quad& v, int q) {                 // (slots past the last key may hold anything)
-        const f32x4 p4 = *reinterpret_cast<const f32x4*>(s_p + 4 * q);
+      auto add = [&](const Quad& v, int q) {                 // (slots past the last key, and repeats of the last four, may hold anything)
+        const f32x4 p4 = *reinterpret_cast<const f32x4*>(s_p + 4 * min(q, GEN_THREADS / 4 - 1));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const bool in = 4 * q + e < cnt_old;
@@ -186,7 +186,7 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
       };
       if (quads > 0) {
 #pragma unroll
-        for (int u = 0; u < GEN_VPRE; ++u) add(vpre[u], min(kg + u * ng, GEN_THREADS / 4 - 1));
+        for (int u = 0; u < GEN_VPRE; ++u) add(vpre[u], kg + u * ng);
       }
 #pragma unroll 1
       for (int q0 = kg + GEN_VPRE * ng; q0 < quads; q0 += 4 * ng) {
@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
         for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const Quad*>(Vp + (s_at[4 * min(q0 + u * ng, quads - 1)] + (uint32_t)(e_own * bs)));
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int u = 0; u < 4; ++u) add(v[u], min(q0 + u * ng, GEN_THREADS / 4 - 1));
+        for (int u = 0; u < 4; ++u) add(v[u], q0 + u * ng);
       }
       if ((bs & 3) != 0) {
 #pragma unroll 8

@@ -69,6 +69,14 @@ def test_appended_rows(k, block_size):
     _check(_opt(256, 4, 64, 256), [1100, 3], [k, 1], block_size)
 
 
+@pytest.mark.parametrize("hd", [8, 16])
+@pytest.mark.parametrize("k", [4, 20])
+def test_narrow_heads_long_contexts(hd, k):
+    """Chunks of 256 and 1024 keys whose groups of four are fewer than the threads' pieces of them: none counts twice."""
+    _check(_opt(128, 128 // hd, hd, 64), [252, 300, 1], [k, 0, 1])
+    _check(_opt(64, 64 // hd, hd, 64), [1100, 3], [k, 1])
+
+
 def test_rotary_and_head_groups():
     desc = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_F32, 2, 256, 8, 2, 32, 256, 1001, 600)
     _check(desc, [33, 0, 300], [4, 16, 1])
