@@ -7,12 +7,15 @@
 //    No partial sums go to memory.
 //  * Because the sums are whole, the output projection and the second FFN projection update the residual stream themselves, and
 //    the norm behind them needs no launch: RMSNorm is a factor per row, which the next projection applies to its sums.  The row
-//    goes out as fp16(x * gain * s), s a power of two near 1 / 64 of the row's last 1 / rms, with the sum of squares of every
+//    goes out as fp16(x * gain * s), s a power of two near 8 times the row's last 1 / rms, with the sum of squares of every
 //    16 columns; the next projection adds those up while its loads are on their way.
-//  * s is a guess, so the row's numbers are checked: a producer marks a tile (sign bit of its sum of squares) that left +-127,
-//    and a consumer counts a row whose rms came out below 2^-9 / s as marked.  A workgroup with a marked row normalises the fp32
-//    rows itself, exactly as norm_kernel does.  Unmarked rows lose nothing: elements are at most 127 * 2^9 after the factor (in
-//    fp16 range, so norm_kernel would not have saturated either), and fp16's smallest step is at most 2^-15 of the row's rms.
+//  * s is a guess, so the row's numbers are checked: a producer marks a tile (sign bit of its sum of squares) that left the fp16
+//    range, and a consumer counts a row whose 1 / rms came out above s as marked.  A workgroup with a marked row normalises the fp32
+//    rows itself, exactly as norm_kernel does.  Unmarked rows lose nothing against norm_kernel's fp16(x * gain / rms), whatever the
+//    gains and however the row's energy is spread: the factor behind the sums is at most 1, so what is stored is no smaller than
+//    what norm_kernel stores (no more of it is subnormal), and norm_kernel would not have saturated either.  (With s 2^9 times
+//    smaller, gains of 2^-12 put the stored rows among the subnormals: the last layer's keys and values of a 256-wide model of two
+//    layers were off by 6e-3, now by 4e-4 as with gains of 1.)
 // Activations travel in operand order (common.h): with row-major ones a wave's fragment is 16 pieces of 64 bytes whose stride of
 // K * 2 bytes puts them on few L2 channels (down projection of 95 rows 10.6 -> 7.5 us).
 // Bound by launch and round trips: at 16 rows a launch takes 4.3 (QKV), 4.8 (output), 5.2 (gate||up) and 6.6 us (down, which
@@ -26,8 +29,8 @@
 namespace mn {
 
 constexpr int SMALL_MAX_D = 1024;             // widest model
-constexpr float ROW_MARK = 127.f;             // largest |x * gain * s|
-constexpr float ROW_FACTOR_MAX = 512.f;       // largest rstd / s
+constexpr float ROW_MARK = 65504.f;           // largest |x * s * gain|
+constexpr float ROW_FACTOR_MAX = 1.f;         // largest rstd / s
 
 __device__ __forceinline__ f16x8 norm8(const float* x, const float* gain, float rstd, bool& bad) {
   const f32x4 a = *reinterpret_cast<const f32x4*>(x), b = *reinterpret_cast<const f32x4*>(x + 4);
@@ -225,9 +228,10 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
   } else {
     if (tid < TILES * 64) {                  // (whole waves)
       f32x4 v = x_old + total(tid >> 6, lane);
-      // 2^-6 times the power of two at or below the row's last 1 / rms (positive and finite: eps > 0 or a row of zeros)
-      const float s = __uint_as_float(min(max(__float_as_uint(rs_old) & 0x7f800000u, 0x08000000u), 0x77000000u) - 0x03000000u);
-      f32x4 h = v * gain * s;
+      // 2^3 times the power of two at or below the row's last 1 / rms (positive and finite: eps > 0 or a row of zeros): the row
+      // may shrink to a quarter of its rms before it is marked, or grow until an element is 8188 times the rms before
+      const float s = __uint_as_float(min(max(__float_as_uint(rs_old) & 0x7f800000u, 0x08000000u), 0x75000000u) + 0x01800000u);
+      f32x4 h = v * s * gain;
       bool over = false;
       float q = 0.f;
 #pragma unroll

@@ -46,13 +46,18 @@ def _check(desc, W, ctx, ks, seed, tol):
         got.append(ses.logits.cpu().numpy().copy())
     assert np.array_equal(got[0], got[1])
     assert np.abs(got[0] - want).max() < tol, np.abs(got[0] - want).max()
+    off = size = 0.0                         # of the rows that the last layer appended
     for l in range(desc.n_layers):
         kp, vp = kvd.download(l)
         img = synth.PagedKV(16, kp.shape[0], kvh.block_tables.shape[1], kvh.block_tables, None, {l: kp}, {l: vp})
         for b in range(B):
             K, V = synth.gather_sequence_kv(img, l, b, int(ctx[b] + ks[b] + 1))
             assert max(np.abs(K - caches[b].K[l]).max(), np.abs(V - caches[b].V[l]).max()) < tol
-    return got[0]
+            if l == desc.n_layers - 1:
+                for have, ref in ((K, caches[b].K[l]), (V, caches[b].V[l])):
+                    off += float(((have - ref)[ctx[b]:] ** 2).sum())
+                    size += float((ref[ctx[b]:] ** 2).sum())
+    return got[0], (off / size) ** 0.5
 
 
 @pytest.mark.parametrize("desc", [NARROW, WIDE, GROUPED], ids=["d256", "d1024", "d768-gqa"])
@@ -93,3 +98,27 @@ def test_rows_that_grow_or_shrink_between_two_norms():
     L["wqkv"][256:384] = np.eye(128, dtype=np.float32)             # values = the normalised row, and no other key to see
     L["wo"] = -np.eye(128, dtype=np.float32) * np.float32(2.0 ** -6 * (1 - 2.0 ** -7))
     _check(desc, W, [0] * 5, [0] * 5, 96, util.TOL[synth.DT_BF16])
+
+
+@pytest.mark.parametrize("rows", [5, 12, 33])
+@pytest.mark.parametrize("gain,channel", [(2.0 ** -12, 1.0), (2.0 ** -10, 64.0)], ids=["small-gains", "dominant-channel"])
+def test_small_normalised_rows_keep_their_bits(gain, channel, rows):
+    """Norms whose output is small everywhere (gains of 2^-12, the matrices behind them 2^12 times theirs) or in all columns but one
+    (a channel 64 times the others', as trained models have them, with its gain taken back): the last layer's new keys and values,
+    which are the projection of a folded norm, are off by what rounding to fp16 gives.  That is 2^-12.2 of a value in the mean
+    (a step of 2^-11 to 2^-10 of it, over sqrt(12)) at each of seven places (embedding's norm, values, attention and its output, FFN
+    norm, activation, last norm, pages), sqrt(7) 2^-12.2 together: below 2^-10."""
+    desc = NARROW
+    W = synth.make_weights(desc, 97)
+    W["tok_emb"] = W["tok_emb"].copy()
+    W["tok_emb"][:, 7] *= channel
+    for L in W["layers"]:
+        for norm, matrix in (("ln1_g", "wqkv"), ("ln2_g", "w1")):
+            L[norm] = L[norm] * np.float32(gain)
+            L[norm][7] /= np.float32(channel)
+            L[matrix] = L[matrix] * np.float32(1.0 / gain)
+    B = -(-rows // 4)
+    ks = [3] * (B - 1) + [rows - 4 * (B - 1) - 1]
+    assert _folded(desc, rows)
+    rel = _check(desc, W, [(37 * b + 5) % 90 for b in range(B)], ks, 98, util.TOL[desc.dtype])[1]
+    assert rel < 2.0 ** -10, rel
