@@ -10,8 +10,8 @@
 //    goes out as fp16(x * gain * s), s a power of two near 8 times the row's last 1 / rms, with the sum of squares of every
 //    16 columns; the next projection adds those up while its loads are on their way.
 //  * s is a guess, so the row's numbers are checked: a producer marks a tile (sign bit of its sum of squares) that left the fp16
-//    range, and a consumer counts a row whose 1 / rms came out above s as marked.  A workgroup with a marked row normalises the fp32
-//    rows itself, exactly as norm_kernel does.  Unmarked rows lose nothing against norm_kernel's fp16(x * gain / rms), whatever the
+//    range, and a consumer counts a row whose 1 / rms came out above s as marked.  A workgroup with marked rows does its sums again and
+//    normalises those of them from fp32, exactly as norm_kernel does; a row's result does not depend on its neighbours' numbers.  Unmarked rows lose nothing against norm_kernel's fp16(x * gain / rms), whatever the
 //    gains and however the row's energy is spread: the factor behind the sums is at most 1, so what is stored is no smaller than
 //    what norm_kernel stores (no more of it is subnormal), and norm_kernel would not have saturated either.  (With s 2^9 times
 //    smaller, gains of 2^-12 put the stored rows among the subnormals: the last layer's keys and values of a 256-wide model of two
@@ -98,6 +98,7 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
   }
   bool bad = false;
   float rstd = 0.f, f = 1.f;                 // of row m0 + lane (lanes below ROWS)
+  bool renorm = false;
   auto sums = [&](auto slow_c) {
     constexpr bool SLOW = decltype(slow_c)::value;
     constexpr int U = SLOW ? 1 : UF;
@@ -120,10 +121,12 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
         }
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
-          if constexpr (SLOW)
-            af[u][r] = norm8(a.x + (size_t)min(m0 + r * 16 + l16, a.M - 1) * a.K + k * KSTEP + g * 8, a.gain + k * KSTEP + g * 8, __shfl(rstd, r * 16 + l16, 64), bad);
-          else
-            af[u][r] = *reinterpret_cast<const f16x8*>(a_tile[r] + (size_t)k * a_step[r]);
+          af[u][r] = *reinterpret_cast<const f16x8*>(a_tile[r] + (size_t)k * a_step[r]);
+          if constexpr (SLOW) {              // (the rows beside a marked one keep their operands and with them every bit)
+            const float rs = __shfl(rstd, r * 16 + l16, 64);
+            if (__shfl((int)renorm, r * 16 + l16, 64))
+              af[u][r] = norm8(a.x + (size_t)min(m0 + r * 16 + l16, a.M - 1) * a.K + k * KSTEP + g * 8, a.gain + k * KSTEP + g * 8, rs, bad);
+          }
         }
       }
       asm volatile("" ::: "memory");         // (every load goes out before the first product)
@@ -190,11 +193,12 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(S
     rstd = 1.f / sqrtf(t * a.inv_d + a.eps);
     f = rstd * inv_sc;
     if (cg == 0 && tid < ROWS && m0 + tid < a.M) a.rstd[m0 + tid] = rstd;
-    if (__any((int)(mark >> 31) || !(f <= ROW_FACTOR_MAX))) {  // (the same in every wave)
+    renorm = mark >> 31 || !(f <= ROW_FACTOR_MAX);
+    if (__any((int)renorm)) {                // (the same in every wave)
       __syncthreads();
       sums(BoolC<true>{});
       __syncthreads();
-      f = 1.f;
+      if (renorm) f = 1.f;
     }
   }
 

@@ -78,6 +78,19 @@ def test_most_rows_of_folded_norms(rows, folded):
     _check(NARROW, synth.make_weights(NARROW, 91), [b % 50 for b in range(len(ks))], ks, 93, util.TOL[synth.DT_BF16])
 
 
+@pytest.mark.parametrize("rows", [25, 33, 48, 113])
+def test_rows_of_every_tiling_that_grow(rows):
+    """All rows outgrow their scale in front of every projection that folds a norm (see below), in row groups of two and three tiles."""
+    W = synth.make_weights(NARROW, 91)
+    W["tok_emb"] = W["tok_emb"] * 2.0 ** -10
+    for L in W["layers"]:
+        L["wo"] = L["wo"] * 2.0 ** 12
+        L["w2"] = L["w2"] * 2.0 ** 13
+    assert _folded(NARROW, rows)
+    B = -(-rows // 4)
+    _check(NARROW, W, [(37 * b + 5) % 90 for b in range(B)], [3] * (B - 1) + [rows - 4 * (B - 1) - 1], 94, util.TOL[synth.DT_BF16])
+
+
 def test_rows_that_grow_or_shrink_between_two_norms():
     """The scale that a row is stored with comes from its norm before: rows that outgrow it (projections 2^12 and 2^13
     times their size on embeddings 2^-10 of theirs) or all but vanish (an output projection that takes the row back to 2^-7 of itself) are
@@ -122,3 +135,50 @@ def test_small_normalised_rows_keep_their_bits(gain, channel, rows):
     assert _folded(desc, rows)
     rel = _check(desc, W, [(37 * b + 5) % 90 for b in range(B)], ks, 98, util.TOL[desc.dtype])[1]
     assert rel < 2.0 ** -10, rel
+
+
+def _logits(desc, W, ctx, ks, last, voted):
+    from paper_2402_15678_amd import harness
+    ctx, ks = np.asarray(ctx, np.int32), np.asarray(ks, np.int32)
+    B, k_max = len(ctx), int(ks.max())
+    model = harness.DeviceModel.from_host(desc, W)
+    kvh = synth.make_paged_kv(desc, ctx, ks, 99)
+    kvd = harness.DeviceKV.from_host(desc, kvh)
+    dev = lambda a: torch.tensor(np.asarray(a, np.int32), device="cuda:0")
+    ses = harness.VerifySession(model, kvd, B, k_max, 1, int((ctx + ks + 1).max()), max_rows=int((ks + 1).sum()), want_logits=True)
+    t_last, t_k, t_voted = dev(last), dev(ks), dev(voted)
+    ses.forward(t_last, t_k, ks.tolist(), voted=t_voted)
+    torch.cuda.synchronize()
+    assert ses.dev_status.item() == 0
+    toks = [[int(last[b])] + voted[b, :ks[b]].tolist() for b in range(B)]
+    want = np.concatenate(orc.decoder_step(desc, util.weights_f64(W), toks, util.oracle_caches(desc, kvh)))
+    got = ses.logits.cpu().numpy()
+    assert np.abs(got - want).max() < util.TOL[desc.dtype], np.abs(got - want).max()
+    return got
+
+
+@pytest.mark.parametrize("rows", [5, 12, 25, 33, 48, 113])
+@pytest.mark.parametrize("grown_by", ["attention", "ffn"])
+def test_marked_rows_leave_their_neighbours_alone(grown_by, rows):
+    """Sequences 1 and 6 (where there is one) take tokens whose embeddings are 2^-18 of the others', so that their rows outgrow the
+    scale they were stored with (in front of gate||up or of the next QKV) while their neighbours' do not: every logit is right, and
+    the neighbours' are bit for bit those of the batch in which these sequences take ordinary tokens."""
+    desc = dataclasses.replace(NARROW, norm_eps=1e-16)
+    assert _folded(desc, rows)
+    W = synth.make_weights(desc, 91)
+    W["tok_emb"] = W["tok_emb"].copy()
+    W["tok_emb"][400:] *= np.float32(2.0 ** -18)
+    if grown_by == "ffn":
+        W["layers"][0]["wo"] = np.zeros_like(W["layers"][0]["wo"])
+    B = -(-rows // 4)
+    ks = [3] * (B - 1) + [rows - 4 * (B - 1) - 1]
+    ctx = [(37 * b + 5) % 90 for b in range(B)]
+    g = synth.stream(99, 2)
+    last, voted = g.integers(0, 400, size=B), g.integers(0, 400, size=(B, 3))
+    plain = _logits(desc, W, ctx, ks, last, voted)
+    small = [b for b in (1, 6) if b < B]
+    last[small] = g.integers(400, 500, size=len(small))
+    voted[small] = g.integers(400, 500, size=(len(small), 3))
+    mixed = _logits(desc, W, ctx, ks, last, voted)
+    other = np.repeat([b not in small for b in range(B)], np.asarray(ks) + 1)
+    assert np.array_equal(mixed[other], plain[other])
