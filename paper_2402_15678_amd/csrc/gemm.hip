@@ -739,7 +739,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
 // normalises row w of the 8 (norm_kernel's arithmetic), while its column's weights are on their way.  Every workgroup of a row group
 // does so, which costs less than the launch it saves while there are few rows: the 256-wide model's step, norms as launches and
 // folded, 5 rows 93 and 80 us, 32 rows 98 and 86, 64 rows 109 and 100, prompts of 128 tokens 129 and 128, of 256 188 and 195.
-constexpr int F32_NORM_K = F32_TRIP * 256;   // widest row: one trip of a wave
+// Rows of one or two pieces per lane: with the 80 registers of four pieces and their 32 KB of LDS too few workgroups are in flight,
+// and the norm is done again for every eight columns.  One layer with a vocabulary of 50272, norms as launches and folded: 512 wide
+// 5 rows 62 and 61 us, 64 rows 252 and 238 (one row 55 and 59); 768 wide 97 and 148, 522 and 871; 1024 wide 100 and 160, 545 and 954;
+// with matrices of 3072 columns at most 768 wide 40 and 40, 71 and 85.
+constexpr int F32_NORM_K = 512;              // widest row
 template <int F32_TRIP>
 __global__ void __launch_bounds__(512) gemm_f32_norm_kernel(NormArgs r, float* __restrict__ x_new, const float* __restrict__ W, float* __restrict__ out,
                                                             const float* __restrict__ bias, int M, int N, int relu) {
@@ -1056,8 +1060,13 @@ static void launch_f32(const GemmArgs& a, hipStream_t st) {
   const float* W = reinterpret_cast<const float*>(a.w);
   float* out = a.relu_act ? reinterpret_cast<float*>(a.relu_act) : a.out;
   const int relu = a.relu_act != nullptr;
-  if (a.norm) gemm_f32_norm_kernel<TRIP><<<dim3((a.N + 7) / 8, (a.M + 7) / 8), 512, 0, st>>>(*a.norm, a.x_new, W, out, a.bias, a.M, a.N, relu);
-  else gemm_f32_kernel<TRIP><<<dim3((a.N + 3) / 4, (a.M + 7) / 8), 256, 0, st>>>(reinterpret_cast<const float*>(a.a), W, out, a.bias, a.M, a.N, a.K, relu);
+  if constexpr (TRIP * 256 <= F32_NORM_K) {
+    if (a.norm) {
+      gemm_f32_norm_kernel<TRIP><<<dim3((a.N + 7) / 8, (a.M + 7) / 8), 512, 0, st>>>(*a.norm, a.x_new, W, out, a.bias, a.M, a.N, relu);
+      return;
+    }
+  }
+  gemm_f32_kernel<TRIP><<<dim3((a.N + 3) / 4, (a.M + 7) / 8), 256, 0, st>>>(reinterpret_cast<const float*>(a.a), W, out, a.bias, a.M, a.N, a.K, relu);
 }
 
 constexpr int F32_NORM_ROWS = 64;

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 
 def _check(desc, ctx, ks, block_size=16, seed=71):
-    from paper_2402_15678_amd import harness
+    from paper_2402_15678_amd import binding, harness
     ctx, ks = np.asarray(ctx, np.int32), np.asarray(ks, np.int32)
     B, k_max = len(ctx), max(1, int(ks.max()))
     W = synth.make_weights(desc, seed)
@@ -28,8 +28,10 @@ def _check(desc, ctx, ks, block_size=16, seed=71):
     caches = util.oracle_caches(desc, kvh)
     toks = [[int(last[b])] + voted[b, :ks[b]].tolist() for b in range(B)]
     want = np.concatenate(orc.decoder_step(desc, W, toks, caches))
+    binding.mn_profile_enable(model.ctx, True)
     ses.forward(t_last, t_k, ks.tolist(), voted=t_voted)
     torch.cuda.synchronize()
+    launches = {k: n for k, (_, n) in binding.mn_profile_collect(model.ctx).items()}
     assert ses.dev_status.item() == 0
     tol = util.TOL[synth.DT_F32]
     assert np.abs(ses.logits.cpu().numpy() - want).max() < tol
@@ -41,23 +43,24 @@ def _check(desc, ctx, ks, block_size=16, seed=71):
         for b in range(B):
             K, V = synth.gather_sequence_kv(img, l, b, int(ctx[b] + ks[b] + 1))
             assert max(np.abs(K - caches[b].K[l]).max(), np.abs(V - caches[b].V[l]).max()) < tol
+    return launches
 
 
 def _opt(d, heads, hd, ffn):
-    return synth.ModelDesc(synth.ARCH_OPT, synth.DT_F32, 2, d, heads, heads, hd, ffn, 1001, 1300)
+    return synth.ModelDesc(synth.ARCH_OPT, synth.DT_F32, 2, d, heads, heads, hd, ffn, max(1001, 3 * d + 1), 1300)  # (the QKV sums lie where the scores will)
 
 
-@pytest.mark.parametrize("d,heads,hd,ffn", [(64, 8, 8, 64), (256, 4, 64, 320), (320, 5, 64, 576), (512, 4, 128, 1024), (1024, 4, 256, 1088), (1088, 17, 64, 256)])
+@pytest.mark.parametrize("d,heads,hd,ffn", [(64, 8, 8, 64), (256, 4, 64, 320), (320, 5, 64, 576), (512, 4, 128, 1024), (576, 9, 64, 320), (1024, 4, 256, 1088), (1088, 17, 64, 256)])
 def test_widths(d, heads, hd, ffn):
-    """One, two and four pieces per row, rows that are no whole number of them, 1088 (norms as launches again)."""
-    _check(_opt(d, heads, hd, ffn), [40, 0, 3], [4, 1, 7])
+    """One, two and four pieces per row, rows that are no whole number of them; norms are launches beyond two pieces."""
+    assert _check(_opt(d, heads, hd, ffn), [40, 0, 3], [4, 1, 7])["norm"] == (0 if d <= 512 else 5)
 
 
 @pytest.mark.parametrize("rows", [1, 8, 9, 64, 65])
 def test_rows(rows):
     """Row groups of 8, the most rows of a folded norm and one more."""
     ks = [7] * (rows // 8) + ([rows % 8 - 1] if rows % 8 else [])
-    _check(_opt(256, 4, 64, 256), [11 * b % 70 for b in range(len(ks))], ks)
+    assert _check(_opt(256, 4, 64, 256), [11 * b % 70 for b in range(len(ks))], ks)["norm"] == (0 if rows <= 64 else 5)
 
 
 @pytest.mark.parametrize("k", [15, 16, 17])
