@@ -1009,9 +1009,9 @@ static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
 
 template <int MT>
 static void launch_few_rows(const GemmArgs& a, hipStream_t st) {
+  constexpr int SMALL_NW = MT <= 2 ? 1 : 2;  // (small matrices: 32 rows or fewer, or more)
   switch (few_rows_nw(a.M, ((a.N + NWG - 1) / NWG) * 4, a.K / KB, a.split_k)) {
-    case 1: launch_bf16_mt<MT, 1>(a, 1, st); break;
-    case 2: launch_bf16_mt<MT, 2>(a, 1, st); break;
+    case SMALL_NW: launch_bf16_mt<MT, SMALL_NW>(a, 1, st); break;
     case 3: launch_bf16_mt<MT, 3>(a, 1, st); break;
     case 7: launch_bf16_mt<MT, 7>(a, 1, st); break;
     case 8: launch_bf16_mt<MT, 8>(a, 1, st); break;

@@ -275,8 +275,13 @@ static void launch_small_u(const SmallGemmArgs& a, hipStream_t st) {
 // waves: three k-steps each for K up to 768, six in 16 waves where the residual stream wants whole sums of a long K
 template <int CT, int RT, int MODE, bool HALF = false>
 static void launch_small(const SmallGemmArgs& a, hipStream_t st) {
-  if (MODE == SMALL_RESIDUAL && a.K > 8 * 3 * KSTEP) launch_small_u<CT, RT, 16, 6, MODE, HALF>(a, st);
-  else launch_small_u<CT, RT, 8, 3, MODE, HALF>(a, st);
+  if constexpr (MODE == SMALL_RESIDUAL) {
+    if (a.K > 8 * 3 * KSTEP) {
+      launch_small_u<CT, RT, 16, 6, MODE, HALF>(a, st);
+      return;
+    }
+  }
+  launch_small_u<CT, RT, 8, 3, MODE, HALF>(a, st);
 }
 
 // Rows up to which a model whose matrices are all small (gemm.hip) takes these kernels.  Every row group reads the weights again
