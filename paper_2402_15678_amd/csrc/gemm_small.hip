@@ -272,16 +272,20 @@ static void launch_small_u(const SmallGemmArgs& a, hipStream_t st) {
   const int groups = ((a.N + 15) / 16 + CT - 1) / CT, rgs = (a.M + ROWS - 1) / ROWS;
   gemm_small_kernel<CT, RT, NW, UF, MODE, HALF><<<(groups + 7) / 8 * 8 * rgs, NW * 64, 0, st>>>(a);
 }
-// waves: three k-steps each for K up to 768, six in 16 waves where the residual stream wants whole sums of a long K
+// Waves and k-steps in flight, so that every wave asks for its whole k range at once: eight waves of three k-steps for K up to 768, of four
+// beyond; where the residual stream wants whole sums of a long K, 16 waves of six up to 3072 and of eight beyond.  With three and six
+// only, models wider than 768 made two round trips of every launch: six layers, 1024 wide, FFN 3584, weights in the caches and not, 1 row
+// 191 -> 179 us and 240 -> 229, 16 rows 196 -> 185 and 245 -> 237, 64 rows 238 -> 230 and 299 -> 294; FFN 3968 1 row 199 -> 186 and 252 -> 237.
 template <int CT, int RT, int MODE, bool HALF = false>
 static void launch_small(const SmallGemmArgs& a, hipStream_t st) {
   if constexpr (MODE == SMALL_RESIDUAL) {
-    if (a.K > 8 * 3 * KSTEP) {
-      launch_small_u<CT, RT, 16, 6, MODE, HALF>(a, st);
-      return;
-    }
+    if (a.K <= 8 * 3 * KSTEP) launch_small_u<CT, RT, 8, 3, MODE, HALF>(a, st);
+    else if (a.K <= 16 * 6 * KSTEP) launch_small_u<CT, RT, 16, 6, MODE, HALF>(a, st);
+    else launch_small_u<CT, RT, 16, 8, MODE, HALF>(a, st);
+  } else {
+    if (a.K <= 8 * 3 * KSTEP) launch_small_u<CT, RT, 8, 3, MODE, HALF>(a, st);
+    else launch_small_u<CT, RT, 8, 4, MODE, HALF>(a, st);
   }
-  launch_small_u<CT, RT, 8, 3, MODE, HALF>(a, st);
 }
 
 // Rows up to which a model whose matrices are all small (gemm.hip) takes these kernels.  Every row group reads the weights again

@@ -13,7 +13,8 @@ from tests import util
 pytestmark = pytest.mark.gpu
 
 NARROW = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 256, 4, 4, 64, 512, 500, 512)
-WIDE = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 1024, 16, 8, 64, 3584, 500, 512)     # longest K and most norm columns
+WIDE = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 1024, 16, 8, 64, 3584, 500, 512)     # most norm columns
+LONG = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 896, 14, 14, 64, 3968, 500, 512)      # k ranges that leave a wave short, or none
 GROUPED = synth.ModelDesc(synth.ARCH_LLAMA, synth.DT_BF16, 2, 768, 6, 2, 128, 896, 500, 512)
 
 
@@ -60,7 +61,7 @@ def _check(desc, W, ctx, ks, seed, tol):
     return got[0], (off / size) ** 0.5
 
 
-@pytest.mark.parametrize("desc", [NARROW, WIDE, GROUPED], ids=["d256", "d1024", "d768-gqa"])
+@pytest.mark.parametrize("desc", [NARROW, WIDE, LONG, GROUPED], ids=["d256", "d1024", "d896", "d768-gqa"])
 @pytest.mark.parametrize("rows", [1, 8, 9, 15, 16, 17, 25, 32, 33, 48, 95, 113])
 def test_folded_norms_match_oracle(desc, rows):
     """Up to half a tile of rows, a whole one (in halves), its edges, two, three and more, with a last tile that is not full."""
