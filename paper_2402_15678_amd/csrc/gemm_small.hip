@@ -300,8 +300,9 @@ bool gemm_small_model(int M, int n_qkv, int d_model, int hdim, int w1_rows, int 
 }
 
 // Tiles per workgroup.  95 rows, microseconds: QKV 1 x 3 tiles (columns x rows) 7.0, 1 x 2 6.0, 2 x 3 6.5, 2 x 2 5.7, 2 x 1 6.2;
-// gate||up 2 x 3 9.2, 2 x 2 9.8, 2 x 1 11.6, 4 x 3 9.1 (48 to 80 rows 1 to 5 % of the pass slower); residual 1 x 1 and 1 x 2 alike,
-// 1 x 3 10.8 (spills).  From 9 to 32 rows the residual kernels take 8 rows per workgroup: as many weights, half the activations for
+// gate||up 2 x 3 9.2, 2 x 2 9.8, 2 x 1 11.6, 4 x 3 9.1; residual 1 x 1 and 1 x 2 alike, 1 x 3 10.8 (spills).  At 33 to 48 rows, one
+// row group of three tiles, 4 x 3 would leave gate||up to half as many CUs as 2 x 3: passes of six layers, weights in the caches and not, 48
+// rows, 768 wide 191 -> 184 us and 242 -> 233, 1024 wide 223 -> 217 and 285 -> 275; at 64 rows 1024 wide 2 x 3 is slower, 237 and 230.  From 9 to 32 rows the residual kernels take 8 rows per workgroup: as many weights, half the activations for
 // each of twice the CUs (16 rows, K = 3072: 6.6 -> 6.0 us; whole passes at 16, 24 and 32 rows 465 -> 455, 512 -> 486, 544 -> 512; at 48 no
 // change, at 96 490 -> 523).  QKV at 17 to 32 rows 2 x 2 tiles -> 1 x 1: 1 % of the pass; gate||up 2 x 2 -> 2 x 1 2 % slower.  4 waves with six k-steps each are no faster than 8 with three.
 void launch_gemm_small(const SmallGemmArgs& a, int mode, hipStream_t st) {
@@ -312,8 +313,8 @@ void launch_gemm_small(const SmallGemmArgs& a, int mode, hipStream_t st) {
   } else if (mode == SMALL_SWIGLU) {
     if (tiles == 1) launch_small<2, 1, SMALL_SWIGLU>(a, st);
     else if (tiles == 2) launch_small<2, 2, SMALL_SWIGLU>(a, st);
-    else if (MN_TUNE("MN_SMALL_RT1", 4) == 4) launch_small<4, 3, SMALL_SWIGLU>(a, st);
-    else launch_small<2, 3, SMALL_SWIGLU>(a, st);
+    else if (tiles == 3) launch_small<2, 3, SMALL_SWIGLU>(a, st);
+    else launch_small<4, 3, SMALL_SWIGLU>(a, st);
   } else {
     if (a.M > 8 && tiles <= 2) launch_small<1, 1, SMALL_RESIDUAL, true>(a, st);
     else if (tiles == 1) launch_small<1, 1, SMALL_RESIDUAL>(a, st);
