@@ -863,10 +863,18 @@ bool gemm_small_matrix(int N, int K) { return small_matrix((N + NWG - 1) / NWG *
 // barrier are paid per workgroup, the stream per wave), so the count that gives the busiest CU the least is taken.  Measured
 // at 40 rows, NW = 2 .. 8: 20480 x 5120 (640 slices) 48.9 38.5 42.2 48.5 53.7 58.6 63.5 us; 50272 x 5120 (1572 slices) 99.6 103.4
 // 92.6 104.3 117.7 81.5 82.3 us.  Small matrices: see stream_split (6144 x 768 at 16 rows, NW = 1 .. 4: 5.5 5.8 6.6 7.4 us).
-// Split matrices have their split picked for 4 waves.
+// Split matrices have their split picked for 4 waves (small ones for 2) and no more workgroups than CUs.  A split that the caller gives may
+// make more: above 96 rows, where the tile is dear, as many waves then as leave a workgroup per CU, eight if none do (97 and 144 rows, with four
+// waves and by this rule: 20480 x 5120 in 2 splits 61.3 69.6 us, 50.5 53.3; 10240 x 8192 in 4 52.1 57.9, 43.6 47.2; 8192 x 28672 in 8
+// 96.6 109, 88.4 95.1; 5120 x 1024 in 8, with two, 20.8 25.9, 18.7 23.1).
 static int few_rows_nw(int M, int slices, int iters, int split) {
-  if (small_matrix(slices, iters)) return M <= 32 ? 1 : 2;
-  if (split > 1) return 4;
+  const bool small = small_matrix(slices, iters);
+  if (small && (M <= 96 || split == 1)) return M <= 32 ? 1 : 2;
+  if (split > 1) {
+    int nw = small ? 2 : 4;
+    while (M > 96 && nw < 8 && (slices + nw - 1) / nw * split > 256) nw += nw == 2 ? 2 : 1;
+    return nw;
+  }
   int best = 4, best_cost = 1 << 30;
   for (int nw : {4, 3, 7, 8}) {
     const int wgs = (slices + nw - 1) / nw, cost = 15 + (wgs + 255) / 256 * (27 + 13 * nw);
@@ -987,7 +995,8 @@ int gemm_step_split(int M, int N, int K, int dtype, size_t room) {
   return (size_t)more * M * N * 4 <= room ? more : s;
 }
 
-template <int MT, int NW, int NTW = 2, int RD = 2>
+// SPLIT: partial sums only
+template <int MT, int NW, bool SPLIT = false, int NTW = 2, int RD = 2>
 static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
   const int iters = a.K / KB;
   const int per = (iters + a.split_k - 1) / a.split_k;  // iterations per split
@@ -999,12 +1008,17 @@ static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
   else if (a.split_k <= 8 && 8 % a.split_k == 0) grid = dim3(8 * ((gx + 8 / a.split_k - 1) / (8 / a.split_k)), 1, 1);
   const f16_t* A = reinterpret_cast<const f16_t*>(a.a);
   const bf16_t* W = reinterpret_cast<const bf16_t*>(a.w);
-  if (a.swiglu_act)
-    gemm_w16_kernel<MT, NTW, EPI_SWIGLU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.swiglu_act, nullptr, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
-  else if (a.relu_act)
-    gemm_w16_kernel<MT, NTW, EPI_RELU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.relu_act, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
-  else
-    gemm_w16_kernel<MT, NTW, EPI_PARTIAL, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.out, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+  if constexpr (!SPLIT) {
+    if (a.swiglu_act) {
+      gemm_w16_kernel<MT, NTW, EPI_SWIGLU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.swiglu_act, nullptr, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+      return;
+    }
+    if (a.relu_act) {
+      gemm_w16_kernel<MT, NTW, EPI_RELU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.relu_act, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+      return;
+    }
+  }
+  gemm_w16_kernel<MT, NTW, EPI_PARTIAL, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.out, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
 }
 
 template <int MT>
@@ -1013,6 +1027,8 @@ static void launch_few_rows(const GemmArgs& a, hipStream_t st) {
   switch (few_rows_nw(a.M, ((a.N + NWG - 1) / NWG) * 4, a.K / KB, a.split_k)) {
     case SMALL_NW: launch_bf16_mt<MT, SMALL_NW>(a, 1, st); break;
     case 3: launch_bf16_mt<MT, 3>(a, 1, st); break;
+    case 5: if constexpr (MT > 6) launch_bf16_mt<9, 5, true>(a, 1, st); break;  // (more than 96 rows: few_rows_nw)
+    case 6: if constexpr (MT > 6) launch_bf16_mt<9, 6, true>(a, 1, st); break;
     case 7: launch_bf16_mt<MT, 7>(a, 1, st); break;
     case 8: launch_bf16_mt<MT, 8>(a, 1, st); break;
     default: launch_bf16_mt<MT, 4>(a, 1, st); break;

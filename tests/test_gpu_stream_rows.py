@@ -1,5 +1,6 @@
 """The streaming projection at 97 to 144 rows (seven, eight and nine row tiles, a last one that is not full) through the component
-entry point: automatic and given splits against an fp64 product, partial columns of the packed matrix included."""
+entry point: automatic and given splits (8: five to eight waves per workgroup) against an fp64 product, partial columns of the packed
+matrix included."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("rows", [97, 112, 113, 128, 129, 144])
-@pytest.mark.parametrize("N,K,split", [(1000, 1024, 0), (5120, 2176, 0), (6152, 512, 1), (2304, 768, 3), (33000, 256, 0)])
+@pytest.mark.parametrize("N,K,split", [(1000, 1024, 0), (5120, 2176, 0), (6152, 512, 1), (2304, 768, 3), (33000, 256, 0),
+                                       (5120, 2048, 8), (6144, 2048, 8), (7168, 2048, 8), (8192, 2048, 8), (10240, 2048, 8), (5000, 2176, 9), (5120, 1024, 8), (768, 768, 6)])
 def test_rows_and_splits(rows, N, K, split):
     from paper_2402_15678_amd import binding, harness, synth
     g = torch.Generator(device="cuda").manual_seed(rows * 131 + N)
