@@ -24,7 +24,7 @@ def _folded(desc, rows):
 
 
 def _check(desc, W, ctx, ks, seed, tol):
-    from paper_2402_15678_amd import harness
+    from paper_2402_15678_amd import binding, harness
     ctx, ks = np.asarray(ctx, np.int32), np.asarray(ks, np.int32)
     B, k_max = len(ctx), max(1, int(ks.max()))
     model = harness.DeviceModel.from_host(desc, W)
@@ -41,9 +41,14 @@ def _check(desc, W, ctx, ks, seed, tol):
     want = np.concatenate(orc.decoder_step(desc, util.weights_f64(W), toks, caches))
     got = []
     for _ in range(2):                       # (the second pass finds the first one's statistics in the workspace)
+        binding.mn_profile_enable(model.ctx, True)
         ses.forward(t_last, t_k, ks.tolist(), voted=t_voted)
         torch.cuda.synchronize()
         assert ses.dev_status.item() == 0
+        launches = {k: n for k, (_, n) in binding.mn_profile_collect(model.ctx).items()}
+        folded = _folded(desc, int((ks + 1).sum()))  # (the whole condition, the fused append included, holds in these tests)
+        assert launches["norm"] == (2 if folded else 2 * desc.n_layers + 1) and launches["gemm"] == 4 * desc.n_layers + 1
+        assert not (folded and launches["rope_append"])
         got.append(ses.logits.cpu().numpy().copy())
     assert np.array_equal(got[0], got[1])
     assert np.abs(got[0] - want).max() < tol, np.abs(got[0] - want).max()
