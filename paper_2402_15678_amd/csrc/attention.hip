@@ -581,8 +581,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
 // Up to 16 * CT query rows per KV head: one row per sequence of a decoding step, the few rows of a model without head
 // groups, a drafting model catching up.  There is nothing for the waves of a workgroup to share, so instead of staging
 // tiles in LDS behind a barrier every wave takes key tiles of its own (wave w of a workgroup the tiles w, w + NW, ... of
-// its range), loads their K and V pieces straight into the operand registers of its MFMAs, the next tile's loads in
-// flight while it works on this one, and keeps its own (max, sum, output).  The waves' results meet once, in LDS, at the end.
+// its range), loads their K and V pieces straight into the operand registers of its MFMAs and keeps its own (max, sum, output).
+// The next tile's loads are in flight during this one's softmax and second product, no earlier: they wait for their two block ids,
+// which are vector loads behind this tile's, and loads complete in order, so that all of this tile has landed by then.  A tile costs
+// one round trip for its ids and one for its data.  The waves' results meet once, in LDS, at the end.
 // Measured per layer, rotary/append included: 95 rows of 16 requests x 12 heads of 64, contexts 200-1500: 139 -> 16.2 us;
 // 16 x 1024 keys of the same model 17.1 -> 15.7 us; 8 x 512 keys x 40 heads of 128 29.2 -> 25.0 us.
 // Bound by the KV stream and, at short contexts, by the chain record -> block table -> first tile -> merge (about 6 us).

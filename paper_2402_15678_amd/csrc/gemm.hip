@@ -960,7 +960,8 @@ static int big_room_split(int M, int N, int K) {
 // sharing) and splits as short as one iteration, up to 192 (128) of them.  One pass of a 12-layer, 768-wide model at 16 rows, up to
 // 64 / 96 / 128 / 192 / 256 workgroups: 600 571 574 552 557 us of kernels; at 95 rows, up to 72 / 96 / 128 / 192: 684 681 677 685
 // (four-wave workgroups, up to 96: 620 and 738).
-// The same waves and splits serve 97 to 144 rows, where the plan once filled the CUs with workgroups of 8 waves and splits of at least
+// But for the small matrices, whose short splits end at 96 rows (a LayerNorm model of 12 layers, 768 wide: 569 us at 96 rows, 739 at 97; in
+// a step the room would mostly allow more, which has not been measured), the same waves and splits serve 97 to 144 rows, where the plan once filled the CUs with workgroups of 8 waves and splits of at least
 // 16 iterations: steps of the 5120-wide model at 104 rows 622 -> 542 us, at 144 671 -> 604 (two layers; its matrices got 40 to 80
 // workgroups), of the 70B one at 104 479 -> 457, at 144 1594 -> 1583 (four layers; the projections take the same time, but the down
 // projection has half the partial sums and the vocabulary projection none).

@@ -650,7 +650,8 @@ __device__ __forceinline__ void arg_better(float& bv, int& bi, float v, int i) {
 // waves: a row of 32000 scores is asked for at once (16 rows 9.6 -> 7.3 us, 6.5 since the row's place is asked for with the scores and
 // one wave compares the waves' results); with more rows the chip is full either way and
 // 4 waves leave more workgroups per CU (618 rows 17.8 us, 25.0 with 16 waves).  It also adds up the partial sums of a
-// split vocabulary projection (144 rows, two splits: 22 us as a launch of its own and the argmax, 14 together).
+// split vocabulary projection (144 rows of 32000 scores in two splits, when that head was still split: 22 us as a launch of its own and the
+// argmax, 14 together).
 constexpr int ARGMAX_WIDE_ROWS = 256;
 template <int ARGMAX_THREADS>
 __global__ void __launch_bounds__(ARGMAX_THREADS) argmax_rows_kernel(float* __restrict__ logits, const float* __restrict__ partials,
