@@ -18,6 +18,8 @@
 #include "launch.h"
 #include "../../include/minions_verify.h"
 
+#include <cmath>
+
 namespace mn {
 
 __device__ __forceinline__ void philox4x32_10(uint32_t c[4], uint32_t k0, uint32_t k1) {
@@ -38,11 +40,11 @@ __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
 }
 
 // One workgroup of 16 waves per row, the row's exponentials in registers.  The kernels are bound by the fp64
-// exponentials of one row on one CU (about 25 fp64 instructions per token, 64 lanes per clock: 6 us for 32000 tokens) and by
-// the chain load -> maximum -> exponentials -> sum -> draw, so a row is read once, every exponential is computed once,
-// and every sum is a wave reduction.  Measured at 32000 tokens: 21.9 us for the 144 positions of 16 requests and 16.8 us
-// for 16 drafted tokens; 149 and 162 us with 256 threads per row, the scores re-read for every pass and one thread
-// adding the 256 partial sums of every tile.
+// exponentials of one row on one CU (15 vector instructions of four cycles per token and lane: 3.1 us for 32000 tokens) and by
+// the chain load -> exponentials -> sum -> masses -> draw, so a row is read once, every exponential is computed once, and the workgroup
+// meets twice: for the sum of the exponentials and for the sums of the segments.  Measured at 32000 tokens: 13.7 us for the 144 positions of 16
+// requests and 11.7 us for 16 drafted tokens (18.8 and 13.5 with the exponentials relative to the row's largest score, a third meeting of the workgroup, and the
+// masses divided by Z).
 constexpr int SV_THREADS = 1024;
 constexpr int SV_WAVES = SV_THREADS / 64;
 constexpr int SV_BLOCK = 256;                         // tokens a wave takes at once: lane l holds 4l .. 4l+3 of them
@@ -55,13 +57,15 @@ constexpr int SV_MAX_VOCAB = 1 << 21;
 // Token order.  The row is cut into segments of `grp` consecutive blocks of 256 tokens; segment s belongs to wave s % 16,
 // so (segment, block, lane, element) is token order.  grp = 1 up to 262144 tokens; larger rows take longer
 // segments, so that their sums fit the shared array.
+__device__ __forceinline__ int wave_of(int tid) { return __builtin_amdgcn_readfirstlane(tid >> 6); }  // (scalar: its branches and addresses are)
 __device__ __forceinline__ int seg_blocks(int V) { return (V + SV_MAX_SEGS * SV_BLOCK - 1) / (SV_MAX_SEGS * SV_BLOCK); }
 
 // (rows start at any multiple of 4 bytes: the vocabulary need not be a multiple of 4)
-// four consecutive values of a row, `pad` past its end
-__device__ __forceinline__ f32x4 load_row4(const float* __restrict__ R, int v, int V, float pad) {
-  if (v + 3 < V) {
-    const f32x4_u x = *reinterpret_cast<const f32x4_u*>(R + v);
+// this lane's four consecutive values of block blk (uniform) of a row, `pad` past its end
+__device__ __forceinline__ f32x4 load_row4(const float* __restrict__ R, int blk, int lane, int V, float pad) {
+  const int v = blk * SV_BLOCK + 4 * lane;
+  if ((blk + 1) * SV_BLOCK <= V || v + 3 < V) {
+    const f32x4_u x = *reinterpret_cast<const f32x4_u*>(R + (size_t)blk * SV_BLOCK + 4 * lane);
     return (f32x4){x[0], x[1], x[2], x[3]};
   }
   f32x4 r = {pad, pad, pad, pad};
@@ -120,8 +124,9 @@ __device__ __forceinline__ double lane_63_d(double v) {
 
 struct DrawShared {
   double seg[SV_MAX_SEGS];    // mass of every segment
-  double2 pow2[64];           // 2^(j/64), rest
+  double2 pow2[256];          // (see PowerLoad)
   double red[SV_WAVES];
+  int ref[SV_WAVES];
   float redf[SV_WAVES];
   double target[2];           // target inside the chosen segment, total mass
   int pick[2];                // chosen segment, chosen token
@@ -178,205 +183,146 @@ __device__ const double kPow2[128] = {
     0x1.f50765b6e4540p+0, 0x1.9d3e12dd8a18bp-54, 0x1.fa7c1819e90d8p+0, 0x1.74853f3a5931ep-55,
 };
 
-// exp((l - max) / T), table-driven (P. T. P. Tang, ACM TOMS 15(2), 1989): (l - max) / T = n ln2/64 + r with |r| <= ln2/128, and
-// exp = 2^(n >> 6) * 2^((n & 63)/64) * (1 + r + .. + r^5/120), the sixth-order term below 2^-54.  The 64 powers lie in LDS, in
-// two pieces (their rounding would be the largest error).  Relative error against 64-bit mantissas, 400000 arguments
-// in [-20, 0]: rms 4.8e-17, largest 1.4e-16 (a correctly rounded exponential: 4.7e-17 and 1.1e-16).
-// About half the instructions of the general function (arguments are never positive), which is most of these kernels' time.
-// The quotient is not rounded on its own: r comes out of one fma with T's reciprocal, so its error is the reciprocal's
-// rounding, what a rounded quotient's would be.  For temperatures so extreme that the reciprocal leaves the normal
-// range (inv == 0) the general function and a division.  Differences below -800 T are cut there (the exponential is zero long
-// before), so that a masked token (minus infinity) stays finite; NaN passes through.  The cut is on the fp64 difference: 800 T
-// may be far below the spacing of the scores in fp32, and the largest score may be the type's lowest value.
-struct Temp {
-  double T, inv, per_step;   // 1 / T, 64 / (T ln2)
-  const double2* pow2;       // [64] 2^(j/64), rest
-  double dmx;                // largest score of the row
-  double lowest;             // -800 T
-  double sixth_order;        // 1 / 120 (in vector registers: an instruction reads one scalar constant)
-  float near;                // scores from here on are within 690 T of the largest (see mass4); NaN or more than any score: none are
-  __device__ __forceinline__ void largest(float mx) {
-    dmx = (double)mx;
-    near = inv == 0.0 ? INFINITY : __double2float_ru(dmx - 690.0 * T);
+// 2^(j/256), j = 0 .. 3
+__device__ const double kPow2Fine[8] = {0x1.0000000000000p+0, 0x0.0p+0, 0x1.00b1afa5abcbfp+0, -0x1.4f6b2a7609f71p-55,
+                                        0x1.0163da9fb3335p+0, 0x1.b61299ab8cdb7p-54, 0x1.02168143b0281p+0, -0x1.2bf310fc54eb6p-55};
+
+// The table in LDS: for every j = 0 .. 255 a double c next to 2^(j/256) and what it leaves over, 2^(j/256) / c - 1.  The high word of c
+// has j << 12 taken off (Temp adds the power of two and the index back in one step).
+struct PowerLoad {
+  double2 a, b;
+  __device__ __forceinline__ void ask(int tid) {
+    const int j = tid & 255;
+    a = make_double2(kPow2[2 * (j >> 2)], kPow2[2 * (j >> 2) + 1]);
+    b = make_double2(kPow2Fine[2 * (j & 3)], kPow2Fine[2 * (j & 3) + 1]);
   }
-  // N exponentials side by side (one is a chain of fifteen dependent operations and an LDS read).  SMALL: a result may be below the
-  // normal range, an argument below the cut or not a number.
-  template <bool SMALL, int N>
-  __device__ __forceinline__ void table_exp(const float (&l)[N], double (&m)[N]) const {
-    double d[N], t[N], nd[N], r[N], p[N], sq[N];
-    double2 c[N];
-    int n[N];
-#pragma unroll
-    for (int e = 0; e < N; ++e) {
-      d[e] = (double)l[e] - dmx;
-      if (SMALL) d[e] = d[e] < lowest ? lowest : d[e];
-    }
-#pragma unroll
-    for (int e = 0; e < N; ++e) t[e] = fma_vvs(d[e], per_step, 6755399441055744.0);  // 1.5 * 2^52: the nearest whole number sits in the low bits
-#pragma unroll
-    for (int e = 0; e < N; ++e) n[e] = (int)(uint32_t)__double_as_longlong(t[e]);
-#pragma unroll
-    for (int e = 0; e < N; ++e) c[e] = pow2[n[e] & 63];
-#pragma unroll
-    for (int e = 0; e < N; ++e) nd[e] = t[e] - 6755399441055744.0;
-#pragma unroll
-    for (int e = 0; e < N; ++e) r[e] = fma(d[e], inv, nd[e] * -0x1.62e42fefap-7);  // ln2/64, its first 33 bits (the product with n is exact) ...
-#pragma unroll
-    for (int e = 0; e < N; ++e) r[e] = fma(nd[e], -0x1.cf79abc9e3b3ap-46, r[e]);   // ... and the rest
-#pragma unroll
-    for (int e = 0; e < N; ++e) p[e] = fma_vvs(r[e], sixth_order, 1.0 / 24.0);
-#pragma unroll
-    for (int e = 0; e < N; ++e) sq[e] = r[e] * r[e];
-#pragma unroll
-    for (int e = 0; e < N; ++e) p[e] = fma_vvs(r[e], p[e], 1.0 / 6.0);
-#pragma unroll
-    for (int e = 0; e < N; ++e) p[e] = fma(r[e], p[e], 0.5);
-#pragma unroll
-    for (int e = 0; e < N; ++e) p[e] = fma(sq[e], p[e], r[e]);
-#pragma unroll
-    for (int e = 0; e < N; ++e) {
-      const double y = c[e].x + fma(c[e].x, p[e], c[e].y);
-      m[e] = SMALL ? ldexp(y, n[e] >> 6) : __hiloint2double(__double2hiint(y) + ((n[e] & ~63) << 14), __double2loint(y));
-    }
-  }
-  __device__ __forceinline__ double mass(float l) const {
-    if (inv == 0.0) return exp(((double)l - dmx) / T);  // (uniform)
-    const float one[1] = {l};
-    double m[1];
-    table_exp<true, 1>(one, m);
-    return m[0];
-  }
-  // The masses of four scores, bit for bit those of mass().  Where every score of the wave is within 690 T of the largest the
-  // powers of two are added to the exponent field and nothing is cut: the comparison, the selections and the ldexp were a quarter
-  // of these kernels' arithmetic.
-  __device__ __forceinline__ void mass4(const f32x4& l, double (&m)[4]) const {
-    const float x[4] = {l[0], l[1], l[2], l[3]};
-    if (__all(l[0] >= near && l[1] >= near && l[2] >= near && l[3] >= near)) {
-      table_exp<false, 4>(x, m);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m[e] = mass(l[e]);
-    }
+  __device__ __forceinline__ void store(DrawShared& sh, int tid) const {
+    if (tid >= 256) return;
+    const double c = a.x * b.x, left = fma(a.x, b.x, -c) + (a.x * b.y + a.y * b.x);
+    sh.pow2[tid] = make_double2(__hiloint2double(__double2hiint(c) - (tid << 12), __double2loint(c)), (double)((float)left / (float)c));
   }
 };
 
-// Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass exceeds u times the
-// total; -1 when the total is not positive.  for_blocks(f) calls f(block, t) for every block of this wave in ascending order
-// (see wave_blocks); mass4(t, v) gives the masses of tokens v .. v+3 of that block (v = 256 block + 4 lane; 0 past the end)
-// and must return the same values every time it is asked.  The masses are summed per segment, one wave finds the segment that holds the target,
-// and the wave that owns it scans it.  Every thread of the workgroup calls it; the result is uniform.  All sums
-// have a fixed order.
-template <bool ONE, typename FB, typename F>  // ONE: a block per segment (rows of up to 262144 tokens)
-__device__ __forceinline__ int cdf_draw(FB for_blocks, F mass4, int V, double u, DrawShared& sh, int tid) {
-  const int lane = tid & 63, wave = tid >> 6;
-  const int grp = ONE ? 1 : seg_blocks(V);
-  const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK, n_seg = (n_blocks + grp - 1) / grp;
-  __syncthreads();  // (the shared arrays of an earlier draw have been read)
-  if constexpr (ONE) {
-    // the wave's eight segments are summed over the lanes together: every exchange with the lane 32, 16, 8 away halves the
-    // segments a lane still carries (10 exchanges instead of 48)
-    static_assert(SV_REG_TILES == 8, "three halvings");
-    double s8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for_blocks([&](int blk, int t) {
-      double m[4];
-      mass4(t, blk * SV_BLOCK + 4 * lane, m);
-      s8[t] = (m[0] + m[1]) + (m[2] + m[3]);
-    });
-    double s4[4], s2[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s4[i] = lane_halve_d<32>(s8[i], s8[4 + i]);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) s2[i] = lane_halve_d<16>(s4[i], s4[2 + i]);
-    const bool lo = lane & 8;
-    double s = (lo ? s2[1] : s2[0]) + lane_swap_d<0x128>(lo ? s2[0] : s2[1]);  // row_ror:8
-    s += lane_swap_d<LANE_1>(s);
-    s += lane_swap_d<LANE_2>(s);
-    s += lane_swap_d<LANE_4>(s);
-    if ((lane & 7) == 0) sh.seg[(lane >> 3) * SV_WAVES + wave] = s;  // (segments past the row's end: zero)
-  } else {
-    double run = 0.0;
-    for_blocks([&](int blk, int t) {
-      double m[4];
-      mass4(t, blk * SV_BLOCK + 4 * lane, m);
-      run += (m[0] + m[1]) + (m[2] + m[3]);
-      if (blk % grp == grp - 1 || blk == n_blocks - 1) {  // (wave-uniform)
-        const double s = wave_sum_d(run);
-        if (lane == 0) sh.seg[blk / grp] = s;
-        run = 0.0;
-      }
-    });
-  }
-  __syncthreads();
-  if (wave == 0) {
-    const int per = (n_seg + 63) >> 6;
-    double mine = 0.0;
-    for (int i = 0; i < per; ++i) {
-      const int s = lane * per + i;
-      if (s < n_seg) mine += sh.seg[s];
-    }
-    const double inc = wave_scan_d(mine);
-    const double total = lane_63_d(inc), target = u * total;
-    double before = lane_before_d(inc);
-    int hit = 0x7fffffff, last = -1;
-    double hit_before = 0.0, last_before = 0.0;
-    for (int i = 0; i < per; ++i) {
-      const int s = lane * per + i;
-      if (s >= n_seg) break;
-      const double m = sh.seg[s];
-      if (m > 0.0) {
-        last = s;
-        last_before = before;
-        if (hit == 0x7fffffff && before + m > target) { hit = s; hit_before = before; }
-      }
-      before += m;
-    }
-    const unsigned long long any = __ballot(hit != 0x7fffffff), pos = __ballot(last >= 0);
-    if (pos == 0ull) {                      // no mass anywhere (or not a number)
-      if (lane == 0) sh.pick[0] = -1;
-    } else if (any) {
-      if (lane == __ffsll(any) - 1) { sh.pick[0] = hit; sh.target[0] = target - hit_before; }
-    } else if (lane == 63 - __clzll(pos)) {  // rounding left the target at the end: the last segment with mass
-      sh.pick[0] = last;
-      sh.target[0] = target - last_before;
-    }
-    if (lane == 0) { sh.target[1] = total; sh.pick[1] = -1; }
-  }
-  __syncthreads();
-  if (!(sh.target[1] > 0.0) || sh.pick[0] < 0) return -1;  // (whole workgroup)
-  const int seg = sh.pick[0];
-  if (wave == seg % SV_WAVES) {  // (the segment's own wave: it holds the masses)
-    const double target = sh.target[0];
-    double base = 0.0;
-    int tok = -1, tail = -1;     // the token; the last token with mass so far
-    for_blocks([&](int blk, int t) {
-      if (blk / grp != seg || tok >= 0) return;
-      const int v = blk * SV_BLOCK + 4 * lane;
-      double m[4];
-      mass4(t, v, m);
-      const double mine = (m[0] + m[1]) + (m[2] + m[3]);
-      const double inc = wave_scan_d(mine);
-      const double sum = lane_63_d(inc);
-      double cum = base + lane_before_d(inc);
-      int hit = -1, last = -1;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        cum += m[e];
-        if (m[e] > 0.0) {
-          last = v + e;
-          if (hit < 0 && cum > target) hit = v + e;
-        }
-      }
-      const unsigned long long any = __ballot(hit >= 0), pos = __ballot(last >= 0);
-      if (any) tok = __shfl(hit, __ffsll(any) - 1, 64);
-      if (pos) tail = __shfl(last, 63 - __clzll(pos), 64);
-      base += sum;
-    });
-    if (tok < 0) tok = tail;     // rounding left the target at the segment's end: its last token with mass
-    if (lane == 0) sh.pick[1] = tok;
-  }
-  __syncthreads();
-  return sh.pick[1];
+// A place that the values pass in program order: without it the compiler takes one operation of every token of the row after the other,
+// and the intermediate values of all of them do not fit the registers (280 spilled; 60000 cycles for the row's exponentials instead of 8000).
+template <typename T>
+__device__ __forceinline__ void in_turn(T& a, T& b, T& c, T& d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+
+// Exponentials of scores at temperature T, table-driven (P. T. P. Tang, ACM TOMS 15(2), 1989): l / T = (n + f) ln2/256 with n whole
+// and |f| <= 1/2, and exp(l / T) = 2^(n >> 8) * 2^((n & 255)/256) * (1 + a1 f + .. + a4 f^4), the fifth-order term spread over a1 and a3.
+// f comes out of two fmas with k = 256 / (T ln2) in two pieces, so nothing is lost to the reciprocal of T.  (Several copies of the table, so
+// that the lanes of a read spread over the banks, change nothing: 8040 cycles for a row of 32768 tokens with one copy and with eight, 5940 without the table.)
+// Relative error against 128-bit arithmetic, 200000 arguments in [-20, 0] at each of five temperatures: rms 4.7e-17, largest 1.1e-16, what a correctly
+// rounded exponential has (4.8e-17 and 1.4e-16 at T = 1, 5e-16 and 1e-15 elsewhere with a reciprocal of T in one piece).
+// About half the instructions of the general function, which is most of these kernels' time.
+// A wave takes the exponentials relative to a power of two of its own, at or above its largest one (`relative_to`): nobody waits for
+// the largest score of the row, and the waves' sums are brought to one scale exactly.  Where that does not work - scores that are not numbers or
+// of a size that leaves n no room, rows beyond the registers - they are taken relative to the row's largest score (`below`),
+// and for temperatures so extreme that the reciprocal leaves the normal range (inv == 0) by the general function and a
+// division.  Scores more than 800 T below the largest are cut there (the exponential is zero long before), so that a masked token (minus
+// infinity) stays finite; NaN passes through.  The cut is on fp64 numbers: 800 T may be far below the spacing of the scores in fp32,
+// and the largest score may be the type's lowest value.
+// the next float at or above x
+__device__ __forceinline__ float float_above(double x) {
+  const float n = (float)x;
+  if (!((double)n < x)) return n;
+  return n == 0.f ? 1e-45f : __uint_as_float(__float_as_uint(n) + (n > 0.f ? 1 : -1));
 }
+constexpr double ROUND_MAGIC = 6755399441055744.0;  // 1.5 * 2^52: added to a number, its nearest whole number sits in the low bits
+struct Temp {
+  double T, inv, k, k_lo;
+  const double2* table;
+  double a4;                 // (in vector registers, as k: an instruction reads one scalar constant)
+  double base;               // taken off the scores (below)
+  double magic;              // ROUND_MAGIC less the reference (relative_to)
+  double lowest;             // of a score, less base
+  float near = INFINITY;     // scores from here on are within 690 T of the largest (see mass4); NaN or more than any score: none are
+
+  __device__ __forceinline__ Temp(double t, double inv_t, double kh, double kl, const DrawShared& sh)
+      : T(t), inv(inv_t), k(kh), k_lo(kl), table(sh.pow2), a4(0x1.3b2ab6fba4e77p-39) {
+    asm("" : "+v"(k), "+v"(a4));
+  }
+  __device__ __forceinline__ void below(float mx) {  // mx the row's largest score
+    base = (double)mx;
+    magic = ROUND_MAGIC;
+    lowest = -800.0 * T;
+    near = inv == 0.0 ? INFINITY : float_above(base - 690.0 * T);
+  }
+  __device__ __forceinline__ void relative_to(int e, double mx) {  // 2^e, mx the largest score (or more)
+    base = 0.0;
+    magic = ROUND_MAGIC - 256.0 * (double)e;
+    magic = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(magic)), __builtin_amdgcn_readfirstlane(__double2loint(magic)));
+    lowest = mx - 800.0 * T;
+    near = float_above(mx - 690.0 * T);
+  }
+  // N exponentials side by side (one is a chain of eleven dependent operations and an LDS read).  SMALL: a result may be below the
+  // normal range, an argument below the cut or not a number.
+  template <bool SMALL, int N>
+  __device__ __forceinline__ void powers(double (&x)[N], double (&m)[N]) const {
+    double t[N], nd[N], f[N], p[N];
+    double2 c[N];
+    int n[N];
+    if (SMALL) {
+#pragma unroll
+      for (int e = 0; e < N; ++e) x[e] = x[e] < lowest ? lowest : x[e];
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) t[e] = fma_vvs(x[e], k, magic);
+#pragma unroll
+    for (int e = 0; e < N; ++e) n[e] = (int)(uint32_t)__double_as_longlong(t[e]);
+#pragma unroll
+    for (int e = 0; e < N; ++e) c[e] = table[n[e] & 255];
+#pragma unroll
+    for (int e = 0; e < N; ++e) nd[e] = t[e] - magic;
+#pragma unroll
+    for (int e = 0; e < N; ++e) f[e] = fma(x[e], k, -nd[e]);
+#pragma unroll
+    for (int e = 0; e < N; ++e) f[e] = fma(x[e], k_lo, f[e]);
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma_vvs(f[e], a4, 0x1.c6b090da1e082p-29);  // (ln2/256)^i / i!, the fifth one folded into the third and first
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma_vvs(f[e], p[e], 0x1.ebfbdff82c58fp-19);
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma_vvs(f[e], p[e], 0x1.62e42fefa39b9p-9);
+#pragma unroll
+    for (int e = 0; e < N; ++e) p[e] = fma(f[e], p[e], c[e].y);
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const double s = __hiloint2double(__double2hiint(c[e].x) + ((SMALL ? n[e] & 255 : n[e]) << 12), __double2loint(c[e].x));
+      const double y = fma(s, p[e], s);
+      m[e] = SMALL ? ldexp(y, n[e] >> 8) : y;
+    }
+  }
+  template <bool BELOW>
+  __device__ __forceinline__ double mass(float l) const {
+    if (BELOW && inv == 0.0) return exp(((double)l - base) / T);  // (uniform)
+    double x[1] = {BELOW ? (double)l - base : (double)l}, m[1];
+    powers<true, 1>(x, m);
+    return m[0];
+  }
+  // The masses of four scores, bit for bit those of mass().  PLAIN: every one of them is within 690 T of the largest (>= near): the
+  // powers of two are added to the exponent field and nothing is cut.
+  template <bool BELOW, bool PLAIN>
+  __device__ __forceinline__ void mass4(const f32x4& l, double (&m)[4]) const {
+    if (BELOW && inv == 0.0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) m[e] = mass<BELOW>(l[e]);
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; e += 2) {
+      double x[2] = {BELOW ? (double)l[e] - base : (double)l[e], BELOW ? (double)l[e + 1] - base : (double)l[e + 1]}, y[2];
+      powers<!PLAIN, 2>(x, y);
+      m[e] = y[0];
+      m[e + 1] = y[1];
+    }
+  }
+  template <bool BELOW>
+  __device__ __forceinline__ void mass4(const f32x4& l, double (&m)[4]) const {
+    if (__all(l[0] >= near && l[1] >= near && l[2] >= near && l[3] >= near)) mass4<BELOW, true>(l, m);
+    else mass4<BELOW, false>(l, m);
+  }
+};
 
 // The blocks of this wave: block b of a row belongs to segment b / grp and so to wave (b / grp) % 16.
 // TILES > 0: the row has at most TILES * 4096 tokens (grp == 1), the loop is unrolled and the block's index in the
@@ -395,41 +341,346 @@ __device__ __forceinline__ void wave_blocks(int V, int wave, F f) {
   }
 }
 
-// Largest score of a row, then Z = sum_v exp((l_v - max) / T), both uniform over the workgroup; with TILES > 0 the
-// exponentials stay in ex (zero past the end of the row).
-template <int TILES>
-__device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, Temp& temp, DrawShared& sh, int tid,
-                                              double (&ex)[TILES > 0 ? TILES : 1][4], double& Z) {
-  const int lane = tid & 63, wave = tid >> 6;
-  double2 power = make_double2(0.0, 0.0);    // (asked for ahead of the row)
-  if (tid < 64) power = make_double2(kPow2[2 * tid], kPow2[2 * tid + 1]);
-  f32x4 raw[TILES > 0 ? TILES : 1];
+// The segment that holds u times the total mass, with the target inside it, found by one wave from the segments' masses (per
+// of them in a lane, in order; those above `floor` count as mass); false when there is no mass (or it is not a number).
+struct Hit {
+  int seg;
+  double target, total;
+};
+__device__ __forceinline__ double lane_any_d(double v, int lane) {  // (lane uniform)
+  return both_halves(v, [&](uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, lane); });
+}
+__device__ __forceinline__ bool find_segment(const double* seg, int n_seg, int per, double u, double floor, int lane, Hit& h) {
+  double mine = 0.0;
+  for (int i = 0; i < per; ++i) {
+    const int s = lane * per + i;
+    if (s < n_seg) mine += seg[s];
+  }
+  const double inc = wave_scan_d(mine);
+  const double total = lane_63_d(inc), target = u * total;
+  double before = lane_before_d(inc);
+  int hit = -1, last = -1;
+  double hit_before = 0.0, last_before = 0.0;
+  for (int i = 0; i < per; ++i) {
+    const int s = lane * per + i;
+    const double m = s < n_seg ? seg[s] : 0.0;
+    if (m > floor) {
+      last = s;
+      last_before = before;
+      if (hit < 0 && before + m > target) { hit = s; hit_before = before; }
+    }
+    before += m;
+  }
+  const unsigned long long any = __ballot(hit >= 0), pos = __ballot(last >= 0);
+  h.total = total;
+  h.seg = -1;
+  h.target = 0.0;
+  if (pos == 0ull) return false;
+  const int from = any ? __ffsll(any) - 1 : 63 - __clzll(pos);  // (rounding may leave the target at the end: the last segment with mass)
+  h.seg = __builtin_amdgcn_readlane(any ? hit : last, from);
+  h.target = target - lane_any_d(any ? hit_before : last_before, from);
+  return true;
+}
+// One block of the segment: sets tok to the token that the running sum (base before the block) passes the target in, tail to the
+// last token with mass; returns the block's mass.
+__device__ __forceinline__ double find_token(const double (&m)[4], int v, double base, double target, double floor, int& tok, int& tail) {
+  const double inc = wave_scan_d((m[0] + m[1]) + (m[2] + m[3]));
+  double cum = base + lane_before_d(inc);
+  int hit = -1, last = -1;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    cum += m[e];
+    if (m[e] > floor) {
+      last = v + e;
+      if (hit < 0 && cum > target) hit = v + e;
+    }
+  }
+  const unsigned long long any = __ballot(hit >= 0), pos = __ballot(last >= 0);
+  if (any) tok = __builtin_amdgcn_readlane(hit, __ffsll(any) - 1);
+  if (pos) tail = __builtin_amdgcn_readlane(last, 63 - __clzll(pos));
+  return lane_63_d(inc);
+}
+
+constexpr double MASS_FLOOR = 0x1p-990;     // RowRegs: nothing below it counts
+constexpr int ROW_NONE = -(1 << 30), ROW_GENERAL = 1 << 30;  // RowRegs: a wave without finite scores; a row that is not for it
+
+// Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass exceeds u times the
+// total; -1 when the total is not positive.  mass4(blk, m) gives the masses of this lane's four tokens of block blk (0 past the end)
+// and must return the same values every time it is asked.  The masses are summed per segment, one wave finds the segment that holds the target,
+// and the wave that owns it scans it.  Every thread of the workgroup calls it; the result is uniform.  All sums
+// have a fixed order.
+template <typename F>
+__device__ __forceinline__ int cdf_draw(F mass4, int V, double u, DrawShared& sh, int tid) {
+  const int lane = tid & 63, wave = wave_of(tid);
+  const int grp = seg_blocks(V);
+  const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK, n_seg = (n_blocks + grp - 1) / grp;
+  __syncthreads();  // (the shared arrays of an earlier draw have been read)
+  double run = 0.0;
+  wave_blocks<0>(V, wave, [&](int blk, int) {
+    double m[4];
+    mass4(blk, m);
+    run += (m[0] + m[1]) + (m[2] + m[3]);
+    if (blk % grp == grp - 1 || blk == n_blocks - 1) {  // (wave-uniform)
+      const double s = wave_sum_d(run);
+      if (lane == 0) sh.seg[blk / grp] = s;
+      run = 0.0;
+    }
+  });
+  __syncthreads();
+  if (wave == 0) {
+    Hit h;
+    const bool any = find_segment(sh.seg, n_seg, (n_seg + 63) >> 6, u, 0.0, lane, h);
+    if (lane == 0) {
+      sh.pick[0] = any ? h.seg : -1;
+      sh.pick[1] = -1;
+      sh.target[0] = h.target;
+      sh.target[1] = h.total;
+    }
+  }
+  __syncthreads();
+  if (!(sh.target[1] > 0.0) || sh.pick[0] < 0) return -1;  // (whole workgroup)
+  const int seg = sh.pick[0];
+  if (wave == seg % SV_WAVES) {  // (the segment's own wave)
+    const double target = sh.target[0];
+    double base = 0.0;
+    int tok = -1, tail = -1;     // the token; the last token with mass so far
+    wave_blocks<0>(V, wave, [&](int blk, int) {
+      if (blk / grp != seg || tok >= 0) return;
+      double m[4];
+      mass4(blk, m);
+      base += find_token(m, blk * SV_BLOCK + 4 * lane, base, target, 0.0, tok, tail);
+    });
+    if (tok < 0) tok = tail;     // rounding left the target at the segment's end: its last token with mass
+    if (lane == 0) sh.pick[1] = tok;
+  }
+  __syncthreads();
+  return sh.pick[1];
+}
+
+// The exponentials of a row of up to TILES * 4096 tokens, in registers.  MORE: those of the tiles behind them are computed when they are asked for
+// (`far`): once for their sum, once for their masses, and for the block that holds the draw.
+template <int TILES, bool MORE>
+struct RowRegs {
+  double ex[TILES][4];        // relative to this wave's power of two; zero past the end of the row
+  int e_all;                  // the row's power of two: the largest of the waves'
+  int down;                   // this wave's, less the row's: at most 0
+  bool dead;                  // nothing of this wave is left beside the row's largest
+  double Z, z_wave;           // sum of the row's exponentials relative to the row's power of two and to this wave's
+
+  // A block's values of this lane, asked for whatever the row's length (V >= 4): blocks past the last repeat it, pieces that reach past the
+  // end hold the last four values and are put in place afterwards (where V is no multiple of 4; what lies past the end is another value of the row).
+  static __device__ __forceinline__ int first_of(int t, int wave, int lane, int V) {
+    return min(t * SV_WAVES + wave, (V + SV_BLOCK - 1) / SV_BLOCK - 1) * SV_BLOCK + 4 * lane;
+  }
+  static __device__ __forceinline__ f32x4 ask(const float* __restrict__ R, int t, int wave, int lane, int V) {
+    const f32x4_u x = *reinterpret_cast<const f32x4_u*>(R + min(first_of(t, wave, lane, V), V - 4));
+    return (f32x4){x[0], x[1], x[2], x[3]};
+  }
+  static __device__ __forceinline__ f32x4 in_place(const f32x4& x, int t, int wave, int lane, int V) {
+    const int past = first_of(t, wave, lane, V) - (V - 4);
+    return (f32x4){past == 1 ? x[1] : past == 2 ? x[2] : past == 3 ? x[3] : x[0], past == 1 ? x[2] : past == 2 ? x[3] : x[1],
+                   past == 1 ? x[3] : x[2], x[3]};
+  }
+  // masses of four scores of tile t, relative to the wave's power of two
+  static __device__ __forceinline__ void masses(f32x4 l, int t, int wave, int lane, int V, const Temp& temp, double (&m)[4]) {
+    const int blk = t * SV_WAVES + wave;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) l[i] = fmaxf(l[i], temp.near);
+    temp.template mass4<false, true>(l, m);
+    if ((blk + 1) * SV_BLOCK > V) {            // (wave-uniform)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (blk * SV_BLOCK + 4 * lane + i >= V) m[i] = 0.0;
+    }
+  }
+  __device__ __forceinline__ void far(const float* __restrict__ L, int t, int wave, int lane, int V, const Temp& temp, double (&m)[4]) const {
+    masses(in_place(ask(L, t, wave, lane, V), t, wave, lane, V), t, wave, lane, V, temp, m);
+    if (dead) m[0] = m[1] = m[2] = m[3] = 0.0;
+  }
+  __device__ __forceinline__ void clear_past_end(int t, int wave, int lane, int V) {
+    const int blk = t * SV_WAVES + wave;
+    if ((blk + 1) * SV_BLOCK > V) {            // (wave-uniform)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (blk * SV_BLOCK + 4 * lane + i >= V) ex[t][i] = 0.0;
+    }
+  }
+
+  // Uniform result; false: the row has scores that are not numbers, or too large for this (or none that is finite).
+  // Scores more than 690 T below the wave's largest count as that far below, at most 2^-995: MASS_FLOOR and the draw tell them from mass.
+  // soon: another row (or null) that the kernel may read next; a line of it per thread is on its way to the L2 while the exponentials are
+  // computed.  (Asked for beside the scores it holds them up: 1 us of 16 at 144 rows.)
+  __device__ __forceinline__ bool load(const float* __restrict__ L, const float* __restrict__ soon, int V, Temp& temp, const PowerLoad& power, DrawShared& sh, int tid) {
+    const int lane = tid & 63, wave = wave_of(tid);
+    f32x4 raw[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) raw[t] = ask(L, t, wave, lane, V);
+    power.store(sh, tid);
+    __syncthreads();
+    if (V & 3) {
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) raw[t] = in_place(raw[t], t, wave, lane, V);
+    }
+    float mx = raw[0][0];                      // (a NaN stays)
+#pragma unroll
+    for (int i = 1; i < 4 * TILES; ++i) mx = __builtin_elementwise_maximum(mx, raw[i / 4][i % 4]);
+    const bool nan = __any(mx != mx);
+    mx = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wave_max(mx))));
+    const double top = (double)mx * temp.k;    // the reference: the next power of two at or above the largest exponential
+    const bool ok = __all(__builtin_fabs(top) < 0x1p38) && !nan;
+    int e = ok ? __builtin_amdgcn_readfirstlane((int)ceil(top * (1.0 / 256.0))) : mx != -INFINITY || nan ? ROW_GENERAL : ROW_NONE;
+    temp.relative_to(ok ? e : 0, ok ? (double)mx : 0.0);
+    float touch = 0.f;
+    if (soon && 32 * tid < V) touch = soon[32 * tid];
+    if (MORE && soon && 32 * (SV_THREADS + tid) < V) touch += soon[32 * (SV_THREADS + tid)];
+    double zp = 0.0;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+      asm volatile("" : "+v"(raw[t]));         // (see in_turn)
+      masses(raw[t], t, wave, lane, V, temp, ex[t]);
+      in_turn(ex[t][0], ex[t][1], ex[t][2], ex[t][3]);
+      zp += (ex[t][0] + ex[t][1]) + (ex[t][2] + ex[t][3]);
+    }
+    if constexpr (MORE) {
+      // the tiles behind the registers keep the reference: up to 100 T above it their exponentials, up to 2^145, leave room for z_wave
+      const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK;
+      float hi = mx;
+      f32x4 next = ask(L, TILES, wave, lane, V);
+      for (int t = TILES; t * SV_WAVES + wave < n_blocks; ++t) {
+        f32x4 l = in_place(next, t, wave, lane, V);
+        next = ask(L, t + 1, wave, lane, V);
+        double m[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) hi = __builtin_elementwise_maximum(hi, l[i]);
+        masses(l, t, wave, lane, V, temp, m);
+        zp += (m[0] + m[1]) + (m[2] + m[3]);
+      }
+      const float above = ok ? (float)((double)mx + 100.0 * temp.T) : mx;
+      if (__any(!(hi <= above)) && e != ROW_GENERAL) e = ROW_GENERAL;
+    }
+    if (e == ROW_NONE) {                       // (wave-uniform) none of these is there
+      zp = 0.0;
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) ex[t][0] = ex[t][1] = ex[t][2] = ex[t][3] = 0.0;
+    }
+    asm volatile("" ::"v"(touch));
+    zp = wave_sum_d(zp);
+    if (lane == 0) {
+      sh.red[wave] = zp;
+      sh.ref[wave] = e;
+    }
+    __syncthreads();
+    e_all = sh.ref[lane % SV_WAVES];           // (a wave's lanes 0 .. 15 hold all of them)
+#pragma unroll
+    for (int w = 0; w < SV_WAVES; ++w) e_all = max(e_all, sh.ref[w]);
+    if (e_all == ROW_GENERAL || e_all == ROW_NONE) return false;
+    Z = 0.0;
+#pragma unroll
+    for (int w = 0; w < SV_WAVES; ++w) Z += ldexp(sh.red[w], sh.ref[w] - e_all);
+    if (!(Z > 0.0 && Z < INFINITY)) return false;
+    down = e - e_all;
+    z_wave = ldexp(Z, -down);
+    dead = down < -850;
+    if (dead) {
+      down = 0;
+      z_wave = 1.0;
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) ex[t][0] = ex[t][1] = ex[t][2] = ex[t][3] = 0.0;
+    }
+    return true;
+  }
+
+  // Inverse-CDF draw as cdf_draw, over the masses ex * 2^down: false when there is no mass, otherwise the wave that owns the token gets it (>= 0) in tok.
+  // Every wave finds the segment for itself: the sums it needs are the only thing that the workgroup waits for.
+  // more(t, first, m): the masses of a tile behind the registers; first: asked for the first time.
+  template <typename F>
+  __device__ __forceinline__ bool draw(int V, double u, int down_by, DrawShared& sh, int tid, int& tok, F more) {
+    // the wave's eight segments are summed over the lanes together: every exchange with the lane 32, 16, 8 away halves the
+    // segments a lane still carries (10 exchanges instead of 48)
+    static_assert(TILES <= 8, "three halvings");
+    const int lane = tid & 63, wave = wave_of(tid);
+    const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK;
+    double s8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) s8[t] = (ex[t][0] + ex[t][1]) + (ex[t][2] + ex[t][3]);
+    auto store = [&](int t0, int tiles) {
+      double s4[4], s2[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s4[i] = lane_halve_d<32>(s8[i], s8[4 + i]);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) s2[i] = lane_halve_d<16>(s4[i], s4[2 + i]);
+      const bool lo = lane & 8;
+      double s = (lo ? s2[1] : s2[0]) + lane_swap_d<0x128>(lo ? s2[0] : s2[1]);  // row_ror:8
+      s += lane_swap_d<LANE_1>(s);
+      s += lane_swap_d<LANE_2>(s);
+      s += lane_swap_d<LANE_4>(s);
+      if ((lane & 7) == 0 && (lane >> 3) < tiles)
+        sh.seg[(t0 + (lane >> 3)) * SV_WAVES + wave] = ldexp(s, down_by);  // (segments past the row's end: zero)
+    };
+    store(0, TILES);
+    if constexpr (MORE) {
+      for (int t0 = TILES; t0 * SV_WAVES < n_blocks; t0 += 8) {  // (t0 < 64: n_blocks <= SV_MAX_SEGS)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          s8[i] = 0.0;
+          if ((t0 + i) * SV_WAVES + wave < n_blocks) {
+            double m[4];
+            more(t0 + i, true, m);
+            s8[i] = (m[0] + m[1]) + (m[2] + m[3]);
+          }
+          asm volatile("" : "+v"(s8[i]));
+        }
+        store(t0, min(8, SV_MAX_SEGS / SV_WAVES - t0));
+      }
+    }
+    __syncthreads();
+    tok = -1;
+    Hit h;
+    if (!find_segment(sh.seg, n_blocks, MORE ? (n_blocks + 63) >> 6 : (TILES * SV_WAVES + 63) / 64, u, 2.0 * SV_BLOCK * MASS_FLOOR, lane, h)) return false;
+    if (wave == h.seg % SV_WAVES) {            // (the segment's own wave: it holds the masses, of which one is above the floor)
+      const double target = ldexp(h.target, -down_by);
+      int tail = -1;
+      double m[4] = {ex[0][0], ex[0][1], ex[0][2], ex[0][3]};
+#pragma unroll
+      for (int t = 1; t < TILES; ++t)
+        if (h.seg / SV_WAVES == t) {           // (wave-uniform)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) m[i] = ex[t][i];
+        }
+      if constexpr (MORE) {
+        if (h.seg / SV_WAVES >= TILES) more(h.seg / SV_WAVES, false, m);
+      }
+      find_token(m, h.seg * SV_BLOCK + 4 * lane, 0.0, target, MASS_FLOOR, tok, tail);
+      if (tok < 0) tok = tail;                 // rounding left the target at the segment's end: its last token with mass
+    }
+    return true;
+  }
+};
+
+// Largest score of a row, then Z = sum_v exp((l_v - max) / T), both uniform over the workgroup, for rows of any kind
+__device__ __forceinline__ void row_max_and_z(const float* __restrict__ L, int V, Temp& temp, DrawShared& sh, int tid, double& Z) {
+  const int lane = tid & 63, wave = wave_of(tid);
   float mx = -INFINITY;
-  wave_blocks<TILES>(V, wave, [&](int blk, int t) { raw[t] = load_row4(L, blk * SV_BLOCK + 4 * lane, V, -INFINITY);
-                                                     if (TILES == 0) mx = fmaxf(mx, fmaxf(fmaxf(raw[0][0], raw[0][1]), fmaxf(raw[0][2], raw[0][3]))); });
-  if constexpr (TILES > 0)
-    wave_blocks<TILES>(V, wave, [&](int, int t) { mx = fmaxf(mx, fmaxf(fmaxf(raw[t][0], raw[t][1]), fmaxf(raw[t][2], raw[t][3]))); });
+  wave_blocks<0>(V, wave, [&](int blk, int) {
+    const f32x4 l = load_row4(L, blk, lane, V, -INFINITY);
+    mx = fmaxf(mx, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
+  });
   mx = wave_max(mx);
   if (lane == 0) sh.redf[wave] = mx;
-  if (tid < 64) sh.pow2[tid] = power;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < SV_WAVES; ++w) mx = fmaxf(mx, sh.redf[w]);
-  temp.largest(mx);
+  temp.below(mx);
   double zp = 0.0;
-  wave_blocks<TILES>(V, wave, [&](int blk, int t) {
+  wave_blocks<0>(V, wave, [&](int blk, int) {
     const int v = blk * SV_BLOCK + 4 * lane;
-    const f32x4 l = TILES > 0 ? raw[t] : load_row4(L, v, V, -INFINITY);
-    temp.mass4(l, ex[t]);
-    if ((blk + 1) * SV_BLOCK > V) {          // (wave-uniform)
+    double m[4];
+    temp.mass4<true>(load_row4(L, blk, lane, V, -INFINITY), m);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (v + e >= V) ex[t][e] = 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) zp += ex[t][e];
+    for (int e = 0; e < 4; ++e) zp += v + e < V ? m[e] : 0.0;
   });
   zp = wave_sum_d(zp);
+  __syncthreads();  // (the sums of the registers' attempt have been read)
   if (lane == 0) sh.red[wave] = zp;
   __syncthreads();
   Z = 0.0;
@@ -449,33 +700,52 @@ __device__ __forceinline__ void position_uniforms(uint32_t b, uint32_t j, uint32
 }
 
 // One workgroup per (position j, sequence b).
-template <int TILES>
+template <int TILES, bool MORE>
 __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ voted, const float* __restrict__ draft_probs,
     const int32_t* __restrict__ spec_len, const int32_t* __restrict__ greedy, int B, int k_max, int M, int V,
-    double temperature, double inv_temperature, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
+    double temperature, double inv_temperature, double k, double k_lo, uint32_t seed_lo, uint32_t seed_hi, uint32_t step_lo, uint32_t step_hi,
     int32_t* __restrict__ sampled, int32_t* dev_status) {
   __shared__ DrawShared sh;
   __shared__ int s_int[2];  // rows before this sequence, bad flag
-  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = wave_of(tid);
   int32_t* out = sampled + (size_t)b * (k_max + 1) + j;
 
-  if (tid < 2) s_int[tid] = 0;
-  __syncthreads();
-  {  // rows of the sequences before b (integer sum: order-free)
-    int part = 0, bad = 0;
+  PowerLoad power;
+  power.ask(tid);
+  const int k_b = spec_len[b], first = greedy[(size_t)b * (k_max + 1)];
+  const int x = j < k_max ? voted[(size_t)b * k_max + j] : -1;  // (looked at below k_b only)
+  int row = j, bad = 0;  // rows of the sequences before b
+  if (b <= 256) {        // every wave for itself, nobody waits
+    int n[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n[i] = i * 64 < b ? spec_len[min(i * 64 + lane, b)] : 0;
+    int part = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (i * 64 + lane < b) {
+        bad |= n[i] < 0 || n[i] > k_max;
+        part += n[i] + 1;
+      }
+    row += wave_sum_i(part);
+    bad = __any(bad);
+  } else {
+    if (tid < 2) s_int[tid] = 0;
+    __syncthreads();
+    int part = 0;
     for (int i = tid; i < b; i += SV_THREADS) {
-      const int k = spec_len[i];
-      if (k < 0 || k > k_max) bad = 1;
-      part += k + 1;
+      const int n = spec_len[i];
+      if (n < 0 || n > k_max) bad = 1;
+      part += n + 1;
     }
-    if (part) atomicAdd(&s_int[0], part);
+    if (part) atomicAdd(&s_int[0], part);  // (integer sum: order-free)
     if (bad) atomicOr(&s_int[1], 1);
+    __syncthreads();
+    row += s_int[0];
+    bad = s_int[1];
   }
-  __syncthreads();
-  const int k_b = spec_len[b];
-  const int row = s_int[0] + j;
-  const bool seq_ok = !s_int[1] && k_b >= 0 && k_b <= k_max && greedy[(size_t)b * (k_max + 1)] >= 0;
+  row = __builtin_amdgcn_readfirstlane(row);
+  const bool seq_ok = !bad && k_b >= 0 && k_b <= k_max && first >= 0;
   if (!seq_ok || j > k_b || row >= M) {  // (whole workgroup)
     if (tid == 0) {
       *out = -1;
@@ -484,75 +754,109 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     return;
   }
   const float* L = logits + (size_t)row * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 1.0 / 120.0, 0.f};  // 64 / ln2
-  double ex[TILES > 0 ? TILES : 1][4];
-  double Z;
-  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
-  double u_acc, u_res;
-  position_uniforms((uint32_t)b, (uint32_t)j, step_lo, step_hi, 0u, seed_lo, seed_hi, u_acc, u_res);
+  const float* Q = j < k_b ? draft_probs + ((size_t)b * k_max + j) * V : nullptr;
+  const bool in_vocab = Q && x >= 0 && x < V;
+  float l_x = 0.f, q_x = 0.f;
+  if (in_vocab) {
+    l_x = L[x];
+    q_x = Q[x];
+  }
+  Temp temp(temperature, inv_temperature, k, k_lo, sh);
+  double u_acc = 0.0, u_res = 0.0;
+  auto uniforms = [&]() { position_uniforms((uint32_t)b, (uint32_t)j, step_lo, step_hi, 0u, seed_lo, seed_hi, u_acc, u_res); };
+  // does the speculated token survive?  (mass_x of Z)
+  auto survives = [&](double mass_x, double Z) {
+    const double ox = mass_x / Z, qx = (double)q_x;
+    return qx <= ox || u_acc < ox / qx;
+  };
 
-  // ---- does the speculated token survive? ----
-  bool keep = false;
-  int x = -1;
-  const float* Q = nullptr;
-  if (j < k_b) {
-    x = voted[(size_t)b * k_max + j];
-    Q = draft_probs + ((size_t)b * k_max + j) * V;
-    if (x >= 0 && x < V) {
-      const double ox = temp.mass(L[x]) / Z;
-      const double qx = (double)Q[x];
-      keep = (qx <= ox) || (u_acc < ox / qx);
-    }
-  }
-  if (keep) {  // (whole workgroup: x, Q, Z, the random numbers are uniform over it)
-    if (tid == 0) *out = x;
-    return;
-  }
-  // ---- a token from max(0, o - q); without q (position k_b) from o.  When nothing of o lies above q (a q that
+  // ---- where it does not, a token from max(0, o - q); without q (position k_b) from o.  When nothing of o lies above q (a q that
   // sums above 1) the replacement comes from o without the rejected token, so that it still differs from what
   // it replaces (the acceptance reads "first entry that differs" as the first rejection); and when all of o
   // sits on that token there is nothing else to emit: it stays ----
+  if constexpr (TILES > 0) {
+    RowRegs<TILES, MORE> regs;
+    if (regs.load(L, Q, V, temp, power, sh, tid)) {
+      uniforms();
+      if (in_vocab) {
+        Temp whole = temp;
+        whole.relative_to(regs.e_all, (double)regs.e_all * 256.0 / temp.k);
+        if (survives(whole.mass<false>(l_x), regs.Z)) {  // (whole workgroup: all of it is uniform)
+          if (tid == 0) *out = x;
+          return;
+        }
+      }
+      if (Q) {  // masses of o - q, times Z and relative to the wave's power of two
+        constexpr int HALF = TILES < 4 ? TILES : TILES % 4 ? 3 : 4;
+        static_assert(TILES % HALF == 0, "whole groups");
+#pragma unroll
+        for (int h = 0; h < TILES; h += HALF) {
+          f32x4 q[HALF];
+#pragma unroll
+          for (int t = 0; t < HALF; ++t) q[t] = regs.ask(Q, h + t, wave, lane, V);
+#pragma unroll
+          for (int t = 0; t < HALF; ++t) {
+            if (V & 3) q[t] = regs.in_place(q[t], h + t, wave, lane, V);
+            asm volatile("" : "+v"(q[t]));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) regs.ex[h + t][e] = fmax(0.0, fma(-(double)q[t][e], regs.z_wave, regs.ex[h + t][e]));
+            in_turn(regs.ex[h + t][0], regs.ex[h + t][1], regs.ex[h + t][2], regs.ex[h + t][3]);
+            regs.clear_past_end(h + t, wave, lane, V);
+          }
+        }
+      }
+      int tok;
+      auto more = [&](int t, bool, double (&m)[4]) {
+        f32x4 q = {0.f, 0.f, 0.f, 0.f};
+        if (Q) q = regs.ask(Q, t, wave, lane, V);
+        regs.far(L, t, wave, lane, V, temp, m);
+        if (Q) {
+          q = regs.in_place(q, t, wave, lane, V);
+          const bool last = ((t * SV_WAVES + wave) + 1) * SV_BLOCK > V;  // (wave-uniform)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m[e] = last && (t * SV_WAVES + wave) * SV_BLOCK + 4 * lane + e >= V ? 0.0 : fmax(0.0, fma(-(double)q[e], regs.z_wave, m[e]));
+        }
+      };
+      if (regs.draw(V, u_res, regs.down, sh, tid, tok, more)) {
+        if (tok >= 0 && lane == 0) *out = tok;  // (one wave)
+        return;
+      }
+    }
+    __syncthreads();                            // (the general form starts over)
+  } else {
+    power.store(sh, tid);
+    __syncthreads();
+  }
+  double Z;
+  row_max_and_z(L, V, temp, sh, tid, Z);
+  uniforms();
+  if (in_vocab && survives(temp.mass<true>(l_x), Z)) {
+    if (tid == 0) *out = x;
+    return;
+  }
   const double inv_z = 1.0 / Z;  // (Z >= 1: the largest score contributes exp(0))
-  auto o4 = [&](int v, double (&o)[4]) {  // probabilities of tokens v .. v+3, recomputed from the scores
-    const f32x4 l = load_row4(L, v, V, -INFINITY);
-    temp.mass4(l, o);
+  auto o4 = [&](int blk, double (&o)[4]) {  // probabilities of a block's tokens, recomputed from the scores
+    const int v = blk * SV_BLOCK + 4 * lane;
+    const f32x4 l = load_row4(L, blk, lane, V, -INFINITY);
+    temp.mass4<true>(l, o);
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = v + e < V ? div_by(o[e], Z, inv_z) : 0.0;
   };
-  int tok = -1;
-  if constexpr (TILES > 0) {
-    // the masses take the place of the exponentials in the registers
-    wave_blocks<TILES>(V, wave, [&](int blk, int t) {
-      f32x4 q = {0.f, 0.f, 0.f, 0.f};
-      if (Q) q = load_row4(Q, blk * SV_BLOCK + 4 * lane, V, 0.f);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double o = div_by(ex[t][e], Z, inv_z);
-        ex[t][e] = Q ? fmax(0.0, o - (double)q[e]) : o;
-      }
-    });
-    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, f); },
-                   [&](int t, int, double (&m)[4]) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; },
-                   V, u_res, sh, tid);
-  } else {
-    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, f); },
-                   [&](int, int v, double (&m)[4]) {
-                     o4(v, m);
+  int tok = cdf_draw([&](int blk, double (&m)[4]) {
+                     o4(blk, m);
                      if (Q) {
-                       const f32x4 q = load_row4(Q, v, V, 0.f);
+                       const f32x4 q = load_row4(Q, blk, lane, V, 0.f);
 #pragma unroll
                        for (int e = 0; e < 4; ++e) m[e] = fmax(0.0, m[e] - (double)q[e]);
                      }
                    },
                    V, u_res, sh, tid);
-  }
   if (Q && tok < 0) {
-    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, f); },
-                   [&](int, int v, double (&m)[4]) {
-                     o4(v, m);
+    tok = cdf_draw([&](int blk, double (&m)[4]) {
+                     o4(blk, m);
 #pragma unroll
                      for (int e = 0; e < 4; ++e)
-                       if (v + e == x) m[e] = 0.0;
+                       if (blk * SV_BLOCK + 4 * lane + e == x) m[e] = 0.0;
                    },
                    V, u_res, sh, tid);
     if (tok < 0) tok = x;
@@ -563,87 +867,141 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
 // One workgroup per sequence: token ~ q = softmax(scores / T) of a drafting SSM, and q itself in fp32.
 // The draw is taken from the fp32 values that are written out, so what the verifier is later told is
 // exactly the distribution the token came from.
-template <int TILES>
+template <int TILES, bool MORE>
 __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* __restrict__ logits, int V,
-                                                                  double temperature, double inv_temperature,
+                                                                  double temperature, double inv_temperature, double k, double k_lo,
                                                                   uint32_t seed_lo, uint32_t seed_hi,
                                                                   uint32_t step_lo, uint32_t step_hi, uint32_t consumer,
                                                                   uint32_t t_pos, int32_t* __restrict__ tokens,
                                                                   long token_stride, float* __restrict__ probs,
                                                                   long probs_stride) {
   __shared__ DrawShared sh;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = wave_of(tid);
   const float* L = logits + (size_t)b * V;
-  Temp temp{temperature, inv_temperature, inv_temperature * 0x1.71547652b82fep+6, sh.pow2, 0.0, -800.0 * temperature, 1.0 / 120.0, 0.f};  // 64 / ln2
-  double ex[TILES > 0 ? TILES : 1][4];
+  int32_t* out = tokens + (size_t)b * token_stride;
+  float* P = probs ? probs + (size_t)b * probs_stride : nullptr;
+  PowerLoad power;
+  power.ask(tid);
+  Temp temp(temperature, inv_temperature, k, k_lo, sh);
+  auto uniform = [&]() {
+    double u_unused, u;
+    position_uniforms((uint32_t)b, t_pos, step_lo, step_hi, consumer, seed_lo, seed_hi, u_unused, u);
+    return u;
+  };
+  auto write = [&](int blk, const double (&m)[4]) {
+    if (!P) return;
+    const int v = blk * SV_BLOCK + 4 * lane;
+    if ((blk + 1) * SV_BLOCK <= V || v + 3 < V) {
+      *reinterpret_cast<f32x4_u*>(P + (size_t)blk * SV_BLOCK + 4 * lane) = (f32x4_u){(float)m[0], (float)m[1], (float)m[2], (float)m[3]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (v + e < V) P[v + e] = (float)m[e];
+    }
+  };
+  if constexpr (TILES > 0) {
+    RowRegs<TILES, MORE> regs;
+    if (regs.load(L, nullptr, V, temp, power, sh, tid)) {
+      const double inv_z = 1.0 / regs.z_wave;
+#pragma unroll
+      for (int t = 0; t < TILES; ++t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) regs.ex[t][e] = (double)(float)div_by(regs.ex[t][e], regs.z_wave, inv_z);
+        in_turn(regs.ex[t][0], regs.ex[t][1], regs.ex[t][2], regs.ex[t][3]);
+        write(t * SV_WAVES + wave, regs.ex[t]);
+      }
+      int tok;
+      auto more = [&](int t, bool first, double (&m)[4]) {
+        regs.far(L, t, wave, lane, V, temp, m);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] = (double)(float)div_by(m[e], regs.z_wave, inv_z);
+        if (first) write(t * SV_WAVES + wave, m);
+      };
+      if (!regs.draw(V, uniform(), 0, sh, tid, tok, more)) {
+        if (tid == 0) *out = -1;
+      } else if (tok >= 0 && lane == 0) {  // (one wave)
+        *out = tok;
+      }
+      return;
+    }
+    __syncthreads();                       // (the general form starts over)
+  } else {
+    power.store(sh, tid);
+    __syncthreads();
+  }
   double Z;
-  row_max_and_z<TILES>(L, V, temp, sh, tid, ex, Z);
-  double u_unused, u;
-  position_uniforms((uint32_t)b, t_pos, step_lo, step_hi, consumer, seed_lo, seed_hi, u_unused, u);
+  row_max_and_z(L, V, temp, sh, tid, Z);
   const double inv_z = 1.0 / Z;
-  auto q4 = [&](int v, double (&m)[4]) {  // the fp32 probabilities of tokens v .. v+3
-    const f32x4 l = load_row4(L, v, V, -INFINITY);
-    temp.mass4(l, m);
+  auto q4 = [&](int blk, double (&m)[4]) {  // the fp32 probabilities of a block's tokens
+    const int v = blk * SV_BLOCK + 4 * lane;
+    const f32x4 l = load_row4(L, blk, lane, V, -INFINITY);
+    temp.mass4<true>(l, m);
 #pragma unroll
     for (int e = 0; e < 4; ++e) m[e] = v + e < V ? (double)(float)div_by(m[e], Z, inv_z) : 0.0;
   };
-  float* P = probs ? probs + (size_t)b * probs_stride : nullptr;
-  wave_blocks<TILES>(V, wave, [&](int blk, int t) {
-    const int v = blk * SV_BLOCK + 4 * lane;
-    double m[4];
-    if constexpr (TILES > 0) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) m[e] = ex[t][e] = (double)(float)div_by(ex[t][e], Z, inv_z);
-    } else if (P) {
-      q4(v, m);
-    }
-    if (P) {
-      if (v + 3 < V) {
-        *reinterpret_cast<f32x4_u*>(P + v) = (f32x4_u){(float)m[0], (float)m[1], (float)m[2], (float)m[3]};
-      } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (v + e < V) P[v + e] = (float)m[e];
-      }
-    }
-  });
-  int tok;
-  if constexpr (TILES > 0)
-    tok = cdf_draw<(TILES > 0)>([&](auto f) { wave_blocks<TILES>(V, wave, f); },
-                   [&](int t, int, double (&m)[4]) { m[0] = ex[t][0]; m[1] = ex[t][1]; m[2] = ex[t][2]; m[3] = ex[t][3]; },
-                   V, u, sh, tid);
-  else
-    tok = cdf_draw<false>([&](auto f) { wave_blocks<0>(V, wave, f); },
-                   [&](int, int v, double (&m)[4]) {
+  if (P)
+    wave_blocks<0>(V, wave, [&](int blk, int) {
+      double m[4];
+      q4(blk, m);
+      write(blk, m);
+    });
+  const int tok = cdf_draw([&](int blk, double (&m)[4]) {
+                     const int v = blk * SV_BLOCK + 4 * lane;
                      if (P && v + 3 < V) {  // (this thread wrote them itself: cheaper than the exponentials again)
                        const f32x4_u q = *reinterpret_cast<const f32x4_u*>(P + v);
                        m[0] = (double)q[0]; m[1] = (double)q[1]; m[2] = (double)q[2]; m[3] = (double)q[3];
                      } else {
-                       q4(v, m);
+                       q4(blk, m);
                      }
                    },
-                   V, u, sh, tid);
-  if (tid == 0) tokens[(size_t)b * token_stride] = tok;
+                   V, uniform(), sh, tid);
+  if (tid == 0) *out = tok;
 }
 
 // 1 / T where both are comfortably normal numbers, 0 otherwise (the kernels then divide)
 static double temperature_reciprocal(double T) { return T > 0x1p-100 && T < 0x1p100 ? 1.0 / T : 0.0; }
+// 256 / (T ln2) in two pieces (about 104 bits: scores far from zero beside T multiply its error)
+struct StepsPerScore {
+  double k, k_lo;
+  explicit StepsPerScore(double T) {
+    const double c = 0x1.71547652b82fep+8, c_lo = 0x1.777d0ffda0d24p-48;  // 256 / ln2
+    k = c / T;
+    k_lo = (std::fma(-k, T, c) + c_lo) / T;
+  }
+};
+
+// Tiles of 4096 tokens that a row's exponentials take in registers (every instance computes all of its tiles), 0: the general form.  Beyond
+// 32768 tokens the first tiles are in registers, up to the segments that the shared array holds.
+constexpr int SV_MAX_FAR = SV_MAX_SEGS * SV_BLOCK;
+static int reg_tiles(int V, double inv) {
+  if (V < 4 || V > SV_MAX_FAR || inv == 0.0) return 0;
+  return V <= SV_TILE ? 1 : V <= 2 * SV_TILE ? 2 : V <= 4 * SV_TILE ? 4 : SV_REG_TILES;
+}
+// FAR: tiles in registers beyond 32768 tokens.  The verifier needs room for q there: 144 positions of 50272 tokens 35.6 us with eight (which spill), 26.5 with six,
+// 28.7 with four, 48.4 in the general form; 16 drafted tokens 20.5, 22.0 and 23.9, 41.5 in the general form.
+#define MN_ROW_KERNEL(K, FAR, V, INV)                                                                                  \
+  (reg_tiles(V, INV) == 1 ? K<1, false> : reg_tiles(V, INV) == 2 ? K<2, false> : reg_tiles(V, INV) == 4 ? K<4, false> \
+   : reg_tiles(V, INV) == 0 ? K<0, false> : (V) <= SV_REG_TILES * SV_TILE ? K<SV_REG_TILES, false> : K<FAR, true>)
 
 void launch_verify_sample(const float* logits, const int32_t* voted, const float* draft_probs, const int32_t* spec_len,
                           const int32_t* greedy, int B, int k_max, int M, int V, double temperature, uint64_t seed,
                           uint64_t step, int32_t* sampled, int32_t* dev_status, hipStream_t st) {
   if (B <= 0) return;
-  auto* kernel = V <= SV_REG_TILES * SV_TILE ? verify_sample_kernel<SV_REG_TILES> : verify_sample_kernel<0>;
+  const double inv = temperature_reciprocal(temperature);
+  const StepsPerScore steps(temperature);
+  auto* kernel = MN_ROW_KERNEL(verify_sample_kernel, 6, V, inv);
   kernel<<<dim3(k_max + 1, B), SV_THREADS, 0, st>>>(
-      logits, voted, draft_probs, spec_len, greedy, B, k_max, M, V, temperature, temperature_reciprocal(temperature),
+      logits, voted, draft_probs, spec_len, greedy, B, k_max, M, V, temperature, inv, steps.k, steps.k_lo,
       (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), sampled, dev_status);
 }
 
 void launch_draft_sample(const float* logits, int B, int V, double temperature, uint64_t seed, uint64_t step, int ssm,
                          int t_pos, int32_t* tokens, long token_stride, float* probs, long probs_stride, hipStream_t st) {
   if (B <= 0) return;
-  auto* kernel = V <= SV_REG_TILES * SV_TILE ? draft_sample_kernel<SV_REG_TILES> : draft_sample_kernel<0>;
-  kernel<<<B, SV_THREADS, 0, st>>>(logits, V, temperature, temperature_reciprocal(temperature), (uint32_t)seed,
+  const double inv = temperature_reciprocal(temperature);
+  const StepsPerScore steps(temperature);
+  auto* kernel = MN_ROW_KERNEL(draft_sample_kernel, 8, V, inv);
+  kernel<<<B, SV_THREADS, 0, st>>>(logits, V, temperature, inv, steps.k, steps.k_lo, (uint32_t)seed,
                                    (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)(1 + ssm),
                                    (uint32_t)t_pos, tokens, token_stride, probs, probs_stride);
 }

@@ -470,3 +470,50 @@ def _check_draft_rows(hb, logits, T):
         assert np.allclose(q[b], q32, rtol=3e-7, atol=1e-45), b
         if gap > 1e-6:
             assert tok[b] == want, (b, tok[b], want)
+
+
+# Where the form with a row's exponentials in registers changes: fewer tokens than a piece, pieces that straddle the end, every number
+# of tiles, tiles behind the registers; whole waves masked, scores far from zero, and a largest score behind the registers that is so far above the
+# rest that the row falls back to the general form
+@pytest.mark.parametrize("V", [2, 4, 5, 1026, 4099, 8191, 8193, 16384, 16387, 32766, 36865, 50272, 65537, 262144])
+def test_rows_in_registers_against_oracle(hb, V):
+    B, k_max, T = 6, 2, 0.7
+    spec, M, logits, q, voted = _case(41, B, k_max, V, T, 1.0)
+    blocks = np.arange(V) // 256 % 16                     # (the wave that holds a token)
+    if V > 5:
+        logits[0, (blocks == 3) & (np.arange(V) > 0)] = -np.inf
+        logits[1, blocks > 0] = -np.inf
+    logits[2] += 3000.0
+    logits[3] -= 1e4
+    logits[4, V - 1] += 60.0
+    logits[5 % M, V - 1] += 300.0
+    ctx0 = np.arange(B).astype(np.int32)
+    for step in (0, 1):
+        res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=7, step=step, ctx0=ctx0)
+        _check_against_oracle(res, spec, logits, q, voted, k_max, T, 7, step, ctx0)
+    _check_draft_rows(hb, logits, T)
+
+
+@pytest.mark.parametrize("V", [300, 32000, 50272])
+def test_scores_that_are_not_numbers_stay_in_their_row(hb, V):
+    """A row with a NaN or an infinite score has no distribution: no token is drawn from it, and the rows beside it keep theirs."""
+    harness, binding = hb
+    g = synth.stream(4107, V)
+    logits = g.normal(0.0, 2.0, (5, V)).astype(np.float32)
+    logits[1, V - 2], logits[3, 4], logits[4] = np.nan, np.inf, -np.inf
+    log_d = _dev(logits, torch.float32)
+    tok_d = torch.full((5,), -5, dtype=torch.int32, device="cuda:0")
+    q_d = torch.full((5, V), -1.0, dtype=torch.float32, device="cuda:0")
+    binding.mn_draft_sample(None, log_d.data_ptr(), 5, V, 1.0, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
+    spec, greedy = _dev(np.zeros(5, np.int32)), _dev(np.zeros((5, 1), np.int32))
+    out = torch.full((5, 1), -9, dtype=torch.int32, device="cuda:0")
+    binding.mn_verify_sample(None, log_d.data_ptr(), None, None, spec.data_ptr(), greedy.data_ptr(), 5, 0, 5, V, 1.0, 9, 2, out.data_ptr(), None,
+                             harness.stream_ptr())
+    torch.cuda.synchronize()
+    tok, q, ver = tok_d.cpu().numpy(), q_d.cpu().numpy(), out.cpu().numpy()[:, 0]
+    for b in range(5):
+        if b in (1, 3, 4):
+            assert tok[b] == -1 and ver[b] == -1 and np.isnan(q[b]).any()
+        else:
+            want, q32, gap = orc.draft_sample(logits[b], 1.0, 9, 2, 1, b, 3)
+            assert np.allclose(q[b], q32, rtol=3e-7, atol=1e-45) and (gap <= 1e-6 or tok[b] == want) and 0 <= ver[b] < V
