@@ -37,8 +37,14 @@ def to_device_act(a: np.ndarray, dtype: int) -> torch.Tensor:
     return torch.from_numpy(a).to(_dev())
 
 
+# The current stream's handle without a Stream object around it (0.3 us, three times a step; 2.7 with one).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def stream_ptr() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def pack_matrix(w: torch.Tensor, interleave_half: int = 0, dev_status: Optional[torch.Tensor] = None) -> torch.Tensor:
