@@ -12,7 +12,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libminions_verify.so")
 SOURCES = ("api.hip", "vote_accept.hip", "rows.hip", "gemm.hip", "gemm_small.hip", "attention.hip", "stochastic.hip", "probe.hip", "selector.cpp")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-variable",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]  # leading kernel arguments in scalar registers (csrc/launch.h)
 
 
 def _hipcc() -> str:

@@ -47,7 +47,11 @@ constexpr int GEN_NEW_ROWS = 17;
 constexpr int GEN_KPIECES = 8;
 constexpr int GEN_VPRE = 4;   // groups of four values of a chunk asked for before its softmax
 template <typename TA, typename T, int GEN_THREADS, bool FUSED>
-__global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(AttnArgs a) {
+__global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(const int32_t* row_seq_, const int32_t* row_pos_, const int32_t* row_j_,
+                                                                    const int32_t* row_slot_, const int32_t* block_tables_, int H_,
+                                                                    int Hkv_, int hd_, int block_size_, AttnArgs a) {
+  a.rows.row_seq = row_seq_; a.rows.row_pos = row_pos_; a.rows.row_j = row_j_; a.rows.row_slot = row_slot_;  // (launch.h: leading
+  a.kv.block_tables = block_tables_; a.H = H_; a.Hkv = Hkv_; a.hd = hd_; a.kv.block_size = block_size_;      // arguments)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float* s_new = reinterpret_cast<float*>(smem);  // [2][rows of the sequence up to m][hd]: K, V
   __shared__ float s_q[256];
@@ -324,14 +328,25 @@ __device__ __forceinline__ f16x8 softmax_tile(const f32x4& S0, const f32x4& S1, 
 
 template <int N> struct IntC { static constexpr int value = N; };
 
+// leading arguments of the two MFMA kernels (launch.h)
+#define MN_ATTN_LEAD                                                                                                    \
+  int32_t *items_, const int32_t *seq_row0_, const int32_t *seq_ok_, const int32_t *seq_ctx_, const int32_t *block_tables_, \
+      int Hkv_, int H_, int max_blocks_, int num_blocks_
+#define MN_ATTN_TAKE_LEAD                                                                                \
+  a.items = items_; a.rows.seq_row0 = seq_row0_; a.rows.seq_ok = seq_ok_; a.rows.seq_ctx = seq_ctx_;     \
+  a.kv.block_tables = block_tables_; a.Hkv = Hkv_; a.H = H_; a.kv.max_blocks_per_seq = max_blocks_; a.kv.num_blocks = num_blocks_;
+#define MN_ATTN_LEAD_OF(a) \
+  (a).items, (a).rows.seq_row0, (a).rows.seq_ok, (a).rows.seq_ctx, (a).kv.block_tables, (a).Hkv, (a).H, (a).kv.max_blocks_per_seq, (a).kv.num_blocks
+
 // Partials: o_part [split][M][H][HD] fp32 (unnormalised), ml_part [split][M][H][2] = (max in log2 units, sum)
 // NW waves per workgroup.  Waves 0-3 are the loaders (the tile's 16 fragments are dealt to four waves); with 5 or
 // 6 waves the others only multiply: a stack of 65-96 query rows (5 or 6 column tiles, e.g. 8 query heads per KV
 // head x 9-12 scored positions) then gives every wave one column tile, where four waves would leave one of them
 // two tiles' worth of products and softmax per key tile while the other three wait at the barrier.
 template <int CTW, int NW>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(AttnArgs a, float* __restrict__ o_part,
+__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_ATTN_LEAD, AttnArgs a, float* __restrict__ o_part,
                                                                              float* __restrict__ ml_part) {
+  MN_ATTN_TAKE_LEAD
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   f16_t* s_kv = reinterpret_cast<f16_t*>(smem);                          // [NS][16 fragments][64 lanes][8]
   int32_t* s_bidx = reinterpret_cast<int32_t*>(smem + NS * TILE_BYTES);  // physical block of every block of the split
@@ -601,7 +616,8 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(Att
 // 1.1 % (17 %) of that rest was lost.
 template <int HDIM, int CT, int NW, bool FUSED>
 __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT == 1 ? 2 : 1))
-    attn_keys_kernel(AttnArgs a, float* __restrict__ o_part, float* __restrict__ ml_part) {
+    attn_keys_kernel(MN_ATTN_LEAD, AttnArgs a, float* __restrict__ o_part, float* __restrict__ ml_part) {
+  MN_ATTN_TAKE_LEAD
   constexpr bool WIDE = HDIM == 64;                          // queries unscaled, probabilities in two terms
   constexpr int HS = HDIM / 32, NU = HDIM / 16, OROW = HDIM + 4;  // (padded rows: the merge's 16-byte accesses spread over the banks)
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -1078,7 +1094,7 @@ static hipError_t launch_keys_nw(const AttnArgs& a, const MfmaShape& sh, float* 
     attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(attn_keys_kernel<HDIM, CT, NW, FUSED>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
   });
   if (attr_err != hipSuccess) return attr_err;
-  attn_keys_kernel<HDIM, CT, NW, FUSED><<<(unsigned)a.Hkv * (unsigned)sh.grid_items, NW * 64, smem, st>>>(a, o_part, ml_part);
+  attn_keys_kernel<HDIM, CT, NW, FUSED><<<(unsigned)a.Hkv * (unsigned)sh.grid_items, NW * 64, smem, st>>>(MN_ATTN_LEAD_OF(a), a, o_part, ml_part);
   return hipSuccess;
 }
 template <int HDIM, int CT>
@@ -1100,8 +1116,10 @@ static void launch_generic(const AttnArgs& a, hipStream_t st) {
   const dim3 grid(a.H, a.M);
   const bool wide = a.max_ctx > 256 && (long)a.M * a.H <= (a.max_ctx > GEN_LONG ? GEN_PAIRS : GEN_ALONE);
   const size_t smem = FUSED ? (size_t)2 * a.max_q * a.hd * sizeof(float) : 0;
-  if (wide) attn_generic_kernel<TA, T, 1024, FUSED><<<grid, 1024, smem, st>>>(a);
-  else attn_generic_kernel<TA, T, 256, FUSED><<<grid, 256, smem, st>>>(a);
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<grid, threads, smem, st>>>(a.rows.row_seq, a.rows.row_pos, a.rows.row_j, a.rows.row_slot, a.kv.block_tables, a.H, a.Hkv, a.hd, a.kv.block_size, a);
+  };
+  wide ? launch(attn_generic_kernel<TA, T, 1024, FUSED>, 1024) : launch(attn_generic_kernel<TA, T, 256, FUSED>, 256);
 }
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
@@ -1142,10 +1160,10 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
     });
     if (attr_err != hipSuccess) return attr_err;
     const unsigned grid = (unsigned)a.Hkv * (unsigned)sh.grid_items;
-    if (sh.nw == 5) attn_mfma_kernel<1, 5><<<grid, 320, smem, st>>>(a, o_part, ml_part);
-    else if (sh.nw == 6) attn_mfma_kernel<1, 6><<<grid, 384, smem, st>>>(a, o_part, ml_part);
-    else if (sh.ctw == 1) attn_mfma_kernel<1, 4><<<grid, 256, smem, st>>>(a, o_part, ml_part);
-    else attn_mfma_kernel<2, 4><<<grid, 256, smem, st>>>(a, o_part, ml_part);
+    if (sh.nw == 5) attn_mfma_kernel<1, 5><<<grid, 320, smem, st>>>(MN_ATTN_LEAD_OF(a), a, o_part, ml_part);
+    else if (sh.nw == 6) attn_mfma_kernel<1, 6><<<grid, 384, smem, st>>>(MN_ATTN_LEAD_OF(a), a, o_part, ml_part);
+    else if (sh.ctw == 1) attn_mfma_kernel<1, 4><<<grid, 256, smem, st>>>(MN_ATTN_LEAD_OF(a), a, o_part, ml_part);
+    else attn_mfma_kernel<2, 4><<<grid, 256, smem, st>>>(MN_ATTN_LEAD_OF(a), a, o_part, ml_part);
     launch_merge(a, n_splits, o_part, ml_part, st);
     return hipSuccess;
   }

@@ -745,8 +745,11 @@ __global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__
 // with matrices of 3072 columns at most 768 wide 40 and 40, 71 and 85.
 constexpr int F32_NORM_K = 512;              // widest row
 template <int F32_TRIP>
-__global__ void __launch_bounds__(512) gemm_f32_norm_kernel(NormArgs r, float* __restrict__ x_new, const float* __restrict__ W, float* __restrict__ out,
-                                                            const float* __restrict__ bias, int M, int N, int relu) {
+__global__ void __launch_bounds__(512) gemm_f32_norm_kernel(const float* __restrict__ W, float* x_, const float* partials_, const float* gain_,
+                                                            const void* tok_emb_, int M, int N, int d_, int n_partials_, NormArgs r,
+                                                            float* __restrict__ x_new, float* __restrict__ out,
+                                                            const float* __restrict__ bias, int relu) {
+  r.x = x_; r.partials = partials_; r.gain = gain_; r.tok_emb = tok_emb_; r.d = d_; r.n_partials = n_partials_;  // (launch.h: leading arguments)
   __shared__ f32x4 s_h[8][F32_TRIP * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, K = r.d;
   const int n = blockIdx.x * 8 + wave, m0 = blockIdx.y * 8, rows = min(8, M - m0);
@@ -1079,7 +1082,8 @@ static void launch_f32(const GemmArgs& a, hipStream_t st) {
   const int relu = a.relu_act != nullptr;
   if constexpr (TRIP * 256 <= F32_NORM_K) {
     if (a.norm) {
-      gemm_f32_norm_kernel<TRIP><<<dim3((a.N + 7) / 8, (a.M + 7) / 8), 512, 0, st>>>(*a.norm, a.x_new, W, out, a.bias, a.M, a.N, relu);
+      gemm_f32_norm_kernel<TRIP><<<dim3((a.N + 7) / 8, (a.M + 7) / 8), 512, 0, st>>>(
+          W, a.norm->x, a.norm->partials, a.norm->gain, a.norm->tok_emb, a.M, a.N, a.norm->d, a.norm->n_partials, *a.norm, a.x_new, out, a.bias, relu);
       return;
     }
   }

@@ -46,7 +46,11 @@ __device__ __forceinline__ f16x8 norm8(const float* x, const float* gain, float 
 // CT x RT tiles of 16 columns x 16 rows per workgroup (HALF: 8 rows, each twice in the MFMA, whose other half is thrown away), NW waves
 // along k, UF k-steps of 32 in flight per wave.
 template <int CT, int RT, int NW, int UF, int MODE, bool HALF = false>
-__global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(SmallGemmArgs a) {
+__global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(const void* a_, const void* w_, int M_, int N_, int K_, int ss_tiles_,
+                                                                                 float* p0_, float* p1_, float* rstd_, SmallGemmArgs a) {
+  a.a = a_; a.w = w_; a.M = M_; a.N = N_; a.K = K_; a.ss_tiles = ss_tiles_; a.rstd = rstd_;  // (launch.h: leading arguments)
+  if (MODE == SMALL_RESIDUAL) { a.x = p0_; a.gain = p1_; }
+  else { a.ss = p0_; a.inv_sc = p1_; }
   constexpr int NT = NW * 64, ROWS = HALF ? 8 : 16 * RT, TILES = CT * RT;
   constexpr bool TWO = NW * TILES > 48;      // the upper half of the waves hands its sums to the lower half first
   constexpr int NA = TWO ? NW / 2 : NW;
@@ -270,7 +274,8 @@ template <int CT, int RT, int NW, int UF, int MODE, bool HALF = false>
 static void launch_small_u(const SmallGemmArgs& a, hipStream_t st) {
   constexpr int ROWS = HALF ? 8 : 16 * RT;
   const int groups = ((a.N + 15) / 16 + CT - 1) / CT, rgs = (a.M + ROWS - 1) / ROWS;
-  gemm_small_kernel<CT, RT, NW, UF, MODE, HALF><<<(groups + 7) / 8 * 8 * rgs, NW * 64, 0, st>>>(a);
+  gemm_small_kernel<CT, RT, NW, UF, MODE, HALF><<<(groups + 7) / 8 * 8 * rgs, NW * 64, 0, st>>>(
+      a.a, a.w, a.M, a.N, a.K, a.ss_tiles, MODE == SMALL_RESIDUAL ? a.x : a.ss, MODE == SMALL_RESIDUAL ? const_cast<float*>(a.gain) : a.inv_sc, a.rstd, a);
 }
 // Waves and k-steps in flight, so that every wave asks for its whole k range at once: eight waves of three k-steps for K up to 768, of four
 // beyond; where the residual stream wants whole sums of a long K, 16 waves of six up to 3072 and of eight beyond.  With three and six

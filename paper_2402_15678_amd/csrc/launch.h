@@ -1,5 +1,10 @@
 // Internal launchers: one per kernel family.  Host-side shape checks happen in api.hip; the
 // launchers assume validated arguments and only translate them into grids.
+//
+// Leading arguments.  The command processor puts the first 14 dwords of a kernel's arguments into scalar registers before its
+// waves start (build.py: -amdgpu-kernarg-preload-count); everything behind them, and every field of a struct wherever it stands,
+// is a scalar load whose round trip the first memory access of every launch waits for.  So what a kernel's first addresses are
+// made of is passed twice, as leading plain arguments and in its struct, and the kernel writes the former over the latter.
 #pragma once
 #include "common.h"
 

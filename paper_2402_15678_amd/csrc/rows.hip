@@ -74,7 +74,11 @@ __device__ __forceinline__ void rope_rows(const PrepArgs& a, const int32_t* s_ro
 }
 
 // LDS: six int32 arrays of B + 1 entries
-__global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(PrepArgs a) {
+__global__ void __launch_bounds__(PREP_THREADS) prepare_kernel(const int32_t* spec_len_, const int32_t* ctx_lens_, const int32_t* block_tables_,
+                                                                const int32_t* last_tok_, const int32_t* voted_, int B_, int max_q_,
+                                                                int max_blocks_, int k_max_, PrepArgs a) {
+  a.spec_len = spec_len_; a.ctx_lens = ctx_lens_; a.block_tables = block_tables_; a.last_tok = last_tok_;  // (launch.h: leading arguments)
+  a.voted = voted_; a.B = B_; a.max_q = max_q_; a.max_blocks_per_seq = max_blocks_; a.k_max = k_max_;
   extern __shared__ __attribute__((aligned(16))) int32_t s_prep[];
   __shared__ int32_t s_wave[PREP_THREADS / 64];
   __shared__ int s_bad;
@@ -323,7 +327,7 @@ hipError_t launch_prepare(const PrepArgs& a, hipStream_t st) {
   if (attr_err != hipSuccess) return attr_err;
   const int rows = a.rope_half > 0 ? PREP_THREADS / a.rope_half : 1;
   const int rope_wgs = a.rope_half > 0 && a.M > 0 ? (a.M + rows - 1) / rows : 0;
-  prepare_kernel<<<1 + rope_wgs, PREP_THREADS, smem, st>>>(a);
+  prepare_kernel<<<1 + rope_wgs, PREP_THREADS, smem, st>>>(a.spec_len, a.ctx_lens, a.block_tables, a.last_tok, a.voted, a.B, a.max_q, a.max_blocks_per_seq, a.k_max, a);
   return hipSuccess;
 }
 
@@ -369,7 +373,10 @@ __device__ __forceinline__ void store1<f16_t>(f16_t* p, float v, bool& bad) { *p
 
 // T: storage type of the embedding tables; TA: activation type of the normalised output
 template <typename T, typename TA, int NORM_THREADS>
-__global__ void __launch_bounds__(NORM_THREADS) norm_kernel(NormArgs a) {
+__global__ void __launch_bounds__(NORM_THREADS) norm_kernel(float* x_, const float* partials_, const float* gain_, const float* shift_,
+                                                             const void* tok_emb_, int d_, int M_, int n_partials_, NormArgs a) {
+  a.x = x_; a.partials = partials_; a.gain = gain_; a.shift = shift_;  // (launch.h: leading arguments)
+  a.tok_emb = tok_emb_; a.d = d_; a.M = M_; a.n_partials = n_partials_;
   __shared__ float red[2][NORM_THREADS / 64];
   const int m = blockIdx.x;
   const int tid = threadIdx.x;
@@ -465,13 +472,11 @@ __global__ void __launch_bounds__(NORM_THREADS) norm_kernel(NormArgs a) {
 void launch_norm(const NormArgs& a, hipStream_t st) {
   if (a.M <= 0) return;
   const bool narrow = a.d <= 1024;
-  if (a.dtype == MN_DT_BF16) {
-    if (narrow) norm_kernel<bf16_t, f16_t, 256><<<a.M, 256, 0, st>>>(a);
-    else norm_kernel<bf16_t, f16_t, 1024><<<a.M, 1024, 0, st>>>(a);
-  } else {
-    if (narrow) norm_kernel<float, float, 256><<<a.M, 256, 0, st>>>(a);
-    else norm_kernel<float, float, 1024><<<a.M, 1024, 0, st>>>(a);
-  }
+  auto launch = [&](auto kernel, int threads) {
+    kernel<<<a.M, threads, 0, st>>>(a.x, a.partials, a.gain, a.shift, a.tok_emb, a.d, a.M, a.n_partials, a);
+  };
+  if (a.dtype == MN_DT_BF16) narrow ? launch(norm_kernel<bf16_t, f16_t, 256>, 256) : launch(norm_kernel<bf16_t, f16_t, 1024>, 1024);
+  else narrow ? launch(norm_kernel<float, float, 256>, 256) : launch(norm_kernel<float, float, 1024>, 1024);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -488,7 +493,11 @@ void launch_norm(const NormArgs& a, hipStream_t st) {
 constexpr int ROPE_THREADS = 256;
 constexpr int ROPE_WIDE_ROWS = 97, ROPE_WIDE_GROUP = 4;  // fewest rows and query heads per KV head for four pairs
 template <typename TA, typename T, int W>
-__global__ void __launch_bounds__(ROPE_THREADS) rope_append_kernel(RopeAppendArgs a) {
+__global__ void __launch_bounds__(ROPE_THREADS) rope_append_kernel(const int32_t* row_slot_, const float* qkv_, const float* rope_cos_,
+                                                                    const float* rope_sin_, int H_, int Hkv_, int hd_, int n_partials_,
+                                                                    int M_, RopeAppendArgs a) {
+  a.rows.row_slot = row_slot_; a.qkv = qkv_; a.rope_cos = rope_cos_; a.rope_sin = rope_sin_;  // (launch.h: leading arguments)
+  a.H = H_; a.Hkv = Hkv_; a.hd = hd_; a.n_partials = n_partials_; a.M = M_;
   struct alignas(4 * W) Piece { float x[W]; };
   struct alignas(4) PieceU { float x[W]; };                    // (biases start at any float's address)
   constexpr int PB = W == 1 ? 8 : 4;                           // partial sums in flight
@@ -582,8 +591,10 @@ template <int W>
 static void launch_rope_w(const RopeAppendArgs& a, hipStream_t st) {
   const int per_block = ROPE_THREADS / (a.hd / (2 * W));  // head_dim is one of 8 ... 256: hd/8 divides 256
   dim3 grid((a.H + 2 * a.Hkv + per_block - 1) / per_block, a.M);
-  if (a.dtype == MN_DT_BF16) rope_append_kernel<f16_t, f16_t, W><<<grid, ROPE_THREADS, 0, st>>>(a);
-  else rope_append_kernel<float, float, W><<<grid, ROPE_THREADS, 0, st>>>(a);
+  auto launch = [&](auto kernel) {
+    kernel<<<grid, ROPE_THREADS, 0, st>>>(a.rows.row_slot, a.qkv, a.rope_cos, a.rope_sin, a.H, a.Hkv, a.hd, a.n_partials, a.M, a);
+  };
+  a.dtype == MN_DT_BF16 ? launch(rope_append_kernel<f16_t, f16_t, W>) : launch(rope_append_kernel<float, float, W>);
 }
 void launch_rope_append(const RopeAppendArgs& a, hipStream_t st) {
   if (a.M <= 0) return;
