@@ -21,7 +21,12 @@
 // Bound by launch and round trips: at 16 rows a launch takes 4.3 (QKV), 4.8 (output), 5.2 (gate||up) and 6.6 us (down, which
 // brings 98 KB of weights and 98 KB of activations to each of 48 CUs); without any loads they take 3.9 to 4.4.  Per launch and
 // layer of the 768-wide model before: norm 2 x 3.8, QKV and output 4.3, gate||up 6.2, down 4.6 us; at 95 rows 2 x 3.9, 6.5,
-// 4.7, 9.9 and 7.0, now 5.1, 4.8, 8.4 and 7.8.
+// 4.7, 9.9 and 7.0, then 5.1, 4.8, 8.4 and 7.8.
+// A launch is one chain, so nothing in it may wait for what it does not need.  The compiler's code had three waits too many: for
+// the sums of squares (or the residual row) before the weights were asked for, because loads of k-steps past the end were pending
+// at the loop's back edge or the row stood behind a condition; for the first weights before the last were asked for; and for every
+// second wave's sums in the LDS.  Without them and without a division per workgroup, 12 layers, whole passes: 16 rows at 16 keys
+// 327 -> 310 us, at 1024 keys 434.6 -> 419.8; 95 rows 501.2 -> 493.6.
 #include "launch.h"
 #include "tune.h"
 #include "../../include/minions_verify.h"
@@ -58,10 +63,10 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(c
   __shared__ f32x4 s_acc[NA][TILES][64];
   __shared__ float s_part[NW][ROWS];
   static_assert(TILES * 64 <= NT || MODE != SMALL_RESIDUAL, "one piece per thread");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, g = lane >> 4;
   // id -> (column group, row group): the row groups of a column group on one XCD, whose L2 then holds its weights once
-  const int groups = ((a.N + 15) / 16 + CT - 1) / CT, rgs = (a.M + ROWS - 1) / ROWS;
-  const int cg = (int)blockIdx.x / (8 * rgs) * 8 + ((int)blockIdx.x & 7), rg = ((int)blockIdx.x >> 3) % rgs;
+  // (ids are dealt to the XCDs in turn, x first)
+  const int groups = ((a.N + 15) / 16 + CT - 1) / CT, cg = (int)blockIdx.z * 8 + (int)blockIdx.x, rg = blockIdx.y;
   if (cg >= groups) return;  // (whole workgroup: padding of the grid)
   const int t0 = cg * CT, m0 = rg * ROWS;
   const bool scaled = MODE != SMALL_RESIDUAL && a.ss != nullptr;
@@ -76,15 +81,18 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(c
 #pragma unroll
     for (int u = 0; u < SS; ++u) ss_v[u] = a.ss[(size_t)min(share + u * SHARES, a.ss_tiles - 1) * a.M + m];
   }
-  // the residual stream's old values and the next norm's gains (each thread owns one piece of four columns of a row)
-  const int pm = m0 + (tid >> 6) % RT * 16 + (HALF ? l16 & 7 : l16), pn = (t0 + (tid >> 6) / RT) * 16 + 4 * g;  // tile = ct * RT + rt
-  f32x4 x_old = {0.f, 0.f, 0.f, 0.f}, gain = x_old;
-  float rs_old = 1.f;
+  // the residual stream's old values and the next norm's gains (each thread owns one piece of four columns of a row; the others
+  // ask for one as well: behind a condition the loads would be waited for before the weights are asked for)
+  const int pt = min(wave, TILES - 1);       // tile = ct * RT + rt
+  const int pm = m0 + pt % RT * 16 + (HALF ? l16 & 7 : l16), pn = (t0 + pt / RT) * 16 + 4 * g;
+  f32x4 x_old, gain;
+  float rs_old;
   const bool piece = MODE == SMALL_RESIDUAL && tid < TILES * 64 && pm < a.M && pn < a.N && !(HALF && l16 >= 8);
-  if (piece) {
-    x_old = *reinterpret_cast<const f32x4*>(a.x + (size_t)pm * a.N + pn);
-    gain = *reinterpret_cast<const f32x4*>(a.gain + pn);
-    rs_old = a.rstd[pm];
+  if (MODE == SMALL_RESIDUAL) {
+    const int cm = min(pm, a.M - 1), cn = min(pn, a.N - 4);
+    x_old = *reinterpret_cast<const f32x4*>(a.x + (size_t)cm * a.N + cn);
+    gain = *reinterpret_cast<const f32x4*>(a.gain + cn);
+    rs_old = a.rstd[cm];
   }
 
   const int ks_all = a.K / KSTEP, per = (ks_all + NW - 1) / NW;
@@ -133,7 +141,9 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(c
           }
         }
       }
-      asm volatile("" ::: "memory");         // (every load goes out before the first product)
+      __builtin_amdgcn_sched_barrier(0);     // (every load goes out before the first product)
+      if constexpr (!SLOW)                   // (and the arguments that the end needs are fetched meanwhile)
+        asm volatile("" ::"s"(a.out), "s"(a.inv_d), "s"(a.eps), "s"(a.dev_status), "s"(a.x), "s"(a.gain), "s"(a.ss), "s"(a.inv_sc));
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (kk + u >= k1) break;             // (wave-uniform)
@@ -142,6 +152,9 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(c
 #pragma unroll
           for (int r = 0; r < RT; ++r) acc[c][r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wf[u][c]), af[u][r], acc[c][r], 0, 0, 0);
       }
+      // (vmcnt(0): loads of k-steps past the end, pending at the back edge, would make the first pass wait for the sums of
+      // squares before it asks for its weights)
+      __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
     }
     if constexpr (TWO) {
       if (wave >= NA) {
@@ -208,9 +221,13 @@ __global__ void __launch_bounds__(NW * 64, NW >= 16 ? 1 : 2) gemm_small_kernel(c
 
   // lane holds D[n = 4g + i][m = l16] of a tile; the waves' sums are added in wave order
   auto total = [&](int tile, int ln) {
-    f32x4 v = s_acc[0][tile][ln];
+    f32x4 p[NA];
 #pragma unroll
-    for (int w = 1; w < NA; ++w) v += s_acc[w][tile][ln];
+    for (int w = 0; w < NA; ++w) p[w] = s_acc[w][tile][ln];
+    __builtin_amdgcn_sched_barrier(0);       // (one round trip to the LDS, not one for every second wave)
+    f32x4 v = p[0];
+#pragma unroll
+    for (int w = 1; w < NA; ++w) v += p[w];
     return v;
   };
   if constexpr (MODE == SMALL_OUT) {
@@ -274,7 +291,7 @@ template <int CT, int RT, int NW, int UF, int MODE, bool HALF = false>
 static void launch_small_u(const SmallGemmArgs& a, hipStream_t st) {
   constexpr int ROWS = HALF ? 8 : 16 * RT;
   const int groups = ((a.N + 15) / 16 + CT - 1) / CT, rgs = (a.M + ROWS - 1) / ROWS;
-  gemm_small_kernel<CT, RT, NW, UF, MODE, HALF><<<(groups + 7) / 8 * 8 * rgs, NW * 64, 0, st>>>(
+  gemm_small_kernel<CT, RT, NW, UF, MODE, HALF><<<dim3(8, rgs, (groups + 7) / 8), NW * 64, 0, st>>>(
       a.a, a.w, a.M, a.N, a.K, a.ss_tiles, MODE == SMALL_RESIDUAL ? a.x : a.ss, MODE == SMALL_RESIDUAL ? const_cast<float*>(a.gain) : a.inv_sc, a.rstd, a);
 }
 // Waves and k-steps in flight, so that every wave asks for its whole k range at once: eight waves of three k-steps for K up to 768, of four
