@@ -597,12 +597,14 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_
 // groups, a drafting model catching up.  There is nothing for the waves of a workgroup to share, so instead of staging
 // tiles in LDS behind a barrier every wave takes key tiles of its own (wave w of a workgroup the tiles w, w + NW, ... of
 // its range), loads their K and V pieces straight into the operand registers of its MFMAs and keeps its own (max, sum, output).
-// The next tile's loads are in flight during this one's softmax and second product, no earlier: they wait for their two block ids,
-// which are vector loads behind this tile's, and loads complete in order, so that all of this tile has landed by then.  A tile costs
-// one round trip for its ids and one for its data.  The waves' results meet once, in LDS, at the end.
+// The waves' results meet once, in LDS, at the end.
 // Measured per layer, rotary/append included: 95 rows of 16 requests x 12 heads of 64, contexts 200-1500: 139 -> 16.2 us;
 // 16 x 1024 keys of the same model 17.1 -> 15.7 us; 8 x 512 keys x 40 heads of 128 29.2 -> 25.0 us.
-// Bound by the KV stream and, at short contexts, by the chain record -> block table -> first tile -> merge (about 6 us).
+// Bound by the KV stream (12 layers of 16 sequences take 8.2 us a layer more at 1024 keys than at 16, 50 MB at 6.1 TB/s) and, at
+// short contexts, by launch and the chain bookkeeping -> block table and QKV sums -> append -> tile -> merge (about 6 us).  The
+// append used to follow the wave's first tile, and every wave's second tile followed both: now it goes ahead of the first, its
+// loads all at once, and with 8 waves the block ids go ahead of the tiles that need them.  12 layers of that model, whole passes:
+// 16 x 1024 keys 419.8 -> 410.7 us, the 95 rows 493.6 -> 485.9.
 // FUSED: the workgroup also turns its rows' QKV partial sums into queries (kept in LDS) and K/V rows (written to the pages
 // before the tiles that hold them are read), which saves a launch of its own per layer; a sequence must then be in one KV
 // split, so that the rows have one writer.  When every workgroup is resident at once and nothing is split (no list:
@@ -636,6 +638,9 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
     b = item;
     row0 = a.rows.seq_row0[b]; qb = a.rows.seq_row0[b + 1] - row0; ok = a.rows.seq_ok[b]; ctx = a.rows.seq_ctx[b];
   }
+  if (FUSED)  // (the arguments that are used next are fetched with these)
+    asm volatile("" ::"s"(a.qkv), "s"(a.rope_cos), "s"(a.rope_sin), "s"(a.rows.row_slot), "s"(a.bias), "s"(a.kv.k), "s"(a.kv.v), "s"(a.M),
+                 "s"(a.n_partials), "s"(row0), "s"(ctx));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, g = lane >> 4;
@@ -663,10 +668,21 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
     u32x4 k[2 * HS], v[NU];
   };
   // (block ids are clamped: a damaged table never becomes a wild address)
-  auto load = [&](Tile& t, int i) {
+  struct Ids {
+    uint32_t a0, a1, b0, b1;
+  };
+  auto ids_of = [&](int i) {                                 // of the wave's tile i
     const int tile = t0 + NW * i;
-    const uint32_t b0 = min((uint32_t)bt[min(2 * tile, last_blk)], blk_last);
-    const uint32_t b1 = min((uint32_t)bt[min(2 * tile + 1, last_blk)], blk_last);
+    const uint32_t b0 = min((uint32_t)bt[min(2 * tile, last_blk)], blk_last), b1 = min((uint32_t)bt[min(2 * tile + 1, last_blk)], blk_last);
+    return Ids{b0, b1, 0, 0};
+  };
+  // of tiles i and i + 1, asked for here (in lanes 0 .. 3) and looked at later
+  auto ask = [&](int i) { return bt[min(2 * (t0 + NW * min(i + ((lane >> 1) & 1), max(n - 1, 0))) + (lane & 1), last_blk)]; };
+  auto answer = [&](int ids) {
+    auto id = [&](int at) -> uint32_t { return min((uint32_t)__builtin_amdgcn_readlane(ids, at), blk_last); };
+    return Ids{id(0), id(1), id(2), id(3)};
+  };
+  auto load = [&](Tile& t, uint32_t b0, uint32_t b1) {
     const char* kp = kbase + (uint64_t)(ksel ? b1 : b0) * blk_bytes;
     const char* vp = vbase + (uint64_t)(vsel ? b1 : b0) * blk_bytes;
     // (the two halves of a K line are asked for by different instructions: with 8 waves, where the workgroup has its CU to
@@ -683,29 +699,38 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
     for (int u = 0; u < NU; ++u) t.v[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vp + u * (16 * BS * (int)sizeof(f16_t))));
   };
   Tile ta, tb;
-  // (FUSED: a first tile that holds rows of this step is asked for after they have been written)
-  const bool early = !FUSED || (t0 + 1) * KT <= ctx;         // (wave-uniform)
-  if (n > 0 && early) load(ta, 0);
+  constexpr bool AHEAD = FUSED && NW == 8;                   // (see the loop over the tiles)
+  // (every wave asks: behind a condition the answers would be waited for once more below)
+  const int ids0 = AHEAD ? ask(0) : 0, ids1 = AHEAD ? ask(1) : 0;
+  Ids first{}, cur{};                                        // of tile 0; AHEAD: of tiles 1 and 2
+  if (!FUSED && n > 0) {
+    first = ids_of(0);
+    load(ta, first.a0, first.a1);
+  }
 
   constexpr int QROW = HDIM + 8;
   f16_t* s_q = reinterpret_cast<f16_t*>(smem);               // [R][QROW] (the merge reuses the space behind a barrier)
   if constexpr (FUSED) {
-    // thread item = four pairs (t .. t+3, and + hd/2) of one head of one row: the G query heads, the key head, the value head
+    // thread item = four pairs (t .. t+3, and + hd/2) of one head of one row: the G query heads, the key head, the value head.
+    // The last waves take them, which have the fewest tiles, and ahead of their first tile: loads complete in order, and behind
+    // it the K/V rows and the barrier, and so every wave's second tile, would wait for it.
     constexpr int HALF = HDIM / 2, Q4 = HALF / 4;
     const int ncols = (a.H + 2 * a.Hkv) * HDIM;
     bool bad = false;
-    for (int idx = tid; idx < (G + 2) * qb * Q4; idx += NW * 64) {
+    for (int idx = NW * 64 - 1 - tid; idx < (G + 2) * qb * Q4; idx += NW * 64) {
       const int t = (idx % Q4) * 4, rr = idx / Q4, j = rr % qb, hh = rr / qb;
       const int m = row0 + j;
+      int slot = a.rows.row_slot[m];                         // (-1: disabled)
       const int head = hh < G ? kvh * G + hh : (hh == G ? a.H + kvh : a.H + a.Hkv + kvh);
       const int c0 = head * HDIM + t;
       f32x4 v0 = {0.f, 0.f, 0.f, 0.f}, v1 = v0;
-      f32x4 cs = {1.f, 1.f, 1.f, 1.f}, sn = v0;
-      if (a.rope_cos && hh <= G) {
-        cs = *reinterpret_cast<const f32x4*>(a.rope_cos + (size_t)m * HALF + t);
-        sn = *reinterpret_cast<const f32x4*>(a.rope_sin + (size_t)m * HALF + t);
-      }
-      // partials fetched four at a time before any is added; the order of the sum is that of rope_append_kernel
+      // (angles and bias are asked for with the rest, there or not)
+      const float *spare = a.qkv + (size_t)m * ncols, *bias = a.bias ? a.bias : spare;
+      const f32x4 cs = *reinterpret_cast<const f32x4*>((a.rope_cos ? a.rope_cos + (size_t)m * HALF : spare) + t);
+      const f32x4 sn = *reinterpret_cast<const f32x4*>((a.rope_cos ? a.rope_sin + (size_t)m * HALF : spare) + t);
+      const f32x4_u b0 = *reinterpret_cast<const f32x4_u*>(bias + c0), b1 = *reinterpret_cast<const f32x4_u*>(bias + c0 + HALF);
+      // partials fetched four at a time before any is added (the fence keeps the compiler from putting the loads beside their
+      // sums); the order of the sum is that of rope_append_kernel
       for (int s0 = 0; s0 < a.n_partials; s0 += 4) {
         f32x4 p0[4], p1[4];
 #pragma unroll
@@ -714,15 +739,20 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
           p0[k] = *reinterpret_cast<const f32x4*>(p);
           p1[k] = *reinterpret_cast<const f32x4*>(p + HALF);
         }
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int k = 0; k < 4; ++k)
           if (s0 + k < a.n_partials) { v0 += p0[k]; v1 += p1[k]; }
+        // (vmcnt(0): repeats that are still on their way would be waited for ahead of the first partials at the back edge, and
+        // below by every wave, its tiles with them)
+        __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));
       }
       if (a.bias) {
-        const f32x4_u b0 = *reinterpret_cast<const f32x4_u*>(a.bias + c0), b1 = *reinterpret_cast<const f32x4_u*>(a.bias + c0 + HALF);
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v0[e] += b0[e]; v1[e] += b1[e]; }
       }
+      // (vmcnt(0): every wave, and its tiles with it, would wait below for partials that were asked for and not added)
+      asm volatile("" : "+v"(slot));                         // (asked for with the rest, not where it is used)
       if (a.rope_cos && hh <= G) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -731,7 +761,7 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
           v1[e] = y * cs[e] + x * sn[e];
         }
       }
-      if (hh > G - 1 && !ok) continue;                       // disabled sequence: nothing is written to the cache
+      if (hh > G - 1 && (!ok || slot < 0)) continue;         // disabled sequence: nothing is written to the cache
       const uint2 w0 = make_uint2(pack2h_sat(v0[0], v0[1], bad), pack2h_sat(v0[2], v0[3], bad));
       const uint2 w1 = make_uint2(pack2h_sat(v1[0], v1[1], bad), pack2h_sat(v1[2], v1[3], bad));
       if (hh < G) {
@@ -739,9 +769,8 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
         *reinterpret_cast<uint2*>(q) = w0;
         *reinterpret_cast<uint2*>(q + HALF) = w1;
       } else {
-        const int p = ctx + j;
-        const uint32_t blk = min((uint32_t)bt[min(p / BS, last_blk)], blk_last);
-        const int off = p % BS;
+        const uint32_t blk = min((uint32_t)(slot / BS), blk_last);
+        const int off = slot % BS;
         if (hh == G) {  // K: [hd/8][bs][8]
           f16_t* base = reinterpret_cast<f16_t*>(a.kv.k) + ((size_t)blk * a.Hkv + kvh) * (HDIM * BS);
           *reinterpret_cast<uint2*>(base + ((t >> 3) * BS + off) * 8 + (t & 7)) = w0;
@@ -755,8 +784,17 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
       }
     }
     if (bad && a.dev_status) atomicOr(a.dev_status, MN_DEV_RANGE);
+    // (a first tile that holds rows of this step is asked for after they have been written)
+    const bool early = (t0 + 1) * KT <= ctx;                 // (wave-uniform)
+    if (AHEAD) {
+      first = answer(ids0);
+      cur = answer(ids1);
+    } else if (n > 0) {
+      first = ids_of(0);
+    }
+    if (n > 0 && early) load(ta, first.a0, first.a1);
     __syncthreads();  // the queries are in LDS; the K/V rows are visible to the whole workgroup
-    if (n > 0 && !early) load(ta, 0);
+    if (n > 0 && !early) load(ta, first.a0, first.a1);
   }
 
   const float sscale = rsqrtf((float)HDIM) * LOG2E;
@@ -841,21 +879,38 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
   // Two tiles per pass of the loop, every load in it unconditional (behind a branch the compiler's wait counts would drain
   // the load queue).  Only a wave's last tile can reach past ctx: the rows of a sequence span at most CT <= NW - 1 tiles
   // beyond the first, and tiles are dealt to the waves in turn.
-  if (n > 0) {
-    int i = 0;
+  // AHEAD: a pass asks for the block ids of the next one ahead of its own tiles (loads complete in order, so they are there when
+  // those are), and two tiles are on their way at a time.  Elsewhere a tile's ids are asked for with it, behind the tile before,
+  // and one is: with 4 waves, and two workgroups per CU, two tiles each are too many (960 workgroups 90 -> 98 us).
+  if (n > 1) {
+    int i = 0;                                               // (AHEAD: cur holds the ids of tiles i + 1 and i + 2)
     for (; i + 2 < n; i += 2) {
-      load(tb, i + 1);
+      const int next = AHEAD ? ask(i + 3) : 0;
+      if (!AHEAD) cur = ids_of(i + 1);
+      load(tb, cur.a0, cur.a1);
+      if (AHEAD) __builtin_amdgcn_sched_barrier(0);
       work(IntC<0>{}, ta, i);
-      load(ta, i + 2);
+      if (AHEAD) {
+        load(ta, cur.b0, cur.b1);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        cur = ids_of(i + 2);
+        load(ta, cur.a0, cur.a1);
+      }
       work(IntC<0>{}, tb, i + 1);
+      if (AHEAD) cur = answer(next);
     }
     if (i + 1 < n) {
-      load(tb, i + 1);
+      if (!AHEAD) cur = ids_of(i + 1);
+      load(tb, cur.a0, cur.a1);
+      if (AHEAD) __builtin_amdgcn_sched_barrier(0);
       work(IntC<0>{}, ta, i);
       work(IntC<1>{}, tb, i + 1);
     } else {
       work(IntC<1>{}, ta, i);
     }
+  } else if (n == 1) {
+    work(IntC<1>{}, ta, 0);
   }
 
   // ---- merge over the waves, output ----

@@ -188,3 +188,18 @@ def test_marked_rows_leave_their_neighbours_alone(grown_by, rows):
     mixed = _logits(desc, W, ctx, ks, last, voted)
     other = np.repeat([b not in small for b in range(B)], np.asarray(ks) + 1)
     assert np.array_equal(mixed[other], plain[other])
+
+
+@pytest.mark.parametrize("desc", [NARROW, GROUPED], ids=["hd64", "hd128"])
+@pytest.mark.parametrize("copies", [1, 5], ids=["8-waves", "4-waves"])
+def test_fused_append_over_tiles_per_wave(desc, copies):
+    """The few-row attention kernel that appends: waves with no tile, one, two (both ends of the pass over two) and up to six, and
+    new rows that start, end or straddle a tile; with 8 waves (up to 256 workgroups) and with 4."""
+    desc = dataclasses.replace(desc, max_pos=1664)
+    ctx = [0, 1, 29, 31, 32, 61, 255, 256, 286, 509, 512, 767, 770, 1023, 1024, 1054, 1279, 1310, 1535, 1570][:20 if copies == 1 else 13]
+    ks = [(3 * i) % 4 for i in range(len(ctx))]
+    if copies > 1 and desc.n_kv_heads == 2:  # (more than 256 workgroups of two KV heads)
+        copies = 10
+    ctx, ks = ctx * copies, ks * copies
+    assert (len(ctx) * desc.n_kv_heads > 256) == (copies > 1)
+    _check(desc, synth.make_weights(desc, 91), ctx, ks, 95, util.TOL[desc.dtype])
