@@ -861,6 +861,14 @@ static bool small_matrix(int slices, int iters) {
 
 bool gemm_small_matrix(int N, int K) { return small_matrix((N + NWG - 1) / NWG * 4, K / KB); }
 
+// Unsplit matrices of 513 to 640 slices would leave 42 and more CUs idle (three waves each: 214 workgroups at most): their waves take 16
+// columns instead of 32, five to a workgroup, one workgroup per CU.  Partial sums of more than 64 rows stay with 32: a wave of 16 columns
+// stores half lines.  Cold weights, three (four below 600 slices) waves of 32 columns and five of 16: 20480 x 5120 at 1, 16, 33, 64, 96,
+// 144 rows 35.8 36.8 38.6 37.6 41.9 53.5 and 34.9 35.7 37.8 37.2 42.3 56.0 us, 17536 x 8192 49.6 51.1 53.8 53.0 60.0 74.9 and 47.3
+// 48.9 51.9 51.6 58.7 77.1; with bias and ReLU in the epilogue the 128 rows of a four-layer step gain too, 912 -> 902 us, its 80 rows
+// 788 -> 778.
+constexpr int NARROW_NW = 5, NARROW_ROWS = 64;
+
 // Waves per workgroup at 144 rows or fewer, for a matrix of so many 32-column slices cut into `split` k-splits.  Unsplit
 // matrices: a CU with w workgroups of NW waves takes about 0.15 + w (0.27 + 0.13 NW) us per iteration (the tile and the
 // barrier are paid per workgroup, the stream per wave), so the count that gives the busiest CU the least is taken.  Measured
@@ -870,7 +878,7 @@ bool gemm_small_matrix(int N, int K) { return small_matrix((N + NWG - 1) / NWG *
 // make more: above 96 rows, where the tile is dear, as many waves then as leave a workgroup per CU, eight if none do (97 and 144 rows, with four
 // waves and by this rule: 20480 x 5120 in 2 splits 61.3 69.6 us, 50.5 53.3; 10240 x 8192 in 4 52.1 57.9, 43.6 47.2; 8192 x 28672 in 8
 // 96.6 109, 88.4 95.1; 5120 x 1024 in 8, with two, 20.8 25.9, 18.7 23.1).
-static int few_rows_nw(int M, int slices, int iters, int split) {
+static int few_rows_nw(int M, int slices, int iters, int split, int epi) {
   const bool small = small_matrix(slices, iters);
   if (small && (M <= 96 || split == 1)) return M <= 32 ? 1 : 2;
   if (split > 1) {
@@ -878,6 +886,7 @@ static int few_rows_nw(int M, int slices, int iters, int split) {
     while (M > 96 && nw < 8 && (slices + nw - 1) / nw * split > 256) nw += nw == 2 ? 2 : 1;
     return nw;
   }
+  if (slices > 512 && slices <= 128 * NARROW_NW && epi != EPI_SWIGLU && (epi == EPI_RELU || M <= NARROW_ROWS)) return NARROW_NW;
   int best = 4, best_cost = 1 << 30;
   for (int nw : {4, 3, 7, 8}) {
     const int wgs = (slices + nw - 1) / nw, cost = 15 + (wgs + 255) / 256 * (27 + 13 * nw);
@@ -1013,9 +1022,11 @@ static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
   const f16_t* A = reinterpret_cast<const f16_t*>(a.a);
   const bf16_t* W = reinterpret_cast<const bf16_t*>(a.w);
   if constexpr (!SPLIT) {
-    if (a.swiglu_act) {
-      gemm_w16_kernel<MT, NTW, EPI_SWIGLU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.swiglu_act, nullptr, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
-      return;
+    if constexpr (NTW % 2 == 0) {  // (gate and up tiles alternate inside a wave)
+      if (a.swiglu_act) {
+        gemm_w16_kernel<MT, NTW, EPI_SWIGLU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.swiglu_act, nullptr, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+        return;
+      }
     }
     if (a.relu_act) {
       gemm_w16_kernel<MT, NTW, EPI_RELU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.relu_act, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
@@ -1028,10 +1039,13 @@ static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
 template <int MT>
 static void launch_few_rows(const GemmArgs& a, hipStream_t st) {
   constexpr int SMALL_NW = MT <= 2 ? 1 : 2;  // (small matrices: 32 rows or fewer, or more)
-  switch (few_rows_nw(a.M, ((a.N + NWG - 1) / NWG) * 4, a.K / KB, a.split_k)) {
+  switch (few_rows_nw(a.M, ((a.N + NWG - 1) / NWG) * 4, a.K / KB, a.split_k, a.swiglu_act ? EPI_SWIGLU : a.relu_act ? EPI_RELU : EPI_PARTIAL)) {
     case SMALL_NW: launch_bf16_mt<MT, SMALL_NW>(a, 1, st); break;
     case 3: launch_bf16_mt<MT, 3>(a, 1, st); break;
-    case 5: if constexpr (MT > 6) launch_bf16_mt<9, 5, true>(a, 1, st); break;  // (more than 96 rows: few_rows_nw)
+    case 5:
+      if (a.split_k == 1) launch_bf16_mt<MT, NARROW_NW, false, 1>(a, 1, st);
+      else if constexpr (MT > 6) launch_bf16_mt<9, 5, true>(a, 1, st);          // (more than 96 rows: few_rows_nw)
+      break;
     case 6: if constexpr (MT > 6) launch_bf16_mt<9, 6, true>(a, 1, st); break;
     case 7: launch_bf16_mt<MT, 7>(a, 1, st); break;
     case 8: launch_bf16_mt<MT, 8>(a, 1, st); break;

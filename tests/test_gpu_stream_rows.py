@@ -1,6 +1,6 @@
 """The streaming projection at 97 to 144 rows (seven, eight and nine row tiles, a last one that is not full) through the component
 entry point: automatic and given splits (8: five to eight waves per workgroup) against an fp64 product, partial columns of the packed
-matrix included."""
+matrix included; and waves of 16 columns."""
 import ctypes
 
 import numpy as np
@@ -34,18 +34,35 @@ def test_rows_and_splits(rows, N, K, split):
     assert bool(((out.double() - want).abs() <= bound).all())
 
 
+@pytest.mark.parametrize("rows", [1, 16, 17, 40, 64, 65])
+@pytest.mark.parametrize("N,K", [(16400, 256), (16500, 384), (20480, 128), (20481, 256), (16384, 256)])
+def test_sixteen_column_slices(rows, N, K):
+    """Unsplit matrices of 513 to 640 32-column slices, and one of each next to them (rows and columns)."""
+    test_rows_and_splits(rows, N, K, 1)
+
+
+@pytest.mark.parametrize("rows", [1, 17, 40, 65, 96, 144])
+def test_sixteen_column_slices_with_relu(rows):
+    _check_step(synth.ModelDesc(synth.ARCH_OPT, synth.DT_BF16, 1, 512, 8, 8, 64, 16512, 500, 256), rows)
+
+
 @pytest.mark.parametrize("rows", [97, 104, 112, 113, 128, 144])
 @pytest.mark.parametrize("arch", [synth.ARCH_OPT, synth.ARCH_LLAMA])
 def test_step_at_its_own_splits(arch, rows):
     """Inside a step these rows may take more splits than the entry points ask room for (the output projection of this width two instead
     of none): scores and cache rows of a layer against the CPU oracle."""
-    from paper_2402_15678_amd import binding, harness
+    from paper_2402_15678_amd import binding
     desc = synth.ModelDesc(arch, synth.DT_BF16, 1, 2048, 16, 16 if arch == synth.ARCH_OPT else 4, 128, 8192, 500, 256)
     pick, step = binding.lib._ZN2mn15gemm_pick_splitEiiii, binding.lib._ZN2mn15gemm_step_splitEiiiim
     room = ctypes.c_size_t(4 * rows * desc.d_ffn)    # (what gate||up or the first FFN matrix alone make of it)
     assert pick(rows, 2048, 2048, desc.dtype) == 1 and step(rows, 2048, 2048, desc.dtype, room) == 2
-    ks = np.asarray([7] * (rows // 8 - 1) + [7 + rows % 8], np.int32)
-    B, k_max = len(ks), int(ks.max())
+    _check_step(desc, rows)
+
+
+def _check_step(desc, rows):
+    from paper_2402_15678_amd import harness
+    ks = np.asarray([7] * (rows // 8 - 1) + [7 + rows % 8] if rows >= 8 else [rows - 1], np.int32)
+    B, k_max = len(ks), max(1, int(ks.max()))
     ctx = np.asarray([(29 * b + 3) % 60 for b in range(B)], np.int32)
     W = synth.make_weights(desc, 61)
     model = harness.DeviceModel.from_host(desc, W)
