@@ -335,6 +335,12 @@ template <int N> struct IntC { static constexpr int value = N; };
 #define MN_ATTN_TAKE_LEAD                                                                                \
   a.items = items_; a.rows.seq_row0 = seq_row0_; a.rows.seq_ok = seq_ok_; a.rows.seq_ctx = seq_ctx_;     \
   a.kv.block_tables = block_tables_; a.Hkv = Hkv_; a.H = H_; a.kv.max_blocks_per_seq = max_blocks_; a.kv.num_blocks = num_blocks_;
+// x / d (x >= 0) from inv = 1 / d: one too few or too many at most before the correction for x below 2^23, in ten instructions where a
+// division by a number that is not known when the kernel is compiled takes forty, each waiting for the one before
+__device__ __forceinline__ int fast_div(int x, int d, float inv) {
+  const int q = (int)((float)x * inv), r = x - q * d;
+  return q + (r >= d ? 1 : 0) - (r < 0 ? 1 : 0);
+}
 #define MN_ATTN_LEAD_OF(a) \
   (a).items, (a).rows.seq_row0, (a).rows.seq_ok, (a).rows.seq_ctx, (a).kv.block_tables, (a).Hkv, (a).H, (a).kv.max_blocks_per_seq, (a).kv.num_blocks
 
@@ -363,11 +369,16 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_
   const int4 rec0 = reinterpret_cast<const int4*>(a.items)[2 * item];
   const int4 rec1 = reinterpret_cast<const int4*>(a.items)[2 * item + 1];
   const int b = rec0.x, rg = rec0.y, split = rec0.z, my_splits = rec0.w;
-  if (b < 0) return;                      // past the end of the list (whole workgroup)
   const int row0 = rec1.x, qb = rec1.y, ok = rec1.z, ctx = rec1.w;
+  // (the whole record, and the arguments that are used next, in one round trip: the compiler would fetch each part where it is used,
+  // three round trips here, four for the queries below and one for the block ids; 32 x 8192 keys 212 -> 210 us, 24 ragged
+  // sequences in the few-row kernel, for its queries, 90.2 -> 89.0)
+  asm volatile("" ::"s"(b), "s"(rg), "s"(split), "s"(my_splits), "s"(row0), "s"(qb), "s"(ok), "s"(ctx), "s"(a.q), "s"(a.kv.k), "s"(a.kv.v));
+  if (b < 0) return;                      // past the end of the list (whole workgroup)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
   const int G = a.H / a.Hkv;
+  const float G_inv = __builtin_amdgcn_rcpf((float)G);
   const int R = G * qb;                   // query rows sharing this KV head; row r = j*G + gi
   const int NT16 = (R + 15) >> 4;         // column tiles in use
   const int tile0 = NW * CTW * rg;        // first column tile of this workgroup
@@ -376,10 +387,13 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_
   const int nkeys = ok ? ctx + qb : 0;
   // keys this row group sees: a prompt's later keys are behind the causal limit of its earlier rows (845 prompt rows in three
   // sequences: 26.7 -> 23.0 us)
-  const int seen = ok ? ctx + (min(R, (tile0 + NW * CTW) * 16) - 1) / G + 1 : 0;
+  const int seen = ok ? ctx + fast_div(min(R, (tile0 + NW * CTW) * 16) - 1, G, G_inv) + 1 : 0;
   const int n_tiles = (seen + KT - 1) / KT;
-  const int t_begin = (int)(((long)n_tiles * split) / my_splits);
-  const int t_end = (int)(((long)n_tiles * (split + 1)) / my_splits);
+  int t_begin = 0, t_end = n_tiles;
+  if (my_splits > 1) {                    // (at most 16)
+    t_begin = (int)(((long)n_tiles * split) / my_splits);
+    t_end = (int)(((long)n_tiles * (split + 1)) / my_splits);
+  }
   const int n_my = max(0, t_end - t_begin);
   const int nct = ok ? min(CTW, max(0, (NT16 - tile0 - wave + NW - 1) / NW)) : 0;  // real column tiles of this wave
 
@@ -387,10 +401,11 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_
   // cost an L2 round trip per tile); entries past the last mapped block repeat the last one
   const int32_t* bt = a.kv.block_tables + (size_t)b * a.kv.max_blocks_per_seq;
   const int last_blk = ok ? (nkeys - 1) / BS : 0;
-  for (int i = tid; i < 2 * n_my; i += NW * 64) s_bidx[i] = bt[min(2 * t_begin + i, last_blk)];
+  const int id_first = bt[min(2 * t_begin + tid, last_blk)];  // (each thread's first entry goes out ahead of the queries)
 
   // ---- Q fragments -> registers, scaled by log2(e)/sqrt(hd) (one more fp16 rounding of q, 2^-11), so
-  // the scores come out of the first product in log2 units.  Rows past R are zero. ----
+  // the scores come out of the first product in log2 units.  Rows past R are zero (they ask for the last row: behind a condition
+  // each of the four loads was a round trip of its own). ----
   const float sscale = rsqrtf((float)HD) * LOG2E;
   const f16_t* Q = reinterpret_cast<const f16_t*>(a.q);
   f16x8 qf[CTW][4];
@@ -399,24 +414,28 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_
   int lim[CTW];
 #pragma unroll
   for (int ct = 0; ct < CTW; ++ct) {
+    const int r = min((tile0 + wave + NW * ct) * 16 + l16, R - 1), j = fast_div(r, G, G_inv);
+    lim[ct] = ctx + min(j, qb - 1);       // last visible key of this lane's query row
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+      qf[ct][s] = *reinterpret_cast<const f16x8*>(Q + ((size_t)(row0 + j) * a.H + kvh * G + r - j * G) * HD + 32 * s + 8 * g);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  if (tid < 2 * n_my) s_bidx[tid] = id_first;
+  for (int i = tid + NW * 64; i < 2 * n_my; i += NW * 64) s_bidx[i] = bt[min(2 * t_begin + i, last_blk)];
+#pragma unroll
+  for (int ct = 0; ct < CTW; ++ct) {
     run_m[ct] = -INFINITY;
     thr[ct] = -INFINITY;
     negm4[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
     L[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const int r = (tile0 + wave + NW * ct) * 16 + l16;
-    lim[ct] = ctx + min(r / G, qb - 1);  // last visible key of this lane's query row
 #pragma unroll
     for (int u = 0; u < 8; ++u) O[ct][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const bool real = (tile0 + wave + NW * ct) * 16 + l16 < R;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      f16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (r < R) {
-        v = *reinterpret_cast<const f16x8*>(Q + ((size_t)(row0 + r / G) * a.H + kvh * G + r % G) * HD + 32 * s + 8 * g);
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (f16_t)((float)v[e] * sscale);
-      }
-      qf[ct][s] = v;
-    }
+      for (int e = 0; e < 8; ++e) qf[ct][s][e] = real ? (f16_t)((float)qf[ct][s][e] * sscale) : (f16_t)0.f;
   }
 
   // Loader role of this thread: the pieces of its own lane in K fragments (t = 0, 1; head-dim step s = wave)
@@ -564,7 +583,7 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) attn_mfma_kernel(MN_
     const int r = tile * 16 + l16;
     if (tile >= NT16 || r >= R) continue;
     const float l = L[ct][0];
-    const int j = r / G, gi = r % G;
+    const int j = fast_div(r, G, G_inv), gi = r - j * G;
     const int m = row0 + j, h = kvh * G + gi;
     if (my_splits == 1) {
       const float inv = (ok && l > 0.f) ? 1.f / l : 0.f;
@@ -810,22 +829,26 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
     negm4[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
     L[ct] = (f32x4){0.f, 0.f, 0.f, 0.f};
     const int r = ct * 16 + l16;
-    lim[ct] = ctx + min(r / G, qb - 1);                      // last visible key of this lane's query row
+    const int j = min(r, R - 1) / G;
+    lim[ct] = ctx + j;                                       // last visible key of this lane's query row
 #pragma unroll
     for (int u = 0; u < NU; ++u) O[ct][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s = 0; s < HS; ++s) {
-      f16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (r < R) {
-        if constexpr (FUSED) v = *reinterpret_cast<const f16x8*>(s_q + (size_t)r * QROW + 32 * s + 8 * g);
-        else v = *reinterpret_cast<const f16x8*>(Q + ((size_t)(row0 + r / G) * a.H + kvh * G + r % G) * HDIM + 32 * s + 8 * g);
-        if (!WIDE) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = (f16_t)((float)v[e] * sscale);
-        }
-      }
-      qf[ct][s] = v;
+    for (int s = 0; s < HS; ++s) {        // (rows past R ask for the last one: behind a condition each load is a round trip of its own)
+      if constexpr (FUSED) qf[ct][s] = *reinterpret_cast<const f16x8*>(s_q + (size_t)min(r, R - 1) * QROW + 32 * s + 8 * g);
+      else qf[ct][s] = *reinterpret_cast<const f16x8*>(Q + ((size_t)(row0 + j) * a.H + kvh * G + min(r, R - 1) - j * G) * HDIM + 32 * s + 8 * g);
     }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+#pragma unroll
+    for (int s = 0; s < HS; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const f16_t v = WIDE ? qf[ct][s][e] : (f16_t)((float)qf[ct][s][e] * sscale);
+        qf[ct][s][e] = ct * 16 + l16 < R ? v : (f16_t)0.f;
+      }
   }
 
   const f16x8 ones = {1, 1, 1, 1, 1, 1, 1, 1};
