@@ -58,9 +58,9 @@ enum { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_RELU = 2 };
 
 template <int MT, int NTW, int EPI, int NW, int RD>
 __global__ void __launch_bounds__(NW * 64, (MT * NTW > 24 || NW > 4) ? 1 : 2) gemm_w16_kernel(const f16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                                           int M, int N, int K, int k_per_split, int m_chunks, int gx, int n_split,
                                                            void* __restrict__ out_, const float* __restrict__ bias,
-                                                           int M, int N, int K, int k_per_split, int m_chunks, int gx,
-                                                           int n_split, int32_t* __restrict__ status) {
+                                                           int32_t* __restrict__ status) {
   // two activation-tile buffers as separate objects: the compiler then knows that a DMA into one
   // does not touch the reads of the other
   __shared__ __attribute__((aligned(1024))) f16_t s_a0[16 * MT * LDS_ROW];
@@ -90,10 +90,12 @@ __global__ void __launch_bounds__(NW * 64, (MT * NTW > 24 || NW > 4) ? 1 : 2) ge
       bz = slot % m_chunks;
       bx = pair % gx;
       split = pair / gx;
-    } else if (n_split <= 8 && 8 % n_split == 0) {
-      const int r = 8 / n_split;         // XCDs per split
-      split = xcd / r;
-      bx = slot * r + xcd % r;
+    } else if (n_split <= 8 && (n_split & (n_split - 1)) == 0) {
+      // 1 << r XCDs per split.  (Shifts: a division by a number that is not known when the kernel is compiled is forty instructions,
+      // each waiting for the one before, ahead of the first load.)
+      const int r = __builtin_clz(n_split) - 28;
+      split = xcd >> r;
+      bx = (slot << r) + (xcd & ((1 << r) - 1));
     } else if (n_split % 8 == 0) {
       const int q = n_split >> 3;        // splits per XCD
       split = (slot % q) * 8 + xcd;
@@ -1024,16 +1026,16 @@ static void launch_bf16_mt(const GemmArgs& a, int m_chunks, hipStream_t st) {
   if constexpr (!SPLIT) {
     if constexpr (NTW % 2 == 0) {  // (gate and up tiles alternate inside a wave)
       if (a.swiglu_act) {
-        gemm_w16_kernel<MT, NTW, EPI_SWIGLU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.swiglu_act, nullptr, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+        gemm_w16_kernel<MT, NTW, EPI_SWIGLU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.swiglu_act, nullptr, a.dev_status);
         return;
       }
     }
     if (a.relu_act) {
-      gemm_w16_kernel<MT, NTW, EPI_RELU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.relu_act, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+      gemm_w16_kernel<MT, NTW, EPI_RELU, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.relu_act, a.bias, a.dev_status);
       return;
     }
   }
-  gemm_w16_kernel<MT, NTW, EPI_PARTIAL, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.out, a.bias, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.dev_status);
+  gemm_w16_kernel<MT, NTW, EPI_PARTIAL, NW, RD><<<grid, NW * 64, 0, st>>>(A, W, a.M, a.N, a.K, per * KB, m_chunks, gx, a.split_k, a.out, a.bias, a.dev_status);
 }
 
 template <int MT>
