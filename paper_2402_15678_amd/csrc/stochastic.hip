@@ -555,8 +555,9 @@ struct RowRegs {
         masses(l, t, wave, lane, V, temp, m);
         zp += (m[0] + m[1]) + (m[2] + m[3]);
       }
-      const float above = ok ? (float)((double)mx + 100.0 * temp.T) : mx;
-      if (__any(!(hi <= above)) && e != ROW_GENERAL) e = ROW_GENERAL;
+      // (compared in 64 bits: rounded to the spacing of the scores the limit may be 133 T, whose exponentials leave z_wave no room)
+      const double above = ok ? (double)mx + 100.0 * temp.T : (double)mx;
+      if (__any(!((double)hi <= above)) && e != ROW_GENERAL) e = ROW_GENERAL;
     }
     if (e == ROW_NONE) {                       // (wave-uniform) none of these is there
       zp = 0.0;

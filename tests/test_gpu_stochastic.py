@@ -517,3 +517,23 @@ def test_scores_that_are_not_numbers_stay_in_their_row(hb, V):
         else:
             want, q32, gap = orc.draft_sample(logits[b], 1.0, 9, 2, 1, b, 3)
             assert np.allclose(q[b], q32, rtol=3e-7, atol=1e-45) and (gap <= 1e-6 or tok[b] == want) and 0 <= ver[b] < V
+
+
+def test_scores_behind_the_registers_far_above_a_wave(hb):
+    """Rows beyond 32768 tokens whose scores lie so far from zero that the next fp32 number is 65 T away: a wave's later score two of them above its
+    earlier ones, and another wave 585 T (844 powers of two) below those."""
+    V, T = 40001, 1.878e-6
+    step = np.float32(2.0 ** -13)                         # of the scores from 1024 on
+    logits = np.full((2, V), -np.inf, np.float32)
+    logits[:, 0] = 1024.0
+    logits[0, 32768 + 5] = 1024.0 + 2 * step
+    logits[1, 32768 + 5] = 1024.0 + step
+    logits[:, 300:400] = 1024.0 - 9 * step                # (the second block: the second wave)
+    _check_draft_rows(hb, logits, T)
+    q = np.zeros((2, 1, V), np.float32)
+    q[:, 0, 32768 + 5], q[:, 0, 310] = 0.25, 0.75
+    spec, voted, ctx0 = np.asarray([1, 1], np.int32), np.full((2, 1), 310, np.int32), np.zeros(2, np.int32)
+    rows = np.repeat(logits, 2, axis=0)
+    for seed in range(4):
+        res = _run_gpu(hb, spec, 4, rows, q, voted, 1, V, T, seed=seed, step=0, ctx0=ctx0)
+        _check_against_oracle(res, spec, rows, q, voted, 1, T, seed, 0, ctx0)
