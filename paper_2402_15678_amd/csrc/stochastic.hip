@@ -401,7 +401,11 @@ __device__ __forceinline__ double find_token(const double (&m)[4], int v, double
   return lane_63_d(inc);
 }
 
-constexpr double MASS_FLOOR = 0x1p-990;     // RowRegs: nothing below it counts
+// RowRegs: nothing below it counts; a row with nothing above it is drawn from in the general form.  It is above all that the registers' form gives a
+// wrong mass: scores cut at 690 T below their wave's largest (the cut is a float, and the spacing of the scores may be 88 T, so that they stand at 601 T,
+// 2^-867) and waves left out beside the row's largest (2^-687 in all: 850 powers of two below it, a score behind the registers up to 145 above its
+// wave's reference, 2^18 of them).
+constexpr double MASS_FLOOR = 0x1p-600;
 constexpr int ROW_NONE = -(1 << 30), ROW_GENERAL = 1 << 30;  // RowRegs: a wave without finite scores; a row that is not for it
 
 // Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass exceeds u times the
@@ -507,7 +511,7 @@ struct RowRegs {
   }
 
   // Uniform result; false: the row has scores that are not numbers, or too large for this (or none that is finite).
-  // Scores more than 690 T below the wave's largest count as that far below, at most 2^-995: MASS_FLOOR and the draw tell them from mass.
+  // Scores more than 690 T below the wave's largest count as that far below: MASS_FLOOR and the draw tell them from mass.
   // soon: another row (or null) that the kernel may read next; a line of it per thread is on its way to the L2 while the exponentials are
   // computed.  (Asked for beside the scores it holds them up: 1 us of 16 at 144 rows.)
   __device__ __forceinline__ bool load(const float* __restrict__ L, const float* __restrict__ soon, int V, Temp& temp, const PowerLoad& power, DrawShared& sh, int tid) {

@@ -537,3 +537,18 @@ def test_scores_behind_the_registers_far_above_a_wave(hb):
     for seed in range(4):
         res = _run_gpu(hb, spec, 4, rows, q, voted, 1, V, T, seed=seed, step=0, ctx0=ctx0)
         _check_against_oracle(res, spec, rows, q, voted, 1, T, seed, 0, ctx0)
+
+
+def test_masked_tokens_stay_masked_at_scores_far_from_zero(hb):
+    """Nothing is left of max(0, o - q), and the next fp32 number is 38 T away from the largest score: a score cut at 690 T would stand at 652 T, which is
+    still no mass.  The replacement is the only other token of o, never a masked one."""
+    V, T, step = 300, 7.957e-7, np.float32(2.0 ** -15)    # (step: of the scores around 400)
+    rows = np.full((2, V), -np.inf, np.float32)
+    rows[:, 5], rows[:, 7] = 400.0, 400.0 - 2 * step
+    q = np.zeros((1, 1, V), np.float32)
+    q[0, 0, 5], q[0, 0, 7] = 1.0, 0.5                     # (a row that sums above 1: it lies above o everywhere)
+    spec, voted, ctx0 = np.ones(1, np.int32), np.full((1, 1), 7, np.int32), np.zeros(1, np.int32)
+    for seed in range(8):
+        res = _run_gpu(hb, spec, 2, rows, q, voted, 1, V, T, seed=seed, step=0, ctx0=ctx0)
+        assert res[0][0, 0] == 5
+        _check_against_oracle(res, spec, rows, q, voted, 1, T, seed, 0, ctx0)
