@@ -521,10 +521,7 @@ struct RowRegs {
     for (int t = 0; t < TILES; ++t) raw[t] = ask(L, t, wave, lane, V);
     power.store(sh, tid);
     __syncthreads();
-    if (V & 3) {
-#pragma unroll
-      for (int t = 0; t < TILES; ++t) raw[t] = in_place(raw[t], t, wave, lane, V);
-    }
+    if (!MORE && V & 3) raw[TILES - 1] = in_place(raw[TILES - 1], TILES - 1, wave, lane, V);  // (the last block's tile)
     float mx = raw[0][0];                      // (a NaN stays)
 #pragma unroll
     for (int i = 1; i < 4 * TILES; ++i) mx = __builtin_elementwise_maximum(mx, raw[i / 4][i % 4]);
@@ -792,16 +789,15 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
         }
       }
       if (Q) {  // masses of o - q, times Z and relative to the wave's power of two
-        constexpr int HALF = TILES < 4 ? TILES : TILES % 4 ? 3 : 4;
-        static_assert(TILES % HALF == 0, "whole groups");
+        constexpr int HALF = TILES <= 4 ? TILES : (TILES + 1) / 2;
 #pragma unroll
         for (int h = 0; h < TILES; h += HALF) {
           f32x4 q[HALF];
 #pragma unroll
-          for (int t = 0; t < HALF; ++t) q[t] = regs.ask(Q, h + t, wave, lane, V);
+          for (int t = 0; t < HALF; ++t) q[t] = regs.ask(Q, min(h + t, TILES - 1), wave, lane, V);
 #pragma unroll
-          for (int t = 0; t < HALF; ++t) {
-            if (V & 3) q[t] = regs.in_place(q[t], h + t, wave, lane, V);
+          for (int t = 0; t < HALF && h + t < TILES; ++t) {
+            if (!MORE && h + t == TILES - 1 && V & 3) q[t] = regs.in_place(q[t], h + t, wave, lane, V);
             asm volatile("" : "+v"(q[t]));
 #pragma unroll
             for (int e = 0; e < 4; ++e) regs.ex[h + t][e] = fmax(0.0, fma(-(double)q[t][e], regs.z_wave, regs.ex[h + t][e]));
@@ -975,18 +971,33 @@ struct StepsPerScore {
   }
 };
 
-// Tiles of 4096 tokens that a row's exponentials take in registers (every instance computes all of its tiles), 0: the general form.  Beyond
-// 32768 tokens the first tiles are in registers, up to the segments that the shared array holds.
+// Tiles of 4096 tokens that a row's exponentials take in registers: an instance for every number of them, since each computes all of its tiles (a branch around
+// those that a wave does not have costs 0.7 us at 32000 tokens; with instances of 1, 2, 4 and 8 tiles alone 16 drafted tokens of 8193, 17000 and 25000 took 9.1, 12.4 and
+// 12.2 us, now 7.6, 9.2 and 10.9).  0: the general form.  Beyond 32768 tokens the first tiles are in registers, up to the segments that the shared array
+// holds.
 constexpr int SV_MAX_FAR = SV_MAX_SEGS * SV_BLOCK;
 static int reg_tiles(int V, double inv) {
   if (V < 4 || V > SV_MAX_FAR || inv == 0.0) return 0;
-  return V <= SV_TILE ? 1 : V <= 2 * SV_TILE ? 2 : V <= 4 * SV_TILE ? 4 : SV_REG_TILES;
+  return min((V + SV_TILE - 1) / SV_TILE, SV_REG_TILES + 1);
 }
 // FAR: tiles in registers beyond 32768 tokens.  The verifier needs room for q there: 144 positions of 50272 tokens 35.6 us with eight (which spill), 26.5 with six,
 // 28.7 with four, 48.4 in the general form; 16 drafted tokens 20.5, 22.0 and 23.9, 41.5 in the general form.
-#define MN_ROW_KERNEL(K, FAR, V, INV)                                                                                  \
-  (reg_tiles(V, INV) == 1 ? K<1, false> : reg_tiles(V, INV) == 2 ? K<2, false> : reg_tiles(V, INV) == 4 ? K<4, false> \
-   : reg_tiles(V, INV) == 0 ? K<0, false> : (V) <= SV_REG_TILES * SV_TILE ? K<SV_REG_TILES, false> : K<FAR, true>)
+#define MN_ROW_KERNEL(K, FAR, V, INV)                                                     \
+  [&] {                                                                                   \
+    switch (reg_tiles(V, INV)) {                                                          \
+      case 0: return K<0, false>;                                                         \
+      case 1: return K<1, false>;                                                         \
+      case 2: return K<2, false>;                                                         \
+      case 3: return K<3, false>;                                                         \
+      case 4: return K<4, false>;                                                         \
+      case 5: return K<5, false>;                                                         \
+      case 6: return K<6, false>;                                                         \
+      case 7: return K<7, false>;                                                         \
+      case 8: return K<8, false>;                                                         \
+      default: return K<FAR, true>;                                                       \
+    }                                                                                     \
+  }()
+static_assert(SV_REG_TILES == 8, "an instance for every number of tiles");
 
 void launch_verify_sample(const float* logits, const int32_t* voted, const float* draft_probs, const int32_t* spec_len,
                           const int32_t* greedy, int B, int k_max, int M, int V, double temperature, uint64_t seed,

@@ -552,3 +552,50 @@ def test_masked_tokens_stay_masked_at_scores_far_from_zero(hb):
         res = _run_gpu(hb, spec, 2, rows, q, voted, 1, V, T, seed=seed, step=0, ctx0=ctx0)
         assert res[0][0, 0] == 5
         _check_against_oracle(res, spec, rows, q, voted, 1, T, seed, 0, ctx0)
+
+
+def _microseconds(call, n=20):
+    """Median time of a call in a graph of n."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(n):
+            call()
+    t = []
+    for _ in range(12):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        t.append(a.elapsed_time(b) / n * 1e3)
+    return sorted(t[2:])[5]
+
+
+# Rows of one token more than fit a number of tiles, against the same entry point on plain rows: each tile of 4096 tokens beyond the first costs about
+# 0.9 us of 6 (8193 and 16385 tokens took 1.40 and 1.63 times as long as 8192 and 16384 where rows were rounded up to 4 and 8 tiles).  Then rows that the form
+# with exponentials in registers serves at its own speed; the general form, begun after it, takes 2.4 to 2.8 times as long.
+@pytest.mark.parametrize("V,T,mask,plain_V,most", [
+    (8193, 1.0, None, 8192, 1.28),
+    (16385, 1.0, None, 16384, 1.35),
+])
+def test_time_of_rows_in_registers(hb, V, T, mask, plain_V, most):
+    harness, binding = hb
+    g = synth.stream(4108, V)
+
+    def draft_time(V, T, mask):
+        logits = g.normal(0.0, 2.0, (16, V)).astype(np.float32)
+        if mask is not None:
+            logits[:, np.setdiff1d(np.arange(V), g.permutation(V)[:50])] = mask
+        log_d, tok_d, q_d = _dev(logits, torch.float32), torch.zeros(16, dtype=torch.int32, device="cuda:0"), torch.zeros(16, V, device="cuda:0")
+        return _microseconds(lambda: binding.mn_draft_sample(None, log_d.data_ptr(), 16, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(),
+                                                             V, harness.stream_ptr()))
+
+    plain, this = draft_time(plain_V, 1.0, None), draft_time(V, T, mask)
+    assert this <= most * plain, (this, plain)
+
+
+@pytest.mark.parametrize("V", [8194, 12288, 12289, 16386, 20480, 20483, 24575, 24577, 28670, 28673, 28676])
+def test_every_number_of_tiles_against_oracle(hb, V):
+    test_rows_in_registers_against_oracle(hb, V)
