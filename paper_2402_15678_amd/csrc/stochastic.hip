@@ -204,9 +204,14 @@ struct PowerLoad {
 };
 
 // A place that the values pass in program order: without it the compiler takes one operation of every token of the row after the other,
-// and the intermediate values of all of them do not fit the registers (280 spilled; 60000 cycles for the row's exponentials instead of 8000).
+// and the intermediate values of all of them do not fit the registers (280 spilled; 60000 cycles for the row's exponentials instead of 8000).  As one
+// value: apart, they stay where the reads of the table put one half of each, and in between no piece of a row fits (22 spilled).
 template <typename T>
-__device__ __forceinline__ void in_turn(T& a, T& b, T& c, T& d) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d)); }
+__device__ __forceinline__ void in_turn(T& a, T& b, T& c, T& d) {
+  T __attribute__((ext_vector_type(4))) v = {a, b, c, d};
+  asm volatile("" : "+v"(v));
+  a = v[0]; b = v[1]; c = v[2]; d = v[3];
+}
 
 // Exponentials of scores at temperature T, table-driven (P. T. P. Tang, ACM TOMS 15(2), 1989): l / T = (n + f) ln2/256 with n whole
 // and |f| <= 1/2, and exp(l / T) = 2^(n >> 8) * 2^((n & 255)/256) * (1 + a1 f + .. + a4 f^4), the fifth-order term spread over a1 and a3.
@@ -311,6 +316,7 @@ struct Temp {
     }
 #pragma unroll
     for (int e = 0; e < 4; e += 2) {
+      if (e) asm volatile("" : "+v"(m[0]), "+v"(m[1]));
       double x[2] = {BELOW ? (double)l[e] - base : (double)l[e], BELOW ? (double)l[e + 1] - base : (double)l[e + 1]}, y[2];
       powers<!PLAIN, 2>(x, y);
       m[e] = y[0];
@@ -406,7 +412,9 @@ __device__ __forceinline__ double find_token(const double (&m)[4], int v, double
 // 2^-867) and waves left out beside the row's largest (2^-687 in all: 850 powers of two below it, a score behind the registers up to 145 above its
 // wave's reference, 2^18 of them).
 constexpr double MASS_FLOOR = 0x1p-600;
-constexpr int ROW_NONE = -(1 << 30), ROW_GENERAL = 1 << 30;  // RowRegs: a wave without finite scores; a row that is not for it
+// RowRegs: a wave whose scores are all masked, with minus infinity or with a number so low (|score / T| 256 / ln2 >= 2^38) that nothing of it is left beside
+// a row's power of two from ROW_LOW on; a row that is not for it
+constexpr int ROW_NONE = -(1 << 30), ROW_LOW = ROW_NONE + 1024, ROW_GENERAL = 1 << 30;
 
 // Inverse-CDF draw over the vocabulary: the first token, in token order, whose running sum of mass exceeds u times the
 // total; -1 when the total is not positive.  mass4(blk, m) gives the masses of this lane's four tokens of block blk (0 past the end)
@@ -465,7 +473,7 @@ __device__ __forceinline__ int cdf_draw(F mass4, int V, double u, DrawShared& sh
 // (`far`): once for their sum, once for their masses, and for the block that holds the draw.
 template <int TILES, bool MORE>
 struct RowRegs {
-  double ex[TILES][4];        // relative to this wave's power of two; zero past the end of the row
+  double ex[TILES][4];        // relative to this wave's power of two; zero past the end of the row (anything finite in a wave that is dead)
   int e_all;                  // the row's power of two: the largest of the waves'
   int down;                   // this wave's, less the row's: at most 0
   bool dead;                  // nothing of this wave is left beside the row's largest
@@ -499,7 +507,6 @@ struct RowRegs {
   }
   __device__ __forceinline__ void far(const float* __restrict__ L, int t, int wave, int lane, int V, const Temp& temp, double (&m)[4]) const {
     masses(in_place(ask(L, t, wave, lane, V), t, wave, lane, V), t, wave, lane, V, temp, m);
-    if (dead) m[0] = m[1] = m[2] = m[3] = 0.0;
   }
   __device__ __forceinline__ void clear_past_end(int t, int wave, int lane, int V) {
     const int blk = t * SV_WAVES + wave;
@@ -510,7 +517,7 @@ struct RowRegs {
     }
   }
 
-  // Uniform result; false: the row has scores that are not numbers, or too large for this (or none that is finite).
+  // Uniform result; false: the row has scores that are not numbers, or too large for this (or none that is not masked).
   // Scores more than 690 T below the wave's largest count as that far below: MASS_FLOOR and the draw tell them from mass.
   // soon: another row (or null) that the kernel may read next; a line of it per thread is on its way to the L2 while the exponentials are
   // computed.  (Asked for beside the scores it holds them up: 1 us of 16 at 144 rows.)
@@ -529,7 +536,7 @@ struct RowRegs {
     mx = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wave_max(mx))));
     const double top = (double)mx * temp.k;    // the reference: the next power of two at or above the largest exponential
     const bool ok = __all(__builtin_fabs(top) < 0x1p38) && !nan;
-    int e = ok ? __builtin_amdgcn_readfirstlane((int)ceil(top * (1.0 / 256.0))) : mx != -INFINITY || nan ? ROW_GENERAL : ROW_NONE;
+    int e = ok ? __builtin_amdgcn_readfirstlane((int)ceil(top * (1.0 / 256.0))) : mx > 0.f || nan ? ROW_GENERAL : ROW_NONE;
     temp.relative_to(ok ? e : 0, ok ? (double)mx : 0.0);
     float touch = 0.f;
     if (soon && 32 * tid < V) touch = soon[32 * tid];
@@ -560,22 +567,18 @@ struct RowRegs {
       const double above = ok ? (double)mx + 100.0 * temp.T : (double)mx;
       if (__any(!((double)hi <= above)) && e != ROW_GENERAL) e = ROW_GENERAL;
     }
-    if (e == ROW_NONE) {                       // (wave-uniform) none of these is there
-      zp = 0.0;
-#pragma unroll
-      for (int t = 0; t < TILES; ++t) ex[t][0] = ex[t][1] = ex[t][2] = ex[t][3] = 0.0;
-    }
     asm volatile("" ::"v"(touch));
     zp = wave_sum_d(zp);
+    if (e == ROW_NONE) zp = 0.0;               // (wave-uniform; what ex holds then is not used)
     if (lane == 0) {
       sh.red[wave] = zp;
       sh.ref[wave] = e;
     }
     __syncthreads();
-    e_all = sh.ref[lane % SV_WAVES];           // (a wave's lanes 0 .. 15 hold all of them)
+    e_all = sh.ref[0];
 #pragma unroll
-    for (int w = 0; w < SV_WAVES; ++w) e_all = max(e_all, sh.ref[w]);
-    if (e_all == ROW_GENERAL || e_all == ROW_NONE) return false;
+    for (int w = 1; w < SV_WAVES; ++w) e_all = max(e_all, sh.ref[w]);
+    if (e_all == ROW_GENERAL || e_all < ROW_LOW) return false;
     Z = 0.0;
 #pragma unroll
     for (int w = 0; w < SV_WAVES; ++w) Z += ldexp(sh.red[w], sh.ref[w] - e_all);
@@ -583,11 +586,9 @@ struct RowRegs {
     down = e - e_all;
     z_wave = ldexp(Z, -down);
     dead = down < -850;
-    if (dead) {
-      down = 0;
+    if (dead) {                                // (ex stays: the verifier's sums of segments become zero by `down`, the drafter multiplies by zero)
+      down = -4096;
       z_wave = 1.0;
-#pragma unroll
-      for (int t = 0; t < TILES; ++t) ex[t][0] = ex[t][1] = ex[t][2] = ex[t][3] = 0.0;
     }
     return true;
   }
@@ -903,7 +904,7 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
   if constexpr (TILES > 0) {
     RowRegs<TILES, MORE> regs;
     if (regs.load(L, nullptr, V, temp, power, sh, tid)) {
-      const double inv_z = 1.0 / regs.z_wave;
+      const double inv_z = regs.dead ? 0.0 : 1.0 / regs.z_wave;
 #pragma unroll
       for (int t = 0; t < TILES; ++t) {
 #pragma unroll

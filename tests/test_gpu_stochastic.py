@@ -579,6 +579,8 @@ def _microseconds(call, n=20):
 @pytest.mark.parametrize("V,T,mask,plain_V,most", [
     (8193, 1.0, None, 8192, 1.28),
     (16385, 1.0, None, 16384, 1.35),
+    (32000, 1.0, -1e9, 32000, 1.4),      # all but 50 tokens masked with a finite value
+    (32000, 1.0, float(np.finfo(np.float32).min), 32000, 1.4),
 ])
 def test_time_of_rows_in_registers(hb, V, T, mask, plain_V, most):
     harness, binding = hb
@@ -599,3 +601,20 @@ def test_time_of_rows_in_registers(hb, V, T, mask, plain_V, most):
 @pytest.mark.parametrize("V", [8194, 12288, 12289, 16386, 20480, 20483, 24575, 24577, 28670, 28673, 28676])
 def test_every_number_of_tiles_against_oracle(hb, V):
     test_rows_in_registers_against_oracle(hb, V)
+
+
+@pytest.mark.parametrize("V", [32000, 50272])
+@pytest.mark.parametrize("mask", [-np.inf, -1e9, np.finfo(np.float32).min])
+def test_rows_with_masked_waves_against_oracle(hb, V, mask):
+    """All but one, a few and many of a row's tokens masked: whole waves have no score, before and behind the registers."""
+    B, k_max, T = 6, 2, 0.9
+    spec, M, logits, q, voted = _case(51, B, k_max, V, T, 1.0)
+    g = synth.stream(4109, V)
+    for m in range(M):
+        keep = g.permutation(V)[:(1, 3, 50, 5000)[m % 4]]
+        logits[m, np.setdiff1d(np.arange(V), keep)] = mask
+    ctx0 = np.arange(B).astype(np.int32)
+    for step in (0, 1):
+        res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=12, step=step, ctx0=ctx0)
+        _check_against_oracle(res, spec, logits, q, voted, k_max, T, 12, step, ctx0)
+    _check_draft_rows(hb, logits[:6], T)
