@@ -517,6 +517,23 @@ struct RowRegs {
     }
   }
 
+  // The power of two that a wave takes its exponentials relative to, the next one at or above its largest (mx: each lane's largest score, which becomes the
+  // wave's; a NaN stays)
+  static __device__ __forceinline__ int reference(float& mx, Temp& temp) {
+    const bool nan = __any(mx != mx);
+    mx = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wave_max(mx))));
+    const double top = (double)mx * temp.k;
+    const bool ok = __all(__builtin_fabs(top) < 0x1p38) && !nan;
+    const int e = ok ? __builtin_amdgcn_readfirstlane((int)ceil(top * (1.0 / 256.0))) : mx > 0.f || nan ? ROW_GENERAL : ROW_NONE;
+    temp.relative_to(ok ? e : 0, ok ? (double)mx : 0.0);
+    return e;
+  }
+  // Scores up to here may be taken relative to a wave's power of two: a float at or below 100 T above the largest that it was chosen for (rounded to the nearest
+  // it could be 133 T)
+  static __device__ __forceinline__ float room_above(float mx, int e, const Temp& temp) {
+    return e == ROW_NONE ? mx : -float_above(-((double)mx + 100.0 * temp.T));
+  }
+
   // Uniform result; false: the row has scores that are not numbers, or too large for this (or none that is not masked).
   // Scores more than 690 T below the wave's largest count as that far below: MASS_FLOOR and the draw tell them from mass.
   // soon: another row (or null) that the kernel may read next; a line of it per thread is on its way to the L2 while the exponentials are
@@ -532,12 +549,7 @@ struct RowRegs {
     float mx = raw[0][0];                      // (a NaN stays)
 #pragma unroll
     for (int i = 1; i < 4 * TILES; ++i) mx = __builtin_elementwise_maximum(mx, raw[i / 4][i % 4]);
-    const bool nan = __any(mx != mx);
-    mx = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wave_max(mx))));
-    const double top = (double)mx * temp.k;    // the reference: the next power of two at or above the largest exponential
-    const bool ok = __all(__builtin_fabs(top) < 0x1p38) && !nan;
-    int e = ok ? __builtin_amdgcn_readfirstlane((int)ceil(top * (1.0 / 256.0))) : mx > 0.f || nan ? ROW_GENERAL : ROW_NONE;
-    temp.relative_to(ok ? e : 0, ok ? (double)mx : 0.0);
+    int e = reference(mx, temp);
     float touch = 0.f;
     if (soon && 32 * tid < V) touch = soon[32 * tid];
     if (MORE && soon && 32 * (SV_THREADS + tid) < V) touch += soon[32 * (SV_THREADS + tid)];
@@ -550,22 +562,28 @@ struct RowRegs {
       zp += (ex[t][0] + ex[t][1]) + (ex[t][2] + ex[t][3]);
     }
     if constexpr (MORE) {
-      // the tiles behind the registers keep the reference: up to 100 T above it their exponentials, up to 2^145, leave room for z_wave
+      // The tiles behind the registers keep the reference up to 100 T above the scores it was taken from: exponentials up to 2^145 leave room for z_wave.  A tile with
+      // more moves it, and what has been computed with it.
       const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK;
-      float hi = mx;
+      float above = room_above(mx, e, temp);
       f32x4 next = ask(L, TILES, wave, lane, V);
       for (int t = TILES; t * SV_WAVES + wave < n_blocks; ++t) {
         f32x4 l = in_place(next, t, wave, lane, V);
         next = ask(L, t + 1, wave, lane, V);
-        double m[4];
+        float hi = __builtin_elementwise_maximum(__builtin_elementwise_maximum(l[0], l[1]), __builtin_elementwise_maximum(l[2], l[3]));
+        if (__any(!(hi <= above)) && e != ROW_GENERAL) {
+          const int was = e;
+          e = reference(hi, temp);
+          above = room_above(hi, e, temp);
+          const double scale = was == ROW_NONE ? 0.0 : ldexp(1.0, was - e);
+          zp *= scale;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) hi = __builtin_elementwise_maximum(hi, l[i]);
+          for (int i = 0; i < 4 * TILES; ++i) ex[i / 4][i % 4] *= scale;
+        }
+        double m[4];
         masses(l, t, wave, lane, V, temp, m);
         zp += (m[0] + m[1]) + (m[2] + m[3]);
       }
-      // (compared in 64 bits: rounded to the spacing of the scores the limit may be 133 T, whose exponentials leave z_wave no room)
-      const double above = ok ? (double)mx + 100.0 * temp.T : (double)mx;
-      if (__any(!((double)hi <= above)) && e != ROW_GENERAL) e = ROW_GENERAL;
     }
     asm volatile("" ::"v"(touch));
     zp = wave_sum_d(zp);

@@ -581,6 +581,8 @@ def _microseconds(call, n=20):
     (16385, 1.0, None, 16384, 1.35),
     (32000, 1.0, -1e9, 32000, 1.4),      # all but 50 tokens masked with a finite value
     (32000, 1.0, float(np.finfo(np.float32).min), 32000, 1.4),
+    (50272, 1.0, -np.inf, 50272, 1.4),   # waves whose first tiles are masked, beyond 32768 tokens
+    (50272, 0.01, None, 50272, 1.4),     # scores behind the registers more than 100 T above a wave's first ones
 ])
 def test_time_of_rows_in_registers(hb, V, T, mask, plain_V, most):
     harness, binding = hb
@@ -618,3 +620,35 @@ def test_rows_with_masked_waves_against_oracle(hb, V, mask):
         res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=12, step=step, ctx0=ctx0)
         _check_against_oracle(res, spec, logits, q, voted, k_max, T, 12, step, ctx0)
     _check_draft_rows(hb, logits[:6], T)
+
+
+@pytest.mark.parametrize("V", [32769, 40961, 50272, 131075])
+@pytest.mark.parametrize("rise", [120.0, 95.0, -120.0, 900.0])
+def test_rows_whose_scores_rise_behind_the_registers(hb, V, rise):
+    """Every tile of 4096 tokens so many T above the one before: a wave's reference moves once, several times or never; one wave without it, one masked up
+    to the last tile, and a NaN or an infinite score in the last one."""
+    B, k_max, T = 5, 2, 0.5
+    spec, M, logits, q, voted = _case(61, B, k_max, V, T, 1.0)
+    tile, wave = np.arange(V) // 4096, np.arange(V) // 256 % 16
+    logits += (rise * T * tile).astype(np.float32)
+    logits[1:, wave == 2] -= np.float32(rise * T) * tile[wave == 2].astype(np.float32)
+    logits[2:, (wave == 0) & (tile < tile[-1])] = -np.inf
+    for m in range(0, M, 2):                              # (q as the scores are now, the speculated token its best one or nothing of it)
+        logits[m, (wave == 5) & (tile < tile[-1])] = -1e9
+    row = 0
+    for b in range(B):
+        for j in range(int(spec[b])):
+            q[b, j] = _softmax64((logits[row + j].astype(np.float64) + synth.stream(4110, b, j).normal(0.0, 1.0, V)) / T)
+            voted[b, j] = np.argmax(logits[row + j]) if (b + j) % 2 else 256 * 7
+        row += int(spec[b]) + 1
+    ctx0 = np.arange(B).astype(np.int32)
+    for step in (0, 1):
+        res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=13, step=step, ctx0=ctx0)
+        _check_against_oracle(res, spec, logits, q, voted, k_max, T, 13, step, ctx0)
+    _check_draft_rows(hb, logits[:5], T)
+    harness, binding = hb
+    bad = logits[:2].copy()
+    bad[0, V - 2], bad[1, V - 1] = np.nan, np.inf
+    log_d, tok_d, q_d = _dev(bad, torch.float32), _dev([-5, -5]), torch.zeros(2, V, device="cuda:0")
+    binding.mn_draft_sample(None, log_d.data_ptr(), 2, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
+    assert tok_d.tolist() == [-1, -1] and bool(torch.isnan(q_d).any(dim=1).all())
