@@ -470,15 +470,19 @@ __device__ __forceinline__ int cdf_draw(F mass4, int V, double u, DrawShared& sh
 }
 
 // The exponentials of a row of up to TILES * 4096 tokens, in registers.  MORE: those of the tiles behind them are computed when they are asked for
-// (`far`): once for their sum, once for their masses, and for the block that holds the draw.
-template <int TILES, bool MORE>
+// (`far`): once for their sum, once for their masses, and for the block that holds the draw.  SHIFT: scores are taken less the row's largest, in fp32, which
+// is exact down to half of it (or twice, below zero); what lies beyond is far below any cut at the temperatures that this is for (see MN_ROW_KERNEL).
+template <int TILES, bool MORE, bool SHIFT>
 struct RowRegs {
   double ex[TILES][4];        // relative to this wave's power of two; zero past the end of the row (anything finite in a wave that is dead)
   int e_all;                  // the row's power of two: the largest of the waves'
   int down;                   // this wave's, less the row's: at most 0
   bool dead;                  // nothing of this wave is left beside the row's largest
+  float shift = 0.f;          // taken off every score
   double Z, z_wave;           // sum of the row's exponentials relative to the row's power of two and to this wave's
 
+  // the row may end in tile t (SHIFT: rows of fewer tiles take this form too)
+  static constexpr __device__ bool may_end(int t) { return !MORE && (SHIFT || t == TILES - 1); }
   // A block's values of this lane, asked for whatever the row's length (V >= 4): blocks past the last repeat it, pieces that reach past the
   // end hold the last four values and are put in place afterwards (where V is no multiple of 4; what lies past the end is another value of the row).
   static __device__ __forceinline__ int first_of(int t, int wave, int lane, int V) {
@@ -505,8 +509,16 @@ struct RowRegs {
         if (blk * SV_BLOCK + 4 * lane + i >= V) m[i] = 0.0;
     }
   }
+  __device__ __forceinline__ void shifted(f32x4& l) const {
+    if constexpr (SHIFT) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) l[i] -= shift;
+    }
+  }
   __device__ __forceinline__ void far(const float* __restrict__ L, int t, int wave, int lane, int V, const Temp& temp, double (&m)[4]) const {
-    masses(in_place(ask(L, t, wave, lane, V), t, wave, lane, V), t, wave, lane, V, temp, m);
+    f32x4 l = in_place(ask(L, t, wave, lane, V), t, wave, lane, V);
+    shifted(l);
+    masses(l, t, wave, lane, V, temp, m);
   }
   __device__ __forceinline__ void clear_past_end(int t, int wave, int lane, int V) {
     const int blk = t * SV_WAVES + wave;
@@ -539,16 +551,37 @@ struct RowRegs {
   // soon: another row (or null) that the kernel may read next; a line of it per thread is on its way to the L2 while the exponentials are
   // computed.  (Asked for beside the scores it holds them up: 1 us of 16 at 144 rows.)
   __device__ __forceinline__ bool load(const float* __restrict__ L, const float* __restrict__ soon, int V, Temp& temp, const PowerLoad& power, DrawShared& sh, int tid) {
-    const int lane = tid & 63, wave = wave_of(tid);
+    const int lane = tid & 63, wave = wave_of(tid), n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK;
     f32x4 raw[TILES];
 #pragma unroll
     for (int t = 0; t < TILES; ++t) raw[t] = ask(L, t, wave, lane, V);
     power.store(sh, tid);
-    __syncthreads();
-    if (!MORE && V & 3) raw[TILES - 1] = in_place(raw[TILES - 1], TILES - 1, wave, lane, V);  // (the last block's tile)
+    if (!SHIFT) __syncthreads();
+    if (V & 3) {
+#pragma unroll
+      for (int t = 0; t < TILES; ++t)
+        if (may_end(t)) raw[t] = in_place(raw[t], t, wave, lane, V);
+    }
     float mx = raw[0][0];                      // (a NaN stays)
 #pragma unroll
     for (int i = 1; i < 4 * TILES; ++i) mx = __builtin_elementwise_maximum(mx, raw[i / 4][i % 4]);
+    if constexpr (SHIFT) {
+      float top = mx;
+      if constexpr (MORE) {
+        for (int t = TILES; t * SV_WAVES < n_blocks; ++t) {
+          const f32x4 l = ask(L, t, wave, lane, V);
+          top = fmaxf(top, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
+        }
+      }
+      top = wave_max(top);
+      if (lane == 0) sh.redf[wave] = top;
+      __syncthreads();
+      shift = sh.redf[0];
+#pragma unroll
+      for (int w = 1; w < SV_WAVES; ++w) shift = fmaxf(shift, sh.redf[w]);
+      shift = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(shift)));  // (one that is not finite makes scores that are not numbers)
+      mx -= shift;
+    }
     int e = reference(mx, temp);
     float touch = 0.f;
     if (soon && 32 * tid < V) touch = soon[32 * tid];
@@ -557,6 +590,7 @@ struct RowRegs {
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
       asm volatile("" : "+v"(raw[t]));         // (see in_turn)
+      shifted(raw[t]);
       masses(raw[t], t, wave, lane, V, temp, ex[t]);
       in_turn(ex[t][0], ex[t][1], ex[t][2], ex[t][3]);
       zp += (ex[t][0] + ex[t][1]) + (ex[t][2] + ex[t][3]);
@@ -564,11 +598,11 @@ struct RowRegs {
     if constexpr (MORE) {
       // The tiles behind the registers keep the reference up to 100 T above the scores it was taken from: exponentials up to 2^145 leave room for z_wave.  A tile with
       // more moves it, and what has been computed with it.
-      const int n_blocks = (V + SV_BLOCK - 1) / SV_BLOCK;
       float above = room_above(mx, e, temp);
       f32x4 next = ask(L, TILES, wave, lane, V);
       for (int t = TILES; t * SV_WAVES + wave < n_blocks; ++t) {
         f32x4 l = in_place(next, t, wave, lane, V);
+        shifted(l);
         next = ask(L, t + 1, wave, lane, V);
         float hi = __builtin_elementwise_maximum(__builtin_elementwise_maximum(l[0], l[1]), __builtin_elementwise_maximum(l[2], l[3]));
         if (__any(!(hi <= above)) && e != ROW_GENERAL) {
@@ -721,7 +755,7 @@ __device__ __forceinline__ void position_uniforms(uint32_t b, uint32_t j, uint32
 }
 
 // One workgroup per (position j, sequence b).
-template <int TILES, bool MORE>
+template <int TILES, bool MORE, bool SHIFT>
 __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
     const float* __restrict__ logits, const int32_t* __restrict__ voted, const float* __restrict__ draft_probs,
     const int32_t* __restrict__ spec_len, const int32_t* __restrict__ greedy, int B, int k_max, int M, int V,
@@ -796,13 +830,13 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
   // it replaces (the acceptance reads "first entry that differs" as the first rejection); and when all of o
   // sits on that token there is nothing else to emit: it stays ----
   if constexpr (TILES > 0) {
-    RowRegs<TILES, MORE> regs;
+    RowRegs<TILES, MORE, SHIFT> regs;
     if (regs.load(L, Q, V, temp, power, sh, tid)) {
       uniforms();
       if (in_vocab) {
         Temp whole = temp;
         whole.relative_to(regs.e_all, (double)regs.e_all * 256.0 / temp.k);
-        if (survives(whole.mass<false>(l_x), regs.Z)) {  // (whole workgroup: all of it is uniform)
+        if (survives(whole.mass<false>(SHIFT ? l_x - regs.shift : l_x), regs.Z)) {  // (whole workgroup: all of it is uniform)
           if (tid == 0) *out = x;
           return;
         }
@@ -816,7 +850,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
           for (int t = 0; t < HALF; ++t) q[t] = regs.ask(Q, min(h + t, TILES - 1), wave, lane, V);
 #pragma unroll
           for (int t = 0; t < HALF && h + t < TILES; ++t) {
-            if (!MORE && h + t == TILES - 1 && V & 3) q[t] = regs.in_place(q[t], h + t, wave, lane, V);
+            if (regs.may_end(h + t) && V & 3) q[t] = regs.in_place(q[t], h + t, wave, lane, V);
             asm volatile("" : "+v"(q[t]));
 #pragma unroll
             for (int e = 0; e < 4; ++e) regs.ex[h + t][e] = fmax(0.0, fma(-(double)q[t][e], regs.z_wave, regs.ex[h + t][e]));
@@ -887,7 +921,7 @@ __global__ void __launch_bounds__(SV_THREADS) verify_sample_kernel(
 // One workgroup per sequence: token ~ q = softmax(scores / T) of a drafting SSM, and q itself in fp32.
 // The draw is taken from the fp32 values that are written out, so what the verifier is later told is
 // exactly the distribution the token came from.
-template <int TILES, bool MORE>
+template <int TILES, bool MORE, bool SHIFT>
 __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* __restrict__ logits, int V,
                                                                   double temperature, double inv_temperature, double k, double k_lo,
                                                                   uint32_t seed_lo, uint32_t seed_hi,
@@ -920,7 +954,7 @@ __global__ void __launch_bounds__(SV_THREADS) draft_sample_kernel(const float* _
     }
   };
   if constexpr (TILES > 0) {
-    RowRegs<TILES, MORE> regs;
+    RowRegs<TILES, MORE, SHIFT> regs;
     if (regs.load(L, nullptr, V, temp, power, sh, tid)) {
       const double inv_z = regs.dead ? 0.0 : 1.0 / regs.z_wave;
 #pragma unroll
@@ -1001,20 +1035,27 @@ static int reg_tiles(int V, double inv) {
 }
 // FAR: tiles in registers beyond 32768 tokens.  The verifier needs room for q there: 144 positions of 50272 tokens 35.6 us with eight (which spill), 26.5 with six,
 // 28.7 with four, 48.4 in the general form; 16 drafted tokens 20.5, 22.0 and 23.9, 41.5 in the general form.
-#define MN_ROW_KERNEL(K, FAR, V, INV)                                                     \
-  [&] {                                                                                   \
-    switch (reg_tiles(V, INV)) {                                                          \
-      case 0: return K<0, false>;                                                         \
-      case 1: return K<1, false>;                                                         \
-      case 2: return K<2, false>;                                                         \
-      case 3: return K<3, false>;                                                         \
-      case 4: return K<4, false>;                                                         \
-      case 5: return K<5, false>;                                                         \
-      case 6: return K<6, false>;                                                         \
-      case 7: return K<7, false>;                                                         \
-      case 8: return K<8, false>;                                                         \
-      default: return K<FAR, true>;                                                       \
-    }                                                                                     \
+// Temperatures below SV_LOW_T, whose scores may be 2^38 steps of the exponentials' table from zero (a score of 709 there, of 20 at T 2.7e-8), take them less the
+// row's largest, which the waves wait for: 32000 tokens at T 1e-9, 144 positions 13.4 us and 16 drafted tokens 11.9 (37.1 and 33.4 in the general form after an attempt
+// that found it out, 12.9 and 11.7 without the row's largest at 1e-6), 50272 tokens 28.4 and 22.1 (56.6 and 49.6; 26.4 and 21.3).  Rows of 3, 5, 6 and 7 tiles go with the next instance.
+constexpr double SV_LOW_T = 0x1p-20;
+#define MN_ROW_KERNEL(K, FAR, V, T, INV)                                                                                               \
+  [&] {                                                                                                                                \
+    const int tiles = reg_tiles(V, INV);                                                                                               \
+    if (tiles > 0 && T < SV_LOW_T)                                                                                                     \
+      return tiles <= 2 ? K<2, false, true> : tiles <= 4 ? K<4, false, true> : tiles <= 8 ? K<8, false, true> : K<FAR, true, true>;    \
+    switch (tiles) {                                                                                                                   \
+      case 0: return K<0, false, false>;                                                                                               \
+      case 1: return K<1, false, false>;                                                                                               \
+      case 2: return K<2, false, false>;                                                                                               \
+      case 3: return K<3, false, false>;                                                                                               \
+      case 4: return K<4, false, false>;                                                                                               \
+      case 5: return K<5, false, false>;                                                                                               \
+      case 6: return K<6, false, false>;                                                                                               \
+      case 7: return K<7, false, false>;                                                                                               \
+      case 8: return K<8, false, false>;                                                                                               \
+      default: return K<FAR, true, false>;                                                                                             \
+    }                                                                                                                                  \
   }()
 static_assert(SV_REG_TILES == 8, "an instance for every number of tiles");
 
@@ -1024,7 +1065,7 @@ void launch_verify_sample(const float* logits, const int32_t* voted, const float
   if (B <= 0) return;
   const double inv = temperature_reciprocal(temperature);
   const StepsPerScore steps(temperature);
-  auto* kernel = MN_ROW_KERNEL(verify_sample_kernel, 6, V, inv);
+  auto* kernel = MN_ROW_KERNEL(verify_sample_kernel, 6, V, temperature, inv);
   kernel<<<dim3(k_max + 1, B), SV_THREADS, 0, st>>>(
       logits, voted, draft_probs, spec_len, greedy, B, k_max, M, V, temperature, inv, steps.k, steps.k_lo,
       (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), sampled, dev_status);
@@ -1035,7 +1076,7 @@ void launch_draft_sample(const float* logits, int B, int V, double temperature, 
   if (B <= 0) return;
   const double inv = temperature_reciprocal(temperature);
   const StepsPerScore steps(temperature);
-  auto* kernel = MN_ROW_KERNEL(draft_sample_kernel, 8, V, inv);
+  auto* kernel = MN_ROW_KERNEL(draft_sample_kernel, 8, V, temperature, inv);
   kernel<<<B, SV_THREADS, 0, st>>>(logits, V, temperature, inv, steps.k, steps.k_lo, (uint32_t)seed,
                                    (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), (uint32_t)(1 + ssm),
                                    (uint32_t)t_pos, tokens, token_stride, probs, probs_stride);

@@ -581,6 +581,7 @@ def _microseconds(call, n=20):
     (16385, 1.0, None, 16384, 1.35),
     (32000, 1.0, -1e9, 32000, 1.4),      # all but 50 tokens masked with a finite value
     (32000, 1.0, float(np.finfo(np.float32).min), 32000, 1.4),
+    (32000, 1e-9, None, 32000, 1.4),     # scores 2^38 steps of the table of exponentials from zero
     (50272, 1.0, -np.inf, 50272, 1.4),   # waves whose first tiles are masked, beyond 32768 tokens
     (50272, 0.01, None, 50272, 1.4),     # scores behind the registers more than 100 T above a wave's first ones
 ])
@@ -652,3 +653,21 @@ def test_rows_whose_scores_rise_behind_the_registers(hb, V, rise):
     log_d, tok_d, q_d = _dev(bad, torch.float32), _dev([-5, -5]), torch.zeros(2, V, device="cuda:0")
     binding.mn_draft_sample(None, log_d.data_ptr(), 2, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
     assert tok_d.tolist() == [-1, -1] and bool(torch.isnan(q_d).any(dim=1).all())
+
+
+@pytest.mark.parametrize("V", [5, 4097, 9001, 20002, 32767, 131075])
+@pytest.mark.parametrize("top,T", [(20.0, 9.5e-7), (20.0, 1e-8), (-3e3, 1e-9), (7e30, 1e-12), (0.0, 1e-20)])
+def test_lowest_temperatures_at_every_length_against_oracle(hb, V, top, T):
+    """Temperatures below 2^-20, whose scores are taken less the row's largest: at both signs, with masked waves, rows that end inside any tile, and rows
+    that are all masked or hold a NaN."""
+    test_low_temperatures_against_oracle(hb, T, top, V)
+    harness, binding = hb
+    logits = synth.stream(4111, V).normal(top, 1.0, (4, V)).astype(np.float32)
+    logits[0, 1:] = np.finfo(np.float32).min
+    logits[1] = -np.inf
+    logits[2, V // 2] = np.nan
+    logits[3, V - 1] = np.inf
+    _check_draft_rows(hb, logits[:1], T)
+    log_d, tok_d, q_d = _dev(logits, torch.float32), _dev([-5] * 4), torch.zeros(4, V, device="cuda:0")
+    binding.mn_draft_sample(None, log_d.data_ptr(), 4, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
+    assert tok_d.tolist()[1:] == [-1, -1, -1]
