@@ -1029,8 +1029,9 @@ struct StepsPerScore {
 // 12.2 us, now 7.6, 9.2 and 10.9).  0: the general form.  Beyond 32768 tokens the first tiles are in registers, up to the segments that the shared array
 // holds.
 constexpr int SV_MAX_FAR = SV_MAX_SEGS * SV_BLOCK;
-static int reg_tiles(int V, double inv) {
-  if (V < 4 || V > SV_MAX_FAR || inv == 0.0) return 0;
+static int reg_tiles(int V, double T, double inv) {
+  // (at 2^90 and more, 690 T below a largest score near the type's lowest value is no float: a cut score would stand level with it)
+  if (V < 4 || V > SV_MAX_FAR || inv == 0.0 || T >= 0x1p90) return 0;
   return min((V + SV_TILE - 1) / SV_TILE, SV_REG_TILES + 1);
 }
 // FAR: tiles in registers beyond 32768 tokens.  The verifier needs room for q there: 144 positions of 50272 tokens 35.6 us with eight (which spill), 26.5 with six,
@@ -1041,7 +1042,7 @@ static int reg_tiles(int V, double inv) {
 constexpr double SV_LOW_T = 0x1p-20;
 #define MN_ROW_KERNEL(K, FAR, V, T, INV)                                                                                               \
   [&] {                                                                                                                                \
-    const int tiles = reg_tiles(V, INV);                                                                                               \
+    const int tiles = reg_tiles(V, T, INV);                                                                                            \
     if (tiles > 0 && T < SV_LOW_T)                                                                                                     \
       return tiles <= 2 ? K<2, false, true> : tiles <= 4 ? K<4, false, true> : tiles <= 8 ? K<8, false, true> : K<FAR, true, true>;    \
     switch (tiles) {                                                                                                                   \

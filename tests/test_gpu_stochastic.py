@@ -671,3 +671,14 @@ def test_lowest_temperatures_at_every_length_against_oracle(hb, V, top, T):
     log_d, tok_d, q_d = _dev(logits, torch.float32), _dev([-5] * 4), torch.zeros(4, V, device="cuda:0")
     binding.mn_draft_sample(None, log_d.data_ptr(), 4, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
     assert tok_d.tolist()[1:] == [-1, -1, -1]
+
+
+@pytest.mark.parametrize("T", [2.0 ** 90, 1e30])
+def test_masked_tokens_stay_masked_beside_the_lowest_scores(hb, T):
+    """The only scores that are not minus infinity are the type's lowest value, at temperatures of its order: no float lies 690 T below them."""
+    logits = np.full((1, 300), -np.inf, np.float32)
+    logits[0, [7, 100, 290]] = np.finfo(np.float32).min
+    _check_draft_rows(hb, logits, T)
+    res = _run_gpu(hb, np.zeros(1, np.int32), 1, logits, np.zeros((1, 1, 300), np.float32), np.full((1, 1), -1, np.int32), 0, 300, T, seed=3, step=0,
+                   ctx0=np.zeros(1, np.int32))
+    assert res[0][0, 0] in (7, 100, 290)
