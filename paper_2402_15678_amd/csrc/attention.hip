@@ -123,7 +123,7 @@ __global__ void __launch_bounds__(GEN_THREADS) attn_generic_kernel(const int32_t
   for (int k0 = 0; k0 < nkeys; k0 += GEN_THREADS) {
     const int key = k0 + tid;
     float s = -INFINITY;
-    const int blk = key / bs, off = key - blk * bs;
+    const int blk = (int)((uint32_t)key / (uint32_t)bs), off = key - blk * bs;  // (as signed numbers two registers more: the fp32 kernel spilled them)
     uint64_t page = 0;
     if (key < old) {
       page = ((uint64_t)(uint32_t)bt[blk] * a.Hkv + kh) * (uint64_t)(hd * bs);
