@@ -682,3 +682,36 @@ def test_masked_tokens_stay_masked_beside_the_lowest_scores(hb, T):
     res = _run_gpu(hb, np.zeros(1, np.int32), 1, logits, np.zeros((1, 1, 300), np.float32), np.full((1, 1), -1, np.int32), 0, 300, T, seed=3, step=0,
                    ctx0=np.zeros(1, np.int32))
     assert res[0][0, 0] in (7, 100, 290)
+
+
+# First row of a sequence: summed by each wave up to 256 sequences, 64 at a time, and by the workgroup beyond
+@pytest.mark.parametrize("B", [65, 129, 200, 256, 257, 258, 300])
+def test_rows_of_many_ragged_sequences_against_oracle(hb, B):
+    k_max, V, T = 3, 61, 0.8
+    spec, M, logits, q, voted = _case(71, B, k_max, V, T, 1.0)
+    ctx0 = np.arange(B).astype(np.int32)
+    res = _run_gpu(hb, spec, M, logits, q, voted, k_max, V, T, seed=15, step=2, ctx0=ctx0)
+    _check_against_oracle(res, spec, logits, q, voted, k_max, T, 15, 2, ctx0)
+
+
+@pytest.mark.parametrize("B,bad", [(70, 0), (70, 64), (200, 63), (200, 130), (256, 255), (300, 5), (300, 256), (300, 299)])
+@pytest.mark.parametrize("value", [-1, 4])
+def test_sequences_behind_an_invalid_length(hb, B, bad, value):
+    """A length outside 0 .. k_max leaves the rows of every later sequence unknown: they get no token; those before it keep theirs."""
+    harness, binding = hb
+    k_max, V = 3, 61
+    spec, M, logits, q, voted = _case(72, B, k_max, V, 1.0, 1.0)
+
+    def run(lengths):
+        out = torch.full((B, k_max + 1), -9, dtype=torch.int32, device="cuda:0")
+        st = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+        t = [_dev(logits, torch.float32), _dev(voted), _dev(q, torch.float32), _dev(lengths), _dev(np.zeros((B, k_max + 1), np.int32))]
+        binding.mn_verify_sample(None, *[x.data_ptr() for x in t], B, k_max, M, V, 1.0, 4, 1, out.data_ptr(), st.data_ptr(), harness.stream_ptr())
+        return out.cpu().numpy(), st.item()
+
+    want, status = run(spec)
+    assert status == 0 and (want[:, 0] >= 0).all()
+    wrong = spec.copy()
+    wrong[bad] = value
+    got = run(wrong)[0]                                   # (the lengths themselves are reported by the step that scored the rows)
+    assert np.array_equal(got[:bad], want[:bad]) and (got[bad:] == -1).all()
