@@ -770,7 +770,6 @@ __global__ void __launch_bounds__(NW * 64, HDIM == 64 ? (CT == 1 ? 3 : 2) : (CT 
 #pragma unroll
         for (int e = 0; e < 4; ++e) { v0[e] += b0[e]; v1[e] += b1[e]; }
       }
-      // (vmcnt(0): every wave, and its tiles with it, would wait below for partials that were asked for and not added)
       asm volatile("" : "+v"(slot));                         // (asked for with the rest, not where it is used)
       if (a.rope_cos && hh <= G) {
 #pragma unroll

@@ -867,14 +867,15 @@ bool gemm_small_matrix(int N, int K) { return small_matrix((N + NWG - 1) / NWG *
 // columns instead of 32, five to a workgroup, one workgroup per CU.  Partial sums of more than 64 rows stay with 32: a wave of 16 columns
 // stores half lines.  Cold weights, three (four below 600 slices) waves of 32 columns and five of 16: 20480 x 5120 at 1, 16, 33, 64, 96,
 // 144 rows 35.8 36.8 38.6 37.6 41.9 53.5 and 34.9 35.7 37.8 37.2 42.3 56.0 us, 17536 x 8192 49.6 51.1 53.8 53.0 60.0 74.9 and 47.3
-// 48.9 51.9 51.6 58.7 77.1; with bias and ReLU in the epilogue the 128 rows of a four-layer step gain too, 912 -> 902 us, its 80 rows
-// 788 -> 778.
+// 48.9 51.9 51.6 58.7 77.1; with bias and ReLU in the epilogue, which stores fp16, all rows gain or are even.  Whole passes with 32 and 16 columns: four layers of 20480 x 5120 at
+// 80, 128, 129, 136, 144 rows 745 878 939 939 920 and 736 870 934 930 911 us, two layers of 17536 x 8192 510 599 639 640 635 and 504 595 637 639 636 (runs of one
+// side differ by up to 3).
 constexpr int NARROW_NW = 5, NARROW_ROWS = 64;
 
 // Waves per workgroup at 144 rows or fewer, for a matrix of so many 32-column slices cut into `split` k-splits.  Unsplit
 // matrices: a CU with w workgroups of NW waves takes about 0.15 + w (0.27 + 0.13 NW) us per iteration (the tile and the
 // barrier are paid per workgroup, the stream per wave), so the count that gives the busiest CU the least is taken.  Measured
-// at 40 rows, NW = 2 .. 8: 20480 x 5120 (640 slices) 48.9 38.5 42.2 48.5 53.7 58.6 63.5 us; 50272 x 5120 (1572 slices) 99.6 103.4
+// at 40 rows, NW = 2 .. 8: 20480 x 5120 (640 slices) 48.9 38.5 42.2 48.5 53.7 58.6 63.5 us (its three waves of 32 columns are five of 16 now, see above); 50272 x 5120 (1572 slices) 99.6 103.4
 // 92.6 104.3 117.7 81.5 82.3 us.  Small matrices: see stream_split (6144 x 768 at 16 rows, NW = 1 .. 4: 5.5 5.8 6.6 7.4 us).
 // Split matrices have their split picked for 4 waves (small ones for 2) and no more workgroups than CUs.  A split that the caller gives may
 // make more: above 96 rows, where the tile is dear, as many waves then as leave a workgroup per CU, eight if none do (97 and 144 rows, with four

@@ -42,8 +42,8 @@ __device__ __forceinline__ double unit_double(uint32_t hi, uint32_t lo) {
 // One workgroup of 16 waves per row, the row's exponentials in registers.  The kernels are bound by the fp64
 // exponentials of one row on one CU (15 vector instructions of four cycles per token and lane: 3.1 us for 32000 tokens) and by
 // the chain load -> exponentials -> sum -> masses -> draw, so a row is read once, every exponential is computed once, and the workgroup
-// meets twice: for the sum of the exponentials and for the sums of the segments.  Measured at 32000 tokens: 13.7 us for the 144 positions of 16
-// requests and 11.7 us for 16 drafted tokens (18.8 and 13.5 with the exponentials relative to the row's largest score, a third meeting of the workgroup, and the
+// meets twice: for the sum of the exponentials and for the sums of the segments.  Measured at 32000 tokens: 13.2 us for the 144 positions of 16
+// requests and 11.8 us for 16 drafted tokens (18.3 and 13.7 with the exponentials relative to the row's largest score, a third meeting of the workgroup, and the
 // masses divided by Z).
 constexpr int SV_THREADS = 1024;
 constexpr int SV_WAVES = SV_THREADS / 64;
@@ -213,6 +213,14 @@ __device__ __forceinline__ void in_turn(T& a, T& b, T& c, T& d) {
   a = v[0]; b = v[1]; c = v[2]; d = v[3];
 }
 
+// the next float at or above x
+__device__ __forceinline__ float float_above(double x) {
+  const float n = (float)x;
+  if (!((double)n < x)) return n;
+  return n == 0.f ? 1e-45f : __uint_as_float(__float_as_uint(n) + (n > 0.f ? 1 : -1));
+}
+constexpr double ROUND_MAGIC = 6755399441055744.0;  // 1.5 * 2^52: added to a number, its nearest whole number sits in the low bits
+
 // Exponentials of scores at temperature T, table-driven (P. T. P. Tang, ACM TOMS 15(2), 1989): l / T = (n + f) ln2/256 with n whole
 // and |f| <= 1/2, and exp(l / T) = 2^(n >> 8) * 2^((n & 255)/256) * (1 + a1 f + .. + a4 f^4), the fifth-order term spread over a1 and a3.
 // f comes out of two fmas with k = 256 / (T ln2) in two pieces, so nothing is lost to the reciprocal of T.  (Several copies of the table, so
@@ -221,19 +229,12 @@ __device__ __forceinline__ void in_turn(T& a, T& b, T& c, T& d) {
 // rounded exponential has (4.8e-17 and 1.4e-16 at T = 1, 5e-16 and 1e-15 elsewhere with a reciprocal of T in one piece).
 // About half the instructions of the general function, which is most of these kernels' time.
 // A wave takes the exponentials relative to a power of two of its own, at or above its largest one (`relative_to`): nobody waits for
-// the largest score of the row, and the waves' sums are brought to one scale exactly.  Where that does not work - scores that are not numbers or
-// of a size that leaves n no room, rows beyond the registers - they are taken relative to the row's largest score (`below`),
+// the largest score of the row, and the waves' sums are brought to one scale exactly.  Where that does not work - scores that are not numbers or,
+// from SV_LOW_T on, of a size that leaves n no room, rows beyond SV_MAX_FAR - they are taken relative to the row's largest score (`below`),
 // and for temperatures so extreme that the reciprocal leaves the normal range (inv == 0) by the general function and a
 // division.  Scores more than 800 T below the largest are cut there (the exponential is zero long before), so that a masked token (minus
 // infinity) stays finite; NaN passes through.  The cut is on fp64 numbers: 800 T may be far below the spacing of the scores in fp32,
 // and the largest score may be the type's lowest value.
-// the next float at or above x
-__device__ __forceinline__ float float_above(double x) {
-  const float n = (float)x;
-  if (!((double)n < x)) return n;
-  return n == 0.f ? 1e-45f : __uint_as_float(__float_as_uint(n) + (n > 0.f ? 1 : -1));
-}
-constexpr double ROUND_MAGIC = 6755399441055744.0;  // 1.5 * 2^52: added to a number, its nearest whole number sits in the low bits
 struct Temp {
   double T, inv, k, k_lo;
   const double2* table;
@@ -1034,8 +1035,8 @@ static int reg_tiles(int V, double T, double inv) {
   if (V < 4 || V > SV_MAX_FAR || inv == 0.0 || T >= 0x1p90) return 0;
   return min((V + SV_TILE - 1) / SV_TILE, SV_REG_TILES + 1);
 }
-// FAR: tiles in registers beyond 32768 tokens.  The verifier needs room for q there: 144 positions of 50272 tokens 35.6 us with eight (which spill), 26.5 with six,
-// 28.7 with four, 48.4 in the general form; 16 drafted tokens 20.5, 22.0 and 23.9, 41.5 in the general form.
+// FAR: tiles in registers beyond 32768 tokens.  144 positions of 50272 tokens 26.2 us with six, 28.6 with four, 25.0 with eight, which keep five registers in scratch memory
+// (an earlier build of them, with more there, took 35.6), 48.4 in the general form; 16 drafted tokens 20.6 with eight, 22.3 with six, 24.4 with four, 41.5 in the general form.
 // Temperatures below SV_LOW_T, whose scores may be 2^38 steps of the exponentials' table from zero (a score of 709 there, of 20 at T 2.7e-8), take them less the
 // row's largest, which the waves wait for: 32000 tokens at T 1e-9, 144 positions 13.4 us and 16 drafted tokens 11.9 (37.1 and 33.4 in the general form after an attempt
 // that found it out, 12.9 and 11.7 without the row's largest at 1e-6), 50272 tokens 28.4 and 22.1 (56.6 and 49.6; 26.4 and 21.3).  Rows of 3, 5, 6 and 7 tiles go with the next instance.
