@@ -589,15 +589,15 @@ def test_time_of_rows_in_registers(hb, V, T, mask, plain_V, most):
     harness, binding = hb
     g = synth.stream(4108, V)
 
-    def draft_time(V, T, mask):
+    def draft_call(V, T, mask):
         logits = g.normal(0.0, 2.0, (16, V)).astype(np.float32)
         if mask is not None:
             logits[:, np.setdiff1d(np.arange(V), g.permutation(V)[:50])] = mask
         log_d, tok_d, q_d = _dev(logits, torch.float32), torch.zeros(16, dtype=torch.int32, device="cuda:0"), torch.zeros(16, V, device="cuda:0")
-        return _microseconds(lambda: binding.mn_draft_sample(None, log_d.data_ptr(), 16, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(),
-                                                             V, harness.stream_ptr()))
+        return lambda: binding.mn_draft_sample(None, log_d.data_ptr(), 16, V, T, 9, 2, 1, 3, tok_d.data_ptr(), 1, q_d.data_ptr(), V, harness.stream_ptr())
 
-    plain, this = draft_time(plain_V, 1.0, None), draft_time(V, T, mask)
+    calls = draft_call(plain_V, 1.0, None), draft_call(V, T, mask)
+    plain, this = np.min([[_microseconds(c) for c in calls] for _ in range(3)], axis=0)
     assert this <= most * plain, (this, plain)
 
 
